@@ -16,11 +16,12 @@
 // Precision.  x0y0 accumulates by itself; the five small products have accumulators of their own, added once at the
 // end.  Then an output sees one rounding at its full magnitude per 16 steps (the fp32 forms: one per step, on four
 // partial sums).  Against 64-bit sums, 2-norm, random operands of 1024 steps: 1.8e-7, four-block fp32 form 2.9e-7
-// (one accumulator for all six: 4.9e-7).  An Inf or NaN operand, or one that rounds to Inf in bf16, makes Inf - Inf of
-// the split: a wave that finds a non-finite sum multiplies its tile again with fp32 MFMAs, which keep Inf as Inf.
+// (one accumulator for all six: 4.9e-7).  Scaling by 2^23 (kUp) keeps every part of every operand a normal bf16 number.
+// An operand that is Inf, NaN or at least 2^105 makes Inf - Inf of the split, and sums from 2^82 on leave fp32's range: a
+// wave that finds a non-finite sum multiplies its tile again with fp32 MFMAs, which keep Inf as Inf.
 //
 // What bounds it: per 16 steps x 32 rows x 128 columns a wave issues 24 MFMAs (768 cycles) and ~240 vector
-// instructions for the splits (960 cycles); two waves share a SIMD, one multiplying while the other splits.  Measured,
+// instructions for the splits (1120 cycles); two waves share a SIMD, one multiplying while the other splits.  Measured,
 // 4096^3 fp32, one row per column set at density 1/8 (34.4 GFLOP on the filled mask): 309 us on the fp32 MFMAs -> 212.
 #include <hip/hip_runtime.h>
 
@@ -35,7 +36,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 typedef uint16_t halfword __attribute__((may_alias));   // (LDS written by halfwords and read as operands)
 
-// the three bf16 parts of eight fp32 values (nearest even each; the differences are exact)
+// The operands are split as 2^23 times their value: every fp32 number is a multiple of 2^-149, so every part is zero or a
+// normal bf16 number however small the operand is.  The sums leave with the factor of both operands taken off.
+constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;
+
+// the three bf16 parts of eight fp32 values, times kUp (nearest even each; the differences are exact)
 struct Split {
   bf16x8 p[3];
 };
@@ -45,31 +50,30 @@ __device__ __forceinline__ Split split8(const float (&x)[8]) {
   u32x4 p0, p1, p2;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    p0[e] = bf16_pair(x[2 * e], x[2 * e + 1]);
-    const float a = x[2 * e] - bf16_lo(p0[e]), b = x[2 * e + 1] - bf16_hi(p0[e]);
+    const float x0 = x[2 * e] * kUp, x1 = x[2 * e + 1] * kUp;
+    p0[e] = bf16_pair(x0, x1);
+    const float a = x0 - bf16_lo(p0[e]), b = x1 - bf16_hi(p0[e]);
     p1[e] = bf16_pair(a, b);
     p2[e] = bf16_pair(a - bf16_lo(p1[e]), b - bf16_hi(p1[e]));
   }
   return Split{{__builtin_bit_cast(bf16x8, p0), __builtin_bit_cast(bf16x8, p1), __builtin_bit_cast(bf16x8, p2)}};
 }
 
-// Adds the small products and marks what the fp32 pass has to give: sums that are not finite, and the lane's sums of a
-// column whose largest is nonzero and below 2^-80 (the parts of operands below 2^-110 run out of bf16's exponents).
-// Returns 1 where a sum is not finite, 2 where the sums are small, 0 elsewhere.
-__device__ __forceinline__ int add_up(f32x16 &acc, const f32x16 &cor) {
-  float zero = 0.f, most = 0.f;   // zero: 0, or NaN where a sum is not finite
+// Adds the small products and takes the operands' factors off.  True: one of the sums is not finite, and the fp32 pass has
+// to give it.
+__device__ __forceinline__ bool add_up(f32x16 &acc, const f32x16 &cor) {
+  float zero = 0.f;   // 0, or NaN where a sum is not finite
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    acc[i] += cor[i];
+    acc[i] = (acc[i] + cor[i]) * kDown;
     zero = __builtin_fmaf(acc[i], 0.f, zero);
-    most = __builtin_fmaxf(most, __builtin_fabsf(acc[i]));
   }
-  return most > 0.f && most < 0x1p-80f ? 2 : zero != 0.f ? 1 : 0;
+  return zero != 0.f;
 }
-// (every other sum stays as it is, bit for bit)
-__device__ __forceinline__ void take_doubtful(f32x16 &acc, const f32x16 &second, int doubt) {
+// (every finite sum stays as it is, bit for bit)
+__device__ __forceinline__ void take_not_finite(f32x16 &acc, const f32x16 &second) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = doubt == 2 || !(acc[i] * 0.f == 0.f) ? second[i] : acc[i];
+  for (int i = 0; i < 16; ++i) acc[i] = acc[i] * 0.f == 0.f ? acc[i] : second[i];
 }
 
 // A stage is walked in p.nq blocks of 16 contraction steps (the last one may be padding in part: zero weights).
@@ -183,13 +187,9 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
       for (int t = 0; t < 4; ++t) cor[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[2], b[t].p[0], cor[t], 0, 0, 0);
     }
   }
-  int doubt[4];
   bool again = false;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    doubt[t] = add_up(acc[t], cor[t]);
-    again |= doubt[t] && n0 + j * 4 + t < out_n;
-  }
+  for (int t = 0; t < 4; ++t) again |= add_up(acc[t], cor[t]) && n0 + j * 4 + t < out_n;
   if (__builtin_amdgcn_ballot_w64(again)) {   // (wave-uniform; no barrier inside)
     clear(cor);
     for (int s = 0; s < cnt; ++s)
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
             cor[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[e / 4][e % 4], B[e][t], cor[t], 0, 0, 0);
       }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) take_doubtful(acc[t], cor[t], doubt[t]);
+    for (int t = 0; t < 4; ++t) take_not_finite(acc[t], cor[t]);
   }
 
   // Epilogue.  Unit i = register i of the four accumulators: weight row 8 (i / 4) + 4 (lane / 32) + i % 4 of the wave's
@@ -391,13 +391,9 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
           }
       }
   }
-  int doubt[4];
   bool again = false;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    doubt[t] = add_up(acc[t], cor[t]);
-    again |= doubt[t] && n0 + 32 * t + j < out_n;
-  }
+  for (int t = 0; t < 4; ++t) again |= add_up(acc[t], cor[t]) && n0 + 32 * t + j < out_n;
   if (__builtin_amdgcn_ballot_w64(again)) {   // (wave-uniform; no barrier inside)
     clear(cor);
     for (int s = 0; s < cnt; ++s)
@@ -412,7 +408,7 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
         }
       }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) take_doubtful(acc[t], cor[t], doubt[t]);
+    for (int t = 0; t < 4; ++t) take_not_finite(acc[t], cor[t]);
   }
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
@@ -433,8 +429,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // the 4x4x1 fp32 form per cycle.  Workgroup: 128 rows of a tile row (32 G_i vertices, a wave eight of them) x 128
 // columns.  A stage's kept weights (one 16-byte load per lane holds four rows of one step; two for KS = 16) are split and
 // scattered to their steps in a wave-private LDS block whose other entries stay zero: the pattern of G_i is the same in
-// every tile.  I as in spmm_reg_split_shared, a round being one stage.  Sums that are not finite or too small for bf16's
-// exponents are added up again from the kept weights.  4096 x 4096, G_o and G_i at 1/4,
+// every tile.  I as in spmm_reg_split_shared, a round being one stage.  Sums that are not finite are added up
+// again from the kept weights.  4096 x 4096, G_o and G_i at 1/4,
 // N = 1531: 126 -> 90 us, error against 64-bit sums 2.0e-7 -> 7.6e-8.
 template <int KS>
 __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
@@ -505,8 +501,9 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     for (int it = 0; it < IT; ++it)
 #pragma unroll
       for (int r = 0; r < 4; r += 2) {
-        const uint32_t p0 = bf16_pair(araw[it][r], araw[it][r + 1]);
-        const float x = araw[it][r] - bf16_lo(p0), y = araw[it][r + 1] - bf16_hi(p0);
+        const float x0 = araw[it][r] * kUp, x1 = araw[it][r + 1] * kUp;
+        const uint32_t p0 = bf16_pair(x0, x1);
+        const float x = x0 - bf16_lo(p0), y = x1 - bf16_hi(p0);
         const uint32_t p1 = bf16_pair(x, y), p2 = bf16_pair(x - bf16_lo(p1), y - bf16_hi(p1));
         const uint32_t part[3] = {p0, p1, p2};
 #pragma unroll
@@ -547,13 +544,13 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   uint64_t again = 0;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int doubt = add_up(acc[t], cor[t]);
+    add_up(acc[t], cor[t]);
     const bool stored = n0 + 32 * t + j < p.N;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int64_t m = ((int64_t(u1) * p.a2 + (i % 4) / p.a4) * p.a3 + ub + 2 * (i / 4) + h) * p.a4 + (i % 4) % p.a4;
       if (stored) __builtin_nontemporal_store(acc[t][i], p.O + m * p.ldO + n0 + 32 * t + j);
-      if (stored && (doubt == 2 || !(acc[t][i] * 0.f == 0.f))) again |= uint64_t(1) << (16 * t + i);
+      if (stored && !(acc[t][i] * 0.f == 0.f)) again |= uint64_t(1) << (16 * t + i);
     }
   }
   while (again) {   // one sum at a time from its kept weights (none, for ordinary operands)

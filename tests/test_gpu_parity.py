@@ -419,6 +419,27 @@ def test_split_operands_keep_infinities_and_other_columns(variant):
     assert (np.abs(small - ref[:, 100:140]) <= bound).all()
 
 
+@pytest.mark.parametrize("kernel,variant", [(REG, 1), (REG, 2), (REG, 3), (MFMA, 1), (MFMA, 2)])
+def test_split_operands_keep_the_bits_of_tiny_operands(kernel, variant):
+    """Rows of W and columns of I down to fp32's denormals among ordinary and huge ones, so that one lane holds sums of
+    very different sizes and tiny weights meet huge activations: every sum by itself is an fp32 sum of its n products,
+    within n + 8 roundings of the products' size (8: the operands' parts that are left out) and of denormals."""
+    shape = ((2, 128, 1, 1), (4, 2, 16, 1), (2, 2, 16, 1)) if kernel == REG else ((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1))
+    w = wl.Workload("split_tiny", *shape, 333, wl.F32, 21, 22, 23, 1.0)
+    N, rng = 200, np.random.default_rng(24)
+    vals, I = wl.kept_weights(w).reshape(w.M, w.rowdeg), wl.activations(w, N)
+    vals = vals * rng.choice(2.0 ** np.array([0, 0, 0, 8, -40, -100, -112, -118, -124, -130]), (w.M, 1)).astype(np.float32)
+    I = I * rng.choice(2.0 ** np.array([0, 0, 0, 60, -20, -60, -90, -118, -126, -135]), (1, N)).astype(np.float32)
+    out, used = gh.library_spmm(w, vals, I, kernel=kernel, tune=(0,) * 8 + (variant,), tag="tiny operands")
+    assert used == kernel
+    mask = rb.rbgp_mask_dense(gh.make_mask(w)).reshape(w.M, w.K).astype(bool)
+    W = np.zeros((w.M, w.K))
+    W[mask] = vals.reshape(-1)
+    X, n = I.astype(np.float64), w.rowdeg
+    bound = (n + 8) * (2.0 ** -24 * (np.abs(W) @ np.abs(X)) + 2.0 ** -150)
+    assert (np.abs(out - W @ X) <= bound).all()
+
+
 @pytest.mark.parametrize("out_bf16", [False, True])
 @pytest.mark.parametrize("idx", [0, 3, 5, 6])
 def test_bf16_register_family_shared_columns(idx, out_bf16):
