@@ -20,9 +20,10 @@
 // An operand that is Inf, NaN or at least 2^105 makes Inf - Inf of the split, and sums from 2^82 on leave fp32's range: a
 // wave that finds a non-finite sum multiplies its tile again with fp32 MFMAs, which keep Inf as Inf.
 //
-// What bounds it: per 16 steps x 32 rows x 128 columns a wave issues 24 MFMAs (768 cycles) and ~240 vector
-// instructions for the splits (1120 cycles); two waves share a SIMD, one multiplying while the other splits.  Measured,
-// 4096^3 fp32, one row per column set at density 1/8 (34.4 GFLOP on the filled mask): 309 us on the fp32 MFMAs -> 212.
+// What bounds it: per 16 steps x 32 rows x 128 columns a wave issues 24 MFMAs (768 cycles) and ~280 vector
+// instructions for the splits (1120 cycles; the scaling is 40 of them and costs 1-5 %); two waves share a SIMD, one
+// multiplying while the other splits.  Measured, 4096^3 fp32, one row per column set at density 1/8 (34.4 GFLOP on the
+// filled mask): 309 us on the fp32 MFMAs -> 212.
 #include <hip/hip_runtime.h>
 
 #include "rbgp_internal.h"
