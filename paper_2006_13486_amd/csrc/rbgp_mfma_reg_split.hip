@@ -430,9 +430,11 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // the 4x4x1 fp32 form per cycle.  Workgroup: 128 rows of a tile row (32 G_i vertices, a wave eight of them) x 128
 // columns.  A stage's kept weights (one 16-byte load per lane holds four rows of one step; two for KS = 16) are split and
 // scattered to their steps in a wave-private LDS block whose other entries stay zero: the pattern of G_i is the same in
-// every tile.  I as in spmm_reg_split_shared, a round being one stage.  Sums that are not finite are added up
-// again from the kept weights.  4096 x 4096, G_o and G_i at 1/4,
-// N = 1531: 126 -> 90 us, error against 64-bit sums 2.0e-7 -> 7.6e-8.
+// every tile.  I as in spmm_reg_split_shared, a round being one stage.  One Inf in I makes every sum of its
+// column in the tile rows with that tile non-finite (the zeros of G_i are multiplied): such sums are added up again from
+// the kept weights, with the 4x4x1 MFMAs and in the order of spmm_mfma.  4096 x 4096, G_o and G_i at 1/4, N = 1531:
+// 126 -> 90 us, error against 64-bit sums 2.0e-7 -> 7.6e-8; with one infinity 240, with no finite column 260 (a lane adding
+// its sums up one by one: 470 and 1420).
 template <int KS>
 __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   constexpr int CW = 128, IT = KS / 8;
@@ -469,12 +471,13 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   };
   float braw[2][8];
   f32x4 araw[IT];
+  // extent: to the last column of the stage's last row (columns past it read zeros or the next row; never stored)
+  auto stage_rsrc = [&](int s) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.I + first_row(s) * p.ldI + n0), 0,
+                                             31 * row_bytes + int((p.N - n0) * 4 < CW * 4 ? (p.N - n0) * 4 : CW * 4), kRsrcFlags);
+  };
   auto load_round = [&](int s) {                // (the last round loads its own stage again)
-    const int64_t k0 = first_row(s);
-    const float *base = p.I + k0 * p.ldI + n0;
-    // extent: to the last column of the stage's last row (columns past it read zeros or the next row; never stored)
-    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(base), 0, 31 * row_bytes + int((p.N - n0) * 4 < CW * 4 ? (p.N - n0) * 4 : CW * 4), kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
 #pragma unroll
     for (int it = 0; it < IT; ++it)
       araw[it] = *reinterpret_cast<const f32x4_u *>(wbase + int64_t(s) * p.a3 * 64 + 32 * it);
@@ -542,31 +545,63 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     __builtin_amdgcn_wave_barrier();            // (the next stage's weights come after these reads: one wave, in order)
   }
   // register i of block t: row 8 (i / 4) + 4 h + i % 4 of the wave's 32 (vertex ub + row / 4, row % 4), column 32 t + j
-  uint64_t again = 0;
+  uint32_t again[2] = {0, 0};                   // sums that are not finite: bit 16 (t % 2) + i of word t / 2
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
     add_up(acc[t], cor[t]);
-    const bool stored = n0 + 32 * t + j < p.N;
+    const bool in = n0 + 32 * t + j < p.N;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int64_t m = ((int64_t(u1) * p.a2 + (i % 4) / p.a4) * p.a3 + ub + 2 * (i / 4) + h) * p.a4 + (i % 4) % p.a4;
-      if (stored) __builtin_nontemporal_store(acc[t][i], p.O + m * p.ldO + n0 + 32 * t + j);
-      if (stored && !(acc[t][i] * 0.f == 0.f)) again |= uint64_t(1) << (16 * t + i);
+      const bool finite = acc[t][i] * 0.f == 0.f;
+      if (in && finite) __builtin_nontemporal_store(acc[t][i], p.O + m * p.ldO + n0 + 32 * t + j);
+      if (in && !finite) again[t / 2] |= 1u << (16 * (t % 2) + i);
     }
   }
-  while (again) {   // one sum at a time from its kept weights (none, for ordinary operands)
-    const int e = __builtin_ctzll(again), t = e >> 4, i = e & 15, r = i % 4, ui = ub + 2 * (i / 4) + h;
-    again &= again - 1;
-    const int64_t n = n0 + 32 * t + j;
-    float sum = 0.f;
-    for (int j1 = 0; j1 < p.d1; ++j1)
-      for (int v2 = 0; v2 < p.c2; ++v2) {
-        const int64_t k0 = (int64_t(p.adj0[u1 * p.d1 + j1]) * p.c2 + v2) * 32;
-        const float *w = p.Wp + ((int64_t(u1) * nstages + j1 * p.c2 + v2) * p.a3 + ui) * 64 + r;
-        for (int b = 0; b < KS; ++b) sum = __builtin_fmaf(w[4 * b], p.I[(k0 + p.rowoff[ui * KS + b]) * p.ldI + n], sum);
+  if (!__builtin_amdgcn_ballot_w64((again[0] | again[1]) != 0)) return;   // (no barrier from here on)
+  // The sums left out, from the kept weights alone and in the order of spmm_mfma: a G_i vertex of the wave after the other,
+  // four rows x 64 columns per MFMA, the lane on the columns lane and 64 + lane.
+  for (int v = 0; v < 8; ++v) {
+    uint32_t need[2];                           // rows of the vertex that miss the lane's columns
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      need[x] = (uint32_t(__builtin_amdgcn_ds_bpermute(((v & 1) * 32 + j) * 4, int(again[x]))) >> (16 * h + 4 * (v >> 1))) & 15u;
+    if (!__builtin_amdgcn_ballot_w64((need[0] | need[1]) != 0)) continue;
+    const int ui = ub + v;
+    const int ro = p.rowoff[ui * KS + lane % KS] * row_bytes;
+    const float *const wv = p.Wp + ((int64_t(u1) * nstages) * p.a3 + ui) * 64 + lane;
+    float wnext, bnext[2][KS];
+    auto load_stage = [&](int s) {
+      const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+      wnext = wv[int64_t(s) * p.a3 * 64];
+#pragma unroll
+      for (int b = 0; b < KS; ++b)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+          bnext[x][b] = __uint_as_float(
+              __builtin_amdgcn_raw_buffer_load_b32(rb, __builtin_amdgcn_readlane(ro, b) + (64 * x + lane) * 4, 0, 0));
+    };
+    f32x4 sum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    load_stage(0);
+    for (int s = 0; s < nstages; ++s) {
+      const float w = wnext;
+      float b[2][KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) b[0][k] = bnext[0][k], b[1][k] = bnext[1][k];
+      load_stage(s + 1 < nstages ? s + 1 : s);
+      static_for<0, KS>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) sum[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(w, b[x][k], sum[x], 4, k, 0);
+      });
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t m = ((int64_t(u1) * p.a2 + r / p.a4) * p.a3 + ui) * p.a4 + r % p.a4;
+        if (need[x] >> r & 1u) p.O[m * p.ldO + n0 + 64 * x + lane] = sum[x][r];
       }
-    const int64_t m = ((int64_t(u1) * p.a2 + r / p.a4) * p.a3 + ui) * p.a4 + r % p.a4;
-    p.O[m * p.ldO + n] = sum;
   }
 }
 

@@ -490,6 +490,65 @@ def test_lds_family_split_operands(rows, cols, deg):
     assert (np.abs(np.where(fin, got, 0).astype(np.float64) - np.where(fin, ref, 0)) <= 1e-6 * scale).all()
 
 
+@pytest.mark.parametrize("rows,cols,deg", [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1)), ((4, 1, 64, 4), (8, 3, 32, 1), (2, 3, 16, 1)),
+                                           ((2, 2, 64, 2), (4, 2, 16, 2), (2, 2, 4, 2))])
+def test_lds_family_split_operands_repair_sums_as_the_fp32_kernel(rows, cols, deg):
+    """Columns that split operands cannot give (infinities, operands of 2^105 and more with finite sums, columns that are
+    not numbers throughout, the last column of a partly empty tile): the sums are the fp32 kernel's, bit for bit."""
+    w = wl.Workload("lds_repair", rows, cols, deg, 333, wl.F32, 41, 42, 43, 1.0)
+    run = lambda X, v: gh.library_spmm(w, vl, X, kernel=MFMA, tune=(0,) * 8 + (v,), tag="repaired sums")[0]
+    for N in (64, 132, 300):
+        vl, Il, vf, If = gh.host_inputs(w, N)
+        bad, cols_bad = Il.copy(), [0, 5, 31, 37, 63, N - 1]
+        bad[3, 0], bad[w.K - 1, 5], bad[:, 31] = np.inf, -np.inf, np.nan
+        bad[:, [37, 63]] *= np.float32(2.0 ** 110)
+        bad[17, N - 1] = np.float32(3e38)
+        clean, got, ref = run(Il, 2), run(bad, 2), run(bad, 1)
+        others = np.ones(N, bool)
+        others[cols_bad] = False
+        assert np.array_equal(got[:, others].view(np.uint32), clean[:, others].view(np.uint32))
+        assert np.isfinite(ref[:, 37]).all()
+        for n in cols_bad:   # (tiles without the operand of 3e38 keep the split's sums)
+            same = got[:, n].view(np.uint32) == ref[:, n].view(np.uint32)
+            kept = got[:, n].view(np.uint32) == clean[:, n].view(np.uint32)
+            assert (same | kept | np.isnan(got[:, n]) & np.isnan(ref[:, n])).all()
+            assert same.all() or n not in (37, 63)
+
+
+def test_lds_family_split_operands_repair_costs_a_few_products():
+    """A product whose inputs are not numbers at all, or in one column, takes a few times an ordinary one's time: the
+    repair runs on the matrix core, a stage's loads ahead (a serial loop took 15 and 5 times)."""
+    import torch
+    w = wl.sdmm4096_table2(2, 2)
+    N = 1536
+    mask = rb.rbgp_make_mask(w.rows, w.cols, w.row_deg, w.mask_seed)
+    rb.rbgp_mask_set_kernel(mask, MFMA)
+    stream = torch.cuda.current_stream().cuda_stream
+    packed = torch.randn(rb.rbgp_packed_bytes(mask, rb.F32) // 4, device="cuda:0")
+    I, O = torch.rand((w.K, N), device="cuda:0"), torch.empty((w.M, N), device="cuda:0")
+
+    def microseconds():
+        times = []
+        for _ in range(9):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(10):
+                rb.rbgp_spmm(mask, rb.F32, w.M, w.K, N, packed.data_ptr(), I.data_ptr(), N, O.data_ptr(), N, stream)
+            e[1].record()
+            torch.cuda.synchronize()
+            times.append(100 * e[0].elapsed_time(e[1]))
+        return sorted(times)[4]
+
+    usual = microseconds()
+    I[5, 77] = float("inf")
+    one = microseconds()
+    I.fill_(float("nan"))
+    every = microseconds()
+    print(f"[gpu] us: {usual:.0f}, one infinity {one:.0f}, not a number throughout {every:.0f}", flush=True)
+    assert torch.isnan(O).all()
+    assert one < 3.5 * usual and every < 7 * usual
+
+
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 def test_kernels_of_row_pairs_on_the_fused_convolution(dtype):
     """The 3x3 convolution through the split-operand and the shared-column kernels: images of 8 and 16 columns, a last
