@@ -66,7 +66,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_bf16_shared(RegParams p) {
   const int tbu = p.conv ? int(uint32_t(tb < 0 ? 0 : tb) / 9u) : (tb < 0 ? 0 : tb);
   const uint64_t i_first = reinterpret_cast<uint64_t>(p.I) + uint64_t(uint32_t(tbu)) * p.row_bytes + n0b;
   const int ib_lo = int(uint32_t(i_first)), ib_hi = int(uint32_t(i_first >> 32));
-  const int rows_left = p.last_row - tbu < p.src_rows ? p.last_row - tbu : p.src_rows;
+  // (to the last column of the stage's last row, so that an extent stays below 2^31: SRC rows of ldI do, checked by the host)
+  const int rows_left = p.last_row - tbu < p.src_rows - 1 ? p.last_row - tbu : p.src_rows - 1;
   const int ib_ext = (tb >= 0 && valid) ? int(uint32_t(rows_left) * p.row_bytes + (p.n_bytes - n0b)) : 0;
   const int aoff = tf >= 0 ? ((u1 * p.fpm + tf) * p.a3 + u3) * p.frag_bytes : kOob;
   float *const out = p.O;

@@ -549,6 +549,37 @@ def test_lds_family_split_operands_repair_costs_a_few_products():
     assert one < 3.5 * usual and every < 7 * usual
 
 
+@pytest.mark.parametrize("dtype,variant", [(wl.F32, 2), (wl.F32, 3), (wl.BF16, 2), (wl.BF16, 4)])
+def test_padding_steps_of_row_pairs_read_nothing(dtype, variant):
+    """Rows of I so far apart that the rows of one stage and the columns of the next one pass 2^31 bytes: the padding
+    steps of a stage (20 of 32 are real) must not bring an infinity of another row and column into the sums."""
+    import torch
+    w = wl.Workload("wide_rows", (2, 128, 2, 1), (2, 1, 10, 2), (1, 1, 10, 2), 400, dtype, 31, 32, 33, 1.0)
+    N, es = 400, 2 if dtype == wl.BF16 else 4
+    ld = (2 ** 31 // es - 200) // 20 // 8 * 8              # (a stage spans 20 rows)
+    assert (20 * ld + 128) * es < 2 ** 31 < (20 * ld + N) * es
+    vl, Il, vf, If = gh.host_inputs(w, N)
+    mask = gh.make_mask(w)
+    rb.rbgp_mask_set_kernel(mask, REG)
+    rb.rbgp_mask_tune(mask, rb.TUNE_SPLIT_OPERANDS if dtype == wl.F32 else rb.TUNE_SHARED_COLUMNS, variant)
+    stream = torch.cuda.current_stream().cuda_stream
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, dtype), dtype=torch.uint8, device="cuda:0")
+    rb.rbgp_pack(mask, dtype, np.ascontiguousarray(vl), packed.data_ptr(), stream)
+    I = torch.zeros((w.K, ld), dtype=torch.float32 if dtype == wl.F32 else torch.int16, device="cuda:0")
+    I[:, :N] = torch.from_numpy(Il.view(np.int16) if dtype == wl.BF16 else Il).to("cuda:0")
+    col = 2 ** 31 // es - 20 * ld + 40                      # what a step at byte 2^31 would read for column 40
+    I[20, col] = float("inf") if dtype == wl.F32 else 0x7F80
+    O = torch.full((w.M, N), float("nan"), dtype=torch.float32, device="cuda:0")
+    print(f"[gpu] padding steps, rows of {ld} elements, variant {variant}", flush=True)
+    rb.rbgp_spmm(mask, dtype, w.M, w.K, N, packed.data_ptr(), I.data_ptr(), ld, O.data_ptr(), N, stream)
+    out = O.cpu().numpy()
+    ref, den = gh.oracle_spmm(w, vf, If)
+    others = np.arange(N) != col
+    assert col < N
+    assert np.isfinite(out[:, others]).all()
+    assert orc.normalised_error(out[:, others], ref[:, others], den[:, others]) <= 4e-6
+
+
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 def test_kernels_of_row_pairs_on_the_fused_convolution(dtype):
     """The 3x3 convolution through the split-operand and the shared-column kernels: images of 8 and 16 columns, a last
