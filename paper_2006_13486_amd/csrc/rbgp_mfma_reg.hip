@@ -839,22 +839,38 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     int pick = tsh - 2;
     if (tsh >= 2 && !fits(pick)) return RBGP_EUNSUPPORTED;
     if (tsh == 0 && can) {
-      // Measured on the masks of Tables 2 and 3 (us; spmm_reg_bf16 -> 1 x 1 / 2 x 1 / 4 x 1 / 1 x 2 / 2 x 2 waves x row
-      // pairs): stages of 64 steps, density 1/8, four rows per column set, N = 4096 85 -> 80 / 66 / 56 / 52 / 45, 2048
-      // 48 -> 43 / 36 / 27 / 40 / 34, 1000 28 -> 31 / 28 / 24 / 38 / 34, 700 23 -> 31 / 27 / 22 / 37 / 34, 400 16 -> 20 at best;
-      // 64 rows per column set, N = 4096 86 -> 52 (1 x 2), 1531 50 -> 43 (2 x 1); 32 rows 74 -> 80 at lists of 16, at 1/16 52 -> 47 (1 x 1).
-      // (spmm_reg_bf16 has since left out the padding of these stages: 9-14 % off its times.)  So: the largest tile that
-      // leaves each of 256 CUs one and a half workgroups, the tall 4 x 1 already with one.  Short stages (32 steps, where spmm_reg_bf16 takes four row groups of long lists): N = 4096
-      // 91 -> 84.5 (2 x 2), 2048 58 -> 47 (4 x 1), 1531 52 -> 54, 1000 30 -> 37; transposed VGG19 layers, short lists:
-      // L3 88 -> 66, L6 60 -> 53, L9 51 -> 44 (1 x 2, 2 x 2), L6 at 37 images 26 -> 28 (2 x 1).  With O in bf16 the old kernel
-      // has half of the stores: 4096 columns of long lists 74 -> 81, 1 x 1 at 2048 38 -> 41, 4 x 1 at 1000 11.0 -> 12.5.
+      // 512 workgroups run at a time (two per CU), and a kernel's time hardly depends on how many of them there are: a shape
+      // is worth its while when its tiles nearly fill a round, and no longer when they have just begun the second.
+      // Measured on the masks of Tables 2 and 3 in us, spmm_reg_bf16 against the shapes (waves along rows x row pairs per wave):
+      //  stages of 64 steps, eight tile rows and more with one list (density 1/8, four rows per column set; lists of 16):
+      //    N = 1000 24.6, 4 x 1 23.1 (256 workgroups); 1536 31.8, 26.3; 2048 48.8, 26.8, 2 x 2 33.8; 2176 46.7, 43.7 (544
+      //    workgroups), 2 x 2 37.0 (288); 3072 55.5, 47.1, 42.9; 4096 76.3, 51.8, 46.2;
+      //    O in bf16 (half of the stores, and the old kernel's time with them): 1000 20.5, 22.4; 1280 (320) 30.2, 24.8; 2048
+      //    31.4, 25.5; 2560 43.2, 42.8, 38.5; lists of 8 (1/16) 4 x 1 at 1000 9.2, 10.7, at 1152 11.6, 11.0;
+      //  the same, four tile rows (two rows per column set): 1280 32.0, 2 x 1 29.2 (320); 1536 32.7, 30.1; 2048 43.2, 34.3;
+      //    2560 50.6, 58.3 (640), 1 x 2 46.9 (320); 3072 56.7, 60.7, 48.7; 4096 66.3, 60.6, 49.5; O in bf16: 1280 30.3, 29.3;
+      //    2560 44.3, 57.3, 46.0; 3072 45.3, 59.9, 48.4 (384); 3200 56.9, 58.3, 47.9 (448);
+      //  two tile rows: lists of 16 74, 1 x 1 80; of 8 52, 47;
+      //  stages of 32 steps, eight tile rows (1/4; spmm_reg_bf16 takes four row groups): 1792 41.2, 4 x 1 43.2 (448); 1920 42.5,
+      //    44.0; 2048 58.4, 44.0 (512); 2176 68.0, 65.7, 2 x 2 66.4; 2816 67.0, 72.8, 69.2; 4096 88.1, 88.7, 75.9;
+      //  transposed VGG19 layers, short lists: L3 88, 66; L6 60, 53; L9 51, 44 (1 x 2, 2 x 2), L6 at 37 images 26, 28 (2 x 1).
+      // With O in bf16, long lists of short stages stay where they are (4096 columns 74, 81).
       const bool long_stages = pl.KC > 36, lists = long_stages || !out_bf16 || m->reg_clusters.max_stages < 32;
-      pick = fits(4) && wgs(4) >= 384 && lists                                              ? 4
-             : fits(3) && !fits(2) && wgs(3) >= 384 && lists                                ? 3
-             : fits(2) && wgs(2) >= (long_stages ? (!out_bf16 ? 256 : m->reg_clusters.max_stages >= 8 ? 320 : 384) : 448) && (long_stages || !out_bf16) ? 2
-             : fits(1) && !fits(2) && long_stages && wgs(1) >= 384                          ? 1
-             : fits(0) && !fits(1) && long_stages && !out_bf16 && m->reg_clusters.max_stages < 16 && wgs(0) >= 512 ? 0
-                                                                                            : -1;
+      const int64_t round = 512;
+      const int64_t tall = !long_stages ? (m->reg_clusters.max_stages >= 32 ? round : 448)
+                           : !out_bf16  ? 256
+                                        : m->reg_clusters.max_stages >= 8 ? 320 : 384;
+      // (O in bf16 and rows of whole 8-byte stores: spmm_reg_bf16 needs 43 us where misaligned rows take it 55)
+      const bool quick_stores = out_bf16 && ldO % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 8 == 0;
+      if (fits(2)) {
+        if (lists && (wgs(4) >= 384 || wgs(2) > round)) pick = 4;
+        else if ((long_stages || !out_bf16) && wgs(2) >= tall && wgs(2) <= round) pick = 2;
+      } else if (fits(1)) {
+        if (lists && ((long_stages && wgs(1) > round && !quick_stores) || wgs(3) >= (long_stages ? 448 : 384))) pick = 3;
+        else if (long_stages && wgs(1) >= 384 && wgs(1) <= round) pick = 1;
+      } else if (fits(0)) {
+        if (long_stages && !out_bf16 && m->reg_clusters.max_stages < 16 && wgs(0) >= 512) pick = 0;
+      }
     }
     if (pick >= 0 && tsh != 1) {
       share_rv = shapes[pick].rv;
