@@ -950,9 +950,20 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // 43.2 -> 40.4) nor lists of 32 blocks and more (L3 at 64 images 27.9 -> 26.4; 1/16, four rows, N = 512 24.4 -> 22.7).
       const int64_t enough = blocks >= 64 ? 1024 : 2048;
       const bool full_round = (waves << 2) == enough && (blocks >= 64 ? pl.KC > 36 : blocks < 32);
+      // Short lists of 32-step stages (transposed layers at 1/2), whose fp32 waves cost mostly latency, two of them on a SIMD
+      // little more than one: 8 blocks only where lists stay whole (L6 at 32 images, split in two, 19.6 -> 21.9), and not with
+      // a second round half empty (L6 at 64 images 30.7 -> 29.9, at 80 40.0 -> 45.5, 96 42 -> 45.8, 112 50.3 -> 47.2, 128
+      // 54 -> 47.5); 16 blocks not where only these kernels need a second round (L8 at 64 images 21.1 -> 20.3, 72 to 112
+      // 21-22.7 -> 28.4-30, 128 31.5 -> 30.8).
+      bool late_round = false;
+      if (pl.KC <= 32 && blocks > 4 && blocks < 32) {
+        const int64_t fp32_waves = int64_t(pl.TR / 2) * m->a[2] * ((N + 63) / 64);
+        late_round = blocks < 16 ? lg > 0 || (waves > 2304 && waves < 3840)
+                                 : fp32_waves <= 1024 ? (waves << lg) > 2048 : fp32_waves <= 2048 && (waves << lg) > 2304;
+      }
       if (can4 && waves / 4 >= 320)
         split_rw = 4;
-      else if ((waves << lg) >= enough && !full_round)
+      else if ((waves << lg) >= enough && !full_round && !late_round)
         split_rw = 1;
     }
     if (split_rw) {
