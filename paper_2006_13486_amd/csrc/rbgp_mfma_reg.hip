@@ -931,10 +931,12 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     // (waves that share columns pass a barrier per round: no split stage lists)
     const bool can4 = can && pl.fold % 8 == 0 && tab->max_stages <= kRegWaveStages && !tune[RBGP_TUNE_K_SPLIT];
     if ((tsp == 2 && !can) || (tsp == 3 && !can4)) return RBGP_EUNSUPPORTED;
-    // waves of a list: enough for two per SIMD, while each keeps four blocks of 16 steps to amortise its start and stores
+    // waves of a list: enough for two per SIMD, while each keeps four blocks of 16 steps to amortise its start and stores;
+    // a split in two that leaves a fifth of those places empty is better than one in four that needs a second round for
+    // them (us, in two / in four: L2 at 112 images 25.5 / 28.4, L3 41.2 / 44.8; 1/16, four rows, N = 896 35.8 / 37.8)
     const int64_t blocks = int64_t(tab->max_stages) * ((pl.KCR + 15) / 16);
     int lg = 0;
-    while (lg < 2 && ((kRegWaveStages << lg) < tab->max_stages || ((waves << lg) < 2048 && (blocks >> (lg + 1)) >= 4))) ++lg;
+    while (lg < 2 && ((kRegWaveStages << lg) < tab->max_stages || ((waves << lg) < (lg == 1 ? 1600 : 2048) && (blocks >> (lg + 1)) >= 4))) ++lg;
     if (tsp >= 2) {
       split_rw = tsp == 2 ? 1 : 4;
     } else if (tsp == 0 && can && rbgp_reg_split_cycles(m) < rbgp_reg_fp32_cycles(m)) {
@@ -948,7 +950,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // 80 40.5 -> 37.5; L9 at 128 46.0 -> 47.1; one tile column, 64 steps, N = 256 23.9 -> 24.7), as do the shortest lists
       // (L2 at 64 images, 20 blocks, 16.5 -> 17.0, at 80 27.5 -> 23.8), but not stages of 32 steps (1/4, one row, N = 256
       // 43.2 -> 40.4) nor lists of 32 blocks and more (L3 at 64 images 27.9 -> 26.4; 1/16, four rows, N = 512 24.4 -> 22.7).
-      const int64_t enough = blocks >= 64 ? 1024 : 2048;
+      const int64_t enough = blocks >= 64 ? 1024 : lg == 1 ? 1600 : 2048;
       const bool full_round = (waves << 2) == enough && (blocks >= 64 ? pl.KC > 36 : blocks < 32);
       // Short lists of 32-step stages (transposed layers at 1/2), whose fp32 waves cost mostly latency, two of them on a SIMD
       // little more than one: 8 blocks only where lists stay whole (L6 at 32 images, split in two, 19.6 -> 21.9), and not with
