@@ -465,6 +465,34 @@ def test_bf16_register_family_shared_columns(idx, out_bf16):
                 assert np.array_equal(out, wl.bf16_bits_as_f32(wl.to_bf16_bits(full)))
 
 
+# masks whose merged tile columns are walked in stages of 64 steps, in the packed layout of 72: one stage, four, sixteen
+STAGES_OF_64 = [((8, 2, 2, 2), (8, 1, 4, 4), (8, 1, 2, 4)), ((8, 2, 2, 2), (32, 1, 4, 4), (32, 1, 2, 4)),
+                ((8, 4, 2, 2), (64, 2, 4, 4), (64, 2, 2, 4))]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("idx", range(len(STAGES_OF_64)))
+def test_stages_of_64_steps_in_the_layout_of_72(idx, dtype):
+    """Every kernel that leaves out the padding of these stages (its weight fragments and row tables are those of 72
+    steps): bf16 on 64 and 128 columns, one and two row groups, one and two register sets; fp32 with one and two row
+    groups; whole and split lists, odd widths, padded rows."""
+    rows, cols, deg = STAGES_OF_64[idx]
+    w = wl.Workload(f"stages64_{idx}", rows, cols, deg, 131, dtype, 51 + idx, 52, 53, 1.0)
+    assert rb.rbgp_mask_reg_plan(gh.make_mask(w))[14] == 16      # (merged: whole groups of 16 rows)
+    ks = (0, 2) if idx else (0,)
+    if dtype == wl.F32:
+        tunes = [(0, 0, 0, 0, g, s, 0, rs, 1, 0) for g, rs in ((1, 1), (1, 2), (2, 0)) for s in ks]
+    else:
+        tunes = [(0, c, 0, 0, g, s, 0, rs, 0, 1) for c, rs in ((64, 0), (128, 1), (128, 2)) for g in (1, 2) for s in ks]
+    for N, pad in ((1, 7), (131, 5), (328, 8)):
+        vl, Il, vf, If = gh.host_inputs(w, N)
+        ref, den = gh.oracle_spmm(w, vf, If)
+        for tune in tunes:
+            out, used = gh.library_spmm(w, vl, Il, kernel=REG, tune=tune, ld_pad=pad, tag="stages of 64")
+            assert used == REG
+            assert orc.normalised_error(out, ref, den) <= 4e-6
+
+
 @pytest.mark.parametrize("rows,cols,deg", [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1)), ((4, 1, 32, 4), (8, 3, 32, 1), (2, 3, 16, 1)),
                                            ((2, 2, 64, 2), (4, 2, 16, 2), (2, 2, 4, 2))])
 def test_lds_family_split_operands(rows, cols, deg):
