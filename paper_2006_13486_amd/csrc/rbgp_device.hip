@@ -384,7 +384,10 @@ bool mfma_covers(const rbgp_mask *m) {
 // LDS family on every VGG19 layer shape, also where several G_i vertices share a row of I),
 // else the LDS family, else GENERIC.
 // Estimated seconds per column of I: one of 1024 SIMDs at ~2.07 GHz serves 64 columns per instruction.  The
-// constants are fitted to the 4096^3 products of Tables 2 and 3 (27 masks, each on every family that covers it).
+// constants are fitted to the 4096^3 products of Tables 2 and 3 (27 masks, each on every family that covers it) on the
+// fp32 MFMA forms; the kernels on split operands (spmm_reg_split*, spmm_mfma_split) and those that share columns are not
+// in them.  One mask of Tables 2 and 3 would go elsewhere with them: G_o and G_i at 1/4, four rows per column set, on the
+// filled mask (us, LDS family -> filled: 64 columns 46 -> 9, 512 46 -> 34, 1000 61 -> 59, 1531 84 -> 77, 4096 168 -> 168).
 // Register family: a wave walks the stages of its (cluster, G_i vertex) pair; a stage of KC steps costs KC 16-row
 // MFMAs of ~36 cycles (fp32), or ~8 cycles per step in bf16 (the loads of the stage; its 32-step MFMAs hide behind
 // them, a second MFMA block for the remainder of a stage does not), plus what does not overlap.
@@ -775,7 +778,8 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
   const int epc = bf16 ? 8 : 4;
   if ((reinterpret_cast<uintptr_t>(dev_I) & 15) || (ldI % epc)) return RBGP_ESHAPE;
   // fp32 on the bf16 matrix core (spmm_mfma_split): four rows per column set, 32 rows of I per stage of which G_i keeps 8 or
-  // 16, whole workgroups of 32 G_i vertices, and five workgroups for eight CUs.  4096 x 4096, G_o and G_i at 1/4, us, spmm_mfma
+  // 16 (16: where a caller asks for this family; AUTO runs such masks filled), whole workgroups of 32 G_i vertices, and
+  // five workgroups for eight CUs.  4096 x 4096, G_o and G_i at 1/4, us, spmm_mfma
   // -> spmm_mfma_split: N = 16 46 -> 54, 512 49 -> 60 (128 workgroups), 600 85 -> 61 (160), 1000 88 -> 64, 1531 126 -> 90, 2048
   // 111 -> 95, 4096 203 -> 176.  (With a non-finite column at 1531 240, without a finite one 260: spmm_mfma's time does not
   // depend on the values.)

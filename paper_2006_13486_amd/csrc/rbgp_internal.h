@@ -61,10 +61,10 @@ struct rbgp_reg_plan {
   int64_t packed_elems_bf16 = 0;  // bf16 layout
 };
 
-// Steps of a stage the kernels walk: the stage size, except for stages of up to 64 steps in the layout of 72 with one tile
-// row per group (runs of 64 on merged tile columns), whose padding past 64 the kernels of 64 steps leave out.  4096 x 4096, density 1/8, one row per column
-// set, us with it -> without: fp32 64 columns 10.2 -> 9.9, 100 15.9 -> 14.7; bf16 64 8.1 -> 7.0, 300 17.1 -> 15.1, 1024 29.7 ->
-// 27.2.
+// Steps of a stage the kernels walk: the stage size, except for stages of up to 64 steps in the layout of 72 with one
+// tile row per group (runs of 64 on merged tile columns), whose padding past 64 the kernels of 64 steps leave out.
+// 4096 x 4096, density 1/8, one row per column set, us with it -> without: fp32 64 columns 10.2 -> 9.9, 100 15.9 -> 14.7;
+// bf16 64 8.1 -> 7.0, 300 17.1 -> 15.1, 1024 29.7 -> 27.2.
 inline int rbgp_reg_walk(const rbgp_reg_plan &p) { return p.KC == 72 && p.KCR <= 64 && p.RS == 16 ? 64 : p.KC; }
 
 // fp32 register-streaming kernels: which step of a stage's contraction list

@@ -841,7 +841,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     if (tsh == 0 && can) {
       // 512 workgroups run at a time (two per CU), and a kernel's time hardly depends on how many of them there are: a shape
       // is worth its while when its tiles nearly fill a round, and no longer when they have just begun the second.
-      // Measured on the masks of Tables 2 and 3 in us, spmm_reg_bf16 against the shapes (waves along rows x row pairs per wave):
+      // Measured on the masks of Tables 2 and 3 in us, spmm_reg_bf16 against the shapes (waves along rows x row pairs each):
       //  stages of 64 steps, eight tile rows and more with one list (density 1/8, four rows per column set; lists of 16):
       //    N = 1000 24.6, 4 x 1 23.1 (256 workgroups); 1536 31.8, 26.3; 2048 48.8, 26.8, 2 x 2 33.8; 2176 46.7, 43.7 (544
       //    workgroups), 2 x 2 37.0 (288); 3072 55.5, 47.1, 42.9; 4096 76.3, 51.8, 46.2;
@@ -851,9 +851,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       //    2560 50.6, 58.3 (640), 1 x 2 46.9 (320); 3072 56.7, 60.7, 48.7; 4096 66.3, 60.6, 49.5; O in bf16: 1280 30.3, 29.3;
       //    2560 44.3, 57.3, 46.0; 3072 45.3, 59.9, 48.4 (384); 3200 56.9, 58.3, 47.9 (448);
       //  two tile rows: lists of 16 74, 1 x 1 80; of 8 52, 47;
-      //  stages of 32 steps, eight tile rows (1/4; spmm_reg_bf16 takes four row groups): 1792 41.2, 4 x 1 43.2 (448); 1920 42.5,
-      //    44.0; 2048 58.4, 44.0 (512); 2176 68.0, 65.7, 2 x 2 66.4; 2816 67.0, 72.8, 69.2; 4096 88.1, 88.7, 75.9;
-      //  transposed VGG19 layers, short lists: L3 88, 66; L6 60, 53; L9 51, 44 (1 x 2, 2 x 2), L6 at 37 images 26, 28 (2 x 1).
+      //  stages of 32 steps, eight tile rows (1/4; spmm_reg_bf16 takes four row groups): 1792 41.2, 4 x 1 43.2 (448);
+      //    1920 42.5, 44.0; 2048 58.4, 44.0 (512); 2176 68.0, 65.7, 2 x 2 66.4; 2816 67.0, 72.8, 69.2; 4096 88.1, 88.7,
+      //    75.9; lists of 16 (G_o at 1/8, G_i at 1/2) 4 x 1 at 1792 23.4, 17.2;
+      //  transposed VGG19 layers, short lists: L3 58, 38; L6 32.5, 26; L9 25, 19 (1 x 2, 2 x 2); L6 at 37 images 26, 28 (2 x 1).
       // With O in bf16, long lists of short stages stay where they are (4096 columns 74, 81).
       const bool long_stages = pl.KC > 36, lists = long_stages || !out_bf16 || m->reg_clusters.max_stages < 32;
       const int64_t round = 512;
@@ -936,7 +937,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     // them (us, in two / in four: L2 at 112 images 25.5 / 28.4, L3 41.2 / 44.8; 1/16, four rows, N = 896 35.8 / 37.8)
     const int64_t blocks = int64_t(tab->max_stages) * ((pl.KCR + 15) / 16);
     int lg = 0;
-    while (lg < 2 && ((kRegWaveStages << lg) < tab->max_stages || ((waves << lg) < (lg == 1 ? 1600 : 2048) && (blocks >> (lg + 1)) >= 4))) ++lg;
+    while (lg < 2 && ((kRegWaveStages << lg) < tab->max_stages ||
+                      ((waves << lg) < (lg == 1 ? 1600 : 2048) && (blocks >> (lg + 1)) >= 4))) ++lg;
     if (tsp >= 2) {
       split_rw = tsp == 2 ? 1 : 4;
     } else if (tsp == 0 && can && rbgp_reg_split_cycles(m) < rbgp_reg_fp32_cycles(m)) {

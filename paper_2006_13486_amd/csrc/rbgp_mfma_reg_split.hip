@@ -1,8 +1,8 @@
 // fp32 product of the register-streaming family on the bf16 matrix core: every fp32 operand is split into three
-// bf16 numbers (8 + 8 + 8 mantissa bits: x = x0 + x1 + x2 exactly, short of underflow) and the six products that
-// reach fp32 accuracy -- x0y0, x0y1, x1y0, x1y1, x0y2, x2y0; the rest is below 2^-26 of |xy| -- go through
-// v_mfma_f32_32x32x16_bf16, which multiplies 16 times as many operands per cycle as the fp32 forms: 2.7 times
-// fewer matrix-core cycles for the six of them.
+// bf16 numbers (8 + 8 + 8 mantissa bits: x = x0 + x1 + x2 exactly) and the six products that reach fp32 accuracy --
+// x0y0, x0y1, x1y0, x1y1, x0y2, x2y0; the rest is at most about 2^-24 of |xy|, an fp32 rounding, as |x1| <= 2^-8 |x|
+// and |x2| <= 2^-17 |x| -- go through v_mfma_f32_32x32x16_bf16, which multiplies 16 times as many operands per cycle
+// as the fp32 forms: 2.7 times fewer matrix-core cycles for the six of them.
 //
 // For masks whose 16-row MFMA groups come in pairs with one stage list (rows of G_r moved into the tile-row index:
 // filled masks, merged columns, layers at density 1/2).  A wave owns 32 rows (two tile rows), one G_i vertex and 128
