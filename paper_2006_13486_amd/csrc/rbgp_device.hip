@@ -50,6 +50,7 @@ struct rbgp_device_state {
   int device = -1;
   int32_t *adj[4] = {nullptr, nullptr, nullptr, nullptr};
   int32_t *rowoff = nullptr;             // [a_i][KS]: stage-relative I row of each contraction step
+  bool one_of_two = false;               // no G_i vertex has steps on rows k and k + 16 of a stage (k < 16)
   // pack permutation per kernel family and dtype; second half: composed with the order of the
   // original mask (transposed masks, values given in the original's canonical order)
   int32_t *perm[4 * RBGP_NUM_KERNELS] = {};
@@ -496,6 +497,7 @@ int ensure_device(const rbgp_mask *m) {
   // the state is touched only when every table is on the device (adj[0] marks "built")
   int32_t *adj[4] = {nullptr, nullptr, nullptr, nullptr}, *rowoff = nullptr;
   int rc = RBGP_OK;
+  bool one_of_two = true;
   for (int i = 0; i < 4 && !rc; ++i) rc = upload(m->adj[i], &adj[i]);
   if (!rc && m->plan.ok) {
     const rbgp_mfma_plan &p = m->plan;
@@ -504,6 +506,14 @@ int ensure_device(const rbgp_mask *m) {
       for (int kk = 0; kk < p.KS; ++kk)
         ro[size_t(u3) * p.KS + kk] = m->adj[2][size_t(u3) * m->d[2] + kk / m->c[3]] * m->c[3] + kk % m->c[3];
     rc = upload(ro, &rowoff);
+    for (int u3 = 0; u3 < m->a[2]; ++u3) {
+      uint32_t seen = 0;
+      for (int kk = 0; kk < p.KS; ++kk) {
+        const uint32_t bit = 1u << (ro[size_t(u3) * p.KS + kk] & 15);
+        if (seen & bit) one_of_two = false;
+        seen |= bit;
+      }
+    }
   }
   if (rc) {
     for (int32_t *t : adj)
@@ -512,6 +522,7 @@ int ensure_device(const rbgp_mask *m) {
     return rc;
   }
   dev->rowoff = rowoff;
+  dev->one_of_two = one_of_two;
   for (int i = 3; i >= 0; --i) dev->adj[i] = adj[i];
   return RBGP_OK;
 }
@@ -800,7 +811,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
       sp.a1 = m->a[0]; sp.a2 = m->a[1]; sp.a3 = m->a[2]; sp.a4 = m->a[3]; sp.d1 = m->d[0]; sp.c2 = m->c[1];
       sp.ntiles = int(tiles);
       const int64_t nblocks = 8 * ((tiles + 7) / 8) * m->a[0] * (m->a[2] / 32);
-      hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS), dim3(unsigned(nblocks)), dim3(256), 0, st, sp);
+      hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS, dev->one_of_two), dim3(unsigned(nblocks)), dim3(256), 0, st, sp);
       RBGP_HIP(hipGetLastError());
       return RBGP_OK;
     }

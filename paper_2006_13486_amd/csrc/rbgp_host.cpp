@@ -399,6 +399,31 @@ static rbgp_mask *filled_twin(const rbgp_mask *m, int kind) {
   return t;
 }
 
+std::vector<int32_t> rbgp_reg_pairs(const rbgp_mask *m, const rbgp_mask *t) {
+  const rbgp_reg_plan &p = t->reg;
+  if (!p.ok || p.KCR != 32 || p.KC != 32 || p.MG != 1) return {};
+  const int a3 = m->a[2], c3 = m->c[2], d3 = m->d[2], a4 = t->a[3], c4 = t->c[3];
+  std::vector<char> edge(size_t(a3) * c3, 0);
+  for (int u = 0; u < a3; ++u)
+    for (int j = 0; j < d3; ++j) edge[size_t(u) * c3 + m->adj[2][size_t(u) * d3 + j]] = 1;
+  std::vector<int32_t> out(size_t(p.fold) * 32, 0);
+  for (int f = 0; f < p.fold; ++f)
+    for (int r = 0; r < p.R; ++r) {
+      const int u3 = (f * p.A2 + r / a4) % a3;
+      auto kept = [&](int sg, int kk) { return edge[size_t(u3) * c3 + (sg * p.VC + kk / c4) % c3]; };
+      for (int h = 0; h < 2; ++h)
+        for (int e = 0; e < 8; ++e) {
+          const int kk = 4 * (e % 4) + 2 * h + e / 4;
+          const char lo = kept(0, kk), hi = kept(0, kk + 16);
+          if (lo && hi) return {};
+          for (int sg = 1; sg < p.NSTG; ++sg)   // (one table for all stages)
+            if (kept(sg, kk) != lo || kept(sg, kk + 16) != hi) return {};
+          out[(size_t(f) * 2 + h) * 16 + r] |= (2 * (e % 2) + hi) << (2 * e);
+        }
+    }
+  return out;
+}
+
 void rbgp_plan_filled(rbgp_mask *m) {
   m->filled = nullptr;
   m->filled_kind = 0;
@@ -419,6 +444,7 @@ void rbgp_plan_filled(rbgp_mask *m) {
   }
   m->filled = t0 ? t0 : t1;
   m->filled_kind = t0 ? 0 : 1;
+  if (t0) t0->pairs = rbgp_reg_pairs(m, t0);
 }
 
 // The same mask with part of G_b's rows moved into G_i, for RBGP_KERNEL_MFMA_REG.  Where more than 16 rows share a

@@ -150,6 +150,7 @@ struct rbgp_mask {
                                       //   G_o is complete, the same mask with G_o (x) G_r merged into one tile column
                                       //   J(a_o, 1) (x) J(a_r, c_o c_r), whose stages are longer (then for bf16 as well)
   bool regroup_bf16 = false;          // the bf16 kernels run on `regroup` too
+  std::vector<int32_t> pairs;         // filled masks (of another mask): where the kept weights of a stage are (rbgp_reg_pairs), or empty
 };
 
 inline bool rbgp_reg_tap_grouped(const rbgp_mask *m) {
@@ -237,6 +238,10 @@ void rbgp_reg_cluster(const rbgp_mask *m, int U, rbgp_reg_clusters *out);
 void rbgp_reg_plan_dual(const rbgp_mask *m, rbgp_reg_dual *out);
 // builds m->filled where the register family covers it (called once, when the mask is made)
 void rbgp_plan_filled(rbgp_mask *m);
+// Of the steps k and k + 16 of a 32-step stage of the filled mask t of m (kind 0), every row keeps at most one: [fold][2][16]
+// words, for row r of tile row f and operand half h the 2-bit places of the eight kept steps 4 (e % 4) + 2 h + e / 4 among
+// the groups of four steps (k, k + 16, k + 4, k + 20), the index operand of the sparse MFMA; empty where a row keeps both
+std::vector<int32_t> rbgp_reg_pairs(const rbgp_mask *m, const rbgp_mask *t);
 // builds m->regroup where that factoring uses more rows of the MFMA group (called once, when the mask is made)
 void rbgp_plan_regroup(rbgp_mask *m);
 // canonical index (m * rowdeg + t) of every packed element, -1 for padding

@@ -584,6 +584,7 @@ struct RegState {
   std::vector<int32_t> rowtab_host, rowtab_conv_host;   //   host copies, plain and fused convolution (they travel in the
                                                         //   kernel arguments of the pairing kernel)
   int32_t *rowtab_bf16 = nullptr;  // bf16 kernels: [a_i][NKB*16]
+  int32_t *pairs = nullptr;        // rbgp_mask::pairs
   int32_t *rowtab_conv[2] = {nullptr, nullptr};   // fused convolution, fp32 / bf16: byte offsets for the geometry below
   int32_t *colbase[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [dtype][wide tile]: pixel offsets of the column groups
   int64_t conv_key[2][3] = {{0, 0, 0}, {0, 0, 0}};  // images, height, width of rowtab_conv
@@ -655,6 +656,7 @@ void rbgp_reg_release(void *state) {
   if (!st) return;
   if (st->rowtab) (void)hipFree(st->rowtab);
   if (st->rowtab_bf16) (void)hipFree(st->rowtab_bf16);
+  if (st->pairs) (void)hipFree(st->pairs);
   for (int32_t *t : st->rowtab_conv)
     if (t) (void)hipFree(t);
   for (auto &pair : st->colbase)
@@ -923,6 +925,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // fp32 on the bf16 matrix core (rbgp_mfma_reg_split.hip): waves of two tile rows and 128 columns, each by itself
   // (split_rw = 1) or four of them sharing the columns (4)
   int split_rw = 0;
+  bool sparse = false;   // those that share columns: the sparse MFMA
   {
     const int tsp = tune[RBGP_TUNE_SPLIT_OPERANDS];
     if (tsp < 0 || tsp > 3) return RBGP_EUNSUPPORTED;
@@ -930,6 +933,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const int64_t tiles = (N + 127) / 128, waves = int64_t(pl.TR / 2) * m->a[2] * tiles;
     const bool can = !bf16 && !dual && ident && !knobs && pl.fold % 2 == 0;
     // (waves that share columns pass a barrier per round: no split stage lists)
+    sparse = !conv && !m->pairs.empty();
     const bool can4 = can && pl.fold % 8 == 0 && tab->max_stages <= kRegWaveStages && !tune[RBGP_TUNE_K_SPLIT];
     if ((tsp == 2 && !can) || (tsp == 3 && !can4)) return RBGP_EUNSUPPORTED;
     // waves of a list: enough for two per SIMD, while each keeps four blocks of 16 steps to amortise its start and stores;
@@ -944,9 +948,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     } else if (tsp == 0 && can && rbgp_reg_split_cycles(m) < rbgp_reg_fp32_cycles(m)) {
       // Measured against the fp32 MFMA kernels (us, fp32 -> waves by themselves / sharing): 4096^3 at density 1/4, one
       // row per column set, N = 4096 514 -> 409 / 337, 1531 207 -> 166 / 152, 1000 140 -> 112 / 116, 512 77 -> 64 / 102,
-      // 256 44 -> 40 / 101, 64 14.4 -> 35 / 100; 1/16, four rows, N = 4096 174 -> 120 / 90, 256 15.3 -> 14.9 / 30; VGG19
+      // 256 44 -> 40 / 101, 64 14.4 -> 35 / 100 (sparse MFMA: 75 up to 1024, by themselves 57 at 512, 82 at 640); 1/16, four rows, N = 4096 174 -> 120 / 90, 256 15.3 -> 14.9 / 30; VGG19
       // layers at density 1/2 forward 30.2 -> 25.1 (L2), 52.9 -> 44.6 (L3), 16.1 -> 40.3 (L13: 256 waves).  So: sharing from
-      // five workgroups per four CUs on; by themselves where every SIMD gets two waves, or one with a long list.  Where it
+      // five workgroups per four CUs on, with the sparse MFMA from five per eight; by themselves where every SIMD gets two waves, or one with a long list.  Where it
       // takes a split in four to reach exactly that many waves, the fp32 kernels, whose waves are half as wide, run one full
       // round: stages of 72 or 64 steps then stay there (us, fp32 -> waves by themselves: L6 at 64 images 24.2 -> 27.0, at
       // 80 40.5 -> 37.5; L9 at 128 46.0 -> 47.1; one tile column, 64 steps, N = 256 23.9 -> 24.7), as do the shortest lists
@@ -965,7 +969,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         late_round = blocks < 16 ? lg > 0 || (waves > 2304 && waves < 3840)
                                  : fp32_waves <= 1024 ? (waves << lg) > 2048 : fp32_waves <= 2048 && (waves << lg) > 2304;
       }
-      if (can4 && waves / 4 >= 320)
+      if (can4 && waves / 4 >= (sparse ? 160 : 320))
         split_rw = 4;
       else if ((waves << lg) >= enough && !full_round && !late_round)
         split_rw = 1;
@@ -977,6 +981,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     }
   }
   const bool split = split_rw > 0;
+  if (split_rw > 1 && sparse && !st->pairs) {
+    int rc = upload(m->pairs, &st->pairs);
+    if (rc) return rc;
+  }
   if (!bf16 && !dual && !split && pl.MG == 1 && pl.fold > 1) {
     auto fits = [&](int ng) {
       const RegGroupEntry *g = find_reg_groups(pl.KC, ng);
@@ -1117,6 +1125,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   }
   rp.a2 = pl.A2; rp.a3 = m->a[2]; rp.a4 = m->a[3]; rp.R = pl.R;
   rp.fpm = fpm;
+  rp.pairs = st->pairs; rp.fold = pl.fold;
   rp.tm = pl.A2 * m->a[2] * m->a[3];
   rp.no4 = bf16 ? 32 * rbgp_bf16_blocks32(pl.KC) + (rbgp_bf16_tail16(pl.KC) ? 16 : 0) : pl.NO * 4;
   rp.kcr = pl.KCR;
@@ -1141,7 +1150,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   reg_fn fn = dual     ? nullptr
               : share_rv ? rbgp_reg_bf16_shared_kernel(share_rv, share_pr)
               : bf16   ? (lean ? rbgp_reg_bf16_lean_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW) : rbgp_reg_bf16_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW))
-              : split  ? rbgp_reg_split_kernel(split_rw)
+              : split  ? rbgp_reg_split_kernel(split_rw, sparse)
               : CT > 1 ? find_reg_tiles(pl.KC, pl.RS, NGf)
               : lean   ? find_reg_lean(taps ? pl.KC : walk, pl.RS, taps, NGf)
               : ge   ? (taps ? ge->taps_fn : ge->global_fn)

@@ -28,36 +28,19 @@
 
 #include "rbgp_internal.h"
 #include "rbgp_reg_common.h"
+#include "rbgp_split.h"
 
 using namespace rbgp_reg;
+using namespace rbgp_split;
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 typedef uint16_t halfword __attribute__((may_alias));   // (LDS written by halfwords and read as operands)
 
-// The operands are split as 2^23 times their value: every fp32 number is a multiple of 2^-149, so every part is zero or a
-// normal bf16 number however small the operand is.  The sums leave with the factor of both operands taken off.
-constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;
-
-// the three bf16 parts of eight fp32 values, times kUp (nearest even each; the differences are exact)
-struct Split {
-  bf16x8 p[3];
-};
-__device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
-__device__ __forceinline__ Split split8(const float (&x)[8]) {
-  u32x4 p0, p1, p2;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float x0 = x[2 * e] * kUp, x1 = x[2 * e + 1] * kUp;
-    p0[e] = bf16_pair(x0, x1);
-    const float a = x0 - bf16_lo(p0[e]), b = x1 - bf16_hi(p0[e]);
-    p1[e] = bf16_pair(a, b);
-    p2[e] = bf16_pair(a - bf16_lo(p1[e]), b - bf16_hi(p1[e]));
-  }
-  return Split{{__builtin_bit_cast(bf16x8, p0), __builtin_bit_cast(bf16x8, p1), __builtin_bit_cast(bf16x8, p2)}};
+__device__ __forceinline__ bf16x16 joined(const u32x4 &lo, const u32x4 &hi) {
+  return __builtin_shufflevector(__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, hi), 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11,
+                                 12, 13, 14, 15);
 }
 
 // Adds the small products and takes the operands' factors off.  True: one of the sums is not finite, and the fp32 pass has
@@ -264,10 +247,23 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
 // 4096^3 fp32, one row per column set at density 1/4 (68.7 GFLOP on the filled mask): 519 us on the fp32 MFMAs -> 330
 // (waves by themselves 409; two waves sharing 64 columns 415, four sharing 64 columns 379).
 // A lane holds one column of a 32-column block.
+//
+// SPARSE: filled masks whose rows keep at most one of the steps k and k + 16 of a 32-step stage (a 2-lift puts an edge on
+// one of two vertices half of G_i apart, never on both).  v_smfmac_f32_32x32x32_bf16 multiplies two weights of every four
+// steps by the rows of I that its index operand names, so the zeros that fill G_i in are not multiplied: half of the
+// MFMAs, each about 1.3 times as long (in bf16 products 3.8 against 2.4 PFLOP/s on registers).  The two blocks of weights of
+// a stage become one (bit by bit or, one of the two is +0), which is split once; places are the same in every stage and
+// are held in a register.  Operands: the lane of half h holds the compressed weights of steps 4 w + 2 h + g (w = 0..3, then
+// g = 0, 1), and the first four belong to the rows of I in the lanes of half 0, the others to half 1, so there the lane of
+// half h holds the rows of steps 4 w + h, then 4 w + 2 + h, each with its partner 16 further.
+// 4096^3 fp32, one row per column set at density 1/4: 316 -> 238 us, error against 64-bit sums 1.53e-7 -> 1.43e-7 (half as
+// many roundings); bound by the vector instructions of the splits and the passes through LDS (waves of 64 rows x 64
+// columns, which read half as much LDS and split the weights twice: 263).
+template <bool SPARSE>
 __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
   constexpr int NT = 4, CW = NT * 32;           // 32-column blocks, columns of a workgroup
   __shared__ __attribute__((aligned(16))) u32x4 parts[2][2][NT][3][64];
-  __shared__ __attribute__((aligned(16))) int rowoff[5 * 16];
+  __shared__ __attribute__((aligned(16))) int rowoff[SPARSE ? 2 : 1][5 * 16];   // [order of the steps][q][lane / 32][e]
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   WgCoord wg;
@@ -283,13 +279,18 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
     const int kk = 16 * q + 4 * (e & 3) + 2 * hh + (e >> 2);
     const int r = kk < p.kcr ? p.rowtab[u3 * p.no4 + kk] : 0;
     // (< 2^31: checked by the host; padding steps lie past every extent and read zeros without a memory access)
-    rowoff[threadIdx.x] = kk >= p.kcr ? int(0x80000000u) : p.conv ? r : r * (int(p.ldI) * 4);
+    rowoff[0][threadIdx.x] = kk >= p.kcr ? int(0x80000000u) : p.conv ? r : r * (int(p.ldI) * 4);
+    if constexpr (SPARSE) {                     // (32 steps, all of them rows of I)
+      const int ks = 16 * q + 4 * (e & 3) + hh + 2 * (e >> 2);
+      rowoff[1][threadIdx.x] = p.rowtab[u3 * p.no4 + ks] * (int(p.ldI) * 4);
+    }
   }
   const int TS = p.tstride;
   const int32_t *stg = p.stages + int64_t(u1) * 2 * TS + lane;   // one stage per lane (at most 64: checked by the host)
   const int tb = stg[0], tf = stg[TS];
   const int cnt = __builtin_amdgcn_readfirstlane(p.counts[u1]);
   const int rov = p.rowofs[lane & 15];
+  const int which = SPARSE ? p.pairs[((u1 + (j >> 4)) % p.fold * 2 + h) * 16 + (j & 15)] : 0;
   int col[NT];                                  // byte offset of the lane's column of every block
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -318,9 +319,9 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
     const int ext = __builtin_amdgcn_readlane(ib_ext, tl);
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(base), 0, s < cnt ? ext : 0, kRsrcFlags);
   };
-  auto load_b = [&](float (&x)[8], int s, int q, int c) {
+  auto load_b = [&](float (&x)[8], int s, int q, int c, int order) {
     const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
-    const int4 *ro = reinterpret_cast<const int4 *>(rowoff + q * 16 + h * 8);
+    const int4 *ro = reinterpret_cast<const int4 *>(rowoff[order] + q * 16 + h * 8);
     const int4 r0 = ro[0], r1 = ro[1];
     const int off[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
 #pragma unroll
@@ -339,8 +340,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
     const int q1 = q0 + 1 < nq ? q0 + 1 : 0, s1 = s0 + (q1 == 0);
     load_a(araw[0], s0, q0);
     load_a(araw[1], s1, q1);
-    load_b(braw[0], s0, q0, own_col);
-    load_b(braw[1], s1, q1, own_col);
+    load_b(braw[0], s0, q0, own_col, SPARSE);
+    load_b(braw[1], s1, q1, own_col, SPARSE);
     q0 = q1 + 1 < nq ? q1 + 1 : 0;
     s0 = s1 + (q0 == 0);
   };
@@ -360,13 +361,26 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
     const int buf = r & 1;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const Split b = split8(braw[u]);
+      Split b;
+      if constexpr (SPARSE) {                   // groups of four: the rows of steps k, k + 16, k + 4, k + 20
+        const float x[8] = {braw[0][4 * u], braw[1][4 * u], braw[0][4 * u + 1], braw[1][4 * u + 1],
+                            braw[0][4 * u + 2], braw[1][4 * u + 2], braw[0][4 * u + 3], braw[1][4 * u + 3]};
+        b = split8(x);
+      } else {
+        b = split8(braw[u]);
+      }
 #pragma unroll
       for (int k = 0; k < 3; ++k) parts[buf][u][wid][k][lane] = __builtin_bit_cast(u32x4, b.p[k]);
     }
     Split a[2];
+    if constexpr (SPARSE) {                     // (one of the two is +0)
+      float w[8];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+      for (int e = 0; e < 8; ++e) w[e] = __uint_as_float(__float_as_uint(araw[0][e / 4][e % 4]) | __float_as_uint(araw[1][e / 4][e % 4]));
+      a[0] = split8(w);
+    }
+#pragma unroll
+    for (int u = 0; u < (SPARSE ? 0 : 2); ++u) {
       const float w[8] = {araw[u][0][0], araw[u][0][1], araw[u][0][2], araw[u][0][3],
                           araw[u][1][0], araw[u][1][1], araw[u][1][2], araw[u][1][3]};
       a[u] = split8(w);
@@ -375,8 +389,27 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
+    if constexpr (SPARSE) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+      for (int t = 0; t < NT; t += 2) {
+        bf16x16 b[2][3];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+            b[x][k] = joined(parts[buf][0][t + x][k][lane], parts[buf][1][t + x][k][lane]);
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            f32x16 &d = k == 0 ? acc[t + x] : cor[t + x];
+            d = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a[0].p[pa[k]], b[x][pb[k]], d, which, 0, 0);
+          }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < (SPARSE ? 0 : 2); ++u)
 #pragma unroll
       for (int t = 0; t < NT; t += 2) {
         bf16x8 b[2][3];
@@ -384,7 +417,6 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
         for (int x = 0; x < 2; ++x)
 #pragma unroll
           for (int k = 0; k < 3; ++k) b[x][k] = __builtin_bit_cast(bf16x8, parts[buf][u][t + x][k][lane]);
-        constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
         for (int k = 0; k < 6; ++k)
 #pragma unroll
@@ -405,7 +437,7 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           float x[8];
-          load_b(x, s, q, col[t]);
+          load_b(x, s, q, col[t], 0);
 #pragma unroll
           for (int e = 0; e < 8; ++e) cor[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(araw[0][e / 4][e % 4], x[e], cor[t], 0, 0, 0);
         }
@@ -435,13 +467,15 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // every tile.  I as in spmm_reg_split_shared, a round being one stage.  One Inf in I makes every sum of its
 // column in the tile rows with that tile non-finite (the zeros of G_i are multiplied): such sums are added up again from
 // the kept weights, with the 4x4x1 MFMAs and in the order of spmm_mfma.  4096 x 4096, G_o and G_i at 1/4, N = 1531:
-// 126 -> 90 us, error against 64-bit sums 2.0e-7 -> 7.6e-8; with one infinity 240, with no finite column 260 (a lane adding
+// 126 -> 83 us, error against 64-bit sums 2.0e-7 -> 7.6e-8, with the sparse MFMA (SPARSE, see spmm_reg_split_shared: no
+// vertex keeps both k and k + 16; the weights are scattered among the 16 steps) 65 and 7.4e-8; with one infinity 240, with no finite column 260 (a lane adding
 // its sums up one by one: 470 and 1420).
-template <int KS>
+template <int KS, bool SPARSE>
 __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   constexpr int CW = 128, IT = KS / 8;
   __shared__ __attribute__((aligned(16))) u32x4 parts[2][2][4][3][64];
-  __shared__ __attribute__((aligned(16))) u32x4 wparts[4][3][2][64];   // [wave][part][16 steps][operand lane]
+  constexpr int WB = SPARSE ? 1 : 2;            // blocks of operands that hold a stage's weights
+  __shared__ __attribute__((aligned(16))) u32x4 wparts[4][3][WB][64];  // [wave][part][16 steps][operand lane]
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;   // (same columns of I -> same XCD, as spmm_mfma)
@@ -454,15 +488,33 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   const int adj_lo = lane < p.d1 ? p.adj0[u1 * p.d1 + lane] : 0;
   const int adj_hi = lane + 64 < p.d1 ? p.adj0[u1 * p.d1 + lane + 64] : 0;
   // the lane's kept weights of a stage: vertex ub + lane / 8, steps lane % 8 (+ 8), four rows each; where they go
-  int to[IT];
+  int to[IT], late[IT];
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int k = p.rowoff[(ub + (lane >> 3)) * KS + (lane & 7) + 8 * it];
-    to[it] = (((k >> 4) * 64 + ((k >> 3) & 1) * 32 + (lane >> 3) * 4) * 8 + (k & 7));   // in halfwords; + 8 per row
+    // in halfwords; + 8 per row.  Sparse: step k or k + 16 is place k % 4 + 4 (k / 8) of operand half k / 4 % 2
+    to[it] = SPARSE ? (((k >> 2) & 1) * 32 + (lane >> 3) * 4) * 8 + (k & 3) + ((k >> 1) & 4)
+                    : ((k >> 4) * 64 + ((k >> 3) & 1) * 32 + (lane >> 3) * 4) * 8 + (k & 7);
+    if constexpr (SPARSE) late[it] = k >> 4;
   }
   halfword *const wl = reinterpret_cast<halfword *>(wparts[wid]);
+  auto no_weights = [&]() {
 #pragma unroll
-  for (int k = 0; k < 6; ++k) wparts[wid][k / 2][k % 2][lane] = u32x4{0, 0, 0, 0};
+    for (int k = 0; k < 3 * WB; ++k) wparts[wid][k / WB][k % WB][lane] = u32x4{0, 0, 0, 0};
+    __builtin_amdgcn_wave_barrier();
+  };
+  no_weights();
+  int which = 0;                                // the sparse MFMA's index operand: 2-bit places in the groups of four
+  if constexpr (SPARSE) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) wl[to[it]] = halfword(late[it]);
+    __builtin_amdgcn_wave_barrier();
+    const u32x4 at = wparts[wid][0][0][lane & ~3];   // (the four rows of a vertex have the same steps)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) which |= (2 * (e & 1) + int((at[e / 2] >> (16 * (e & 1))) & 1u)) << (2 * e);
+    __builtin_amdgcn_wave_barrier();
+    no_weights();
+  }
   const int nstages = p.d1 * p.c2;
   const float *const wbase = p.Wp + ((int64_t(u1) * nstages) * p.a3 + ub + (lane >> 3)) * 64 + (lane & 7) * 4;
   const int row_bytes = int(p.ldI * 4);         // (32 rows and a column tile stay below 2^31 bytes: checked by the host)
@@ -499,7 +551,14 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     const int buf = s & 1;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const Split b = split8(braw[u]);
+      Split b;
+      if constexpr (SPARSE) {                   // groups of four: the rows of steps k, k + 16, k + 1, k + 17
+        const float x[8] = {braw[0][4 * u], braw[1][4 * u], braw[0][4 * u + 1], braw[1][4 * u + 1],
+                            braw[0][4 * u + 2], braw[1][4 * u + 2], braw[0][4 * u + 3], braw[1][4 * u + 3]};
+        b = split8(x);
+      } else {
+        b = split8(braw[u]);
+      }
 #pragma unroll
       for (int k = 0; k < 3; ++k) parts[buf][u][wid][k][lane] = __builtin_bit_cast(u32x4, b.p[k]);
     }
@@ -514,19 +573,40 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
         const uint32_t part[3] = {p0, p1, p2};
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          wl[k * 1024 + to[it] + 8 * r] = halfword(part[k]);
-          wl[k * 1024 + to[it] + 8 * (r + 1)] = halfword(part[k] >> 16);
+          wl[k * 512 * WB + to[it] + 8 * r] = halfword(part[k]);
+          wl[k * 512 * WB + to[it] + 8 * (r + 1)] = halfword(part[k] >> 16);
         }
       }
     load_round(s + 1 < nstages ? s + 1 : s);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
+    if constexpr (SPARSE) {
       bf16x8 a[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wid][k][u][lane]);
+      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wid][k][0][lane]);
+#pragma unroll
+      for (int t = 0; t < 4; t += 2) {
+        bf16x16 b[2][3];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) b[x][k] = joined(parts[buf][0][t + x][k][lane], parts[buf][1][t + x][k][lane]);
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            f32x16 &d = k == 0 ? acc[t + x] : cor[t + x];
+            d = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a[pa[k]], b[x][pb[k]], d, which, 0, 0);
+          }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < (SPARSE ? 0 : 2); ++u) {
+      bf16x8 a[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wid][k][u % WB][lane]);
 #pragma unroll
       for (int t = 0; t < 4; t += 2) {
         bf16x8 b[2][3];
@@ -534,7 +614,6 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
         for (int x = 0; x < 2; ++x)
 #pragma unroll
           for (int k = 0; k < 3; ++k) b[x][k] = __builtin_bit_cast(bf16x8, parts[buf][u][t + x][k][lane]);
-        constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
         for (int k = 0; k < 6; ++k)
 #pragma unroll
@@ -609,8 +688,12 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
 
 }  // namespace
 
-rbgp_reg_fn rbgp_reg_split_kernel(int RW) {
-  return RW == 4 ? spmm_reg_split_shared : RW == 1 ? spmm_reg_split : nullptr;
+rbgp_reg_fn rbgp_reg_split_kernel(int RW, bool sparse) {
+  return RW == 4 ? (sparse ? spmm_reg_split_shared<true> : spmm_reg_split_shared<false>) : RW == 1 ? spmm_reg_split : nullptr;
 }
 
-rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS) { return KS == 8 ? spmm_mfma_split<8> : KS == 16 ? spmm_mfma_split<16> : nullptr; }
+rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse) {
+  return KS == 8    ? (sparse ? spmm_mfma_split<8, true> : spmm_mfma_split<8, false>)
+         : KS == 16 ? (sparse ? spmm_mfma_split<16, true> : spmm_mfma_split<16, false>)
+                    : nullptr;
+}

@@ -64,6 +64,9 @@ struct RegParams {
   int fpm;                 // weight fragments per member: d_o * NSTG
   int no4, kcr, frag_bytes, nq;   // split-operand and shared bf16 kernels: entries of a G_i vertex's row table and how many
                            //   are steps, bytes of one weight fragment, blocks of 16 (bf16: 32) steps of a stage
+  const int32_t *pairs;    // split operands, filled masks whose kept weights share the steps of a stage two by two: [fold][2][16],
+                           //   see rbgp_reg_pairs
+  int fold;                // tile rows per row of G_o
   int rowofs[16];          // output row of weight row r of a group, relative to its (tile row, u_i) base
   int tm;                  // rows of one tile row: a_r * a_i * a_b
   int ntiles;              // column tiles: ceil(N / columns per wave)
@@ -170,10 +173,12 @@ rbgp_reg_fn rbgp_reg_bf16_lean_kernel(int KC, int RS, int G, int CW);
 // nullptr: not built
 rbgp_reg_fn rbgp_reg_bf16_shared_kernel(int RV, int PR);
 // fp32 kernel on the bf16 matrix core (operands split in three), 128 columns per wave; RW = 1: a
-// wave by itself, 4: the four waves of a workgroup share the columns; nullptr: not built
-rbgp_reg_fn rbgp_reg_split_kernel(int RW);
-// LDS family, fp32, on the bf16 matrix core: KS kept steps of 32 per stage (8 or 16); nullptr: not built
-rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS);
+// wave by itself, 4: the four waves of a workgroup share the columns (sparse: on the sparse MFMA, RegParams::pairs);
+// nullptr: not built
+rbgp_reg_fn rbgp_reg_split_kernel(int RW, bool sparse);
+// LDS family, fp32, on the bf16 matrix core: KS kept steps of 32 per stage (8 or 16; sparse: never both k and k + 16);
+// nullptr: not built
+rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse);
 // fp32 kernel with lo/hi pairing of the tile rows (8-row halves; tables of rbgp_reg_dual in the
 // stages / counts / members fields); nullptr when KC is not built.
 rbgp_dual_fn rbgp_reg_dual_kernel(int KC);

@@ -493,8 +493,43 @@ def test_stages_of_64_steps_in_the_layout_of_72(idx, dtype):
             assert orc.normalised_error(out, ref, den) <= 4e-6
 
 
+# masks whose filled twin walks stages of 32 steps with at most one of k and k + 16 kept (G_i at 1/2 and 1/4, |G_b.V| of 1
+# and 2), and one whose rows keep both (a complete G_i with a sparse G_b beside it)
+FILLED_PAIRS = [((8, 1, 128, 1), (16, 1, 32, 1), (2, 1, 16, 1)), ((8, 1, 256, 1), (16, 1, 32, 1), (2, 1, 8, 1)),
+                ((8, 2, 64, 1), (16, 1, 32, 1), (2, 1, 16, 1)), ((8, 1, 64, 2), (16, 1, 16, 2), (2, 1, 4, 2)),
+                ((8, 1, 32, 4), (16, 1, 8, 4), (2, 1, 8, 2))]
+
+
+@pytest.mark.parametrize("rows,cols,deg", FILLED_PAIRS)
+def test_filled_masks_with_one_kept_weight_in_two_steps(rows, cols, deg):
+    """The kernels of filled masks that share their columns, on the sparse MFMA where every row keeps at most one weight of
+    two steps: widths around the 128-column tile; an infinity reaches the rows that keep its row of I, and of the others
+    at most those of the same column."""
+    w = wl.Workload("pairs", rows, cols, deg, 333, wl.F32, 61, 62, 63, 1.0)
+    tune = (0,) * 8 + (3,)
+    for N, pad in ((1, 0), (97, 3), (128, 0), (129, 5), (400, 4)):
+        gh.check_parity(w, N=N, kernel=FILLED, tune=tune, ld_pad=pad, expect_kernel=FILLED)
+    N = 140
+    vl, Il, vf, If = gh.host_inputs(w, N)
+    bad, k = Il.copy(), 21
+    bad[k, 5], bad[k, 130] = np.inf, -np.inf
+    run = lambda X: gh.library_spmm(w, vl, X, kernel=FILLED, tune=tune, tag="pairs")[0]
+    clean, got = run(Il), run(bad)
+    others = np.ones(N, bool)
+    others[[5, 130]] = False
+    assert np.array_equal(got[:, others].view(np.uint32), clean[:, others].view(np.uint32))
+    mask = rb.rbgp_mask_dense(gh.make_mask(w)).reshape(w.M, w.K).astype(bool)
+    keeps = mask[:, k]
+    W = np.zeros((w.M, w.K), np.float32)
+    W[mask] = vf.reshape(-1)
+    for n, sign in ((5, 1.0), (130, -1.0)):
+        assert np.array_equal(got[keeps, n], np.sign(W[keeps, k]) * np.float32(sign * np.inf))
+        rest = got[~keeps, n]
+        assert (np.isnan(rest) | (np.abs(rest - clean[~keeps, n]) <= 1e-5 * np.abs(clean[:, n]).max())).all()
+
+
 @pytest.mark.parametrize("rows,cols,deg", [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1)), ((4, 1, 32, 4), (8, 3, 32, 1), (2, 3, 16, 1)),
-                                           ((2, 2, 64, 2), (4, 2, 16, 2), (2, 2, 4, 2))])
+                                           ((2, 2, 64, 2), (4, 2, 16, 2), (2, 2, 4, 2)), ((4, 4, 8, 4), (8, 1, 8, 4), (4, 1, 8, 2))])
 def test_lds_family_split_operands(rows, cols, deg):
     """RBGP_TUNE_SPLIT_OPERANDS on the LDS family: widths around the 128-column tile, one and two groups of G_i vertices,
     8 and 16 kept steps; infinities and tiny operands as the fp32 kernel gives them."""
