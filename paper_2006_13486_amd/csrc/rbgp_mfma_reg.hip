@@ -819,8 +819,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   if (!e) return RBGP_EUNSUPPORTED;
   const int walk = rbgp_reg_walk(pl);
   // tile rows that come in groups of `fold` with the same stage list, in order (one tile row per cluster)
-  bool ident = pl.MG == 1 && pl.fold > 1 && m->reg_clusters.U == 1;
-  for (int c = 0; c < m->reg_clusters.ncl && ident; ++c) ident = m->reg_clusters.members[size_t(c)] == c;
+  bool in_order = pl.MG == 1 && m->reg_clusters.U == 1;   // cluster c is tile row c
+  for (int c = 0; c < m->reg_clusters.ncl && in_order; ++c) in_order = m->reg_clusters.members[size_t(c)] == c;
+  const bool ident = in_order && pl.fold > 1;
   // bf16: workgroups of share_rv x (4 / share_rv) waves that pass I through LDS, each wave 2 share_pr of these tile rows
   // and 128 columns (rbgp_mfma_reg_bf16_shared.hip)
   int share_rv = 0, share_pr = 1;
@@ -1147,6 +1148,35 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   rp.ncl = ncl;
   rp.per_xcd = int(per_xcd);
   rp.ngroups = int(nquads);
+  // Many rows per tile, one stage of 32 rows of I with two of every four kept (transposes of lowered 3x3 layers): workgroups
+  // of all rows of a row of G_o x 64 columns (rbgp_mfma_reg_rows.hip), from five workgroups per eight CUs on (us, the kernels
+  // above -> this one: VGG19 layer 6 at 1/4, 128 workgroups 8.9 -> 9.6, 192 13.6 -> 10.0, 256 15.3 -> 10.4, 512 26.9 -> 17.4;
+  // layer 9, 128 14.0 -> 14.0, 192 22.2 -> 14.8; layer 3, 128 6.6 -> 8.2, 256 10.2 -> 8.5), where groups of 32 rows are nearly
+  // full (layer 2: 72 rows, 31.5 -> 31.2).
+  const int rows_wg = pl.fold * m->a[2] * pl.R, groups = (rows_wg + 31) / 32;
+  if (!bf16 && !conv && !dual && in_order && pl.VC == 4 && pl.NSTG == 1 && m->c[2] == 4 && m->d[2] == 2 && m->c[3] == 2 && m->d[3] == 2 &&
+      tab->max_stages <= 12 && 8 * groups * 32 <= 9 * rows_wg && groups <= 64 && !tune[RBGP_TUNE_ROW_GROUPS] && !tune[RBGP_TUNE_K_SPLIT] &&
+      !tune[RBGP_TUNE_COLUMN_TILES] && !tune[RBGP_TUNE_REGISTER_SETS] && !tune[RBGP_TUNE_SPLIT_OPERANDS]) {
+    const int64_t tiles = (N + 63) / 64, all = tiles * (pl.TR / pl.fold);
+    const int64_t wgs = tiles >= 8 ? 8 * ((tiles + 7) / 8) * (pl.TR / pl.fold) : all;
+    const size_t bytes = size_t(tab->max_stages) * 12288 + size_t(groups) * 512;
+    if (all >= 160 && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
+      rp.ntiles = int(tiles);
+      rp.ncl = pl.TR / pl.fold;
+      rp.order = tiles >= 8 ? 2 : 0;
+      rp.ct_cnt = tab->max_stages;
+      // A wave per group while every workgroup has a CU to itself, or LDS holds one only (lists of more than four stages: 4
+      // waves 36, 9 waves 27 at 512 workgroups); else four waves, three workgroups a CU (layer 6: 4 waves / 9, 256 workgroups
+      // 14.1 / 10.4, 296 16.5 / 18.1, 768 21.4 / 27.0).
+      const int waves = all <= 256 || tab->max_stages > 4 ? std::min(groups, 9) : 4;
+      reg_fn rows = rbgp_reg_rows_kernel();
+      if (bytes > 64 * 1024)
+        RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(rows), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
+      hipLaunchKernelGGL(rows, dim3(unsigned(wgs)), dim3(unsigned(64 * waves)), bytes, static_cast<hipStream_t>(stream), rp);
+      RBGP_HIP(hipGetLastError());
+      return RBGP_OK;
+    }
+  }
   reg_fn fn = dual     ? nullptr
               : share_rv ? rbgp_reg_bf16_shared_kernel(share_rv, share_pr)
               : bf16   ? (lean ? rbgp_reg_bf16_lean_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW) : rbgp_reg_bf16_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW))

@@ -1,0 +1,206 @@
+// fp32 product of the register-streaming family for masks with short stages and many rows per tile, on the sparse bf16
+// matrix core with split operands (rbgp_split.h): the transposes of lowered 3x3 layers (dI = W_s^T x dO), whose tiles are
+// nine times as high as they are wide.  A tile of G_o holds |G_r.U| |G_i.U| |G_b.U| rows (288 in VGG19's layers) and one
+// stage of |G_r.V| |G_i.V| |G_b.V| = 4 x 4 x 2 rows of I, of which a row keeps two of every four (G_i: two edges, four
+// columns).  spmm_reg walks such a tile once per G_i vertex, in stages of 16 steps, each row of I loaded |G_i.U| / 2 times
+// for 9 to 12 of 16 MFMA rows: it waits for the load path.
+//
+// Here a workgroup takes all rows of a row of G_o (p.fold tile rows x G_i vertices x R) x 64 columns: every stage's 32 rows x 64 columns are loaded and split once, by one wave, and stay in LDS (12 KB a
+// stage); then every wave multiplies groups of 32 rows, whatever G_i vertices they belong to, with
+// v_smfmac_f32_32x32x32_bf16: its index operand names the kept ones among the four columns of G_i, row by row, so that one
+// instruction serves rows of different G_i vertices and no zero of G_i is multiplied.  The packed weights are those of
+// spmm_reg, loaded four stages ahead.
+// Operands: the lane of half h holds the kept weights of G_b vertex h, in groups of four (all G_i vertices of one G_r vertex
+// v); the groups v = 0, 1 belong to rows of I in the lanes of half 0, v = 2, 3 to those of half 1.
+//
+// What bounds it: a workgroup's chain of latencies (tables, rows of I, four to eight stages of six dependent products each),
+// and from a few hundred workgroups on the stores of O, 9 |G_r.U| rows for every 32 of I.  us, before -> after: VGG19 layer 6
+// at density 1/4, 2368 columns 24.3 -> 16, 8192 49 -> 30; layer 9 at 1/4, 2048 columns 44 -> 27; layer 3, 32768 columns
+// 62 -> 42; error against 64-bit sums 8.3e-8 -> 5.0e-8.
+// Tried: waves of 32 columns at four waves per SIMD (15.7 / 32 / 29 / 48), two stages of weights ahead with 14 spilled
+// registers (15.6 / 33 / 33 / 41), one edge of four (half of the weights zero; VGG19 conv5 24.9 -> 26.2), the next stage's operands prepared beside the products (21 / 39 / 32 / 53).
+#include <hip/hip_runtime.h>
+
+#include "rbgp_internal.h"
+#include "rbgp_reg_common.h"
+#include "rbgp_split.h"
+
+using namespace rbgp_reg;
+using namespace rbgp_split;
+
+namespace {
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2_s __attribute__((ext_vector_type(2)));
+
+constexpr int kAhead = 4;                       // stages of weights in flight
+
+__global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
+  constexpr int CW = 64;
+  // [stage][column block][part][half of the 16 steps of a lane][lane], then what every row needs (info)
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), W = int(blockDim.x) >> 6;
+  const int h = lane >> 5, j = lane & 31;
+  int uo, nt;                                   // row of G_o, column tile (order 2: one on XCD tile % 8, as in wg_coord)
+  if (p.order == 2) {
+    const int slot = blockIdx.x >> 3;
+    nt = int(blockIdx.x & 7) + 8 * (slot / p.ncl);
+    uo = slot % p.ncl;
+  } else {
+    nt = int(blockIdx.x) / p.ncl;
+    uo = int(blockIdx.x) % p.ncl;
+  }
+  if (nt >= p.ntiles) return;                   // (the whole workgroup)
+  const int64_t n0 = int64_t(nt) * CW;
+  const int u1 = uo * p.fold, TS = p.tstride;
+  const int32_t *stg = p.stages + int64_t(u1) * 2 * TS;
+  const int cnt = __builtin_amdgcn_readfirstlane(p.counts[u1]);
+  const int tb = lane < cnt ? stg[lane] : 0, tf = lane < cnt ? stg[TS + lane] : 0;   // (at most 12 stages)
+  u32x4 *const parts = reinterpret_cast<u32x4 *>(lds);
+  // of every row: its row of O relative to the tile row's first (-1: none), its weights relative to a stage's, the places
+  // of its G_i vertex's two edges (the index operand)
+  int4 *const info = reinterpret_cast<int4 *>(lds + p.ct_cnt * 12288);
+  const int per_row = p.a3 * p.R, rows = p.fold * per_row, groups = (rows + 31) >> 5;
+  const int row_bytes = int(p.row_bytes);
+  const __amdgpu_buffer_rsrc_t rw =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.Wp), 0, p.w_bytes, kRsrcFlags);
+  auto stage_rsrc = [&](int s) {
+    const uint32_t b = uint32_t(__builtin_amdgcn_readlane(tb, s));
+    // (to the last column of the stage's last row; columns past it read zeros or the next row and are never stored)
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(p.I) + (uint64_t(b) * p.row_bytes >> 2) + n0, 0,
+        int(31u * p.row_bytes + (p.n_bytes - uint32_t(n0) * 4u)), kRsrcFlags);
+  };
+  // row of the stage of step e of a lane of half hb: G_r vertex 2 hb + (e % 8) / 4, G_i vertex e % 4, G_b vertex e / 8
+  auto row_of = [&](int hb, int e) { return ((2 * hb + (e % 8) / 4) * 4 + e % 4) * 2 + e / 8; };
+
+  // two pieces of a row's fragment, steps of G_b vertex h: piece i is edge i of the row's G_i vertex, element v G_r vertex v
+  struct A {
+    f32x4 x[2];
+  };
+  auto a_of = [&](int r) {                      // its weights; kOob: no such row
+    const int f = r / per_row, q = r - f * per_row, ui = q / p.R, i = q - ui * p.R;
+    return r < rows ? ((u1 + f) * p.fpm * p.a3 + ui) * p.frag_bytes + i * 16 : kOob;
+  };
+  auto load_a = [&](A &a, int base, int s) {
+    const int pos = __builtin_amdgcn_readlane(tf, s) * p.a3 * p.frag_bytes;
+    a.x[0] = load_x4(rw, base + pos, 0);
+    a.x[1] = load_x4(rw, base + pos, 512);
+  };
+  A ring[kAhead];
+  int a_base = a_of(wid * 32 + j) + h * 256;
+#pragma unroll
+  for (int d = 0; d < kAhead; ++d) load_a(ring[d], d < cnt ? a_base : kOob, d < cnt ? d : 0);
+
+  for (int x = threadIdx.x; x < groups * 32; x += blockDim.x) {
+    const int f = x / per_row, q = x - f * per_row, ui = q / p.R, i = q - ui * p.R;
+    const bool in = x < rows;
+    const int e0 = in ? p.rowtab[ui * p.no4] >> 1 : 0, e1 = in ? p.rowtab[ui * p.no4 + 2] >> 1 : 0;
+    info[x] = int4{in ? f * p.tm + ui * p.a4 + (i / p.a4) * p.a3 * p.a4 + i % p.a4 : -1, a_of(x), (e0 | e1 << 2) * 0x1111, 0};
+  }
+  // every wave splits the rows of some stages
+  for (int s = wid; s < cnt; s += W) {
+    const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+    float x[2][16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rb, row_of(h, e) * row_bytes + j * 8, 0, 0);
+      x[0][e] = __uint_as_float(v[0]);
+      x[1][e] = __uint_as_float(v[1]);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const float y[8] = {x[t][8 * half], x[t][8 * half + 1], x[t][8 * half + 2], x[t][8 * half + 3],
+                            x[t][8 * half + 4], x[t][8 * half + 5], x[t][8 * half + 6], x[t][8 * half + 7]};
+        const Split b = split8(y);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) parts[(((s * 2 + t) * 3 + k) * 2 + half) * 64 + lane] = __builtin_bit_cast(u32x4, b.p[k]);
+      }
+  }
+  __syncthreads();
+
+  float *const out = p.O;
+  const int64_t out_ld = p.ldO, out_n = p.N;
+  const bool vec_ok = (out_ld % 2 == 0) && (reinterpret_cast<uintptr_t>(out) % 8 == 0) && n0 + 2 * j + 2 <= out_n;
+  for (int g = wid; g < groups; g += W) {
+    const int which = info[g * 32 + j].z, base = a_base;
+    a_base = g + W < groups ? info[(g + W) * 32 + j].y + h * 256 : kOob;
+    f32x16 acc[2], cor[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][i] = cor[t][i] = 0.f;
+    for (int s0 = 0; s0 < cnt; s0 += kAhead) {
+#pragma unroll
+      for (int d = 0; d < kAhead; ++d) {
+        const int s = s0 + d;
+        if (s < cnt) {
+          const float w[8] = {ring[d].x[0][0], ring[d].x[1][0], ring[d].x[0][1], ring[d].x[1][1],
+                              ring[d].x[0][2], ring[d].x[1][2], ring[d].x[0][3], ring[d].x[1][3]};
+          const Split a = split8(w);
+          const bool more = s + kAhead < cnt;
+          load_a(ring[d], more ? base : a_base, more ? s + kAhead : d);
+          constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            bf16x16 b[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+              b[k] = joined(parts[(((s * 2 + t) * 3 + k) * 2) * 64 + lane], parts[(((s * 2 + t) * 3 + k) * 2 + 1) * 64 + lane]);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+              f32x16 &c = k == 0 ? acc[t] : cor[t];
+              c = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a.p[pa[k]], b[pb[k]], c, which, 0, 0);
+            }
+          }
+        }
+      }
+    }
+    bool again = false;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) again |= add_up(acc[t], cor[t]) && n0 + 2 * j + t < out_n;
+    if (__builtin_amdgcn_ballot_w64(again)) {   // (wave-uniform; no barrier inside)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) cor[t][i] = 0.f;
+      for (int s = 0; s < cnt; ++s) {
+        const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+        A a;
+        load_a(a, base, s);
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rb, ((w * 4 + v) * 2 + h) * row_bytes + j * 8, 0, 0);
+            const float y = v == (which & 3) ? a.x[0][w] : v == (which >> 2 & 3) ? a.x[1][w] : 0.f;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) cor[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, __uint_as_float(x[t]), cor[t], 0, 0, 0);
+          }
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) take_not_finite(acc[t], cor[t]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int m = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].x;
+      if (m >= 0) {
+        float *o = out + (int64_t(u1) * p.tm + m) * out_ld + n0 + 2 * j;
+        if (vec_ok) {
+          __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_s *>(o));
+        } else {
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            if (n0 + 2 * j + t < out_n) o[t] = acc[t][i];
+        }
+      }
+    }
+  }
+}
+
+}  // namespace
+
+rbgp_reg_fn rbgp_reg_rows_kernel() { return spmm_reg_rows; }

@@ -38,28 +38,6 @@ namespace {
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 typedef uint16_t halfword __attribute__((may_alias));   // (LDS written by halfwords and read as operands)
 
-__device__ __forceinline__ bf16x16 joined(const u32x4 &lo, const u32x4 &hi) {
-  return __builtin_shufflevector(__builtin_bit_cast(bf16x8, lo), __builtin_bit_cast(bf16x8, hi), 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11,
-                                 12, 13, 14, 15);
-}
-
-// Adds the small products and takes the operands' factors off.  True: one of the sums is not finite, and the fp32 pass has
-// to give it.
-__device__ __forceinline__ bool add_up(f32x16 &acc, const f32x16 &cor) {
-  float zero = 0.f;   // 0, or NaN where a sum is not finite
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    acc[i] = (acc[i] + cor[i]) * kDown;
-    zero = __builtin_fmaf(acc[i], 0.f, zero);
-  }
-  return zero != 0.f;
-}
-// (every finite sum stays as it is, bit for bit)
-__device__ __forceinline__ void take_not_finite(f32x16 &acc, const f32x16 &second) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = acc[i] * 0.f == 0.f ? acc[i] : second[i];
-}
-
 // A stage is walked in p.nq blocks of 16 contraction steps (the last one may be padding in part: zero weights).
 __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
   constexpr int CW = 128;                       // columns per wave

@@ -72,6 +72,7 @@ struct RegParams {
   int ntiles;              // column tiles: ceil(N / columns per wave)
   int lgS;                 // log2 of the waves that share a column tile (split of the stage list)
   int ncl;                 // clusters of tile rows (pairing kernel: quads)
+  // (spmm_reg_rows: ncl = rows of G_o, ct_cnt = longest stage list)
   int ct, ct_cnt;          // fp32 kernels with stages of up to 8 steps: column tiles a wave takes one after the other (1 elsewhere)
                            //   and, when that is more than one, the stages of every cluster's list (all equal, a multiple of 4)
   // Workgroups (one-dimensional grid) are dealt round-robin to the 8 XCDs, so workgroup id & 7 is the XCD, each with
@@ -176,6 +177,8 @@ rbgp_reg_fn rbgp_reg_bf16_shared_kernel(int RV, int PR);
 // wave by itself, 4: the four waves of a workgroup share the columns (sparse: on the sparse MFMA, RegParams::pairs);
 // nullptr: not built
 rbgp_reg_fn rbgp_reg_split_kernel(int RW, bool sparse);
+// fp32 kernel of workgroups that take all rows of a row of G_o (rbgp_mfma_reg_rows.hip)
+rbgp_reg_fn rbgp_reg_rows_kernel();
 // LDS family, fp32, on the bf16 matrix core: KS kept steps of 32 per stage (8 or 16; sparse: never both k and k + 16);
 // nullptr: not built
 rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse);

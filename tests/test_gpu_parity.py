@@ -493,6 +493,37 @@ def test_stages_of_64_steps_in_the_layout_of_72(idx, dtype):
             assert orc.normalised_error(out, ref, den) <= 4e-6
 
 
+# many rows per tile, two of four columns of G_i kept: 96 and 120 rows (the last group of 32 in part), nine tile rows per
+# row of G_o, lists of one, four, eight and twelve stages
+MANY_ROWS = [((4, 4, 8, 3), (8, 4, 4, 2), (4, 4, 2, 2)), ((4, 4, 10, 3), (4, 4, 4, 2), (2, 4, 2, 2)),
+             ((4, 36, 2, 4), (4, 4, 4, 2), (1, 4, 2, 2)), ((2, 4, 8, 9), (16, 4, 4, 2), (8, 4, 2, 2)),
+             ((4, 1, 24, 12), (24, 4, 4, 2), (12, 4, 2, 2))]
+
+
+@pytest.mark.parametrize("rows,cols,deg", MANY_ROWS)
+def test_many_rows_per_tile_with_two_of_four_kept(rows, cols, deg):
+    """The kernel that takes all rows of a row of G_o, on batches wide enough for it (and just below): widths around its
+    64-column tile, odd leading dimensions; an infinity reaches the rows that keep its row of I, and no other column."""
+    w = wl.Workload("many_rows", rows, cols, deg, 333, wl.F32, 71, 72, 73, 1.0)
+    enough = -(-160 // rows[0]) * 64 - 63
+    for N, pad in ((enough - 1, 0), (enough, 1), (enough + 63, 0), (enough + 64, 3)):
+        gh.check_parity(w, N=N, ld_pad=pad, expect_kernel=REG)
+    N = enough + 1
+    vl, Il, vf, If = gh.host_inputs(w, N)
+    bad, k = Il.copy(), 21
+    bad[k, 5], bad[k, N - 1], bad[k + 1, 70] = np.inf, -np.inf, np.float32(1e37)
+    run = lambda X, tune=None: gh.library_spmm(w, vl, X, tune=tune, tag="many rows")[0]
+    clean, got, ref = run(Il), run(bad), run(bad, (0,) * 8 + (1,))
+    others = np.ones(N, bool)
+    others[[5, 70, N - 1]] = False
+    assert np.array_equal(got[:, others].view(np.uint32), clean[:, others].view(np.uint32))
+    assert np.array_equal(got[:, [5, N - 1]] == np.inf, ref[:, [5, N - 1]] == np.inf)
+    assert np.array_equal(got[:, [5, N - 1]] == -np.inf, ref[:, [5, N - 1]] == -np.inf)
+    assert np.isfinite(got[:, [5, 70, N - 1]]).sum() == np.isfinite(ref[:, [5, 70, N - 1]]).sum()
+    bound = 1e-6 * np.abs(ref[:, 70]).max()      # (a few rounding errors of 6e-8 of the largest sum)
+    assert (np.abs(got[:, 70].astype(np.float64) - ref[:, 70]) <= bound).all()
+
+
 # masks whose filled twin walks stages of 32 steps with at most one of k and k + 16 kept (G_i at 1/2 and 1/4, |G_b.V| of 1
 # and 2), and one whose rows keep both (a complete G_i with a sparse G_b beside it)
 FILLED_PAIRS = [((8, 1, 128, 1), (16, 1, 32, 1), (2, 1, 16, 1)), ((8, 1, 256, 1), (16, 1, 32, 1), (2, 1, 8, 1)),
