@@ -37,6 +37,7 @@
 #include <vector>
 
 #include "rbgp_internal.h"
+#include "rbgp_sddmm.h"
 
 #define RBGP_HIP(call)                                                          \
   do {                                                                          \
@@ -49,6 +50,9 @@
     }                                                                           \
   } while (0)
 
+using rbgp_sddmm_detail::SddmmParams;
+using rbgp_sddmm_detail::kLinesWaves;
+
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -57,35 +61,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 typedef bf16x8 bf16x8_u __attribute__((aligned(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-struct SddmmParams {
-  const void *dO, *I;
-  float *out;               // [workgroups per unit][nnz] partial sums (dW itself when there is one)
-  const int32_t *colrows;   // [c_o][EO]: tile rows that have tile column v_o, ascending
-  const int32_t *colpos;    // [c_o][EO]: position of v_o in that tile row's adjacency list
-  const int32_t *rowtab;    // [a_i][16 * NB]: stage-relative row of I of contraction step kk (padding -> 0)
-  int64_t N, ld_dO, ldI, nnz;
-  int64_t chunk;            // columns per range (a multiple of the columns per iteration)
-  int EO, RBG;              // tile rows per tile column; groups of RB row groups per unit
-  int nbt, halves;          // 16-step groups of a stage; workgroups that share them (each takes NB consecutive ones)
-  int NSTG, stage_rows;     // stages per tile; rows of I between the bases of consecutive stages (VC * c_i * c_b)
-  int tile_rows;            // rows of I per tile column (c_r * c_i * c_b)
-  int a2, a3, a4, R, lgRS, MG, KCR, rowdeg;
-  // "All of G_i" units (GI kernels): a unit is a (tile column, stage) and takes the rows of every G_i vertex
-  // together -- 16-row groups run over (tile row of the list, u_i, row of R) -- against ALL rows of I the
-  // stage spans, whether G_i connects them or not; the epilogue stores the kept products only.  For
-  // masks with few rows per (tile column, u_i) (sparse G_o, small G_r, G_b) this fills the 16 MFMA rows
-  // that would be padding, and every row of I is loaded once instead of once per adjacent u_i.
-  int src_rows;             // gi: rows of I one stage spans (VC * c_i * c_b)
-  const int32_t *spos;      // gi: [a_i][16 * NB]: position inside the stage's kept values of (u_i, stage row), -1: not kept
-  // Fused 3x3 convolution (CONV kernels): I is not materialised; row k = 9 * channel + tap of it is read
-  // from the zero-padded activations X[channel][image][H + 2][W + 2] (pointer I).
-  const int32_t *colbase;   // element offset, inside a channel of X, of the first pixel of every group of
-                            //   columns one lane loads (4 fp32 / 8 bf16), padded with valid offsets
-  int64_t chan_elems;       // elements of one channel of X
-  int64_t x_bytes;          // size of X
-  int conv_w2;              // W + 2
-};
 
 template <bool BF16>
 struct Operand;
@@ -420,7 +395,7 @@ int upload(const std::vector<T> &h, T **d) {
   return RBGP_OK;
 }
 
-typedef void (*sddmm_fn)(SddmmParams);
+typedef rbgp_sddmm_fn sddmm_fn;
 template <int RB, bool BF16, bool CONV, bool GI>
 sddmm_fn pick_nb(int NB) {
   switch (NB) {
@@ -587,29 +562,77 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   const bool gi = gi_NB <= 5 && gi_RBG * gi_RB * gi_NB < m->a[2] * RBG * RB * NB;
   if (gi) { NB = gi_NB; groups = gi_groups; RB = gi_RB; RBG = gi_RBG; }
   const int nbt = NB;
-  // ranges of the batch: enough waves for a few per SIMD (1024 SIMDs), at least two iterations each
-  const int cpi = bf16 ? 32 : 16;
-  int64_t blocks = int64_t(m->c[0]) * pl.NSTG * (gi ? 1 : m->a[2]) * RBG;
-  // Where one wave per SIMD would need five to eight column ranges per unit, i.e. two workgroups and the
-  // second kernel that adds their partial sums, two workgroups that split the stage's 16-step groups
-  // instead need neither (conv5 shape: 24.4 -> 22.5 us fp32, 13.7 -> 11.0 us bf16; the fused-convolution
-  // variant, whose loads of X cost more, is slower that way and keeps whole stages).
-  int halves = 1;
-  if (!conv && NB >= 4 && blocks * 4 < 1024 && blocks * 8 >= 1024 && N >= 8 * 2 * cpi) {
-    halves = 2;
-    NB = (NB + 1) / 2;
-    blocks *= 2;
+  const int64_t units = int64_t(m->c[0]) * pl.NSTG * (gi ? 1 : m->a[2]);
+  // The kernel of whole cache lines (rbgp_sddmm_lines.hip): workgroups of RBl row groups x NBl step groups
+  int RBl = RB, NBl = std::min(nbt, bf16 ? 5 : 3);
+  int64_t parts = 1;
+  auto count = [&](int r, int n) { return units * ((groups + r - 1) / r) * ((nbt + n - 1) / n); };
+  // (sddmm_reg writes dW itself: one workgroup per unit, see below)
+  const bool one_launch = count(RB, nbt) >= 256 || (!conv && nbt >= 4 && count(RB, nbt) >= 128 && N >= 16 * (bf16 ? 32 : 16));
+  bool lines;
+  if (bf16) {
+    // Workgroups enough for the chip by splitting a unit's steps (3 + 2 groups of 16) and rows first, the batch last: that
+    // costs loads, this partial sums and a second launch; at least four steps per wave.  us, before (sddmm_reg) -> two row
+    // groups x 5 step groups / 2 x 3 / 1 x 3, each with as many parts of the batch as fill the chip: VGG19 conv3, 8192 columns
+    // 20.5 -> 18.0 / 16.1 / 15.5, fused 19.0 -> 14.2 / 14.3 / 13.7, 2368 columns 13.0 -> 13.6 / 10.9 / 8.2; conv5 11.8 ->
+    // 13.8 / 10.1 / 13.3; layer 6 at 1/2 26.3 -> 20.2 / 18.6 / 21, at 1/8 16.8 -> 14.8 / 13.5 / 13.6.
+    // With sddmm_reg stay batches of less than a wave's two steps, many units of a short batch (its four waves reach further
+    // into it; layer 9 at 1/2: 208 columns 9.7 / 14.9, 1024 16.2 / 19.1, 1536 23.9 / 20.3), and where it needs one launch and
+    // the eight waves' steps of 64 columns come out uneven (layer 9 at 1/4, 1696 columns 13.6 / 16.5, layer 8, 1760 10.5 / 12.5).
+    const int64_t most = std::max<int64_t>(1, N / 2048);
+    const bool uneven = N < 4096 && 10 * N < 9 * ((N + 511) / 512 * 512);
+    lines = N >= 128 && !(count(RBl, NBl) >= 512 && N < 1536) && !(one_launch && uneven);
+    if (count(RBl, NBl) < 256) {
+      NBl = std::min(nbt, 3);
+      if (RBl == 2 && count(2, NBl) < 256 && (count(1, NBl) >= 256 || count(2, NBl) * most < 256)) RBl = 1;
+      parts = std::min((256 + count(RBl, NBl) - 1) / count(RBl, NBl), most);
+    }
+  } else {
+    // fp32: where one round of workgroups of 2 x 3 groups (or, on short batches, 1 x 3) covers the units (us, before -> 2 x 3
+    // / 1 x 3: conv5, 2048 columns 22.9 -> 20.5 / 26, fused 23.2 -> 20.6; layer 6 at 1/2, 8192 columns 72.7 -> 59.1; at 1/4,
+    // 2368 columns 19.1 -> 21.4 / 16.3, 8192 38.1 -> 56 / 43.9); below 1024 columns not where sddmm_reg needs one launch on the
+    // lowered input (layer 6 at 1/4, 320 columns 10.9 -> 6.7; conv5 fused, 512 columns 13.7 -> 10.2, lowered 9.8 -> 10.3).
+    if (RBl == 2 && count(2, NBl) < 224) RBl = 1;
+    lines = count(RBl, NBl) <= 256 &&
+            (N < 1024 ? N > 64 && (conv || !one_launch || N <= 256) : count(RBl, NBl) >= 224 && (RBl == RB || N <= 2560));
   }
-  sddmm_fn fn = conv ? (gi ? find_kernel<true, true>(RB, NB, bf16) : find_kernel<true, false>(RB, NB, bf16))
-                     : (gi ? find_kernel<false, true>(RB, NB, bf16) : find_kernel<false, false>(RB, NB, bf16));
+  int64_t blocks, chunk, nsplit;
+  int halves = 1;
+  sddmm_fn fn;
+  if (lines) {
+    const int cpi = bf16 ? 64 : 32;
+    RB = RBl;
+    NB = NBl;
+    RBG = (groups + RB - 1) / RB;
+    halves = (nbt + NB - 1) / NB;
+    blocks = units * RBG * halves;
+    chunk = ((N + parts * kLinesWaves - 1) / (parts * kLinesWaves) + cpi - 1) / cpi * cpi;
+    nsplit = (N + chunk * kLinesWaves - 1) / (chunk * kLinesWaves);      // workgroups per unit = partial sums
+    fn = rbgp_sddmm_lines_kernel(RB, NB, bf16, conv != nullptr, gi);
+  } else {
+    // ranges of the batch: enough waves for a few per SIMD (1024 SIMDs), at least two iterations each
+    const int cpi = bf16 ? 32 : 16;
+    blocks = units * RBG;
+    // Where one wave per SIMD would need five to eight column ranges per unit, i.e. two workgroups and the
+    // second kernel that adds their partial sums, two workgroups that split the stage's 16-step groups
+    // instead need neither (conv5 shape fp32: 24.4 -> 22.5 us; the fused-convolution
+    // variant, whose loads of X cost more, is slower that way and keeps whole stages).
+    if (!conv && NB >= 4 && blocks * 4 < 1024 && blocks * 8 >= 1024 && N >= 8 * 2 * cpi) {
+      halves = 2;
+      NB = (NB + 1) / 2;
+      blocks *= 2;
+    }
+    fn = conv ? (gi ? find_kernel<true, true>(RB, NB, bf16) : find_kernel<true, false>(RB, NB, bf16))
+              : (gi ? find_kernel<false, true>(RB, NB, bf16) : find_kernel<false, false>(RB, NB, bf16));
+    // one wave per SIMD (1024 SIMDs): longer ranges amortise the fill of the load pipeline and keep
+    // the partial sums few; more waves per SIMD measured slower
+    int64_t ranges = (1024 + blocks - 1) / blocks;                         // column ranges = waves per unit
+    ranges = std::max<int64_t>(1, std::min(ranges, (N + 2 * cpi - 1) / (2 * cpi)));
+    ranges = std::min<int64_t>((ranges + 3) / 4 * 4, 4096);                // four per workgroup
+    chunk = ((N + ranges - 1) / ranges + cpi - 1) / cpi * cpi;
+    nsplit = ((N + chunk - 1) / chunk + 3) / 4;                            // workgroups per unit = partial sums
+  }
   if (!fn) return RBGP_EUNSUPPORTED;
-  // one wave per SIMD (1024 SIMDs): longer ranges amortise the fill of the load pipeline and keep
-  // the partial sums few; more waves per SIMD measured slower
-  int64_t ranges = (1024 + blocks - 1) / blocks;                         // column ranges = waves per unit
-  ranges = std::max<int64_t>(1, std::min(ranges, (N + 2 * cpi - 1) / (2 * cpi)));
-  ranges = std::min<int64_t>((ranges + 3) / 4 * 4, 4096);                // four per workgroup
-  const int64_t chunk = ((N + ranges - 1) / ranges + cpi - 1) / cpi * cpi;
-  const int64_t nsplit = ((N + chunk - 1) / chunk + 3) / 4;              // workgroups per unit = partial sums
   if (nsplit > 1) {
     const size_t need = size_t(nsplit) * size_t(nnz) * sizeof(float);
     if (B.partial_bytes < need) {
@@ -657,14 +680,23 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   p.colrows = B.colrows; p.colpos = B.colpos; p.rowtab = B.rowtab;
   p.N = N; p.ld_dO = ld_dO; p.ldI = ldI; p.nnz = nnz; p.chunk = chunk;
   p.src_rows = pl.SRC; p.spos = B.spos;
-  p.nbt = nbt; p.halves = halves;
+  p.nbt = nbt; p.halves = halves; p.c1 = m->c[0]; p.order = 0;
+  if (!gi) {
+    // rows of dO and I that the eight XCDs fetch with the units dealt to them by G_i vertex first, or by tile column first
+    // (us, conv3 bf16 lowered 17.4 / 15.5, fused 13.7 / 13.9; conv5 10.1 / 10.7)
+    const int64_t s = std::min(m->a[2], 8), k = conv ? m->K / 9 : m->K;
+    p.order = 8 / s * m->M + std::min<int64_t>(m->e[2], s) * k < std::min(m->c[0], 8) * m->M + k;
+  }
   p.EO = B.EO; p.RBG = RBG; p.NSTG = pl.NSTG; p.stage_rows = pl.SRC;
   p.tile_rows = m->c[1] * m->c[2] * m->c[3];
   p.a2 = pl.A2; p.a3 = m->a[2]; p.a4 = m->a[3]; p.R = pl.R;
   p.lgRS = 0;
   while ((1 << p.lgRS) < pl.RS) ++p.lgRS;
   p.MG = pl.MG; p.KCR = pl.KCR; p.rowdeg = int(m->rowdeg);
-  fn<<<dim3(unsigned(blocks), unsigned(nsplit)), dim3(256), 0, hs>>>(p);
+  if (lines)
+    fn<<<dim3(unsigned(blocks * nsplit)), dim3(64 * kLinesWaves), 0, hs>>>(p);
+  else
+    fn<<<dim3(unsigned(blocks), unsigned(nsplit)), dim3(256), 0, hs>>>(p);
   RBGP_HIP(hipGetLastError());
   if (nsplit > 1) {
     sddmm_reduce<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));

@@ -55,6 +55,55 @@ def test_backward_products_config_full_size(w):
     _check_backward(w)
 
 
+# a stage in pieces of three and two groups of 16 steps, whole stages of 36 and 48 steps, one row group per unit, units over all
+# of G_i, and 80 stage rows of it
+LINES_SHAPES = [((4, 2, 4, 2), (4, 2, 8, 9), (2, 2, 4, 9)), ((8, 4, 4, 4), (8, 2, 4, 9), (4, 2, 2, 9)),
+                ((4, 4, 2, 4), (4, 6, 4, 4), (2, 6, 2, 4)), ((8, 2, 4, 1), (8, 2, 4, 9), (2, 2, 2, 9)),
+                ((8, 1, 2, 1), (8, 5, 4, 4), (2, 5, 2, 4))]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("rows,cols,deg", LINES_SHAPES)
+def test_weight_gradient_whole_lines(rows, cols, deg, dtype):
+    """Batches from where sddmm_lines starts to several parts of the batch: widths around a step of a wave (32 columns in
+    fp32, 64 in bf16) and of a workgroup (eight of them), rows that do not start at 16 bytes."""
+    w = wl.Workload(f"lines_{dtype}", rows, cols, deg, 0, dtype, 81, 82, 83, 1.0)
+    for N, pad in ((65, 1), (128, 0), (130, 2), (255, 5), (511, 1), (512, 0), (514, 4), (1030, 2), (4160, 0), (8250, 6)):
+        lib, f32 = gh.backward_inputs(w, N)
+        _, _, ref, den = gh.oracle_backward(w, *f32)
+        dW = gh.library_sddmm(w, lib[2], lib[1], ld_pad=pad)
+        err = orc.normalised_error(dW, ref, den)
+        print(f"[gpu]   dW normalised error {err:.3e}", flush=True)
+        assert err <= 4e-6, (N, pad, err)     # (a chain of at most 1030 fp32 roundings of 2^-24 per wave grows like its root)
+
+
+@pytest.mark.parametrize("N", [130, 200])
+def test_weight_gradient_split_operands_keep_infinities_and_tiny_operands(N):
+    """fp32 weight gradients on split operands against the plain kernel: the same sums are infinite or not a number, operands
+    beyond bf16's largest number give finite sums, rows down to fp32's denormals lose nothing."""
+    w = wl.Workload("lines_inf", (4, 2, 4, 2), (4, 2, 8, 9), (2, 2, 4, 9), 0, wl.F32, 84, 85, 86, 1.0)
+    lib, _ = gh.backward_inputs(w, N)
+    I, dO = lib[1].copy(), lib[2].copy()
+    clean = gh.library_sddmm(w, dO, I)
+    I[5, 7], I[40, N - 1], dO[3, 20], dO[9, 21] = np.inf, np.nan, -np.inf, np.float32(1e37)
+    got, ref = gh.library_sddmm(w, dO, I), gh.library_sddmm(w, dO, I, kernel=GEN)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    fin = np.isfinite(ref)
+    rows = np.ones(w.M, bool)
+    rows[[3, 9]] = False
+    assert np.allclose(got[9][fin[9]], ref[9][fin[9]], rtol=1e-5)
+    same = fin & rows[:, None]
+    assert np.array_equal(got[same], clean[same])
+    scale = 2.0 ** np.random.default_rng(7).choice([0, -40, -100, -118, -130], (w.M, 1))
+    tiny = (lib[2] * scale).astype(np.float32)
+    got = gh.library_sddmm(w, tiny, lib[1])
+    cols = rb.rbgp_mask_columns(gh.make_mask(w)).reshape(w.M, -1)
+    X, D = lib[1].astype(np.float64), tiny.astype(np.float64)
+    exact = np.stack([X[cols[m]] @ D[m] for m in range(w.M)])
+    size = np.stack([np.abs(X[cols[m]]) @ np.abs(D[m]) for m in range(w.M)])
+    assert (np.abs(got - exact) <= (N + 8) * (2.0 ** -24 * size + 2.0 ** -150)).all()
+
+
 def test_weight_gradient_wrn_full_batch():
     """131072 columns: the batch is cut into many ranges whose partial sums are added in a second kernel."""
     _check_backward(wl.WRN_G1, data=False)
