@@ -585,6 +585,7 @@ struct RegState {
                                                         //   kernel arguments of the pairing kernel)
   int32_t *rowtab_bf16 = nullptr;  // bf16 kernels: [a_i][NKB*16]
   int32_t *pairs = nullptr;        // rbgp_mask::pairs
+  uint64_t *conv_tiles = nullptr;  // conv_tile: ConvTileParams::sel, ::tiles
   int32_t *rowtab_conv[2] = {nullptr, nullptr};   // fused convolution, fp32 / bf16: byte offsets for the geometry below
   int32_t *colbase[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [dtype][wide tile]: pixel offsets of the column groups
   int64_t conv_key[2][3] = {{0, 0, 0}, {0, 0, 0}};  // images, height, width of rowtab_conv
@@ -600,6 +601,76 @@ template <typename T>
 int upload(const std::vector<T> &h, T **d) {
   RBGP_HIP(hipMalloc(reinterpret_cast<void **>(d), h.size() * sizeof(T) + 16));
   RBGP_HIP(hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
+  return RBGP_OK;
+}
+
+// bf16 fused convolution of 32-row, 32-channel tiles with one column of G_i kept of every v and v + 4 (rbgp_conv_tile.hip),
+// four rows of G_o x 64 pixels per workgroup, 32 where 64 would leave CUs idle; from one workgroup per CU on.  The register
+// kernels stay where eight rows share their columns and a row has few tiles (layers 3, 4), 32-pixel workgroups would not have
+// sixteen rows of G_o, or the chip is filled just once and the two rows of G_o of their groups have the same tiles.
+// us, register kernels -> this one, VGG19, fp32 sums:
+//  layer 6 at 1/4, 8192 pixels 13.6 -> 13.8 (the same tiles: not taken; layers 5, 7 16.0 -> 13.7), 16384 22.5 -> 19.2;
+//  its input gradient 17.3 -> 13.6, 16384 30.0 -> 19.0, 6144 (32 pixels) 17.1 -> 14.8, 4096 11.7 -> 11.3 (forward 9.2 -> 11.1:
+//  not taken); layer 9 at 1/4, 2048 18.2 -> 18.0 and 20.0 -> 17.7, 8192 53 -> 35 and 61 -> 35; gradients of layer 3 at 1/4, 16384
+//  14.9 -> 10.9, 51200 46 -> 25; with half a workgroup per CU layer 4's: 12.0 -> 14.
+// *taken: the launch went this way.  (The tables are made at the first such launch.)
+int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out_bf16, const rbgp_conv_geometry &conv, int64_t N,
+                     const void *packed, uint32_t w_bytes, const void *X, int64_t chan, void *O, int64_t ldO, void *stream, bool *taken) {
+  const rbgp_reg_plan &pl = m->reg;
+  *taken = false;
+  if (!(pl.fold == 1 && m->c[0] <= 64 && m->c[1] == 4 && m->c[2] == 8 && m->d[2] == 4 && pl.KCR == 72 && pl.KC == 72 && pl.NSTG == 2 &&
+        (pl.RS == 4 || pl.RS == 8) && pl.R * m->a[2] == 32 && pl.A2 == m->a[1] && m->a[1] * m->a[3] == pl.R))
+    return RBGP_OK;
+  const int64_t per = (m->a[0] + 3) / 4;
+  const int T = (N + 63) / 64 * per >= 256 ? 2 : 1, cw = 32 * T;
+  const int64_t tiles = (N + cw - 1) / cw, wgs = 8 * ((tiles + 7) / 8) * per, W = conv.width, H = conv.height;
+  // padded rows of a workgroup's pixels: its rows, two for every image border among them, one on either side
+  const int64_t rows = cw / W, tile_bytes = 64 * (rows + 2 * ((rows + H - 2) / H) + 2) * (W + 2), most = 75 * 1024;
+  if (tiles * per < 256 || wgs > 0x7fffffff || N >= (int64_t(1) << 30) || cw % W || tile_bytes > most ||
+      (pl.RS == 8 && (T == 2 ? m->d[0] < 4 : m->a[0] < 16)))
+    return RBGP_OK;
+  for (int k = 0; k < RBGP_NUM_TUNE; ++k)
+    if (tune[k]) return RBGP_OK;
+  if (pl.RS == 8 && T == 2 && tiles * per <= 256 && m->reg_clusters.max_stages == 2 * m->d[0]) return RBGP_OK;
+  std::vector<uint64_t> t(size_t(m->a[2]) * 2 + m->a[0], 0);   // ConvTileParams::sel, then ::tiles
+  for (int u = 0; u < m->a[2]; ++u) {
+    int at[4] = {-1, -1, -1, -1}, late[4];   // place in the adjacency list, and upper half, of the column kept of v and v + 4
+    for (int k = 0; k < 4; ++k) {
+      const int v = m->adj[2][size_t(u) * 4 + k];
+      at[v & 3] = k;
+      late[v & 3] = v >> 2;
+    }
+    for (int k = 0; k < 4; ++k)
+      if (at[k] < 0) return RBGP_OK;
+    auto bytes_of = [&](int k) { return (2 * at[k] | (2 * at[k] + 1) << 8) | (2 * at[k + 1] | (2 * at[k + 1] + 1) << 8) << 16; };
+    const int places = late[0] | (2 + late[1]) << 2 | late[2] << 4 | (2 + late[3]) << 6;
+    t[size_t(u) * 2] = uint64_t(bytes_of(2)) << 32 | uint64_t(bytes_of(0));
+    t[size_t(u) * 2 + 1] = uint64_t(places | places << 8);
+  }
+  if (!st->conv_tiles) {
+    for (int u = 0; u < m->a[0]; ++u)
+      for (int k = 0; k < m->d[0]; ++k) t[size_t(m->a[2]) * 2 + u] |= uint64_t(1) << m->adj[0][size_t(u) * m->d[0] + k];
+    int rc = upload(t, &st->conv_tiles);
+    if (rc) return rc;
+  }
+  ConvTileParams cp;
+  cp.Wp = packed; cp.X = X; cp.O = O;
+  cp.sel = reinterpret_cast<const int4 *>(st->conv_tiles); cp.tiles = st->conv_tiles + m->a[2] * 2;
+  cp.ldO = ldO; cp.chan = chan; cp.w_bytes = w_bytes;
+  cp.n = int(N); cp.ntiles = int(tiles);
+  cp.h = int(H); cp.w = int(W); cp.w2 = int(W + 2); cp.hw = int(H * W);
+  cp.a1 = m->a[0]; cp.a2 = m->a[1]; cp.a3 = m->a[2]; cp.a4 = m->a[3]; cp.d1 = m->d[0];
+  cp.R = pl.R; cp.RS = pl.RS;
+  cp.frag_bytes = (rbgp_bf16_blocks32(pl.KC) + (rbgp_bf16_tail16(pl.KC) ? 1 : 0)) * 4 * pl.RS * 16;
+  cp.chunk = int(std::min<int64_t>(m->c[0], most / tile_bytes));   // (two workgroups per CU)
+  cp.obf16 = out_bf16 ? 1 : 0;
+  const size_t bytes = size_t(cp.chunk * tile_bytes);
+  rbgp_conv_tile_fn fn = rbgp_conv_tile_kernel(T);
+  if (bytes > 64 * 1024)
+    RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
+  hipLaunchKernelGGL(fn, dim3(unsigned(wgs)), dim3(256), bytes, static_cast<hipStream_t>(stream), cp);
+  RBGP_HIP(hipGetLastError());
+  *taken = true;
   return RBGP_OK;
 }
 
@@ -657,6 +728,7 @@ void rbgp_reg_release(void *state) {
   if (st->rowtab) (void)hipFree(st->rowtab);
   if (st->rowtab_bf16) (void)hipFree(st->rowtab_bf16);
   if (st->pairs) (void)hipFree(st->pairs);
+  if (st->conv_tiles) (void)hipFree(st->conv_tiles);
   for (int32_t *t : st->rowtab_conv)
     if (t) (void)hipFree(t);
   for (auto &pair : st->colbase)
@@ -719,6 +791,11 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     st = new (std::nothrow) RegState();
     if (!st) return RBGP_ENOMEM;
     *state = st;
+  }
+  if (bf16 && conv) {
+    bool taken;
+    int rc = launch_conv_tile(m, st, tune, out_bf16, *conv, N, packed, uint32_t(w_bytes), I, chs / es, O, ldO, stream, &taken);
+    if (rc || taken) return rc;
   }
   int32_t **rowtab = conv ? &st->rowtab_conv[bf16] : bf16 ? &st->rowtab_bf16 : &st->rowtab;
   int64_t *ckey = st->conv_key[bf16];

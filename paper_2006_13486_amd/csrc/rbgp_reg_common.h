@@ -162,7 +162,27 @@ struct SplitTileParams {
 };
 }  // namespace rbgp_reg
 
+namespace rbgp_reg {
+// Parameter block of conv_tile (rbgp_conv_tile.hip).
+struct ConvTileParams {
+  const void *Wp, *X;
+  void *O;
+  const uint64_t *tiles;   // [a_o] tile columns of a row of G_o (at most 64 of them), a bit each
+  const int4 *sel;         // [a_i] byte selectors and index operand of a G_i vertex (see the kernel)
+  int64_t ldO, chan;       // elements of one channel of X
+  uint32_t w_bytes;
+  int n, ntiles;           // pixels, column tiles
+  int h, w, w2, hw;        // image height, width, width + 2, height * width
+  int a1, a2, a3, a4, d1, R, RS, frag_bytes;
+  int chunk;               // tiles staged at once
+  int obf16;
+};
+}  // namespace rbgp_reg
+
 typedef void (*rbgp_reg_fn)(rbgp_reg::RegParams);
+typedef void (*rbgp_conv_tile_fn)(rbgp_reg::ConvTileParams);
+// bf16 fused convolution with the channels of a tile as an image in LDS (rbgp_conv_tile.hip), 32 T pixels per workgroup (T = 1, 2)
+rbgp_conv_tile_fn rbgp_conv_tile_kernel(int T);
 typedef void (*rbgp_split_tile_fn)(rbgp_reg::SplitTileParams);
 typedef void (*rbgp_dual_fn)(rbgp_reg::DualParams);
 // bf16 kernel for KC contraction steps per stage, RS weight rows per tile row, G 16-row

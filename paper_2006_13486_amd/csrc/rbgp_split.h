@@ -21,16 +21,24 @@ struct Split {
 };
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
-__device__ __forceinline__ Split split8(const float (&x)[8]) {
+// the parts of two values, a pair each
+__device__ __forceinline__ void split2(float y0, float y1, uint32_t (&p)[3]) {
 #pragma clang fp contract(off)   // (x * kUp is needed by itself, and a subtraction runs at twice the rate of a fused one)
+  const float x0 = y0 * kUp, x1 = y1 * kUp;
+  p[0] = bf16_pair(x0, x1);
+  const float a = x0 - bf16_lo(p[0]), b = x1 - bf16_hi(p[0]);
+  p[1] = bf16_pair(a, b);
+  p[2] = bf16_pair(a - bf16_lo(p[1]), b - bf16_hi(p[1]));
+}
+__device__ __forceinline__ Split split8(const float (&x)[8]) {
   u32x4 p0, p1, p2;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float x0 = x[2 * e] * kUp, x1 = x[2 * e + 1] * kUp;
-    p0[e] = bf16_pair(x0, x1);
-    const float a = x0 - bf16_lo(p0[e]), b = x1 - bf16_hi(p0[e]);
-    p1[e] = bf16_pair(a, b);
-    p2[e] = bf16_pair(a - bf16_lo(p1[e]), b - bf16_hi(p1[e]));
+    uint32_t p[3];
+    split2(x[2 * e], x[2 * e + 1], p);
+    p0[e] = p[0];
+    p1[e] = p[1];
+    p2[e] = p[2];
   }
   return Split{{__builtin_bit_cast(bf16x8, p0), __builtin_bit_cast(bf16x8, p1), __builtin_bit_cast(bf16x8, p2)}};
 }

@@ -100,6 +100,36 @@ def test_fused_conv3x3(case):
         assert float(np.max(np.abs(out16.astype(np.float64) - exact) / bound)) <= 1.0
 
 
+IMAGE_TILES = [  # rows of G_o no multiple of four, ragged last tiles, one or several chunks of tiles; 32 and 64 pixels, R = 4 and 8
+    (wl.Workload("tiles32_r4", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 101, 102, 103, 1.0), 343, 3, 4),
+    (wl.Workload("tiles64_r4", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 104, 105, 106, 1.0), 129, 2, 32),
+    (wl.Workload("tiles32_r8", (18, 2, 4, 4), (3, 4, 8, 9), (3, 4, 4, 9), 0, wl.BF16, 107, 108, 109, 1.0), 42, 5, 8),
+    (wl.Workload("tiles64_r8", (8, 4, 4, 2), (16, 4, 8, 9), (8, 4, 4, 9), 0, wl.BF16, 110, 111, 112, 1.0), 129, 1, 64),
+]
+
+
+@pytest.mark.parametrize("case", IMAGE_TILES, ids=lambda c: c[0].name)
+def test_fused_conv3x3_with_channels_in_lds(case):
+    """The kernel that keeps the channels of its tiles in LDS, fp32 and bf16 sums; an infinite activation reaches the sums of
+    its neighbours and of the rows that keep its channel, no others."""
+    w, B, H, W = case
+    X = wl.conv_activations(w, B, H, W)
+    X[5, B - 1, H - 1, W - 1] = X[40, 0, 0, 0] = np.inf
+    vals_lib, X_lib = wl.to_bf16_bits(wl.kept_weights(w)), wl.to_bf16_bits(X)
+    vals, X = wl.bf16_bits_as_f32(vals_lib), wl.bf16_bits_as_f32(X_lib)
+    with np.errstate(invalid="ignore"):
+        exact, den = gh.oracle_spmm(w, vals, orc.im2col_3x3(X))
+    out32 = gh.library_conv3x3(w, vals_lib, X_lib)
+    out16 = gh.library_conv3x3(w, vals_lib, X_lib, out_bf16=True)
+    assert np.array_equal((out16.view(np.uint32) >> 16).astype(np.uint16), orc.f32_to_bf16_bits(out32))
+    finite = np.isfinite(exact)
+    assert not finite.all() and np.array_equal(np.isfinite(out32), finite)
+    # nine taps of a tile in two sums of at most five instructions, tiles in a chain: far below the shared tolerance
+    err = orc.normalised_error(out32[finite], exact[finite], den[finite])
+    print(f"[gpu]   normalised error {err:.3e}", flush=True)
+    assert err <= ACC_TOL
+
+
 def test_transposed_product_and_weight_gradient_take_the_mode():
     """dI = W_s^T dO stored as bf16 (what the layer below consumes in a bf16 training step);
     rbgp_sddmm treats the two bf16 modes alike (dW stays fp32)."""
