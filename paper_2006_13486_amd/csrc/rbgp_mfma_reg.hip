@@ -1026,10 +1026,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     } else if (tsp == 0 && can && rbgp_reg_split_cycles(m) < rbgp_reg_fp32_cycles(m)) {
       // Measured against the fp32 MFMA kernels (us, fp32 -> waves by themselves / sharing): 4096^3 at density 1/4, one
       // row per column set, N = 4096 514 -> 409 / 337, 1531 207 -> 166 / 152, 1000 140 -> 112 / 116, 512 77 -> 64 / 102,
-      // 256 44 -> 40 / 101, 64 14.4 -> 35 / 100 (sparse MFMA: 75 up to 1024, by themselves 57 at 512, 82 at 640); 1/16, four rows, N = 4096 174 -> 120 / 90, 256 15.3 -> 14.9 / 30; VGG19
-      // layers at density 1/2 forward 30.2 -> 25.1 (L2), 52.9 -> 44.6 (L3), 16.1 -> 40.3 (L13: 256 waves).  So: sharing from
-      // five workgroups per four CUs on, with the sparse MFMA from five per eight; by themselves where every SIMD gets two waves, or one with a long list.  Where it
-      // takes a split in four to reach exactly that many waves, the fp32 kernels, whose waves are half as wide, run one full
+      // 256 44 -> 40 / 101, 64 14.4 -> 35 / 100 (sparse MFMA: 75 up to 1024, by themselves 57 at 512, 82 at 640); 1/16, four
+      // rows, N = 4096 174 -> 120 / 90, 256 15.3 -> 14.9 / 30; VGG19 layers at density 1/2 forward 30.2 -> 25.1 (L2), 52.9 -> 44.6 (L3), 16.1 -> 40.3 (L13: 256 waves).  So: sharing from
+      // five workgroups per four CUs on, with the sparse MFMA from five per eight; by themselves where every SIMD gets two
+      // waves, or one with a long list.  Where it takes a split in four to reach exactly that many waves, the fp32 kernels, whose waves are half as wide, run one full
       // round: stages of 72 or 64 steps then stay there (us, fp32 -> waves by themselves: L6 at 64 images 24.2 -> 27.0, at
       // 80 40.5 -> 37.5; L9 at 128 46.0 -> 47.1; one tile column, 64 steps, N = 256 23.9 -> 24.7), as do the shortest lists
       // (L2 at 64 images, 20 blocks, 16.5 -> 17.0, at 80 27.5 -> 23.8), but not stages of 32 steps (1/4, one row, N = 256

@@ -5,8 +5,8 @@
 // columns).  spmm_reg walks such a tile once per G_i vertex, in stages of 16 steps, each row of I loaded |G_i.U| / 2 times
 // for 9 to 12 of 16 MFMA rows: it waits for the load path.
 //
-// Here a workgroup takes all rows of a row of G_o (p.fold tile rows x G_i vertices x R) x 64 columns: every stage's 32 rows x 64 columns are loaded and split once, by one wave, and stay in LDS (12 KB a
-// stage); then every wave multiplies groups of 32 rows, whatever G_i vertices they belong to, with
+// Here a workgroup takes all rows of a row of G_o (p.fold tile rows x G_i vertices x R) x 64 columns: every stage's 32 rows x
+// 64 columns are loaded and split once, by one wave, and stay in LDS (12 KB a stage); then every wave multiplies groups of 32 rows, whatever G_i vertices they belong to, with
 // v_smfmac_f32_32x32x32_bf16: its index operand names the kept ones among the four columns of G_i, row by row, so that one
 // instruction serves rows of different G_i vertices and no zero of G_i is multiplied.  The packed weights are those of
 // spmm_reg, loaded four stages ahead.
@@ -18,7 +18,8 @@
 // at density 1/4, 2368 columns 24.3 -> 16, 8192 49 -> 30; layer 9 at 1/4, 2048 columns 44 -> 27; layer 3, 32768 columns
 // 62 -> 42; error against 64-bit sums 8.3e-8 -> 5.0e-8.
 // Tried: waves of 32 columns at four waves per SIMD (15.7 / 32 / 29 / 48), two stages of weights ahead with 14 spilled
-// registers (15.6 / 33 / 33 / 41), one edge of four (half of the weights zero; VGG19 conv5 24.9 -> 26.2), the next stage's operands prepared beside the products (21 / 39 / 32 / 53).
+// registers (15.6 / 33 / 33 / 41), one edge of four (half of the weights zero; VGG19 conv5 24.9 -> 26.2), the next stage's
+// operands prepared beside the products (21 / 39 / 32 / 53).
 #include <hip/hip_runtime.h>
 
 #include "rbgp_internal.h"
