@@ -164,26 +164,39 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) again |= add_up(acc[t], cor[t]) && n0 + 2 * j + t < out_n;
     if (__builtin_amdgcn_ballot_w64(again)) {   // (wave-uniform; no barrier inside)
+      // The rows of one pair of edges at a time, with the rows of I at these edges only: a row of I that is not finite must not
+      // meet a zero in the place of a weight.
+      uint64_t left = __builtin_amdgcn_ballot_w64(info[g * 32 + j].x >= 0);
+      while (left) {
+        const int pair = __builtin_amdgcn_readlane(which, __builtin_ctzll(left));
+        left &= ~__builtin_amdgcn_ballot_w64(which == pair);
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) cor[t][i] = 0.f;
-      for (int s = 0; s < cnt; ++s) {
-        const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
-        A a;
-        load_a(a, base, s);
+          for (int i = 0; i < 16; ++i) cor[t][i] = 0.f;
+        for (int s = 0; s < cnt; ++s) {
+          const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+          A a;
+          load_a(a, base, s);
 #pragma unroll
-        for (int w = 0; w < 4; ++w)
+          for (int w = 0; w < 4; ++w)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(rb, ((w * 4 + v) * 2 + h) * row_bytes + j * 8, 0, 0);
-            const float y = v == (which & 3) ? a.x[0][w] : v == (which >> 2 & 3) ? a.x[1][w] : 0.f;
+            for (int e = 0; e < 2; ++e) {
+              const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(
+                  rb, ((w * 4 + (pair >> (2 * e) & 3)) * 2 + h) * row_bytes + j * 8, 0, 0);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) cor[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y, __uint_as_float(x[t]), cor[t], 0, 0, 0);
-          }
+              for (int t = 0; t < 2; ++t)
+                cor[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x[e][w], __uint_as_float(x[t]), cor[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const bool mine = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].z == pair;
+#pragma unroll
+          for (int t = 0; t < 2; ++t)   // (every finite sum stays as it is, bit for bit)
+            acc[t][i] = acc[t][i] * 0.f == 0.f || !mine ? acc[t][i] : cor[t][i];
+        }
       }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) take_not_finite(acc[t], cor[t]);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {

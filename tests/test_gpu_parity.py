@@ -524,6 +524,33 @@ def test_many_rows_per_tile_with_two_of_four_kept(rows, cols, deg):
     assert (np.abs(got[:, 70].astype(np.float64) - ref[:, 70]) <= bound).all()
 
 
+@pytest.mark.parametrize("rows,cols,deg", MANY_ROWS[:2])
+def test_many_rows_per_tile_infinities_of_columns_a_row_does_not_keep(rows, cols, deg):
+    """Two rows of one stage of I that are not finite in the same column: a row that keeps one of them has the sum of its own kept
+    products, infinite or finite, whatever the other one holds."""
+    w = wl.Workload("many_rows", rows, cols, deg, -(-160 // rows[0]) * 64, wl.F32, 71, 72, 73, 1.0)
+    vl, Il, vf, _ = gh.host_inputs(w)
+    bad, n = Il.copy(), 0
+    at = lambda v: 64 + (4 + v) * 2 + 1          # stage 2, G_r vertex 1, G_i vertex v, G_b vertex 1
+    for v in range(4):
+        for u in range(4):
+            if u == v:
+                continue
+            for x, y in ((np.inf, np.inf), (np.inf, -np.inf), (np.nan, np.inf), (np.float32(2.0 ** 110), np.inf)):
+                bad[at(v), n], bad[at(u), n] = x, y
+                n += 1
+    got = gh.library_spmm(w, vl, bad, tag="many rows")[0][:, :n]
+    kept = rb.rbgp_mask_columns(gh.make_mask(w)).reshape(w.M, -1)
+    W, X = vf.reshape(w.M, -1).astype(np.float64), bad[:, :n].astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = np.stack([W[m] @ X[kept[m]] for m in range(w.M)])
+        size = np.stack([np.abs(W[m]) @ np.abs(X[kept[m]]) for m in range(w.M)])
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got == np.inf, ref == np.inf) and np.array_equal(got == -np.inf, ref == -np.inf)
+    fin = np.isfinite(ref)
+    assert (np.abs(got[fin] - ref[fin]) <= 1e-6 * size[fin]).all()
+
+
 # masks whose filled twin walks stages of 32 steps with at most one of k and k + 16 kept (G_i at 1/2 and 1/4, |G_b.V| of 1
 # and 2), and one whose rows keep both (a complete G_i with a sparse G_b beside it)
 FILLED_PAIRS = [((8, 1, 128, 1), (16, 1, 32, 1), (2, 1, 16, 1)), ((8, 1, 256, 1), (16, 1, 32, 1), (2, 1, 8, 1)),
