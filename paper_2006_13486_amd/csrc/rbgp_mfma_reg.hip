@@ -1059,7 +1059,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     }
   }
   const bool split = split_rw > 0;
-  if (split_rw > 1 && sparse && !st->pairs) {
+  if (!bf16 && sparse && !st->pairs) {   // (with the first call, whatever N: a wider batch may come under capture)
     int rc = upload(m->pairs, &st->pairs);
     if (rc) return rc;
   }

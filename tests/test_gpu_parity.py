@@ -586,6 +586,37 @@ def test_filled_masks_with_one_kept_weight_in_two_steps(rows, cols, deg):
         assert (np.isnan(rest) | (np.abs(rest - clean[~keeps, n]) <= 1e-5 * np.abs(clean[:, n]).max())).all()
 
 
+def test_filled_mask_on_a_wider_batch_allocates_nothing():
+    """fp32 on a filled mask: a call on a small batch, then the capture of one wide enough for the kernels that share their
+    columns, three replays on fresh inputs against the eager result."""
+    import torch
+    rows, cols, deg = FILLED_PAIRS[0]
+    w = wl.Workload("pairs_graph", rows, cols, deg, 2560, wl.F32, 61, 62, 63, 1.0)
+    mask = gh.make_mask(w)
+    rb.rbgp_mask_set_kernel(mask, FILLED)
+    stream = lambda: torch.cuda.current_stream().cuda_stream
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, w.dtype), dtype=torch.uint8, device="cuda:0")
+    rb.rbgp_pack(mask, w.dtype, wl.kept_weights(w), packed.data_ptr(), stream())
+    I = torch.zeros((w.K, w.N), device="cuda:0")
+    O = torch.zeros((w.M, w.N), device="cuda:0")
+    call = lambda n: rb.rbgp_spmm(mask, w.dtype, w.M, w.K, n, packed.data_ptr(), I.data_ptr(), w.N, O.data_ptr(), w.N, stream())
+    call(40)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(w.N)
+    for seed in (1, 2, 3):
+        I.copy_(torch.randn(I.shape, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(seed)))
+        call(w.N)
+        torch.cuda.synchronize()
+        want = O.clone()
+        O.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(O, want)
+
+
 @pytest.mark.parametrize("rows,cols,deg", [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1)), ((4, 1, 32, 4), (8, 3, 32, 1), (2, 3, 16, 1)),
                                            ((2, 2, 64, 2), (4, 2, 16, 2), (2, 2, 4, 2)), ((4, 4, 8, 4), (8, 1, 8, 4), (4, 1, 8, 2))])
 def test_lds_family_split_operands(rows, cols, deg):
