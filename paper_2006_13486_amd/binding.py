@@ -66,6 +66,7 @@ SIGNATURES = {
     "rbgp_mask_check_tables": (ctypes.c_int, [_vp]),
     "rbgp_strerror": (ctypes.c_char_p, [ctypes.c_int]),
     "rbgp_last_hip_error": (ctypes.c_char_p, []),
+    "rbgp_last_kernel": (ctypes.c_char_p, []),
 }
 
 
@@ -315,3 +316,8 @@ def rbgp_spmm(mask: Mask, dtype: int, M: int, K: int, N: int, dev_packed_ptr: in
               dev_O_ptr: int, ldO: int, stream: int = 0):
     _check(load().rbgp_spmm(mask.handle, dtype, M, K, N, dev_packed_ptr, dev_I_ptr, ldI, dev_O_ptr, ldO, stream),
            "rbgp_spmm")
+
+
+def rbgp_last_kernel() -> str:
+    """Kernel of the last product this thread launched, as a profiler lists it ("" before the first)."""
+    return load().rbgp_last_kernel().decode()

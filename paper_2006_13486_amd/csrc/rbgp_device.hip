@@ -781,6 +781,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
                                                          static_cast<const float *>(dev_I),
                                                          static_cast<float *>(dev_O));
     RBGP_HIP(hipGetLastError());
+    rbgp_set_last_kernel("spmm_generic");
     return RBGP_OK;
   }
 
@@ -813,6 +814,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
       const int64_t nblocks = 8 * ((tiles + 7) / 8) * m->a[0] * (m->a[2] / 32);
       hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS, dev->one_of_two), dim3(unsigned(nblocks)), dim3(256), 0, st, sp);
       RBGP_HIP(hipGetLastError());
+      rbgp_set_last_kernel("spmm_mfma_split", {pl.KS, dev->one_of_two});
       return RBGP_OK;
     }
   }
@@ -855,6 +857,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
   if (nblocks > 0x7fffffff) return RBGP_EUNSUPPORTED;
   hipLaunchKernelGGL(e->fn, dim3(unsigned(nblocks)), dim3(unsigned(GW * nsub * 64)), lds, st, mp);
   RBGP_HIP(hipGetLastError());
+  rbgp_set_last_kernel("spmm_mfma");
   return RBGP_OK;
 }
 

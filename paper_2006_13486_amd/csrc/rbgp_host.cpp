@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdio>
 #include <cstring>
 #include <new>
 
@@ -256,6 +257,12 @@ int ilog2_exact(int q) {  // log2(q) if q is a power of two, else -1
 
 thread_local char g_hip_error[256] = "";
 
+struct LastKernel {
+  const char *name = "", *then = nullptr;
+  int nargs = 0, args[5] = {};
+};
+thread_local LastKernel g_last_kernel;   // (put into words only when asked for: every launch writes it)
+
 }  // namespace
 
 uint64_t rbgp_next_uid() {
@@ -266,6 +273,15 @@ uint64_t rbgp_next_uid() {
 void rbgp_set_hip_error(const char *msg) {
   std::strncpy(g_hip_error, msg ? msg : "", sizeof(g_hip_error) - 1);
   g_hip_error[sizeof(g_hip_error) - 1] = 0;
+}
+
+void rbgp_set_last_kernel(const char *name, std::initializer_list<int> args, const char *then) {
+  LastKernel &k = g_last_kernel;
+  k.name = name;
+  k.then = then;
+  k.nargs = 0;
+  for (int a : args)
+    if (k.nargs < 5) k.args[k.nargs++] = a;
 }
 
 // Decide whether the MFMA kernels cover this mask and derive their tile shape.
@@ -1713,5 +1729,15 @@ const char *rbgp_strerror(int code) {
 }
 
 const char *rbgp_last_hip_error(void) { return g_hip_error; }
+
+const char *rbgp_last_kernel(void) {
+  thread_local char text[128];
+  const LastKernel &k = g_last_kernel;
+  int n = std::snprintf(text, sizeof(text), "%s", k.name);
+  for (int i = 0; i < k.nargs; ++i) n += std::snprintf(text + n, sizeof(text) - n, "%s%d", i ? ", " : "<", k.args[i]);
+  if (k.nargs) n += std::snprintf(text + n, sizeof(text) - n, ">");
+  if (k.then) std::snprintf(text + n, sizeof(text) - n, " + %s", k.then);
+  return text;
+}
 
 }  // extern "C"

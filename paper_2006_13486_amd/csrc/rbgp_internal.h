@@ -4,6 +4,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <initializer_list>
 #include <new>
 #include <vector>
 
@@ -204,6 +205,8 @@ inline rbgp_tile_plan rbgp_plan_tile(const rbgp_mask *m) {
 // device part
 void rbgp_device_release(rbgp_device_state *dev);
 void rbgp_set_hip_error(const char *msg);
+// what rbgp_last_kernel reports: name<args...>, and the launch that follows it (the strings are literals)
+void rbgp_set_last_kernel(const char *name, std::initializer_list<int> args = {}, const char *then = nullptr);
 // register-streaming family (rbgp_mfma_reg.hip); `state` is its lazily built table cache
 bool rbgp_reg_covers(const rbgp_mask *m);
 // geometry of a fused 3x3 convolution (stride 1, zero padding 1): N = images * height * width

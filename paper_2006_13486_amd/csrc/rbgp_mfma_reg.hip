@@ -670,6 +670,7 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
     RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
   hipLaunchKernelGGL(fn, dim3(unsigned(wgs)), dim3(256), bytes, static_cast<hipStream_t>(stream), cp);
   RBGP_HIP(hipGetLastError());
+  rbgp_set_last_kernel("conv_tile", {T});
   *taken = true;
   return RBGP_OK;
 }
@@ -1251,6 +1252,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(rows), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
       hipLaunchKernelGGL(rows, dim3(unsigned(wgs)), dim3(unsigned(64 * waves)), bytes, static_cast<hipStream_t>(stream), rp);
       RBGP_HIP(hipGetLastError());
+      rbgp_set_last_kernel("spmm_reg_rows");
       return RBGP_OK;
     }
   }
@@ -1302,5 +1304,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     hipLaunchKernelGGL(fn, dim3(unsigned(8 * per_xcd)), dim3(256), lds, static_cast<hipStream_t>(stream), rp);
   }
   RBGP_HIP(hipGetLastError());
+  if (dual) rbgp_set_last_kernel("spmm_reg_dual");
+  else if (share_rv) rbgp_set_last_kernel("spmm_reg_bf16_shared", {share_rv, share_pr});
+  else if (split_rw > 1) rbgp_set_last_kernel("spmm_reg_split_shared", {sparse});
+  else if (split) rbgp_set_last_kernel("spmm_reg_split");
+  else rbgp_set_last_kernel(bf16 ? "spmm_reg_bf16" : "spmm_reg");
   return RBGP_OK;
 }

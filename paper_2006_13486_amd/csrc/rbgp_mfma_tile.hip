@@ -483,5 +483,6 @@ int rbgp_tile_launch(const rbgp_mask *m, void **state, bool out_bf16, int64_t N,
   }
   hipLaunchKernelGGL(fn, dim3(unsigned(blocks)), dim3(512), lds, static_cast<hipStream_t>(stream), p);
   RBGP_HIP(hipGetLastError());
+  rbgp_set_last_kernel("spmm_tile_bf16");
   return RBGP_OK;
 }

@@ -528,6 +528,7 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   if (N == 0) {
     sddmm_zero<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(dW, nnz);
     RBGP_HIP(hipGetLastError());
+    rbgp_set_last_kernel("sddmm_zero");
     return RBGP_OK;
   }
   if (!use_mfma) {
@@ -545,6 +546,7 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
       sddmm_generic<float><<<dim3(unsigned(blocks)), dim3(256), 0, hs>>>(gp, static_cast<const float *>(dO),
                                                                         static_cast<const float *>(I), dW);
     RBGP_HIP(hipGetLastError());
+    rbgp_set_last_kernel("sddmm_generic");
     return RBGP_OK;
   }
 
@@ -702,6 +704,7 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     sddmm_reduce<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
     RBGP_HIP(hipGetLastError());
   }
+  rbgp_set_last_kernel(lines ? "sddmm_lines" : "sddmm_reg", {RB, NB, bf16, conv != nullptr, gi}, nsplit > 1 ? "sddmm_reduce" : nullptr);
   return RBGP_OK;
 }
 

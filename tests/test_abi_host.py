@@ -33,6 +33,7 @@ def test_library_exports_every_declared_symbol():
     for name in declared:
         assert hasattr(lib, name), name
     assert sorted(rb.SIGNATURES) == declared      # the binding covers the whole header
+    assert isinstance(rb.rbgp_last_kernel(), str)
 
 
 SHAPES = [w for w in wl.CONFIGS] + [wl.sdmm4096_table2(1, 2), wl.sdmm4096_table3(2, 2, 3),

@@ -65,16 +65,122 @@ LINES_SHAPES = [((4, 2, 4, 2), (4, 2, 8, 9), (2, 2, 4, 9)), ((8, 4, 4, 4), (8, 2
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("rows,cols,deg", LINES_SHAPES)
 def test_weight_gradient_whole_lines(rows, cols, deg, dtype):
-    """Batches from where sddmm_lines starts to several parts of the batch: widths around a step of a wave (32 columns in
-    fp32, 64 in bf16) and of a workgroup (eight of them), rows that do not start at 16 bytes."""
+    """Batches from where sddmm_lines starts to several parts of the batch (bf16) or where sddmm_reg takes over (fp32, from 1024
+    columns on; bf16 below 128): widths around a step of a wave (32 columns in fp32, 64 in bf16) and of a workgroup (eight of
+    them), rows that do not start at 16 bytes."""
     w = wl.Workload(f"lines_{dtype}", rows, cols, deg, 0, dtype, 81, 82, 83, 1.0)
     for N, pad in ((65, 1), (128, 0), (130, 2), (255, 5), (511, 1), (512, 0), (514, 4), (1030, 2), (4160, 0), (8250, 6)):
         lib, f32 = gh.backward_inputs(w, N)
         _, _, ref, den = gh.oracle_backward(w, *f32)
         dW = gh.library_sddmm(w, lib[2], lib[1], ld_pad=pad)
+        ran = rb.rbgp_last_kernel()
+        if dtype == wl.BF16:
+            want = "sddmm_generic" if (N + pad) % 2 else "sddmm_reg" if N < 128 else "sddmm_lines"
+        else:
+            want = "sddmm_lines" if N < 1024 else "sddmm_reg"
+        assert ran.startswith(want + "<") or ran == want, (N, ran)
+        assert ("sddmm_reduce" in ran) == (N >= (4160 if dtype == wl.BF16 else 1030)), (N, ran)
         err = orc.normalised_error(dW, ref, den)
-        print(f"[gpu]   dW normalised error {err:.3e}", flush=True)
+        print(f"[gpu]   {ran}: dW normalised error {err:.3e}", flush=True)
         assert err <= 4e-6, (N, pad, err)     # (a chain of at most 1030 fp32 roundings of 2^-24 per wave grows like its root)
+
+
+# one mask for every sddmm_lines<row groups, step groups, all of G_i>: (dtype, those three, columns, rows, cols, degrees)
+LINES_KERNELS = [
+    (wl.F32, 1, 1, 0, 505, (4, 1, 1, 1), (4, 1, 1, 9), (2, 1, 1, 9)),
+    (wl.F32, 1, 2, 0, 505, (4, 2, 4, 4), (4, 1, 4, 9), (2, 1, 2, 9)),
+    (wl.F32, 1, 3, 0, 505, (4, 1, 4, 1), (4, 3, 4, 9), (2, 3, 2, 9)),
+    (wl.F32, 2, 1, 0, 1155, (4, 4, 8, 4), (32, 1, 1, 9), (16, 1, 1, 9)),
+    (wl.F32, 2, 2, 0, 505, (4, 4, 8, 4), (4, 7, 4, 9), (2, 7, 2, 9)),
+    (wl.F32, 2, 3, 0, 1155, (32, 1, 8, 1), (8, 6, 4, 9), (4, 6, 2, 9)),
+    (wl.F32, 1, 1, 1, 505, (4, 1, 2, 1), (4, 1, 4, 1), (2, 1, 2, 1)),
+    (wl.F32, 1, 2, 1, 505, (4, 1, 4, 1), (4, 1, 2, 9), (2, 1, 1, 9)),
+    (wl.F32, 1, 3, 1, 505, (4, 1, 4, 1), (4, 1, 4, 9), (2, 1, 2, 9)),
+    (wl.F32, 2, 1, 1, 1155, (4, 1, 8, 2), (128, 1, 4, 1), (128, 1, 2, 1)),
+    (wl.F32, 2, 2, 1, 505, (4, 1, 8, 1), (32, 7, 8, 3), (32, 7, 4, 3)),
+    (wl.F32, 2, 3, 1, 505, (4, 1, 8, 4), (8, 7, 8, 9), (4, 7, 4, 9)),
+    (wl.BF16, 1, 1, 0, 505, (4, 1, 1, 1), (4, 1, 1, 9), (2, 1, 1, 9)),
+    (wl.BF16, 1, 2, 0, 505, (4, 2, 4, 4), (4, 1, 4, 9), (2, 1, 2, 9)),
+    (wl.BF16, 1, 3, 0, 4199, (4, 1, 4, 1), (4, 3, 4, 9), (2, 3, 2, 9)),
+    (wl.BF16, 1, 4, 0, 505, (4, 1, 8, 1), (16, 6, 4, 9), (8, 6, 2, 9)),
+    (wl.BF16, 1, 5, 0, 505, (4, 1, 8, 1), (16, 4, 8, 9), (8, 4, 4, 9)),
+    (wl.BF16, 2, 1, 0, 505, (4, 4, 8, 4), (32, 1, 1, 9), (16, 1, 1, 9)),
+    (wl.BF16, 2, 2, 0, 505, (4, 4, 8, 4), (32, 1, 4, 9), (16, 1, 2, 9)),
+    (wl.BF16, 2, 3, 0, 505, (32, 1, 8, 1), (8, 6, 4, 9), (4, 6, 2, 9)),
+    (wl.BF16, 2, 4, 0, 505, (32, 1, 8, 1), (16, 6, 4, 9), (8, 6, 2, 9)),
+    (wl.BF16, 2, 5, 0, 505, (32, 1, 8, 1), (16, 4, 8, 9), (8, 4, 4, 9)),
+    (wl.BF16, 1, 1, 1, 505, (4, 1, 2, 1), (4, 1, 4, 1), (2, 1, 2, 1)),
+    (wl.BF16, 1, 2, 1, 505, (4, 1, 4, 1), (4, 1, 2, 9), (2, 1, 1, 9)),
+    (wl.BF16, 1, 3, 1, 4199, (4, 1, 4, 1), (4, 1, 4, 9), (2, 1, 2, 9)),
+    (wl.BF16, 1, 4, 1, 505, (4, 1, 4, 1), (256, 3, 2, 9), (256, 3, 1, 9)),
+    (wl.BF16, 1, 5, 1, 505, (4, 1, 2, 1), (256, 1, 8, 9), (256, 1, 4, 9)),
+    (wl.BF16, 2, 1, 1, 505, (4, 1, 8, 2), (128, 1, 4, 1), (128, 1, 2, 1)),
+    (wl.BF16, 2, 2, 1, 505, (4, 1, 8, 1), (256, 1, 2, 9), (256, 1, 1, 9)),
+    (wl.BF16, 2, 3, 1, 505, (4, 1, 8, 4), (64, 1, 8, 9), (32, 1, 4, 9)),
+    (wl.BF16, 2, 4, 1, 505, (4, 1, 8, 1), (256, 3, 2, 9), (256, 3, 1, 9)),
+    (wl.BF16, 2, 5, 1, 505, (4, 1, 8, 4), (128, 1, 8, 9), (64, 1, 4, 9)),
+]
+
+
+def _kept_products(w, dO, I):
+    """sum_n dO[m][n] I[k][n] of every kept (m, k) in float64, laid out as dW."""
+    cols = rb.rbgp_mask_columns(gh.make_mask(w)).reshape(w.M, -1)
+    with np.errstate(invalid="ignore"):
+        return np.take_along_axis(dO.astype(np.float64) @ I.astype(np.float64).T, cols, axis=1)
+
+
+@pytest.mark.parametrize("dtype,RB,NB,gi,N,rows,cols,deg", LINES_KERNELS)
+def test_weight_gradient_every_kernel_of_whole_lines(dtype, RB, NB, gi, N, rows, cols, deg):
+    """On the lowered input, with a ragged last step and rows at odd dwords, and (nine taps) as a convolution of 7 x 8 images."""
+    w = wl.Workload("lines", rows, cols, deg, 0, dtype, 91, 92, 93, 1.0)
+    images = N // 56
+    name = lambda conv: f"sddmm_lines<{RB}, {NB}, {int(dtype == wl.BF16)}, {conv}, {gi}>" + (" + sddmm_reduce" if N >= 4096 else "")
+
+    def check(got, dO, I, want):
+        assert rb.rbgp_last_kernel() == want
+        err = orc.normalised_error(got, _kept_products(w, dO, I), _kept_products(w, np.abs(dO), np.abs(I)))
+        print(f"[gpu]   {want}: dW normalised error {err:.3e}", flush=True)
+        assert err <= 4e-6, (want, err)      # (as test_weight_gradient_whole_lines: chains are no longer)
+
+    lib, f32 = gh.backward_inputs(w, N)
+    check(gh.library_sddmm(w, lib[2], lib[1], ld_pad=1 if dtype == wl.BF16 else 2), f32[2], f32[1], name(0))
+    if cols[3] != 9:
+        return
+    X, dO = wl.conv_activations(w, images, 7, 8), wl.output_gradients(w, images * 56)
+    if dtype == wl.BF16:
+        Xl, dOl = wl.to_bf16_bits(X), wl.to_bf16_bits(dO)
+        X, dO = wl.bf16_bits_as_f32(Xl), wl.bf16_bits_as_f32(dOl)
+    else:
+        Xl, dOl = X, dO
+    check(gh.library_conv3x3_sddmm(w, dOl, Xl), dO, orc.im2col_3x3(X), name(1))
+
+
+@pytest.mark.parametrize("case", [c for c in LINES_KERNELS if c[0] == wl.F32 and c[1:4] in ((1, 3, 0), (1, 3, 1), (2, 2, 0))])
+def test_weight_gradient_of_a_convolution_keeps_infinities(case):
+    """fp32 on split operands with pixels and gradients that are not finite or beyond the range of the split: the second pass
+    of the fused form gives the sums of the definition, the other sums stay as they are."""
+    _, RB, NB, gi, N, rows, cols, deg = case
+    w = wl.Workload("lines_conv_inf", rows, cols, deg, 0, wl.F32, 94, 95, 96, 1.0)
+    images = N // 56
+    X, dO = wl.conv_activations(w, images, 7, 8), wl.output_gradients(w, images * 56)
+    clean = gh.library_conv3x3_sddmm(w, dO, X)
+    assert rb.rbgp_last_kernel() == f"sddmm_lines<{RB}, {NB}, 0, 1, {gi}>"
+    bad, dO_bad = X.copy(), dO.copy()
+    bad[1, 0, 0, 0], bad[2, images - 1, 6, 7], bad[0, 1, 3, 4] = np.inf, np.nan, np.float32(2.0 ** 106)
+    dO_bad[1, 60], dO_bad[2, images * 56 - 1] = -np.inf, np.float32(2.0 ** 107)
+    got = gh.library_conv3x3_sddmm(w, dO_bad, bad)
+    I = orc.im2col_3x3(bad)
+    ref, size = _kept_products(w, dO_bad, I), _kept_products(w, np.abs(dO_bad), np.abs(I))
+    # (a product of two operands near the top of fp32 leaves its range)
+    over = np.abs(ref) > np.finfo(np.float32).max
+    ref[over] = np.sign(ref[over]) * np.inf
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got == np.inf, ref == np.inf) and np.array_equal(got == -np.inf, ref == -np.inf)
+    fin = np.isfinite(ref)
+    assert fin.any() and not fin.all() and (np.abs(got[fin] - ref[fin]) <= 4e-6 * size[fin]).all()
+    kept = rb.rbgp_mask_columns(gh.make_mask(w)).reshape(w.M, -1)
+    same = ~np.any(I != orc.im2col_3x3(X), axis=1)[kept] & ~np.any(dO_bad != dO, axis=1)[:, None]
+    assert same.any() and np.array_equal(got[same], clean[same])
 
 
 @pytest.mark.parametrize("N", [130, 200])

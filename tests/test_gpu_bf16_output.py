@@ -120,6 +120,7 @@ def test_fused_conv3x3_with_channels_in_lds(case):
     with np.errstate(invalid="ignore"):
         exact, den = gh.oracle_spmm(w, vals, orc.im2col_3x3(X))
     out32 = gh.library_conv3x3(w, vals_lib, X_lib)
+    assert rb.rbgp_last_kernel() == f"conv_tile<{1 if 'tiles32' in w.name else 2}>"
     out16 = gh.library_conv3x3(w, vals_lib, X_lib, out_bf16=True)
     assert np.array_equal((out16.view(np.uint32) >> 16).astype(np.uint16), orc.f32_to_bf16_bits(out32))
     finite = np.isfinite(exact)

@@ -508,6 +508,7 @@ def test_many_rows_per_tile_with_two_of_four_kept(rows, cols, deg):
     enough = -(-160 // rows[0]) * 64 - 63
     for N, pad in ((enough - 1, 0), (enough, 1), (enough + 63, 0), (enough + 64, 3)):
         gh.check_parity(w, N=N, ld_pad=pad, expect_kernel=REG)
+        assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == (N >= enough)
     N = enough + 1
     vl, Il, vf, If = gh.host_inputs(w, N)
     bad, k = Il.copy(), 21
@@ -540,6 +541,7 @@ def test_many_rows_per_tile_infinities_of_columns_a_row_does_not_keep(rows, cols
                 bad[at(v), n], bad[at(u), n] = x, y
                 n += 1
     got = gh.library_spmm(w, vl, bad, tag="many rows")[0][:, :n]
+    assert rb.rbgp_last_kernel() == "spmm_reg_rows"
     kept = rb.rbgp_mask_columns(gh.make_mask(w)).reshape(w.M, -1)
     W, X = vf.reshape(w.M, -1).astype(np.float64), bad[:, :n].astype(np.float64)
     with np.errstate(invalid="ignore"):
@@ -567,6 +569,7 @@ def test_filled_masks_with_one_kept_weight_in_two_steps(rows, cols, deg):
     tune = (0,) * 8 + (3,)
     for N, pad in ((1, 0), (97, 3), (128, 0), (129, 5), (400, 4)):
         gh.check_parity(w, N=N, kernel=FILLED, tune=tune, ld_pad=pad, expect_kernel=FILLED)
+        assert rb.rbgp_last_kernel() == f"spmm_reg_split_shared<{int(deg[2] < cols[2])}>"   # (the last one keeps both steps)
     N = 140
     vl, Il, vf, If = gh.host_inputs(w, N)
     bad, k = Il.copy(), 21
@@ -608,6 +611,7 @@ def test_filled_mask_on_a_wider_batch_allocates_nothing():
     for seed in (1, 2, 3):
         I.copy_(torch.randn(I.shape, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(seed)))
         call(w.N)
+        assert rb.rbgp_last_kernel() == "spmm_reg_split_shared<1>"
         torch.cuda.synchronize()
         want = O.clone()
         O.fill_(float("nan"))
@@ -626,6 +630,7 @@ def test_lds_family_split_operands(rows, cols, deg):
     forced, never = (0,) * 8 + (2,), (0,) * 8 + (1,)
     for N, pad in ((4, 0), (100, 4), (128, 0), (129, 3), (300, 0)):
         gh.check_parity(w, N=N, kernel=MFMA, tune=forced, ld_pad=pad, expect_kernel=MFMA)
+        assert rb.rbgp_last_kernel() == f"spmm_mfma_split<{deg[2] * deg[3]}, {int(deg[2] < cols[2])}>"
     N = 132
     vl, Il, vf, If = gh.host_inputs(w, N)
     bad = Il.copy()
