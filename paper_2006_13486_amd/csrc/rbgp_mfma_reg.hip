@@ -586,6 +586,7 @@ struct RegState {
   int32_t *rowtab_bf16 = nullptr;  // bf16 kernels: [a_i][NKB*16]
   int32_t *pairs = nullptr;        // rbgp_mask::pairs
   uint64_t *conv_tiles = nullptr;  // conv_tile: ConvTileParams::sel, ::tiles
+  bool conv_tiles_none = false;    //   G_i does not keep one of v and v + 4 everywhere: no such tables
   int32_t *rowtab_conv[2] = {nullptr, nullptr};   // fused convolution, fp32 / bf16: byte offsets for the geometry below
   int32_t *colbase[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [dtype][wide tile]: pixel offsets of the column groups
   int64_t conv_key[2][3] = {{0, 0, 0}, {0, 0, 0}};  // images, height, width of rowtab_conv
@@ -632,22 +633,26 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
   for (int k = 0; k < RBGP_NUM_TUNE; ++k)
     if (tune[k]) return RBGP_OK;
   if (pl.RS == 8 && T == 2 && tiles * per <= 256 && m->reg_clusters.max_stages == 2 * m->d[0]) return RBGP_OK;
-  std::vector<uint64_t> t(size_t(m->a[2]) * 2 + m->a[0], 0);   // ConvTileParams::sel, then ::tiles
-  for (int u = 0; u < m->a[2]; ++u) {
-    int at[4] = {-1, -1, -1, -1}, late[4];   // place in the adjacency list, and upper half, of the column kept of v and v + 4
-    for (int k = 0; k < 4; ++k) {
-      const int v = m->adj[2][size_t(u) * 4 + k];
-      at[v & 3] = k;
-      late[v & 3] = v >> 2;
-    }
-    for (int k = 0; k < 4; ++k)
-      if (at[k] < 0) return RBGP_OK;
-    auto bytes_of = [&](int k) { return (2 * at[k] | (2 * at[k] + 1) << 8) | (2 * at[k + 1] | (2 * at[k + 1] + 1) << 8) << 16; };
-    const int places = late[0] | (2 + late[1]) << 2 | late[2] << 4 | (2 + late[3]) << 6;
-    t[size_t(u) * 2] = uint64_t(bytes_of(2)) << 32 | uint64_t(bytes_of(0));
-    t[size_t(u) * 2 + 1] = uint64_t(places | places << 8);
-  }
   if (!st->conv_tiles) {
+    if (st->conv_tiles_none) return RBGP_OK;
+    std::vector<uint64_t> t(size_t(m->a[2]) * 2 + m->a[0], 0);   // ConvTileParams::sel, then ::tiles
+    for (int u = 0; u < m->a[2]; ++u) {
+      int at[4] = {-1, -1, -1, -1}, late[4];   // place in the adjacency list, and upper half, of the column kept of v and v + 4
+      for (int k = 0; k < 4; ++k) {
+        const int v = m->adj[2][size_t(u) * 4 + k];
+        at[v & 3] = k;
+        late[v & 3] = v >> 2;
+      }
+      for (int k = 0; k < 4; ++k)
+        if (at[k] < 0) {
+          st->conv_tiles_none = true;
+          return RBGP_OK;
+        }
+      auto bytes_of = [&](int k) { return (2 * at[k] | (2 * at[k] + 1) << 8) | (2 * at[k + 1] | (2 * at[k + 1] + 1) << 8) << 16; };
+      const int places = late[0] | (2 + late[1]) << 2 | late[2] << 4 | (2 + late[3]) << 6;
+      t[size_t(u) * 2] = uint64_t(bytes_of(2)) << 32 | uint64_t(bytes_of(0));
+      t[size_t(u) * 2 + 1] = uint64_t(places | places << 8);
+    }
     for (int u = 0; u < m->a[0]; ++u)
       for (int k = 0; k < m->d[0]; ++k) t[size_t(m->a[2]) * 2 + u] |= uint64_t(1) << m->adj[0][size_t(u) * m->d[0] + k];
     int rc = upload(t, &st->conv_tiles);

@@ -73,7 +73,7 @@ def library_spmm(w, vals_lib, I_lib, kernel=rb.KERNEL_AUTO, tune=None, ld_pad=0,
     return out[:, :N], used
 
 
-def library_conv3x3(w, vals, X, dtype=None, tune=None, tag="", out_bf16=False, kernel=rb.KERNEL_AUTO):
+def library_conv3x3(w, vals, X, dtype=None, tune=None, tag="", out_bf16=False, kernel=rb.KERNEL_AUTO, calls=1):
     """Run rbgp_conv3x3 on X[C][B][H][W] (padded here: layout work, not arithmetic)."""
     import torch
     dev = torch.device("cuda:0")
@@ -92,8 +92,9 @@ def library_conv3x3(w, vals, X, dtype=None, tune=None, tag="", out_bf16=False, k
     Xp = wl.zero_padded(X)
     X_d = torch.from_numpy(Xp.view(np.int16) if Xp.dtype == np.uint16 else Xp).to(dev)
     O_d = _output(w.M, N, out_bf16)
-    rb.rbgp_conv3x3(mask, rb.BF16 if out_bf16 else dtype, w.M, C, B, H, W, packed.data_ptr(), X_d.data_ptr(),
-                    O_d.data_ptr(), N, stream)
+    for _ in range(calls):
+        rb.rbgp_conv3x3(mask, rb.BF16 if out_bf16 else dtype, w.M, C, B, H, W, packed.data_ptr(), X_d.data_ptr(),
+                        O_d.data_ptr(), N, stream)
     torch.cuda.synchronize()
     return _output_to_host(O_d, out_bf16)
 

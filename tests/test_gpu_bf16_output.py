@@ -131,6 +131,18 @@ def test_fused_conv3x3_with_channels_in_lds(case):
     assert err <= ACC_TOL
 
 
+def test_fused_conv3x3_of_tiles_that_keep_both_of_two_columns():
+    """The sizes of the kernel with channels in LDS, but a G_i (a complete graph times a sparse one) whose vertices keep columns v and
+    v + 4 both: the register kernels, on every call."""
+    w = wl.Workload("tiles_both", (6, 4, 2, 4, 1), (4, 4, 2, 4, 9), (2, 4, 2, 2, 9), 0, wl.BF16, 113, 114, 115, 1.0, roles=(0, 1, 2, 2, 3))
+    vals_lib, X_lib = wl.to_bf16_bits(wl.kept_weights(w)), wl.to_bf16_bits(wl.conv_activations(w, 129, 2, 32))
+    exact, den = gh.oracle_spmm(w, wl.bf16_bits_as_f32(vals_lib), orc.im2col_3x3(wl.bf16_bits_as_f32(X_lib)))
+    for calls in (1, 2):
+        out = gh.library_conv3x3(w, vals_lib, X_lib, calls=calls)
+        assert rb.rbgp_last_kernel() == "spmm_reg_bf16"
+        assert orc.normalised_error(out, exact, den) <= ACC_TOL
+
+
 def test_transposed_product_and_weight_gradient_take_the_mode():
     """dI = W_s^T dO stored as bf16 (what the layer below consumes in a bf16 training step);
     rbgp_sddmm treats the two bf16 modes alike (dW stays fp32)."""
