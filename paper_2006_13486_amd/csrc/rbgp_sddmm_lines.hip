@@ -29,6 +29,7 @@ namespace {
 constexpr int kWaves = rbgp_sddmm_detail::kLinesWaves;
 typedef f32x4 f32x4_u __attribute__((aligned(4)));
 typedef bf16x8 bf16x8_u __attribute__((aligned(4)));
+typedef bf16x8 bf16x8_any __attribute__((aligned(2)));
 
 template <bool BF16>
 struct Operand;
@@ -40,12 +41,11 @@ struct Operand<false> {
   static __device__ __forceinline__ u32x4 load(const void *base, int64_t elem) {
     return __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4_u *>(static_cast<const float *>(base) + elem));
   }
-  static __device__ __forceinline__ u32x4 load_tail(const void *base, int64_t elem, int valid) {
-    const float *p = static_cast<const float *>(base) + elem;
-    f32x4 r;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = e < valid ? p[e] : 0.f;
-    return __builtin_bit_cast(u32x4, r);
+  static __device__ __forceinline__ u32x4 load_any(const void *base, int64_t elem) { return load(base, elem); }
+  // moved down by s columns (1 to 3), zeros behind
+  static __device__ __forceinline__ u32x4 moved(u32x4 x, int s) {
+    x = s & 1 ? u32x4{x[1], x[2], x[3], 0} : x;
+    return s & 2 ? u32x4{x[2], x[3], 0, 0} : x;
   }
   typedef Split frag;             // operand of 16 rows x 32 columns
   static __device__ __forceinline__ frag make(const u32x4 &lo, const u32x4 &hi) {
@@ -76,12 +76,14 @@ struct Operand<true> {
   static __device__ __forceinline__ u32x4 load(const void *base, int64_t elem) {
     return __builtin_bit_cast(u32x4, *reinterpret_cast<const bf16x8_u *>(static_cast<const uint16_t *>(base) + elem));
   }
-  static __device__ __forceinline__ u32x4 load_tail(const void *base, int64_t elem, int valid) {
-    const uint16_t *p = static_cast<const uint16_t *>(base) + elem;
-    union { u32x4 v; uint16_t h[8]; } r;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r.h[e] = e < valid ? p[e] : uint16_t(0);
-    return r.v;
+  static __device__ __forceinline__ u32x4 load_any(const void *base, int64_t elem) {   // (any alignment)
+    return __builtin_bit_cast(u32x4, *reinterpret_cast<const bf16x8_any *>(static_cast<const uint16_t *>(base) + elem));
+  }
+  static __device__ __forceinline__ u32x4 moved(u32x4 x, int s) {   // (1 to 7)
+    x = s & 1 ? u32x4{__builtin_amdgcn_alignbit(x[1], x[0], 16), __builtin_amdgcn_alignbit(x[2], x[1], 16),
+                      __builtin_amdgcn_alignbit(x[3], x[2], 16), x[3] >> 16} : x;
+    x = s & 2 ? u32x4{x[1], x[2], x[3], 0} : x;
+    return s & 4 ? u32x4{x[2], x[3], 0, 0} : x;
   }
   struct frag {                   // operand of 16 rows x 64 columns
     u32x4 lo, hi;
@@ -273,16 +275,27 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) Op::template mac<RB>(a, Op::make(o[RB + b][0], o[RB + b][1]), acc[b], cor[b]);
   };
-  // the last, partly empty step: columns at and past n_hi count as zero on both sides
-  auto load_ragged = [&](Raw &r, int64_t n, int64_t n_hi) {
-    const int64_t left = n_hi - (n + ls * CPL);
-    const int valid = left <= 0 ? 0 : left >= CPL ? CPL : int(left);
-    auto part = [&](const void *base, int64_t elem) {   // (a lane's columns are mostly all there or none)
-      return valid == CPL ? Op::load(base, elem) : Op::load_tail(base, elem, valid);
+  // The last, partly empty step: columns at and past N count as zero on both sides.  A lane whose columns are not all there
+  // loads the row's last CPL ones (the host takes this kernel for N >= CPL) and moves them down: no load waits for another
+  // (column by column, and lane by lane behind branches: 3 us for the one step).
+  auto load_ragged = [&](Raw &r, int64_t n) {
+    const int64_t own = n + ls * CPL, at = own < p.N - CPL ? own : p.N - CPL, off = at - ls * CPL;
+    const int s = own - at < CPL ? int(own - at) : CPL;
+    const bool valid = s == 0;
+    const bool odd = p.N % CPL != 0;
+#pragma unroll
+    for (int i = 0; i < 2 * RB; ++i) r.a[i] = Op::load_any(p.dO, offA[i] + off);
+    if constexpr (!CONV)
+#pragma unroll
+      for (int i = 0; i < NLI; ++i) r.b[i] = Op::load_any(p.I, offB[i] + off);
+    auto cut = [&](u32x4 &x) {
+      if (odd) x = Op::moved(x, s);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = s < CPL ? x[e] : 0u;
     };
 #pragma unroll
-    for (int i = 0; i < 2 * RB; ++i) r.a[i] = part(p.dO, offA[i] + n);
-    if constexpr (CONV) {   // (N is a multiple of the group, so `valid` is all or nothing)
+    for (int i = 0; i < 2 * RB; ++i) cut(r.a[i]);
+    if constexpr (CONV) {   // (N is a multiple of the group: s is 0 or CPL)
       Raw t;
       load_all(t, 0, pixel(n));
 #pragma unroll
@@ -294,7 +307,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < NLI; ++i) r.b[i] = part(p.I, offB[i] + n);
+      for (int i = 0; i < NLI; ++i) cut(r.b[i]);
     }
   };
 
@@ -334,7 +347,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   }
   if (n_lo + steps * CPI < n_hi) {
     Raw r;
-    load_ragged(r, n_lo + steps * CPI, n_hi);
+    load_ragged(r, n_lo + steps * CPI);
     u32x4 o[NG][2];
     transpose_all(o, r);
     mac_all(o);
@@ -354,7 +367,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       clear(cor);
       for (int64_t n = n_lo; n < n_hi; n += CPI) {
         Raw r;
-        load_ragged(r, n, n_hi);
+        load_ragged(r, n);
         u32x4 o[NG][2];
         transpose_all(o, r);
 #pragma unroll
