@@ -1235,7 +1235,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // of all rows of a row of G_o x 64 columns (rbgp_mfma_reg_rows.hip), from five workgroups per eight CUs on (us, the kernels
   // above -> this one: VGG19 layer 6 at 1/4, 128 workgroups 8.9 -> 9.6, 192 13.6 -> 10.0, 256 15.3 -> 10.4, 512 26.9 -> 17.4;
   // layer 9, 128 14.0 -> 14.0, 192 22.2 -> 14.8; layer 3, 128 6.6 -> 8.2, 256 10.2 -> 8.5), where groups of 32 rows are nearly
-  // full (layer 2: 72 rows, 31.5 -> 31.2).
+  // full (layer 2: 72 rows, 31.5 -> 31.2).  Not lists of up to two stages in 17 to 23 column tiles, which leave some XCDs half as
+  // many workgroups again as others and CUs two (layer 9 at 1/16: 16 tiles 9.8 -> 8.3, 17 11.6 -> 13.6, 20 11.7 -> 12.7, 22
+  // 12.9 -> 12.8 to 13.6, 24 13.0 -> 13.0, 25 15.1 -> 13.7).
   const int rows_wg = pl.fold * m->a[2] * pl.R, groups = (rows_wg + 31) / 32;
   if (!bf16 && !conv && !dual && in_order && pl.VC == 4 && pl.NSTG == 1 && m->c[2] == 4 && m->d[2] == 2 && m->c[3] == 2 && m->d[3] == 2 &&
       tab->max_stages <= 12 && 8 * groups * 32 <= 9 * rows_wg && groups <= 64 && !tune[RBGP_TUNE_ROW_GROUPS] && !tune[RBGP_TUNE_K_SPLIT] &&
@@ -1243,14 +1245,17 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const int64_t tiles = (N + 63) / 64, all = tiles * (pl.TR / pl.fold);
     const int64_t wgs = tiles >= 8 ? 8 * ((tiles + 7) / 8) * (pl.TR / pl.fold) : all;
     const size_t bytes = size_t(tab->max_stages) * 12288 + size_t(groups) * 512;
-    if (all >= 160 && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
+    const bool uneven = tab->max_stages <= 2 && all > 256 && tiles < 24;
+    if (all >= 160 && !uneven && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
       rp.ntiles = int(tiles);
       rp.ncl = pl.TR / pl.fold;
       rp.order = tiles >= 8 ? 2 : 0;
       rp.ct_cnt = tab->max_stages;
-      // A wave per group while every workgroup has a CU to itself, or LDS holds one only (lists of more than four stages: 4
-      // waves 36, 9 waves 27 at 512 workgroups); else four waves, three workgroups a CU (layer 6: 4 waves / 9, 256 workgroups
-      // 14.1 / 10.4, 296 16.5 / 18.1, 768 21.4 / 27.0).
+      // A wave per group while every workgroup has a CU to itself, or lists are longer than four stages (eight: LDS holds one
+      // workgroup, 4 waves 36, 9 waves 27 at 512 workgroups; five and six: two of four waves fit, nine leave registers for
+      // one, 4 waves / 9: six stages, 592 workgroups 33.9 / 31.9, 1024 40.9 / 44.9, five, 296 18.3 / 19.7, 768 32.3 / 30.8);
+      // else four waves, three workgroups a CU (layer 6: 4 waves / 9, 256 workgroups 14.1 / 10.4, 296 16.5 / 18.1, 768 21.4 /
+      // 27.0).
       const int waves = all <= 256 || tab->max_stages > 4 ? std::min(groups, 9) : 4;
       reg_fn rows = rbgp_reg_rows_kernel();
       if (bytes > 64 * 1024)

@@ -525,6 +525,14 @@ def test_many_rows_per_tile_with_two_of_four_kept(rows, cols, deg):
     assert (np.abs(got[:, 70].astype(np.float64) - ref[:, 70]) <= bound).all()
 
 
+def test_many_rows_per_tile_of_short_lists_by_batch():
+    """Lists of two stages, 16 rows of G_o: up to 16 column tiles and from 24 on, not where they load the XCDs unevenly."""
+    w = wl.Workload("many_rows", (16, 4, 8, 3), (16, 4, 4, 2), (2, 4, 2, 2), 333, wl.F32, 71, 72, 73, 1.0)
+    for N, taken in ((1024, True), (1025, False), (1472, False), (1473, True)):
+        gh.check_parity(w, N=N, expect_kernel=REG)
+        assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == taken, N
+
+
 @pytest.mark.parametrize("rows,cols,deg", MANY_ROWS[:2])
 def test_many_rows_per_tile_infinities_of_columns_a_row_does_not_keep(rows, cols, deg):
     """Two rows of one stage of I that are not finite in the same column: a row that keeps one of them has the sum of its own kept
