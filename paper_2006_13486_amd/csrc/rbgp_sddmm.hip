@@ -569,6 +569,7 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   int RBl = RB, NBl = std::min(nbt, bf16 ? 5 : 3);
   int64_t parts = 1;
   auto count = [&](int r, int n) { return units * ((groups + r - 1) / r) * ((nbt + n - 1) / n); };
+  const int64_t most_parts = (256 + count(RB, nbt) - 1) / count(RB, nbt);   // partial sums that any batch takes, in either kernel
   // (sddmm_reg writes dW itself: one workgroup per unit, see below)
   const bool one_launch = count(RB, nbt) >= 256 || (!conv && nbt >= 4 && count(RB, nbt) >= 128 && N >= 16 * (bf16 ? 32 : 16));
   bool lines;
@@ -580,23 +581,40 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     // 13.8 / 10.1 / 13.3; layer 6 at 1/2 26.3 -> 20.2 / 18.6 / 21, at 1/8 16.8 -> 14.8 / 13.5 / 13.6.
     // With sddmm_reg stay batches of less than a wave's two steps, many units of a short batch (its four waves reach further
     // into it; layer 9 at 1/2: 208 columns 9.7 / 14.9, 1024 16.2 / 19.1, 1536 23.9 / 20.3), and where it needs one launch and
-    // the eight waves' steps of 64 columns come out uneven (layer 9 at 1/4, 1696 columns 13.6 / 16.5, layer 8, 1760 10.5 / 12.5).
+    // the eight waves' steps of 64 columns come out uneven (layer 9 at 1/4, 1696 columns 13.6 / 16.5, layer 8, 1760 10.5 / 12.5)
+    // or, on the lowered input, are two per wave, or rows do not start at whole lines (ratios: layers 8-11 at 1/2 to 1/8, 928
+    // to 1024 columns 1.00-1.19, 1408 0.96-1.03, layer 9 at 1/2, 1952 1.10, 1920 0.94; layer 9 at 1/16, 1504 1.11, 1536 0.97).
     const int64_t most = std::max<int64_t>(1, N / 2048);
     const bool uneven = N < 4096 && 10 * N < 9 * ((N + 511) / 512 * 512);
-    lines = N >= 128 && !(count(RBl, NBl) >= 512 && N < 1536) && !(one_launch && uneven);
+    const bool broken = N < 4096 && (ld_dO % 64 || ldI % 64);
+    lines = N >= 128 && !(count(RBl, NBl) >= 512 && N < 1536) &&
+            !(one_launch && (uneven || (!conv && N > 512 && (N < 1408 || broken))));
     if (count(RBl, NBl) < 256) {
       NBl = std::min(nbt, 3);
       if (RBl == 2 && count(2, NBl) < 256 && (count(1, NBl) >= 256 || count(2, NBl) * most < 256)) RBl = 1;
       parts = std::min((256 + count(RBl, NBl) - 1) / count(RBl, NBl), most);
     }
+    // A unit that stays with one workgroup has only its longer steps to gain from, on the lowered input: not where the batch
+    // gives half of the waves none (layer 2 at 1/4, 256 columns 1.05, 512 0.76), nor where its parts do not fill the chip, as
+    // sddmm_reg's ranges do (3072 0.93, 3328 to 14336 1.00-1.11, 16384 0.88; fewer units than 32 0.92-1.04 and better).
+    if (!conv && count(RBl, NBl) == units && (N <= 256 || (!gi && units >= 32 && N > 3200 && units * parts < 256))) lines = false;
   } else {
     // fp32: where one round of workgroups of 2 x 3 groups (or, on short batches, 1 x 3) covers the units (us, before -> 2 x 3
     // / 1 x 3: conv5, 2048 columns 22.9 -> 20.5 / 26, fused 23.2 -> 20.6; layer 6 at 1/2, 8192 columns 72.7 -> 59.1; at 1/4,
     // 2368 columns 19.1 -> 21.4 / 16.3, 8192 38.1 -> 56 / 43.9); below 1024 columns not where sddmm_reg needs one launch on the
-    // lowered input (layer 6 at 1/4, 320 columns 10.9 -> 6.7; conv5 fused, 512 columns 13.7 -> 10.2, lowered 9.8 -> 10.3).
+    // lowered input (layer 6 at 1/4, 320 columns 10.9 -> 6.7; conv5 fused, 512 columns 13.7 -> 10.2, lowered 9.8 -> 10.3), and
+    // from 512 on only where a unit is split over workgroups (layer 2 at 1/4, 512 0.98, 768 1.05; split 0.60-0.95).
+    // From 1024 on (ratios): two row groups 0.87-0.97, fused until the loads of the windows outweigh the second launch (layer 6
+    // at 1/2, 4352 columns 0.97, 5248 1.04, 8192 1.07); halved to one row group until 2560 (layers 4 at 1/2 and 5 at 1/4, 2560
+    // 0.91 and 0.87, fused 0.95, 2816 0.97 and 0.95, fused 1.0-1.02, 4096 1.03 and 1.00, fused 1.06, 8192 1.24, fused 1.33);
+    // one row group to begin with fused only (layer 9 at 1/16, 1024 0.89, 1696 0.99, 1760 to 2048 1.02-1.06; lowered 1024
+    // 1.10, 1536 0.97, 2048 1.12).
     if (RBl == 2 && count(2, NBl) < 224) RBl = 1;
-    lines = count(RBl, NBl) <= 256 &&
-            (N < 1024 ? N > 64 && (conv || !one_launch || N <= 256) : count(RBl, NBl) >= 224 && (RBl == RB || N <= 2560));
+    const int64_t wgs = count(RBl, NBl);
+    if (N < 1024)
+      lines = wgs <= 256 && N > 64 && (conv || !one_launch || N <= 256) && (N <= 512 || wgs > units);
+    else
+      lines = wgs <= 256 && wgs >= 224 && (RBl == 2 ? !conv || N < 4480 : RB == 2 ? N <= 2560 : conv && N < 1728);
   }
   int64_t blocks, chunk, nsplit;
   int halves = 1;
@@ -636,9 +654,10 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   }
   if (!fn) return RBGP_EUNSUPPORTED;
   if (nsplit > 1) {
-    const size_t need = size_t(nsplit) * size_t(nnz) * sizeof(float);
+    size_t need = size_t(nsplit) * size_t(nnz) * sizeof(float);
     if (B.partial_bytes < need) {
       if (!B.grow) return RBGP_ETOOLARGE;
+      need = size_t(std::max(nsplit, most_parts)) * size_t(nnz) * sizeof(float);
       SddmmState *g = B.grow;
       if (g->partial) RBGP_HIP(hipFree(g->partial));   // (waits for launches that still use it)
       g->partial = nullptr;

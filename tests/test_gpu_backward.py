@@ -155,6 +155,67 @@ def test_weight_gradient_every_kernel_of_whole_lines(dtype, RB, NB, gi, N, rows,
     check(gh.library_conv3x3_sddmm(w, dOl, Xl), dO, orc.im2col_3x3(X), name(1))
 
 
+# (mask, dtype, side of the images or 0 on the lowered input, columns, padding of the rows, kernel): both sides of the lines
+# that the dispatch draws by the batch
+ONE_LAUNCH = ((16, 4, 4, 2), (16, 4, 8, 9), (2, 4, 4, 9))     # (one row group per unit)
+UNSPLIT = ((4, 4, 4, 2), (8, 2, 4, 9), (4, 2, 2, 9))          # (a workgroup per unit)
+TWO_GROUPS = ((8, 4, 4, 2), (8, 4, 8, 9), (4, 4, 8, 9))
+BY_BATCH = [(ONE_LAUNCH, wl.BF16, 0, 512, 0, "lines"), (ONE_LAUNCH, wl.BF16, 0, 960, 0, "reg"), (ONE_LAUNCH, wl.BF16, 0, 1408, 0, "lines"),
+            (ONE_LAUNCH, wl.BF16, 0, 1408, 8, "reg"), (ONE_LAUNCH, wl.F32, 0, 256, 0, "lines"), (ONE_LAUNCH, wl.F32, 0, 1024, 0, "reg"),
+            (ONE_LAUNCH, wl.F32, 4, 1712, 0, "lines"), (ONE_LAUNCH, wl.F32, 4, 1728, 0, "reg"),
+            (UNSPLIT, wl.BF16, 0, 256, 0, "reg"), (UNSPLIT, wl.BF16, 0, 258, 6, "lines"), (UNSPLIT, wl.BF16, 0, 3200, 0, "lines"),
+            (UNSPLIT, wl.BF16, 0, 3328, 0, "reg"), (UNSPLIT, wl.BF16, 8, 3328, 0, "lines"), (UNSPLIT, wl.BF16, 0, 16384, 0, "lines"),
+            (UNSPLIT, wl.F32, 0, 512, 0, "lines"), (UNSPLIT, wl.F32, 0, 514, 1, "reg"),
+            (TWO_GROUPS, wl.F32, 8, 4416, 0, "lines"), (TWO_GROUPS, wl.F32, 8, 4480, 0, "reg"), (TWO_GROUPS, wl.F32, 0, 4480, 3, "lines")]
+
+
+@pytest.mark.parametrize("mask,dtype,side,N,pad,kernel", BY_BATCH)
+def test_weight_gradient_kernel_by_batch(mask, dtype, side, N, pad, kernel):
+    w = wl.Workload("by_batch", *mask, 0, dtype, 97, 98, 99, 1.0)
+    dO = wl.output_gradients(w, N)
+    I = wl.conv_activations(w, N // side ** 2, side, side) if side else wl.activations(w, N)
+    bits = wl.to_bf16_bits if dtype == wl.BF16 else lambda x: x
+    back = wl.bf16_bits_as_f32 if dtype == wl.BF16 else lambda x: x
+    dO_lib, I_lib = bits(dO), bits(I)
+    got = gh.library_conv3x3_sddmm(w, dO_lib, I_lib) if side else gh.library_sddmm(w, dO_lib, I_lib, ld_pad=pad)
+    assert rb.rbgp_last_kernel().startswith(f"sddmm_{kernel}<")
+    dO, I = back(dO_lib), back(I_lib)
+    I = orc.im2col_3x3(I) if side else I
+    err = orc.normalised_error(got, _kept_products(w, dO, I), _kept_products(w, np.abs(dO), np.abs(I)))
+    print(f"[gpu]   {rb.rbgp_last_kernel()}: dW normalised error {err:.3e}", flush=True)
+    assert err <= 4e-6
+
+
+@pytest.mark.parametrize("dtype,large,small", [(wl.F32, 2100, 2048), (wl.BF16, 20992, 10240)])
+def test_weight_gradient_of_a_smaller_batch_allocates_nothing(dtype, large, small):
+    """An eager call on a batch that takes fewer partial sums than a smaller one does, then the capture of the smaller one:
+    three replays on fresh inputs against the eager result."""
+    import torch
+    w = wl.Workload("smaller", *UNSPLIT, 0, dtype, 97, 98, 99, 1.0)
+    mask = gh.make_mask(w)
+    t = torch.float32 if dtype == wl.F32 else torch.bfloat16
+    dO, I = (torch.randn((rows, large), device="cuda:0").to(t) for rows in (w.M, w.K))
+    dW = torch.zeros(w.nnz, device="cuda:0")
+    call = lambda N: rb.rbgp_sddmm(mask, dtype, w.M, w.K, N, dO.data_ptr(), large, I.data_ptr(), large, dW.data_ptr(),
+                                   torch.cuda.current_stream().cuda_stream)
+    call(large)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(small)
+    assert "sddmm_reduce" in rb.rbgp_last_kernel()
+    for _ in range(3):
+        dO.copy_(torch.randn(dO.shape, device="cuda:0"))
+        call(small)
+        torch.cuda.synchronize()
+        want = dW.clone()
+        dW.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dW, want)
+
+
 @pytest.mark.parametrize("case", [c for c in LINES_KERNELS if c[0] == wl.F32 and c[1:4] in ((1, 3, 0), (1, 3, 1), (2, 2, 0))])
 def test_weight_gradient_of_a_convolution_keeps_infinities(case):
     """fp32 on split operands with pixels and gradients that are not finite or beyond the range of the split: the second pass
