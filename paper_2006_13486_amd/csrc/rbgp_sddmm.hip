@@ -653,20 +653,20 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     nsplit = ((N + chunk - 1) / chunk + 3) / 4;                            // workgroups per unit = partial sums
   }
   if (!fn) return RBGP_EUNSUPPORTED;
-  if (nsplit > 1) {
-    size_t need = size_t(nsplit) * size_t(nnz) * sizeof(float);
-    if (B.partial_bytes < need) {
-      if (!B.grow) return RBGP_ETOOLARGE;
-      need = size_t(std::max(nsplit, most_parts)) * size_t(nnz) * sizeof(float);
-      SddmmState *g = B.grow;
-      if (g->partial) RBGP_HIP(hipFree(g->partial));   // (waits for launches that still use it)
-      g->partial = nullptr;
-      g->partial_bytes = 0;
-      RBGP_HIP(hipMalloc(reinterpret_cast<void **>(&g->partial), need));
-      g->partial_bytes = need;
-      B.partial = g->partial;
-      B.partial_bytes = need;
-    }
+  // Partial sums: a mask's first call makes room for the most that any batch takes, also where its own needs none (a larger
+  // batch may go to sddmm_lines in one launch and a smaller one, under capture, to sddmm_reg in two).
+  const int64_t room = B.grow ? std::max(nsplit, most_parts) : nsplit;
+  const size_t need = room > 1 ? size_t(room) * size_t(nnz) * sizeof(float) : 0;
+  if (B.partial_bytes < need) {
+    if (!B.grow) return RBGP_ETOOLARGE;
+    SddmmState *g = B.grow;
+    if (g->partial) RBGP_HIP(hipFree(g->partial));   // (waits for launches that still use it)
+    g->partial = nullptr;
+    g->partial_bytes = 0;
+    RBGP_HIP(hipMalloc(reinterpret_cast<void **>(&g->partial), need));
+    g->partial_bytes = need;
+    B.partial = g->partial;
+    B.partial_bytes = need;
   }
   SddmmParams p;
   p.colbase = nullptr; p.chan_elems = 0; p.conv_w2 = 0; p.x_bytes = 0;

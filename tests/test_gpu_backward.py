@@ -186,12 +186,16 @@ def test_weight_gradient_kernel_by_batch(mask, dtype, side, N, pad, kernel):
     assert err <= 4e-6
 
 
-@pytest.mark.parametrize("dtype,large,small", [(wl.F32, 2100, 2048), (wl.BF16, 20992, 10240)])
-def test_weight_gradient_of_a_smaller_batch_allocates_nothing(dtype, large, small):
-    """An eager call on a batch that takes fewer partial sums than a smaller one does, then the capture of the smaller one:
-    three replays on fresh inputs against the eager result."""
+FEW_UNITS = ((4, 4, 8, 4), (28, 1, 8, 9), (14, 1, 4, 9))      # (224 units of one workgroup: partial sums in sddmm_reg only)
+
+
+@pytest.mark.parametrize("mask_of,dtype,large,small", [(UNSPLIT, wl.F32, 2100, 2048), (UNSPLIT, wl.BF16, 20992, 10240),
+                                                       (FEW_UNITS, wl.F32, 2000, 700)])
+def test_weight_gradient_of_a_smaller_batch_allocates_nothing(mask_of, dtype, large, small):
+    """An eager call on a batch that takes fewer partial sums than a smaller one does, or none, then the capture of the smaller
+    one: three replays on fresh inputs against the eager result."""
     import torch
-    w = wl.Workload("smaller", *UNSPLIT, 0, dtype, 97, 98, 99, 1.0)
+    w = wl.Workload("smaller", *mask_of, 0, dtype, 97, 98, 99, 1.0)
     mask = gh.make_mask(w)
     t = torch.float32 if dtype == wl.F32 else torch.bfloat16
     dO, I = (torch.randn((rows, large), device="cuda:0").to(t) for rows in (w.M, w.K))
