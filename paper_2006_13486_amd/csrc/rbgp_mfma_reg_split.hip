@@ -544,11 +544,8 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     for (int it = 0; it < IT; ++it)
 #pragma unroll
       for (int r = 0; r < 4; r += 2) {
-        const float x0 = araw[it][r] * kUp, x1 = araw[it][r + 1] * kUp;
-        const uint32_t p0 = bf16_pair(x0, x1);
-        const float x = x0 - bf16_lo(p0), y = x1 - bf16_hi(p0);
-        const uint32_t p1 = bf16_pair(x, y), p2 = bf16_pair(x - bf16_lo(p1), y - bf16_hi(p1));
-        const uint32_t part[3] = {p0, p1, p2};
+        uint32_t part[3];
+        split2(araw[it][r], araw[it][r + 1], part);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
           wl[k * 512 * WB + to[it] + 8 * r] = halfword(part[k]);
