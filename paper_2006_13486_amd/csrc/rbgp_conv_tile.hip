@@ -1,6 +1,8 @@
 // bf16 fused 3x3 convolution on the sparse matrix core, for masks whose tiles are 32 rows by 32 channels (|G_r.V| = 4,
-// |G_i.V| = 8, the nine taps in G_b) and whose G_i keeps exactly one of the columns v and v + 4 (one 2-lift): VGG19's layers from
-// 128 channels on at densities 1/4 and below, and their transposes, which give the input gradient.
+// |G_i.V| = 8, the nine taps in G_b) and whose G_i keeps exactly one of the columns v and v + 4 (one 2-lift).  Of VGG19 with 128
+// images, by the dispatch rule: forward layers 5, 7 at 1/4, 8 at 1/4 and 1/8, 9-11 at 1/4 to 1/16; input gradients of layers 3, 4 at
+// 1/4, 5-7 at 1/4 and 1/8, 9-11 at 1/4 to 1/16.  (The rest have other tiles, few or the same tiles in
+// a row, or fewer workgroups than CUs.)
 //
 // The register kernels load a channel nine times, once per tap, six of them at 2-byte alignment, and transpose it in
 // registers.  Here a workgroup takes four rows of G_o x 32 T pixels in image order; the channels of the tiles that any of
@@ -19,8 +21,10 @@
 // What bounds it (conv3, timing-only builds of one chain): 13.6 in all, 9.5 without the products (launch 2.5; tables, channels
 // and weights one after the other; stores 1), 11.2 without the staging, 12 without the reads of the image: one workgroup per CU
 // has nothing to overlap these with, a larger batch has (16384 pixels: 19.3, not 28).
-// Tried: fp32, operands split in three: layer 6 at 1/4, 8192 pixels 25.7 -> 29, gradient 34.7 -> 29, layer 9 25 -> 51 (three times the
-// LDS: one or two tiles at once).  Stores that pair the bf16 sums of two lanes: 14.3 -> 16.9.
+// Counters (conv3): matrix core 7 % busy, waves wait for 41 % of their cycles, LDS bank conflicts of 5000 cycles per CU (the stores
+// of the image's pixels and their reads).
+// Tried: fp32, operands split in three: layer 6 at 1/4, 8192 pixels 25.7 -> 29, its gradient 34.7 -> 29 (the one that gained), layer 9
+// 25 -> 51 (three times the LDS: one or two tiles at once).  Stores that pair the bf16 sums of two lanes: 14.3 -> 16.9.
 #include <hip/hip_runtime.h>
 
 #include "rbgp_internal.h"

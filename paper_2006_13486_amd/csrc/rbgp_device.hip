@@ -791,10 +791,10 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
   if ((reinterpret_cast<uintptr_t>(dev_I) & 15) || (ldI % epc)) return RBGP_ESHAPE;
   // fp32 on the bf16 matrix core (spmm_mfma_split): four rows per column set, 32 rows of I per stage of which G_i keeps 8 or
   // 16 (16: where a caller asks for this family; AUTO runs such masks filled), whole workgroups of 32 G_i vertices, and
-  // five workgroups for eight CUs.  4096 x 4096, G_o and G_i at 1/4, us, spmm_mfma
-  // -> spmm_mfma_split: N = 16 46 -> 54, 512 49 -> 60 (128 workgroups), 600 85 -> 61 (160), 1000 88 -> 64, 1531 126 -> 90, 2048
-  // 111 -> 95, 4096 203 -> 176.  (With a non-finite column at 1531 240, without a finite one 260: spmm_mfma's time does not
-  // depend on the values.)
+  // five workgroups for eight CUs.  4096 x 4096, G_o and G_i at 1/4 (a vertex keeps one weight of two steps: the sparse MFMA),
+  // us, spmm_mfma -> spmm_mfma_split: N = 16 46.1 -> 45.1, 256 48.2 -> 50.8, 512 48.9 -> 51.1 (128 workgroups), 600 84.8 -> 51.0
+  // (160), 1000 90.6 -> 54.6, 1531 127.9 -> 77.5, 2048 112 -> 83, 4096 200 -> 151.  (With a non-finite column at 1531 103, without
+  // a finite one 115: spmm_mfma's time does not depend on the values.)
   {
     const int tsp = dev->tune[RBGP_TUNE_SPLIT_OPERANDS];
     const int64_t tiles = (N + 127) / 128, wgs = int64_t(m->a[0]) * (m->a[2] / 32) * tiles;

@@ -20,8 +20,8 @@
 // An operand that is Inf, NaN or at least 2^105 makes Inf - Inf of the split, and sums from 2^82 on leave fp32's range: a
 // wave that finds a non-finite sum multiplies its tile again with fp32 MFMAs, which keep Inf as Inf.
 //
-// What bounds it: per 16 steps x 32 rows x 128 columns a wave issues 24 MFMAs (768 cycles) and ~280 vector
-// instructions for the splits (1120 cycles; the scaling is 40 of them and costs 1-5 %); two waves share a SIMD, one
+// What bounds it: per 16 steps x 32 rows x 128 columns a wave issues 24 MFMAs (768 cycles) and 275 vector
+// instructions, most of them the splits (1100 cycles; the scaling is 40 of them and costs 1-5 %); two waves share a SIMD, one
 // multiplying while the other splits.  Measured, 4096^3 fp32, one row per column set at density 1/8 (34.4 GFLOP on the
 // filled mask): 309 us on the fp32 MFMAs -> 212.
 #include <hip/hip_runtime.h>
@@ -219,8 +219,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
 
 // The same product where four pairs of tile rows have one stage list: the four waves of a workgroup take one pair each
 // on the same 128 columns, split every value of I once between them and pass the parts through LDS (stored in the
-// operand layout, 16 bytes per lane: no bank conflicts).  Vector instructions per MFMA fall from 10 to 4.5, which leaves
-// the matrix core as the bound (61 % busy at the 1.7-1.9 GHz the card clocks down to under this load: 1.2 PFLOP/s of bf16
+// operand layout, 16 bytes per lane: no bank conflicts).  Vector instructions per MFMA fall from 11 to 5, which leaves
+// the matrix core as the bound (58 % busy at the 1.7-1.9 GHz the card clocks down to under this load: 1.2 PFLOP/s of bf16
 // products, what a large library product in bf16 reaches); one barrier per two blocks of 16 steps, double-buffered.
 // 4096^3 fp32, one row per column set at density 1/4 (68.7 GFLOP on the filled mask): 519 us on the fp32 MFMAs -> 330
 // (waves by themselves 409; two waves sharing 64 columns 415, four sharing 64 columns 379).
@@ -234,9 +234,10 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
 // are held in a register.  Operands: the lane of half h holds the compressed weights of steps 4 w + 2 h + g (w = 0..3, then
 // g = 0, 1), and the first four belong to the rows of I in the lanes of half 0, the others to half 1, so there the lane of
 // half h holds the rows of steps 4 w + h, then 4 w + 2 + h, each with its partner 16 further.
-// 4096^3 fp32, one row per column set at density 1/4: 316 -> 238 us, error against 64-bit sums 1.53e-7 -> 1.43e-7 (half as
-// many roundings); bound by the vector instructions of the splits and the passes through LDS (waves of 64 rows x 64
-// columns, which read half as much LDS and split the weights twice: 263).
+// 4096^3 fp32, one row per column set at density 1/4: 330 -> 247 us, error against 64-bit sums 1.53e-7 -> 1.43e-7 (half as
+// many roundings); bound by issue: a stage's 24 MFMAs and 198 vector instructions per wave keep the matrix core busy for 40 %
+// and the vector units for 50 % of the launch, at 1.8 GHz, and waves wait for 14 % of theirs (waves of 64 rows x 64 columns, which
+// read half as much LDS and split the weights twice: 263 against 238 on one machine).
 template <bool SPARSE>
 __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
   constexpr int NT = 4, CW = NT * 32;           // 32-column blocks, columns of a workgroup
@@ -446,8 +447,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // column in the tile rows with that tile non-finite (the zeros of G_i are multiplied): such sums are added up again from
 // the kept weights, with the 4x4x1 MFMAs and in the order of spmm_mfma.  4096 x 4096, G_o and G_i at 1/4, N = 1531:
 // 126 -> 83 us, error against 64-bit sums 2.0e-7 -> 7.6e-8, with the sparse MFMA (SPARSE, see spmm_reg_split_shared: no
-// vertex keeps both k and k + 16; the weights are scattered among the 16 steps) 65 and 7.4e-8; with one infinity 240, with no finite column 260 (a lane adding
-// its sums up one by one: 470 and 1420).
+// vertex keeps both k and k + 16; the weights are scattered among the 16 steps) 65 and 7.4e-8; inputs with one infinity 1.34 times
+// that, with no finite column 1.49 times (dense, a lane adding its sums up one by one: 3.7 and 11 times).
 template <int KS, bool SPARSE>
 __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   constexpr int CW = 128, IT = KS / 8;
