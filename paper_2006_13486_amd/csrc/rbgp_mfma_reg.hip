@@ -1237,7 +1237,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // layer 9, 128 14.0 -> 14.0, 192 22.2 -> 14.8; layer 3, 128 6.6 -> 8.2, 256 10.2 -> 8.5), where groups of 32 rows are nearly
   // full (layer 2: 72 rows, 31.5 -> 31.2).  Not lists of up to two stages in 17 to 23 column tiles, which leave some XCDs half as
   // many workgroups again as others and CUs two (layer 9 at 1/16: 16 tiles 9.8 -> 8.3, 17 11.6 -> 13.6, 20 11.7 -> 12.7, 22
-  // 12.9 -> 12.8 to 13.6, 24 13.0 -> 13.0, 25 15.1 -> 13.7).
+  // 12.9 -> 12.8 to 13.6, 24 13.0 -> 13.0, 25 15.1 -> 13.7), nor on a CU each in 17 to 20, which spmm_reg walks a sixth faster than 21
+  // (layers 5-7 at 1/8: 20 tiles 7.6 -> 8.3, 21 9.0 -> 8.4, 24 9.0 -> 8.5).
   const int rows_wg = pl.fold * m->a[2] * pl.R, groups = (rows_wg + 31) / 32;
   if (!bf16 && !conv && !dual && in_order && pl.VC == 4 && pl.NSTG == 1 && m->c[2] == 4 && m->d[2] == 2 && m->c[3] == 2 && m->d[3] == 2 &&
       tab->max_stages <= 12 && 8 * groups * 32 <= 9 * rows_wg && groups <= 64 && !tune[RBGP_TUNE_ROW_GROUPS] && !tune[RBGP_TUNE_K_SPLIT] &&
@@ -1245,7 +1246,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const int64_t tiles = (N + 63) / 64, all = tiles * (pl.TR / pl.fold);
     const int64_t wgs = tiles >= 8 ? 8 * ((tiles + 7) / 8) * (pl.TR / pl.fold) : all;
     const size_t bytes = size_t(tab->max_stages) * 12288 + size_t(groups) * 512;
-    const bool uneven = tab->max_stages <= 2 && all > 256 && tiles < 24;
+    const bool uneven = tab->max_stages <= 2 && (all > 256 ? tiles < 24 : tiles > 16 && tiles <= 20);
     if (all >= 160 && !uneven && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
       rp.ntiles = int(tiles);
       rp.ncl = pl.TR / pl.fold;

@@ -526,11 +526,13 @@ def test_many_rows_per_tile_with_two_of_four_kept(rows, cols, deg):
 
 
 def test_many_rows_per_tile_of_short_lists_by_batch():
-    """Lists of two stages, 16 rows of G_o: up to 16 column tiles and from 24 on, not where they load the XCDs unevenly."""
-    w = wl.Workload("many_rows", (16, 4, 8, 3), (16, 4, 4, 2), (2, 4, 2, 2), 333, wl.F32, 71, 72, 73, 1.0)
-    for N, taken in ((1024, True), (1025, False), (1472, False), (1473, True)):
-        gh.check_parity(w, N=N, expect_kernel=REG)
-        assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == taken, N
+    """Lists of two stages: 16 rows of G_o up to 16 column tiles and from 24 on, not where they load the XCDs unevenly, 8 rows
+    from 21 tiles on."""
+    for rows, widths in ((16, ((1024, True), (1025, False), (1472, False), (1473, True))), (8, ((1280, False), (1281, True)))):
+        w = wl.Workload("many_rows", (rows, 4, 8, 3), (rows, 4, 4, 2), (2, 4, 2, 2), 333, wl.F32, 71, 72, 73, 1.0)
+        for N, taken in widths:
+            gh.check_parity(w, N=N, expect_kernel=REG)
+            assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == taken, (rows, N)
 
 
 @pytest.mark.parametrize("rows,cols,deg", MANY_ROWS[:2])
