@@ -598,6 +598,13 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     // gives half of the waves none (layer 2 at 1/4, 256 columns 1.05, 512 0.76), nor where its parts do not fill the chip, as
     // sddmm_reg's ranges do (3072 0.93, 3328 to 14336 1.00-1.11, 16384 0.88; fewer units than 32 0.92-1.04 and better).
     if (!conv && count(RBl, NBl) == units && (N <= 256 || (!gi && units >= 32 && N > 3200 && units * parts < 256))) lines = false;
+    // Long batches: a row group by itself loads every row of I for half as many rows of dO.  Not where both groups of a unit
+    // would go to one workgroup of sddmm_reg (layers 4 at 1/2 and 5 at 1/4, ratios: lowered 16384 columns 0.90-0.95, 24576
+    // 0.95-0.99, 32768 0.98-1.03, 49152 1.12-1.18; fused 16384 0.96, 20480 1.00, 24576 1.02, 65536 1.20), nor, on the lowered
+    // input, where a unit has one row group, full, and needs partial sums as well (layer 8 at 1/16: 3584 columns 0.91, in two
+    // parts 4096 1.06, 16384 1.34; half full, layer 5 at 1/16, 0.83-1.02).
+    if (RB == 2 && RBl == 1 && parts == 1 && N > (conv ? 20480 : 24576)) lines = false;
+    if (!conv && !gi && RB == 1 && parts > 1 && nbt > 3 && B.EO == pl.MG) lines = false;
   } else {
     // fp32: where one round of workgroups of 2 x 3 groups (or, on short batches, 1 x 3) covers the units (us, before -> 2 x 3
     // / 1 x 3: conv5, 2048 columns 22.9 -> 20.5 / 26, fused 23.2 -> 20.6; layer 6 at 1/2, 8192 columns 72.7 -> 59.1; at 1/4,

@@ -160,12 +160,17 @@ def test_weight_gradient_every_kernel_of_whole_lines(dtype, RB, NB, gi, N, rows,
 ONE_LAUNCH = ((16, 4, 4, 2), (16, 4, 8, 9), (2, 4, 4, 9))     # (one row group per unit)
 UNSPLIT = ((4, 4, 4, 2), (8, 2, 4, 9), (4, 2, 2, 9))          # (a workgroup per unit)
 TWO_GROUPS = ((8, 4, 4, 2), (8, 4, 8, 9), (4, 4, 8, 9))
+HALVED = ((8, 4, 4, 2), (8, 4, 8, 9), (4, 4, 4, 9))           # (bf16: a workgroup per row group; sddmm_reg takes both)
+ONE_FULL_GROUP = ((32, 2, 4, 2), (16, 2, 8, 9), (2, 2, 4, 9))
 BY_BATCH = [(ONE_LAUNCH, wl.BF16, 0, 512, 0, "lines"), (ONE_LAUNCH, wl.BF16, 0, 960, 0, "reg"), (ONE_LAUNCH, wl.BF16, 0, 1408, 0, "lines"),
             (ONE_LAUNCH, wl.BF16, 0, 1408, 8, "reg"), (ONE_LAUNCH, wl.F32, 0, 256, 0, "lines"), (ONE_LAUNCH, wl.F32, 0, 1024, 0, "reg"),
             (ONE_LAUNCH, wl.F32, 4, 1712, 0, "lines"), (ONE_LAUNCH, wl.F32, 4, 1728, 0, "reg"),
             (UNSPLIT, wl.BF16, 0, 256, 0, "reg"), (UNSPLIT, wl.BF16, 0, 258, 6, "lines"), (UNSPLIT, wl.BF16, 0, 3200, 0, "lines"),
             (UNSPLIT, wl.BF16, 0, 3328, 0, "reg"), (UNSPLIT, wl.BF16, 8, 3328, 0, "lines"), (UNSPLIT, wl.BF16, 0, 16384, 0, "lines"),
             (UNSPLIT, wl.F32, 0, 512, 0, "lines"), (UNSPLIT, wl.F32, 0, 514, 1, "reg"),
+            (HALVED, wl.BF16, 0, 24576, 0, "lines"), (HALVED, wl.BF16, 0, 24640, 0, "reg"),
+            (HALVED, wl.BF16, 8, 20480, 0, "lines"), (HALVED, wl.BF16, 8, 20544, 0, "reg"),
+            (ONE_FULL_GROUP, wl.BF16, 0, 3584, 0, "lines"), (ONE_FULL_GROUP, wl.BF16, 0, 4096, 0, "reg"),
             (TWO_GROUPS, wl.F32, 8, 4416, 0, "lines"), (TWO_GROUPS, wl.F32, 8, 4480, 0, "reg"), (TWO_GROUPS, wl.F32, 0, 4480, 3, "lines")]
 
 
