@@ -605,6 +605,13 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     // parts 4096 1.06, 16384 1.34; half full, layer 5 at 1/16, 0.83-1.02).
     if (RB == 2 && RBl == 1 && parts == 1 && N > (conv ? 20480 : 24576)) lines = false;
     if (!conv && !gi && RB == 1 && parts > 1 && nbt > 3 && B.EO == pl.MG) lines = false;
+    // Stages of one step group have nothing to split.  With many units (4096 x 4096 masks, ratios) not around four steps per wave
+    // (1536 columns 0.82-1.00, 1920 0.96-1.06, 2048 1.00-1.12, 2304 0.90-1.00; 16 steps, 1920 0.89-0.96, 2048 0.97-1.05), unless a
+    // stage reads few rows of I for full rows of dO (up to four steps: 1536 0.73, 2048 0.65, 8192 0.39), nor below six where the
+    // rows of a group are half padding (R = 1: up to eight steps, 1536 1.17 and 1.34, 2560 1.01 and 1.11, 3072 0.90 and 1.00).
+    if (!conv && !gi && nbt == 1 && count(RBl, NBl) >= 512 &&
+        ((N > (pl.KCR < 16 ? 1536 : 1920) && N < 2304 && (pl.KCR > 4 || pl.MG > 4)) || (N < 3072 && pl.KCR < 16 && pl.R == 1)))
+      lines = false;
   } else {
     // fp32: where one round of workgroups of 2 x 3 groups (or, on short batches, 1 x 3) covers the units (us, before -> 2 x 3
     // / 1 x 3: conv5, 2048 columns 22.9 -> 20.5 / 26, fused 23.2 -> 20.6; layer 6 at 1/2, 8192 columns 72.7 -> 59.1; at 1/4,

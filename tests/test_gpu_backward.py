@@ -162,6 +162,9 @@ UNSPLIT = ((4, 4, 4, 2), (8, 2, 4, 9), (4, 2, 2, 9))          # (a workgroup per
 TWO_GROUPS = ((8, 4, 4, 2), (8, 4, 8, 9), (4, 4, 8, 9))
 HALVED = ((8, 4, 4, 2), (8, 4, 8, 9), (4, 4, 4, 9))           # (bf16: a workgroup per row group; sddmm_reg takes both)
 ONE_FULL_GROUP = ((32, 2, 4, 2), (16, 2, 8, 9), (2, 2, 4, 9))
+MANY_UNITS = ((32, 4, 32, 1), (32, 1, 32, 1), (16, 1, 8, 1))  # (one step group per stage: eight steps, four, one row per column set)
+FOUR_STEPS = ((32, 4, 32, 1), (32, 1, 32, 1), (16, 1, 4, 1))
+LONE_ROWS = ((32, 1, 128, 1), (32, 1, 32, 1), (16, 1, 8, 1))
 BY_BATCH = [(ONE_LAUNCH, wl.BF16, 0, 512, 0, "lines"), (ONE_LAUNCH, wl.BF16, 0, 960, 0, "reg"), (ONE_LAUNCH, wl.BF16, 0, 1408, 0, "lines"),
             (ONE_LAUNCH, wl.BF16, 0, 1408, 8, "reg"), (ONE_LAUNCH, wl.F32, 0, 256, 0, "lines"), (ONE_LAUNCH, wl.F32, 0, 1024, 0, "reg"),
             (ONE_LAUNCH, wl.F32, 4, 1712, 0, "lines"), (ONE_LAUNCH, wl.F32, 4, 1728, 0, "reg"),
@@ -171,6 +174,8 @@ BY_BATCH = [(ONE_LAUNCH, wl.BF16, 0, 512, 0, "lines"), (ONE_LAUNCH, wl.BF16, 0, 
             (HALVED, wl.BF16, 0, 24576, 0, "lines"), (HALVED, wl.BF16, 0, 24640, 0, "reg"),
             (HALVED, wl.BF16, 8, 20480, 0, "lines"), (HALVED, wl.BF16, 8, 20544, 0, "reg"),
             (ONE_FULL_GROUP, wl.BF16, 0, 3584, 0, "lines"), (ONE_FULL_GROUP, wl.BF16, 0, 4096, 0, "reg"),
+            (MANY_UNITS, wl.BF16, 0, 1536, 0, "lines"), (MANY_UNITS, wl.BF16, 0, 2048, 0, "reg"), (MANY_UNITS, wl.BF16, 0, 2304, 0, "lines"),
+            (FOUR_STEPS, wl.BF16, 0, 2048, 0, "lines"), (LONE_ROWS, wl.BF16, 0, 2560, 0, "reg"), (LONE_ROWS, wl.BF16, 0, 3072, 0, "lines"),
             (TWO_GROUPS, wl.F32, 8, 4416, 0, "lines"), (TWO_GROUPS, wl.F32, 8, 4480, 0, "reg"), (TWO_GROUPS, wl.F32, 0, 4480, 3, "lines")]
 
 
