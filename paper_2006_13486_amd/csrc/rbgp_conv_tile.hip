@@ -14,7 +14,7 @@
 // taps) with ten 16-byte loads, and pairs the channels of a tap with byte permutes whose selectors put the kept channel of
 // column v mod 4 in place v: they depend on the row's G_i vertex only.
 // A tile is summed by itself, its first five and its last four taps apart, and added to the total: the error against 64-bit
-// sums is then that of the register kernels or less (VGG19 layer 9 at 1/4: 6.8e-8 against 8.2e-8; one chain 13e-8).
+// sums is then that of the register kernels or less (VGG19 layer 9 at 1/4: 6.7e-8 against 9.2e-8; one chain 13e-8).
 //
 // us, register kernels -> this one: VGG19 conv3 at 8192 pixels 15.3 -> 13.6, its input gradient 16.7 -> 13.5, layer 6's at 32768
 // pixels 53 -> 33; layer 9 at 1/8, 2048 pixels 14.6 -> 12.6, gradient 17.8 -> 12.7; the other sizes stand at the dispatch rule.
