@@ -1,30 +1,29 @@
 // bf16 fused 3x3 convolution on the sparse matrix core, for masks whose tiles are 32 rows by 32 channels (|G_r.V| = 4,
-// |G_i.V| = 8, the nine taps in G_b) and whose G_i keeps exactly one of the columns v and v + 4 (one 2-lift).  Of VGG19 with 128
-// images, by the dispatch rule: forward layers 5, 7 at 1/4, 8 at 1/4 and 1/8, 9-11 at 1/4 to 1/16; input gradients of layers 3, 4 at
-// 1/4, 5-7 at 1/4 and 1/8, 9-11 at 1/4 to 1/16.  (The rest have other tiles, few or the same tiles in
-// a row, or fewer workgroups than CUs.)
+// |G_i.V| = 8, the nine taps in G_b) and whose G_i keeps exactly one of the columns v and v + 4 (one 2-lift): of VGG19's layers
+// with images of four rows and more most from layer 3 at 1/4 on, both ways, but for long lists and large tiles of few images (the rule
+// stands at the dispatch).
 //
 // The register kernels load a channel nine times, once per tap, six of them at 2-byte alignment, and transpose it in
 // registers.  Here a workgroup takes four rows of G_o x 32 T pixels in image order; the channels of the tiles that any of
-// its rows has are loaded once, with the rows of pixels around them, and kept in LDS as an image [G_r vertex][pixel][8
-// channels]: a tap is the same image read from another pixel, and eight channels of a pixel are the 16 bytes that a lane
-// feeds the matrix core.  v_smfmac_f32_32x32x32_bf16 multiplies 32 rows x 32 pixels x 32 channels of one tap; a row keeps two of
-// every four channels (columns 0, 4, 1, 5 and 2, 6, 3, 7 of G_i), which its index operand names.
+// its rows has are loaded once (eight pixels of eight channels per thread, transposed with byte permutes), with the rows of
+// pixels around them, and kept in LDS as an image [G_r vertex][pixel][8 channels]: a tap is the same image read from another
+// pixel, and eight channels of a pixel are the 16 bytes that a lane feeds the matrix core.  v_smfmac_f32_32x32x32_bf16
+// multiplies 32 rows x 32 pixels x 32 channels of one tap; a row keeps two of every four channels (columns 0, 4, 1, 5 and 2, 6,
+// 3, 7 of G_i), which its index operand names.
 // Weights: the lane of half h loads, of its row, stage h of the packed fragments (two G_r vertices, four kept channels, nine
 // taps) with ten 16-byte loads, and pairs the channels of a tap with byte permutes whose selectors put the kept channel of
 // column v mod 4 in place v: they depend on the row's G_i vertex only.
 // A tile is summed by itself, its first five and its last four taps apart, and added to the total: the error against 64-bit
 // sums is then that of the register kernels or less (VGG19 layer 9 at 1/4: 6.7e-8 against 9.2e-8; one chain 13e-8).
 //
-// us, register kernels -> this one: VGG19 conv3 at 8192 pixels 15.3 -> 13.6, its input gradient 16.7 -> 13.5, layer 6's at 32768
-// pixels 53 -> 33; layer 9 at 1/8, 2048 pixels 14.6 -> 12.6, gradient 17.8 -> 12.7; the other sizes stand at the dispatch rule.
-// What bounds it (conv3, timing-only builds of one chain): 13.6 in all, 9.5 without the products (launch 2.5; tables, channels
-// and weights one after the other; stores 1), 11.2 without the staging, 12 without the reads of the image: one workgroup per CU
-// has nothing to overlap these with, a larger batch has (16384 pixels: 19.3, not 28).
-// Counters (conv3): matrix core 7 % busy, waves wait for 41 % of their cycles, LDS bank conflicts of 5000 cycles per CU (the stores
-// of the image's pixels and their reads).
+// us, VGG19 conv3 at 8192 pixels, both ways: register kernels 15.3 and 16.7, four waves that load two pixels of a channel at a
+// time and pass the phases one after the other 13.5, this one 10.1; layer 9 at 1/8, 2048 pixels 14.6, 11.2, 8.5; the other sizes
+// stand at the dispatch rule.  What bounds it: a chain of latencies (launch 2.5; tables 1; the channels, all of conv3's in one
+// round of loads; their first use) and then issue: 1000 vector instructions and 800 cycles of products a wave, two waves a SIMD.
+// Counters (conv3): waves wait for 44 % of their cycles (four waves 41, of a longer launch), matrix core 11 % busy, vector
+// instructions 40 % of a SIMD's cycles, bank conflicts 3400 cycles per CU (5000 without the places of place_of).
 // Tried: fp32, operands split in three: layer 6 at 1/4, 8192 pixels 25.7 -> 29, its gradient 34.7 -> 29 (the one that gained), layer 9
-// 25 -> 51 (three times the LDS: one or two tiles at once).  Stores that pair the bf16 sums of two lanes: 14.3 -> 16.9.
+// 25 -> 51 (three times the LDS: one or two tiles at once).
 #include <hip/hip_runtime.h>
 
 #include "rbgp_internal.h"
@@ -35,6 +34,8 @@ using namespace rbgp_reg;
 using namespace rbgp_split;
 
 namespace {
+
+typedef u32x4 u32x4_u __attribute__((aligned(4)));
 
 // where a lane's fragment of 72 steps holds channel ch (0..7) of its stage at a tap: 16-byte load and element
 struct Place {
@@ -49,20 +50,30 @@ __device__ __forceinline__ uint32_t two_halves(const u32x4 &x0, const u32x4 &x1)
   return __builtin_amdgcn_perm(x1[E1 / 2], x0[E0 / 2], (E0 % 2 ? 0x0302u : 0x0100u) | (E1 % 2 ? 0x07060000u : 0x05040000u));
 }
 
-template <int T>
-__global__ __launch_bounds__(256, 2) void conv_tile(ConvTileParams p) {
-  constexpr int NL = 10;
-  extern __shared__ __attribute__((aligned(16))) u32x4 image[];   // [tile of the chunk][G_r vertex][pixel]
+// Wave (r, s) multiplies, of row r of the workgroup's four rows of G_o, every S-th tile from the s-th on (S = 1, 2).
+template <int T, int S>
+__global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
+  constexpr int NL = 10, kRows = 4;
+  extern __shared__ __attribute__((aligned(16))) u32x4 image[];   // twice [tile of the chunk][G_r vertex][pixel]
   const int lane = threadIdx.x & 63, h = lane >> 5, j = lane & 31;
-  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), W = int(blockDim.x) >> 6;
-  const int per = (p.a1 + W - 1) / W;           // workgroups of one column tile, all on XCD tile % 8
+  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), wr = wid & (kRows - 1), ws = wid / kRows;
+  const int per = (p.a1 + kRows - 1) / kRows;   // workgroups of one column tile, all on XCD tile % 8
   const int slot = blockIdx.x >> 3, nt = int(blockIdx.x & 7) + 8 * (slot / per), ug = slot % per;
   if (nt >= p.ntiles) return;
-  const int u1 = ug * W + wid;
-  const bool has_row = u1 < p.a1;
-  const uint64_t mine = has_row ? p.tiles[u1] : 0;
-  uint64_t left = 0;                            // tile columns of the workgroup's rows that are still to come
-  for (int w = 0; w < W; ++w) left |= ug * W + w < p.a1 ? p.tiles[ug * W + w] : 0;
+  const int u1 = ug * kRows + wr;
+  uint64_t mine = 0, left = 0;                  // tile columns of the wave's row; those of the workgroup's rows still to come
+#pragma unroll
+  for (int w = 0; w < kRows; ++w) {
+    const uint64_t t = ug * kRows + w < p.a1 ? p.tiles[ug * kRows + w] : 0;
+    left |= t;
+    if (w == wr) mine = t;
+  }
+  uint64_t todo = 0;                            // those that are this wave's (in ascending order, as the chunks are)
+  {
+    uint64_t m = mine;
+    for (int k = 0; m; ++k, m &= m - 1)
+      if (k % S == ws) todo |= m & -m;
+  }
 
   // the padded pixels from the row above the first pixel to the row below the last one (whole rows: W divides 32 T)
   auto center = [&](int n) {
@@ -71,11 +82,15 @@ __global__ __launch_bounds__(256, 2) void conv_tile(ConvTileParams p) {
   };
   const int n0 = nt * 32 * T, n_last = (n0 + 32 * T < p.n ? n0 + 32 * T : p.n) - 1;
   const int p_lo = center(n0) - p.w2 - 1, px = center(n_last) + p.w2 + 2 - p_lo;
-  int at[T];                                    // the lane's pixel of every column block: bytes into a plane of the image
+  // Pixel q of a plane lies in place q ^ (q / 8) % 8 of its octet: the eight pixels that a lane stores and the runs of pixels
+  // that neighbouring lanes read then fall on different banks.
+  const int plane8 = (px + 7) & ~7, plane = plane8 * 16;   // places, bytes
+  auto place_of = [](int q) { return q ^ ((q >> 3) & 7); };
+  int at[T];                                    // the lane's pixel of every column block, counted from p_lo
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int n = n0 + 32 * t + j;
-    at[t] = (center(n < p.n ? n : n_last) - p_lo) * 16;
+    at[t] = center(n < p.n ? n : n_last) - p_lo;
   }
   // the lane's row of a tile: G_i vertex and row of R
   const int ui = j / p.R, i = j - ui * p.R;
@@ -89,69 +104,64 @@ __global__ __launch_bounds__(256, 2) void conv_tile(ConvTileParams p) {
 #pragma unroll
     for (int l = 0; l < NL; ++l) r[l] = __builtin_amdgcn_raw_buffer_load_b128(rw, base + l * p.RS * 16, 0, 0);
   };
+  // One task per thread and chunk (p.chunk tiles): eight pixels of the eight channels of a (tile, G_r vertex).  The last task of
+  // a plane ends with the plane (and repeats pixels of the one before it: nothing past the end of X is read).
+  const int octets = plane8 >> 3;
+  u32x4 d[8];
+  int dst = -1, dst_px = 0;                     // plane of the task's pixels in a buffer, first of them; -1: no task
+  auto take = [&]() {                           // the next tiles, as many as a buffer holds
+    uint64_t c = 0;
+    for (int k = 0; k < p.chunk && left; ++k) {
+      c |= left & -left;
+      left &= left - 1;
+    }
+    return c;
+  };
+  auto fetch = [&](uint64_t chunk) {
+    const int pl = int(threadIdx.x) / octets, q = int(threadIdx.x) - pl * octets, k = pl >> 2;
+    dst = -1;
+    if (k >= __popcll(chunk)) return;
+    uint64_t c = chunk;
+    for (int s = 0; s < k; ++s) c &= c - 1;
+    dst = pl;
+    dst_px = 8 * q < px - 8 ? 8 * q : px - 8;
+    const uint16_t *x = static_cast<const uint16_t *>(p.X) + int64_t(__builtin_ctzll(c) * 32 + (pl & 3) * 8) * p.chan + p_lo + dst_px;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)                 // channels in the order 0, 4, 1, 5, 2, 6, 3, 7 of G_i's columns
+      d[e] = *reinterpret_cast<const u32x4_u *>(x + int64_t((e >> 1) + 4 * (e & 1)) * p.chan);
+  };
+  auto store = [&](int buf) {
+    if (dst < 0) return;
+    u32x4 *const to = image + (buf * p.chunk * 4 + dst) * plane8;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      u32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(d[2 * e + 1][x / 2], d[2 * e][x / 2], x % 2 ? 0x07060302u : 0x05040100u);
+      to[place_of(dst_px + x)] = v;
+    }
+  };
 
   f32x16 acc[T];
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  const int plane = px * 16;                    // bytes
   u32x4 raw[NL];
-  while (left) {
-    uint64_t chunk = 0;                         // the next tiles, as many as LDS holds
-    for (int k = 0; k < p.chunk && left; ++k) {
-      chunk |= left & -left;
-      left &= left - 1;
-    }
-    uint64_t own = mine & chunk;
-    if (own) load_w(raw, __builtin_ctzll(own));
-    // items of a tile x 64 lanes along the pixels, two pixels each; two items of 32 loads in flight per wave
-    const int span = px >> 1, nq = (span + 63) >> 6, items = __popcll(chunk) * nq;   // (px is even)
-    struct Item {
-      int64_t x;
-      int dst;                                  // -1: nothing
-    };
-    auto item = [&](int it) {
-      const int k = it / nq, q = (it - k * nq) * 64 + lane;
-      uint64_t c = chunk;
-      for (int s = 0; s < k; ++s) c &= c - 1;
-      return Item{int64_t(__builtin_ctzll(c) * 32) * p.chan + p_lo + 2 * (q < span ? q : 0), q < span ? k * 4 * px + 2 * q : -1};
-    };
-    for (int it = wid; it < items; it += 2 * W) {
-      const bool two = it + W < items;
-      const Item at2[2] = {item(it), item(two ? it + W : it)};
-      uint32_t d[2][4][8];
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int vr = 0; vr < 4; ++vr)
-#pragma unroll
-          for (int e = 0; e < 8; ++e)   // channels in the order 0, 4, 1, 5, 2, 6, 3, 7 of G_i's columns
-            d[u][vr][e] = *reinterpret_cast<const uint32_t *>(static_cast<const uint16_t *>(p.X) + at2[u].x +
-                                                              int64_t(vr * 8 + (e >> 1) + 4 * (e & 1)) * p.chan);
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (at2[u].dst < 0 || (u == 1 && !two)) continue;
-        u32x4 *const dst = image + at2[u].dst;
-#pragma unroll
-        for (int vr = 0; vr < 4; ++vr) {
-          u32x4 lo, hi;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            lo[e] = __builtin_amdgcn_perm(d[u][vr][2 * e + 1], d[u][vr][2 * e], 0x05040100u);
-            hi[e] = __builtin_amdgcn_perm(d[u][vr][2 * e + 1], d[u][vr][2 * e], 0x07060302u);
-          }
-          dst[vr * px] = lo;
-          dst[vr * px + 1] = hi;
-        }
-      }
-    }
-    __syncthreads();
-    while (own) {
-      const int v = __builtin_ctzll(own);
-      own &= own - 1;
-      const int k = __popcll(chunk & ((uint64_t(1) << v) - 1));
-      const unsigned char *img = reinterpret_cast<const unsigned char *>(image) + k * 4 * plane;
+  uint64_t chunk = take();
+  if (todo) load_w(raw, __builtin_ctzll(todo));
+  fetch(chunk);
+  store(0);
+  __syncthreads();
+  for (int buf = 0;; buf ^= 1) {
+    const uint64_t here = chunk;
+    chunk = take();
+    if (chunk) fetch(chunk);
+    while (todo & here) {
+      const int v = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int k = __popcll(here & ((uint64_t(1) << v) - 1));
+      const unsigned char *img = reinterpret_cast<const unsigned char *>(image) + (buf * p.chunk + k) * 4 * plane + h * plane;
       u32x4 a[9];
       static_for<0, 9>([&](auto tc) {
         constexpr int tap = decltype(tc)::value;
@@ -165,46 +175,76 @@ __global__ __launch_bounds__(256, 2) void conv_tile(ConvTileParams p) {
         });
       });
       // the lanes of half 0 hold G_r vertices 0 and 2, those of half 1 vertices 1 and 3 (first and second half of the lane's 16 steps)
-      f32x16 sum[2][T];                         // of this tile
 #pragma unroll
-      for (int t = 0; t < T; ++t)
+      for (int t = 0; t < T; ++t) {
+        f32x16 sum[2];                          // of this tile: taps 0-4 and 5-8, in turn
 #pragma unroll
-        for (int e = 0; e < 16; ++e) sum[0][t][e] = sum[1][t][e] = 0.f;
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        if (tap == 4 && own) load_w(raw, __builtin_ctzll(own));   // (issued before the first tap: 0.7 us more)
-        const int shift = ((tap / 3 - 1) * p.w2 + tap % 3 - 1) * 16 + h * plane;
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-          const unsigned char *x = img + at[t] + shift;
+        for (int e = 0; e < 16; ++e) sum[0][e] = sum[1][e] = 0.f;
+        static_for<0, 9>([&](auto kc) {
+          constexpr int kk = decltype(kc)::value, late = kk % 2, tap = kk / 2 + 5 * late;
+          if (t == T - 1 && kk == 4 && todo) load_w(raw, __builtin_ctzll(todo));
+          const unsigned char *x = img + place_of(at[t] + (tap / 3 - 1) * p.w2 + tap % 3 - 1) * 16;
           const bf16x16 b = joined(*reinterpret_cast<const u32x4 *>(x), *reinterpret_cast<const u32x4 *>(x + 2 * plane));
-          sum[tap >= 5][t] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, a[tap]), b, sum[tap >= 5][t], sel.z, 0, 0);
-        }
+          sum[late] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(bf16x8, a[tap]), b, sum[late], sel.z, 0, 0);
+        });
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] += sum[0][e] + sum[1][e];
       }
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] += sum[0][t][e] + sum[1][t][e];
     }
-    if (left) __syncthreads();
+    if (!chunk) break;
+    store(buf ^ 1);                             // (last read before the barrier that opened this round)
+    __syncthreads();
   }
-  if (!has_row) return;
+
+  // The waves of a row add their sums through LDS, which hands them on as rows of pixels: a thread stores eight at a time.
+  __syncthreads();
+  float *const red = reinterpret_cast<float *>(image);   // [s][r][row of the tile][pixel]
+  constexpr int PX = 32 * T;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int r = 8 * (e / 4) + 4 * h + e % 4, rui = r / p.R, ri = r - rui * p.R;
-    const int64_t m = ((int64_t(u1) * p.a2 + ri / p.a4) * p.a3 + rui) * p.a4 + ri % p.a4;
+  for (int e = 0; e < 16; ++e)
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int n = n0 + 32 * t + j;
-      if (n >= p.n) continue;
-      if (p.obf16)
-        __builtin_nontemporal_store(uint16_t(bf16_bits(acc[t][e])), reinterpret_cast<uint16_t *>(p.O) + m * p.ldO + n);
-      else
-        __builtin_nontemporal_store(acc[t][e], reinterpret_cast<float *>(p.O) + m * p.ldO + n);
+    for (int t = 0; t < T; ++t)
+      red[((ws * kRows + wr) * 32 + 8 * (e / 4) + 4 * h + e % 4) * PX + 32 * t + j] = acc[t][e];
+  __syncthreads();
+  const int es = p.obf16 ? 2 : 4;
+  const bool wide = (reinterpret_cast<uintptr_t>(p.O) | uintptr_t(p.ldO * es)) % 16 == 0;
+#pragma unroll
+  for (int u = 0; u < 2 * T / S; ++u) {
+    const int it = u * 256 * S + int(threadIdx.x), row = it / (PX / 8), x = it % (PX / 8) * 8;   // 128 rows of PX / 8 pieces
+    const int o1 = ug * kRows + row / 32, r = row % 32;
+    if (o1 >= p.a1 || n0 + x >= p.n) continue;
+    const f32x4 *s0 = reinterpret_cast<const f32x4 *>(red + row * PX + x), *s1 = s0 + kRows * 32 * PX / 4;
+    f32x4 v[2] = {s0[0], s0[1]};
+    if constexpr (S == 2) {
+      v[0] += s1[0];
+      v[1] += s1[1];
+    }
+    const int rui = r / p.R, ri = r - rui * p.R;
+    const int64_t o = (((int64_t(o1) * p.a2 + ri / p.a4) * p.a3 + rui) * p.a4 + ri % p.a4) * p.ldO + n0 + x;
+    if (p.obf16) {
+      uint16_t *const out = static_cast<uint16_t *>(p.O) + o;
+      const u32x4 w = {bf16_pair(v[0][0], v[0][1]), bf16_pair(v[0][2], v[0][3]), bf16_pair(v[1][0], v[1][1]), bf16_pair(v[1][2], v[1][3])};
+      if (wide && n0 + x + 8 <= p.n) {
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(out));
+      } else {
+        for (int e = 0; e < 8 && n0 + x + e < p.n; ++e) out[e] = uint16_t(w[e / 2] >> (16 * (e % 2)));
+      }
+    } else {
+      float *const out = static_cast<float *>(p.O) + o;
+      if (wide && n0 + x + 8 <= p.n) {
+        __builtin_nontemporal_store(v[0], reinterpret_cast<f32x4 *>(out));
+        __builtin_nontemporal_store(v[1], reinterpret_cast<f32x4 *>(out) + 1);
+      } else {
+        for (int e = 0; e < 8 && n0 + x + e < p.n; ++e) out[e] = v[e / 4][e % 4];
+      }
     }
   }
 }
 
 }  // namespace
 
-rbgp_conv_tile_fn rbgp_conv_tile_kernel(int T) { return T == 1 ? conv_tile<1> : T == 2 ? conv_tile<2> : nullptr; }
+rbgp_conv_tile_fn rbgp_conv_tile_kernel(int T, int S) {
+  if (T == 1) return S == 1 ? conv_tile<1, 1> : S == 2 ? conv_tile<1, 2> : nullptr;
+  if (T == 2) return S == 1 ? conv_tile<2, 1> : S == 2 ? conv_tile<2, 2> : nullptr;
+  return nullptr;
+}

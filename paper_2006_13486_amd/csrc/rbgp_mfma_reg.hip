@@ -605,15 +605,19 @@ int upload(const std::vector<T> &h, T **d) {
   return RBGP_OK;
 }
 
-// bf16 fused convolution of 32-row, 32-channel tiles with one column of G_i kept of every v and v + 4 (rbgp_conv_tile.hip),
-// four rows of G_o x 64 pixels per workgroup, 32 where 64 would leave CUs idle; from one workgroup per CU on.  The register
-// kernels stay where eight rows share their columns and a row has few tiles (layers 3, 4), 32-pixel workgroups would not have
-// sixteen rows of G_o, or the chip is filled just once and the two rows of G_o of their groups have the same tiles.
-// us, register kernels -> this one, VGG19, fp32 sums:
-//  layer 6 at 1/4, 8192 pixels 13.6 -> 13.8 (the same tiles: not taken; layers 5, 7 16.0 -> 13.7), 16384 22.5 -> 19.2;
-//  its input gradient 17.3 -> 13.6, 16384 30.0 -> 19.0, 6144 (32 pixels) 17.1 -> 14.8, 4096 11.7 -> 11.3 (forward 9.2 -> 11.1:
-//  not taken); layer 9 at 1/4, 2048 18.2 -> 18.0 and 20.0 -> 17.7, 8192 53 -> 35 and 61 -> 35; gradients of layer 3 at 1/4, 16384
-//  14.9 -> 10.9, 51200 46 -> 25; with half a workgroup per CU layer 4's: 12.0 -> 14.
+// bf16 fused convolution of 32-row, 32-channel tiles with one column of G_i kept of every v and v + 4 (rbgp_conv_tile.hip).
+// Workgroups of four rows of G_o x 32 T pixels, S waves a row.  While 32-pixel workgroups have a CU each, two waves a row (T, S =
+// 1, 2); while 64-pixel ones do, those where a row has four tiles and more (2, 2), else two 32-pixel ones of one wave a row on a
+// CU (1, 1); from then on two 64-pixel ones on a CU (2, 1), which stage a chunk while the other multiplies.
+// us, register kernels / (1, 1) / (1, 2) / (2, 1) / (2, 2), VGG19, fp32 sums, input gradient unless said:
+//  layer 6 at 1/4 (eight rows of G_o, four tiles a row): 576 pixels 10.2 / 8.0 / 6.9 / 11.9 / 9.1, 4096 11.7 / 8.6 / 7.8 / 12.0 / 9.5,
+//  5120 17.1 / 10.3 / 12.5 / 12.1 / 9.6, 8192 17.3 / 10.6 / 13.3 / 12.9 / 10.4, 10240 - / 16.3 / 18.9 / 15.0 / 17.6;
+//  at 1/8 (two tiles): 4096 8.6 / 6.5 / 6.6 / 8.9 / 7.8, 8192 17.8 / 7.9 / 11.1 / 9.8 / 8.5, 16384 - / 14.6 / 22.2 / 12.7 / 15.8;
+//  layer 9 at 1/4 (16 rows, eight tiles): 1024 13.1 / 13.1 / 11.4 / 22 / 15.7, 2048 20.0 / 13.3 / 11.6 / 22 / 15.7, 4096 - / 17.2 / 21.9 /
+//  22.5 / 16.8; layer 3 at 1/4, 16384 pixels 9.7 / 8.0 / 10.7 / 9.1 / 8.1, 32768 14.9 / 14.6 / 21.4 / 12.3 / 15.0.
+// The register kernels stay with up to 64 workgroups where 16 channels' tiles and more are to be staged for rows of eight tiles, or
+// for tiles that share eight rows a column set (layer 9 at 1/4, 512 pixels: 10.6 against 11.0, forward 8.9 / 10.6, forward at 1/8
+// 7.2 / 7.6; from 592 pixels on 16.6 / 11.1, 13.4 / 10.6, 9.8 / 7.8): their split lists then run in one round.
 // *taken: the launch went this way.  (The tables are made at the first such launch.)
 int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out_bf16, const rbgp_conv_geometry &conv, int64_t N,
                      const void *packed, uint32_t w_bytes, const void *X, int64_t chan, void *O, int64_t ldO, void *stream, bool *taken) {
@@ -622,17 +626,17 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
   if (!(pl.fold == 1 && m->c[0] <= 64 && m->c[1] == 4 && m->c[2] == 8 && m->d[2] == 4 && pl.KCR == 72 && pl.KC == 72 && pl.NSTG == 2 &&
         (pl.RS == 4 || pl.RS == 8) && pl.R * m->a[2] == 32 && pl.A2 == m->a[1] && m->a[1] * m->a[3] == pl.R))
     return RBGP_OK;
-  const int64_t per = (m->a[0] + 3) / 4;
-  const int T = (N + 63) / 64 * per >= 256 ? 2 : 1, cw = 32 * T;
-  const int64_t tiles = (N + cw - 1) / cw, wgs = 8 * ((tiles + 7) / 8) * per, W = conv.width, H = conv.height;
-  // padded rows of a workgroup's pixels: its rows, two for every image border among them, one on either side
-  const int64_t rows = cw / W, tile_bytes = 64 * (rows + 2 * ((rows + H - 2) / H) + 2) * (W + 2), most = 75 * 1024;
-  if (tiles * per < 256 || wgs > 0x7fffffff || N >= (int64_t(1) << 30) || cw % W || tile_bytes > most ||
-      (pl.RS == 8 && (T == 2 ? m->d[0] < 4 : m->a[0] < 16)))
-    return RBGP_OK;
   for (int k = 0; k < RBGP_NUM_TUNE; ++k)
     if (tune[k]) return RBGP_OK;
-  if (pl.RS == 8 && T == 2 && tiles * per <= 256 && m->reg_clusters.max_stages == 2 * m->d[0]) return RBGP_OK;
+  const int64_t per = (m->a[0] + 3) / 4, W = conv.width, H = conv.height;
+  const int64_t narrow = (N + 31) / 32 * per, wide = (N + 63) / 64 * per;   // workgroups with T = 1, 2
+  if (64 % W || N >= (int64_t(1) << 30) || (narrow <= 64 && m->c[0] >= 16 && (pl.RS == 8 || m->d[0] >= 8))) return RBGP_OK;
+  const int T = 32 % W || (narrow > 256 && (wide > 256 || m->d[0] >= 4)) ? 2 : 1, S = (T == 1 ? narrow : wide) <= 256 ? 2 : 1;
+  const int64_t cw = 32 * T, tiles = (N + cw - 1) / cw, wgs = 8 * ((tiles + 7) / 8) * per;
+  // padded rows of a workgroup's pixels: its rows, two for every image border among them, one on either side
+  const int64_t rows = cw / W, px = (rows + 2 * ((rows + H - 2) / H) + 2) * (W + 2), octets = (px + 7) / 8,
+                tile_bytes = 512 * octets, most = 75 * 1024;
+  if (wgs > 0x7fffffff || tile_bytes > most) return RBGP_OK;
   if (!st->conv_tiles) {
     if (st->conv_tiles_none) return RBGP_OK;
     std::vector<uint64_t> t(size_t(m->a[2]) * 2 + m->a[0], 0);   // ConvTileParams::sel, then ::tiles
@@ -667,13 +671,13 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
   cp.a1 = m->a[0]; cp.a2 = m->a[1]; cp.a3 = m->a[2]; cp.a4 = m->a[3]; cp.d1 = m->d[0];
   cp.R = pl.R; cp.RS = pl.RS;
   cp.frag_bytes = (rbgp_bf16_blocks32(pl.KC) + (rbgp_bf16_tail16(pl.KC) ? 1 : 0)) * 4 * pl.RS * 16;
-  cp.chunk = int(std::min<int64_t>(m->c[0], most / tile_bytes));   // (two workgroups per CU)
+  cp.chunk = int(std::min({int64_t(m->c[0]), most / tile_bytes, 64 * S / octets}));   // (a thread stages one octet of a plane; two buffers)
   cp.obf16 = out_bf16 ? 1 : 0;
-  const size_t bytes = size_t(cp.chunk * tile_bytes);
-  rbgp_conv_tile_fn fn = rbgp_conv_tile_kernel(T);
+  const size_t bytes = size_t(std::max((cp.chunk < m->c[0] ? 2 : 1) * cp.chunk * tile_bytes, int64_t(S * T) * 16 * 1024));   // (sums of a row's waves)
+  rbgp_conv_tile_fn fn = rbgp_conv_tile_kernel(T, S);
   if (bytes > 64 * 1024)
     RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
-  hipLaunchKernelGGL(fn, dim3(unsigned(wgs)), dim3(256), bytes, static_cast<hipStream_t>(stream), cp);
+  hipLaunchKernelGGL(fn, dim3(unsigned(wgs)), dim3(unsigned(256 * S)), bytes, static_cast<hipStream_t>(stream), cp);
   RBGP_HIP(hipGetLastError());
   rbgp_set_last_kernel("conv_tile", {T});
   *taken = true;

@@ -181,8 +181,9 @@ struct ConvTileParams {
 
 typedef void (*rbgp_reg_fn)(rbgp_reg::RegParams);
 typedef void (*rbgp_conv_tile_fn)(rbgp_reg::ConvTileParams);
-// bf16 fused convolution with the channels of a tile as an image in LDS (rbgp_conv_tile.hip), 32 T pixels per workgroup (T = 1, 2)
-rbgp_conv_tile_fn rbgp_conv_tile_kernel(int T);
+// bf16 fused convolution with the channels of a tile as an image in LDS (rbgp_conv_tile.hip), 32 T pixels (T = 1, 2) and 4 S waves
+// (S = 1, 2) per workgroup
+rbgp_conv_tile_fn rbgp_conv_tile_kernel(int T, int S);
 typedef void (*rbgp_split_tile_fn)(rbgp_reg::SplitTileParams);
 typedef void (*rbgp_dual_fn)(rbgp_reg::DualParams);
 // bf16 kernel for KC contraction steps per stage, RS weight rows per tile row, G 16-row

@@ -108,6 +108,14 @@ IMAGE_TILES = [  # rows of G_o no multiple of four, ragged last tiles, one or se
 ]
 
 
+IMAGE_TILES += [  # two waves a row: one image, a row of pixels that is no multiple of eight, two chunks; three; one wave a row, two chunks
+    (wl.Workload("tiles32_one", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 131, 132, 133, 1.0), 1, 2, 8),
+    (wl.Workload("tiles32_odd", (8, 4, 8, 1), (24, 4, 8, 9), (6, 4, 4, 9), 0, wl.BF16, 134, 135, 136, 1.0), 61, 1, 4),
+    (wl.Workload("tiles64_rows", (16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 4, 9), 0, wl.BF16, 137, 138, 139, 1.0), 132, 4, 4),
+    (wl.Workload("tiles32_pairs", (16, 4, 4, 2), (16, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 140, 141, 142, 1.0), 139, 3, 4),
+]
+
+
 @pytest.mark.parametrize("case", IMAGE_TILES, ids=lambda c: c[0].name)
 def test_fused_conv3x3_with_channels_in_lds(case):
     """The kernel that keeps the channels of its tiles in LDS, fp32 and bf16 sums; an infinite activation reaches the sums of
