@@ -485,13 +485,16 @@ int upload(const std::vector<T> &h, T **d) {
   return RBGP_OK;
 }
 
+// All that a filled or regrouped mask needs, on which only the register family runs (it makes its own tables).
+int ensure_state(const rbgp_mask *m) {
+  if (!m->dev) m->dev = new (std::nothrow) rbgp_device_state();
+  return m->dev ? RBGP_OK : RBGP_ENOMEM;
+}
+
 // Create the device tables of a mask on the current device (first GPU use).
 int ensure_device(const rbgp_mask *m) {
   if (m->dev && m->dev->adj[0]) return RBGP_OK;
-  if (!m->dev) {
-    m->dev = new (std::nothrow) rbgp_device_state();
-    if (!m->dev) return RBGP_ENOMEM;
-  }
+  if (const int rc = ensure_state(m)) return rc;
   rbgp_device_state *dev = m->dev;
   RBGP_HIP(hipGetDevice(&dev->device));
   // the state is touched only when every table is on the device (adj[0] marks "built")
@@ -739,7 +742,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
   // matrix core has room, the load path does not, and the regrouped mask has fewer tile rows that share their loads
   // (VGG19 backward data products: fp32 17-36 % faster, bf16 5-25 % slower).
   if (kernel == RBGP_KERNEL_MFMA_REG && m->regroup && (!bf16 || m->regroup_bf16)) {
-    rc = ensure_device(m->regroup);
+    rc = ensure_state(m->regroup);
     if (rc) return rc;
     return rbgp_reg_launch(m->regroup, &m->regroup->dev->reg_state, dev->tune, bf16, out_bf16, N, dev_packed, dev_I,
                            ldI, dev_O, ldO, hip_stream);
@@ -749,7 +752,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
                            hip_stream);
 
   if (kernel == RBGP_KERNEL_MFMA_REG_FILLED) {   // the same kernels on the filled mask (its own tables, this mask's knobs)
-    rc = ensure_device(m->filled);
+    rc = ensure_state(m->filled);
     if (rc) return rc;
     return rbgp_reg_launch(m->filled, &m->filled->dev->reg_state, dev->tune, bf16, out_bf16, N, dev_packed, dev_I, ldI,
                            dev_O, ldO, hip_stream);
@@ -884,7 +887,10 @@ static int conv3x3_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t channe
   if (kernel == RBGP_KERNEL_MFMA_TILE)
     return rbgp_tile_launch(m, &m->dev->tile_state, dtype == RBGP_BF16, N, dev_packed, dev_X, N, dev_O, ldO, hip_stream,
                             &geom);
-  return rbgp_reg_launch(m, &m->dev->reg_state, m->dev->tune, bf16_in(dtype), dtype == RBGP_BF16, N, dev_packed, dev_X,
+  const rbgp_mask *run = m->regroup && (!bf16_in(dtype) || m->regroup_bf16) ? m->regroup : m;   // (as for rbgp_spmm)
+  rc = ensure_state(run);
+  if (rc) return rc;
+  return rbgp_reg_launch(run, &run->dev->reg_state, m->dev->tune, bf16_in(dtype), dtype == RBGP_BF16, N, dev_packed, dev_X,
                          N, dev_O, ldO, hip_stream, &geom);
 }
 

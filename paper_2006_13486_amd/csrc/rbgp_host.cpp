@@ -478,13 +478,25 @@ void rbgp_plan_filled(rbgp_mask *m) {
 // one tile column that holds all of K.  A stage is a run of columns of G_r inside a tile, so with few columns in G_r
 // the stages are short however dense the mask (Table 2's cells with a complete G_o: |G_r.V| = 1, stages of 2 to 8
 // steps padded to 8, 128 of them per wave); on the merged factoring they are 64 steps of 72.  Both dtypes.
+//
+// And where the vertices of G_i come in groups of q with one adjacency list (the transpose of a G_i that keeps one of four
+// columns: stars), G_i is, its rows permuted, G_i' (x) J(q, 1): the q vertices go to G_r, J(a_r, c_r) (x) J(q, 1) = J(a_r q, c_r),
+// and q times as many rows share a column set.  Rows are permuted (rbgp_mask::merged), columns and their order are not.  For the
+// masks of 3x3 convolutions with up to four rows per column set, whose clusters of four tile rows and more share few tiles; with eight
+// rows the fp32 kernels pair them up tile by tile (rbgp_reg_plan_dual).  us, as given -> merged, 128 images, fp32: conv5's input
+// gradient 20.2 -> 14.1 (51 stages, 32 with pairs), WRN group 1 fused 46.5 -> 30.8 (8 -> 3 stages a list), lowered 72.5 -> 68.5, VGG19
+// layer 1 at 1/4 and 1/8 fused 47 -> 36 and 27, gradients of layers 7, 8, 11 at 1/4 36.7 -> 31.7, 20.9 -> 18, 36.2 -> 23.5;
+// one image 0.8-0.95.  bf16, where the mask does not go to conv_tile (which takes four rows a set, and is the faster): conv5's
+// gradient 13.2 -> 12.0, lowered 10.0 -> 8.7, WRN fused 35.0 -> 33.3, layer 1 at 1/8 36.4 -> 25.7, lowered 39.6 -> 36.5.
 static bool plan_regroup_columns(rbgp_mask *m);
+static void plan_merge_rows(rbgp_mask *m);
 
 void rbgp_plan_regroup(rbgp_mask *m) {
   m->regroup = nullptr;
   m->regroup_bf16 = false;
   const rbgp_reg_plan &p = m->reg;
   if (!p.ok || !rbgp_reg_covers(m)) return;
+  if (m->c[3] == 9 && m->d[3] == 9 && m->d[1] == m->c[1]) return plan_merge_rows(m);
   if ((m->c[3] == 9 && m->d[3] == 9) || m->d[3] != m->c[3] || m->d[1] != m->c[1]) return;
   if (plan_regroup_columns(m)) return;
   if (p.fold <= 1) return;
@@ -542,6 +554,61 @@ void rbgp_plan_regroup(rbgp_mask *m) {
     throw;
   }
   m->regroup = t;
+}
+
+static void plan_merge_rows(rbgp_mask *m) {
+  const rbgp_reg_plan &p = m->reg;
+  const int a3 = m->a[2], d3 = m->d[2];
+  if (p.R > 4 || p.fold != 1 || a3 < 2) return;
+  std::vector<std::vector<int32_t>> groups;   // G_i vertices with one adjacency list, in order of their first
+  auto list = [&](int u) { return m->adj[2].begin() + size_t(u) * d3; };
+  for (int u = 0; u < a3; ++u) {
+    size_t g = 0;
+    while (g < groups.size() && !std::equal(list(u), list(u) + d3, list(groups[g][0]))) ++g;
+    if (g == groups.size()) groups.emplace_back();
+    groups[g].push_back(u);
+  }
+  const int q = int(groups[0].size());
+  if (q < 2 || p.R * q > 16) return;
+  for (const auto &g : groups)
+    if (int(g.size()) != q) return;
+  rbgp_mask *t = new rbgp_mask();
+  try {
+    for (int i = 0; i < 4; ++i) {
+      t->a[i] = m->a[i]; t->c[i] = m->c[i]; t->d[i] = m->d[i]; t->e[i] = m->e[i];
+      t->sigma1[i] = m->sigma1[i]; t->sigma2[i] = m->sigma2[i]; t->bound[i] = m->bound[i];
+      t->status[i] = m->status[i]; t->tries[i] = 0;
+      t->adj[i] = m->adj[i];
+    }
+    t->a[1] = m->a[1] * q; t->e[1] = m->e[1] * q;
+    t->sigma1[1] = std::sqrt(double(t->a[1]) * t->c[1]);
+    t->adj[1].resize(size_t(t->a[1]) * t->c[1]);
+    for (int u = 0; u < t->a[1]; ++u)
+      for (int v = 0; v < t->c[1]; ++v) t->adj[1][size_t(u) * t->c[1] + v] = v;
+    t->a[2] = a3 / q; t->e[2] = m->e[2] / q;
+    t->sigma1[2] = m->sigma1[2] / std::sqrt(double(q)); t->sigma2[2] = m->sigma2[2] / std::sqrt(double(q));
+    t->adj[2].clear();
+    for (const auto &g : groups) {
+      t->adj[2].insert(t->adj[2].end(), list(g[0]), list(g[0]) + d3);
+      t->merged.insert(t->merged.end(), g.begin(), g.end());
+    }
+    t->merged_q = q;
+    t->M = m->M; t->K = m->K; t->rowdeg = m->rowdeg; t->coldeg = m->coldeg; t->nnz = m->nnz;
+    t->kernel_choice = RBGP_KERNEL_MFMA_REG;
+    t->uid = rbgp_next_uid();
+    t->dev = nullptr;
+    rbgp_plan_mfma(t);
+    rbgp_plan_reg(t);
+    if (!rbgp_reg_covers(t) || t->reg.fold != 1 || t->reg.R != p.R * q) {
+      delete t;
+      return;
+    }
+  } catch (...) {
+    delete t;
+    throw;
+  }
+  m->regroup = t;
+  m->regroup_bf16 = m->c[1] != 4 || m->c[2] != 8 || d3 != 4;
 }
 
 static bool plan_regroup_columns(rbgp_mask *m) {
@@ -676,14 +743,21 @@ void rbgp_reg_cluster(const rbgp_mask *m, int U, rbgp_reg_clusters *out) {
       best_max = std::max(best_max, n);
       best_sum += n;
     }
+    std::vector<int> least(a1, c1 + 1);   // of a row's unions with the others
+    int least_sum = 0;
+    for (int x = 0; x < a1; ++x) {
+      for (int y = 0; y < a1; ++y)
+        if (y != x) least[x] = std::min(least[x], un[x][y]);
+      least_sum += least[x];
+    }
     std::vector<int32_t> cur(members.size()), best = members;
     std::vector<char> taken(a1, 0);
     long budget = 4000000;
     // recursive lambda via explicit std::function-free trick
     struct Rec {
-      const std::vector<std::vector<int>> &un; std::vector<int32_t> &cur, &best; std::vector<char> &taken;
+      const std::vector<std::vector<int>> &un; const std::vector<int> &least; std::vector<int32_t> &cur, &best; std::vector<char> &taken;
       int a1; int &best_max, &best_sum; long &budget;
-      void go(int depth, int cmax, int csum) {
+      void go(int depth, int cmax, int csum, int rest) {   // rest: `least` of the rows that are not taken, added up
         if (budget-- <= 0) return;
         int x = 0;
         while (x < a1 && taken[x]) ++x;
@@ -694,17 +768,17 @@ void rbgp_reg_cluster(const rbgp_mask *m, int U, rbgp_reg_clusters *out) {
         taken[x] = 1;
         for (int y = x + 1; y < a1; ++y) {
           if (taken[y]) continue;
-          const int n = un[x][y], nmax = std::max(cmax, n), nsum = csum + n;
-          if (nmax > best_max || (nmax == best_max && nsum >= best_sum)) continue;
+          const int n = un[x][y], nmax = std::max(cmax, n), nsum = csum + n, after = rest - least[x] - least[y];
+          if (nmax > best_max || (nmax == best_max && nsum + (after + 1) / 2 >= best_sum)) continue;
           taken[y] = 1;
           cur[2 * depth] = x; cur[2 * depth + 1] = y;
-          go(depth + 1, nmax, nsum);
+          go(depth + 1, nmax, nsum, after);
           taken[y] = 0;
         }
         taken[x] = 0;
       }
-    } rec{un, cur, best, taken, a1, best_max, best_sum, budget};
-    rec.go(0, 0, 0);
+    } rec{un, least, cur, best, taken, a1, best_max, best_sum, budget};
+    rec.go(0, 0, 0, least_sum);
     members = best;
   }
   std::vector<int32_t> counts(ncl, 0);
@@ -944,7 +1018,10 @@ void rbgp_reg_plan_dual(const rbgp_mask *m, rbgp_reg_dual *out) {
 //           the consecutive contraction steps one lane feeds to the matrix core.
 void rbgp_build_pack_perm(const rbgp_mask *m, int kernel, bool bf16, std::vector<int32_t> &perm) {
   if (kernel == RBGP_KERNEL_MFMA_REG && m->regroup && (!bf16 || m->regroup_bf16)) {   // the register layout of the regrouped mask
-    rbgp_build_pack_perm(m->regroup, kernel, bf16, perm);         //   (same kept values, same canonical indices)
+    rbgp_build_pack_perm(m->regroup, kernel, bf16, perm);         //   (same kept values, same canonical indices, rows apart)
+    if (!m->regroup->merged.empty())
+      for (int32_t &s : perm)
+        if (s >= 0) s = int32_t(rbgp_twin_row(m->regroup, s / m->rowdeg) * m->rowdeg + s % m->rowdeg);
     return;
   }
   if (kernel == RBGP_KERNEL_MFMA_REG_FILLED) {
@@ -1622,8 +1699,12 @@ int rbgp_mask_check_tables(const rbgp_mask_t *m) {
     if (rc) return rc;
     try {
       std::vector<int32_t> mine(size_t(m->nnz)), theirs(size_t(m->nnz));
-      if (mask_columns_impl(m, mine.data()) || mask_columns_impl(m->regroup, theirs.data()) || mine != theirs)
-        return RBGP_EINTERNAL;
+      if (mask_columns_impl(m, mine.data()) || mask_columns_impl(m->regroup, theirs.data())) return RBGP_EINTERNAL;
+      for (int64_t r = 0; r < m->M; ++r) {
+        const int64_t own = rbgp_twin_row(m->regroup, r);
+        if (own < 0 || own >= m->M || !std::equal(&theirs[size_t(r * m->rowdeg)], &theirs[size_t(r * m->rowdeg)] + m->rowdeg, &mine[size_t(own * m->rowdeg)]))
+          return RBGP_EINTERNAL;
+      }
       for (bool bf16 : {false, true}) {
         std::vector<int32_t> perm;
         rbgp_build_pack_perm(m, RBGP_KERNEL_MFMA_REG, bf16, perm);

@@ -151,6 +151,8 @@ struct rbgp_mask {
                                       //   G_o is complete, the same mask with G_o (x) G_r merged into one tile column
                                       //   J(a_o, 1) (x) J(a_r, c_o c_r), whose stages are longer (then for bf16 as well)
   bool regroup_bf16 = false;          // the bf16 kernels run on `regroup` too
+  std::vector<int32_t> merged;        // a `regroup` mask whose G_i vertices each stand for merged_q vertices of the original's with one
+  int merged_q = 1;                   //   adjacency list, taken into G_r: [|G_i.U|][merged_q] those vertices (rows are permuted)
   std::vector<int32_t> pairs;         // filled masks (of another mask): where the kept weights of a stage are (rbgp_reg_pairs), or empty
 };
 
@@ -245,6 +247,12 @@ void rbgp_plan_filled(rbgp_mask *m);
 // words, for row r of tile row f and operand half h the 2-bit places of the eight kept steps 4 (e % 4) + 2 h + e / 4 among
 // the groups of four steps (k, k + 16, k + 4, k + 20), the index operand of the sparse MFMA; empty where a row keeps both
 std::vector<int32_t> rbgp_reg_pairs(const rbgp_mask *m, const rbgp_mask *t);
+// row of the mask that t is a regrouped twin of
+inline int64_t rbgp_twin_row(const rbgp_mask *t, int64_t row) {
+  if (t->merged.empty()) return row;
+  const int64_t q = t->merged_q, a4 = t->a[3], u4 = row % a4, u3 = row / a4 % t->a[2], ur = row / (a4 * t->a[2]);
+  return (ur / q * (q * t->a[2]) + t->merged[size_t(u3 * q + ur % q)]) * a4 + u4;
+}
 // builds m->regroup where that factoring uses more rows of the MFMA group (called once, when the mask is made)
 void rbgp_plan_regroup(rbgp_mask *m);
 // canonical index (m * rowdeg + t) of every packed element, -1 for padding

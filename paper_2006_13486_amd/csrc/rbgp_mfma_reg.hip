@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256, (LEAN || (NG == 2 && (KC <= 32 || (KC == 36 &&
   const int tiles_here = p.ntiles - nt < ct ? p.ntiles - nt : ct;
   const int cnt = __builtin_amdgcn_readfirstlane(   // stages of this wave
       CTILES ? p.ct_cnt * (tiles_here > 0 ? tiles_here : 0) : cnt0 > ks ? (cnt0 - ks + S - 1) >> lgS : 0);
-  const int rov = p.rowofs[lane & 15];   // lane-held copies, read back with bpermute in the epilogue
+  const int rov = row_offset(p, u3, lane & 15);   // lane-held copies, read back with bpermute in the epilogue
   const int memv = p.members[cl * MG + (lane & (MG - 1))];
   // table lane of the wave's s-th stage (all 64 lanes may hold stages: a stage past the wave's count is made a
   // sentinel where it is read back -- zero extent, weights past the end of the buffer)
@@ -585,6 +585,7 @@ struct RegState {
                                                         //   kernel arguments of the pairing kernel)
   int32_t *rowtab_bf16 = nullptr;  // bf16 kernels: [a_i][NKB*16]
   int32_t *pairs = nullptr;        // rbgp_mask::pairs
+  int32_t *rowmap = nullptr;       // RegParams::rowmap of a mask with merged G_i vertices
   uint64_t *conv_tiles = nullptr;  // conv_tile: ConvTileParams::sel, ::tiles
   bool conv_tiles_none = false;    //   G_i does not keep one of v and v + 4 everywhere: no such tables
   int32_t *rowtab_conv[2] = {nullptr, nullptr};   // fused convolution, fp32 / bf16: byte offsets for the geometry below
@@ -738,6 +739,7 @@ void rbgp_reg_release(void *state) {
   if (st->rowtab) (void)hipFree(st->rowtab);
   if (st->rowtab_bf16) (void)hipFree(st->rowtab_bf16);
   if (st->pairs) (void)hipFree(st->pairs);
+  if (st->rowmap) (void)hipFree(st->rowmap);
   if (st->conv_tiles) (void)hipFree(st->conv_tiles);
   for (int32_t *t : st->rowtab_conv)
     if (t) (void)hipFree(t);
@@ -780,10 +782,14 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const bool ok64 = conv ? true : (ldI % 4 == 0) && (reinterpret_cast<uintptr_t>(I) % 8 == 0);
     const bool ok128 = conv ? conv->width % 8 == 0 : (ldI % 8 == 0) && (reinterpret_cast<uintptr_t>(I) % 16 == 0);
     const int tc = tune[RBGP_TUNE_COLS_PER_WORKGROUP];
+    // Masks with merged rows, fp32 sums: rows of I a multiple of 128 KiB apart that the 256 MB Infinity Cache holds are read faster in
+    // narrow tiles (us, mask as given / merged, 128 / 64 columns: WRN group 1, 65536 columns 17.9 / 19.4 / 18.0, 131072 37.4 / 38.7 /
+    // 36.2; past the cache 262144 77.5 / 68 / 74, other strides 57344 16.2 / 15.3 / 16.6).
+    const bool crowded = !m->merged.empty() && !conv && !out_bf16 && ldI % 65536 == 0 && m->K * ldI * 2 <= (int64_t(256) << 20);
     if (tc != 0 && tc != 64 && tc != 128) return RBGP_EUNSUPPORTED;
     if (tc)
       CW = tc;
-    else if (ok128 && int64_t((pl.TR + pl.MG - 1) / pl.MG) * m->a[2] * ((N + 127) / 128) >= 512)
+    else if (ok128 && int64_t((pl.TR + pl.MG - 1) / pl.MG) * m->a[2] * ((N + 127) / 128) >= 512 && !crowded)
       CW = 128;
     if (!(CW == 128 ? ok128 : ok64)) return RBGP_ESHAPE;
   }
@@ -1220,6 +1226,17 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   rp.frag_bytes = bf16 ? (rbgp_bf16_blocks32(pl.KC) + (rbgp_bf16_tail16(pl.KC) ? 1 : 0)) * 4 * pl.RS * 16 : pl.NQ * 4 * pl.RS * 16;
   rp.nq = bf16 ? (pl.KCR + 31) / 32 : (pl.KCR + 15) / 16;
   for (int r = 0; r < 16; ++r) rp.rowofs[r] = (r / m->a[3]) * m->a[2] * m->a[3] + r % m->a[3];
+  if (!m->merged.empty() && !st->rowmap) {
+    std::vector<int32_t> h(size_t(m->a[2]) * 16, 0);
+    for (int u = 0; u < m->a[2]; ++u)
+      for (int r = 0; r < pl.R; ++r) {
+        const int64_t row = (int64_t(r / m->a[3]) * m->a[2] + u) * m->a[3] + r % m->a[3];   // (of tile row 0)
+        h[size_t(u) * 16 + r] = int32_t(rbgp_twin_row(m, row) - u * m->a[3]);
+      }
+    int rc = upload(h, &st->rowmap);
+    if (rc) return rc;
+  }
+  rp.rowmap = st->rowmap;
   rp.ntiles = int(ntiles);
   rp.lgS = lgS;
   const int64_t tiles_per_wg = split_rw > 1 ? 1 : share_rv ? 1 : (4 >> lgS) * CT;

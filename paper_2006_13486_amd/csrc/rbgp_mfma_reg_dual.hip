@@ -80,7 +80,7 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
   const int rowH = __builtin_amdgcn_readfirstlane(y ? quad_rows[3] : quad_rows[2]);
   const int cnt = __builtin_amdgcn_readfirstlane(quad_counts[x * 2 + y]);   // stages of this wave
   const int tb = lane < cnt ? entry[0] : -1, tflo = lane < cnt ? entry[1] : -1, tfhi = lane < cnt ? entry[2] : -1;
-  const int rov = p.rowofs[lane & 15];   // lane-held copy, read back with bpermute in the epilogue
+  const int rov = row_offset(p, u3, lane & 15);   // lane-held copy, read back with bpermute in the epilogue
   auto table_lane = [&](int s) { return s < 63 ? s : 63; };   // lanes past the count hold sentinels
 
   // byte offset of this lane's 16 bytes in every slot, relative to the stage base

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
   for (int mm = 0; mm < U; ++mm) tf[mm] = stg[(1 + mm) * TS];
   const int cnt = p.counts[cl];
   const int cntw = __builtin_amdgcn_readfirstlane(cnt > ks ? (cnt - ks + S - 1) >> lgS : 0);   // stages of this wave
-  const int rov = p.rowofs[lane & 15];   // lane-held copies, read back with bpermute in the epilogue
+  const int rov = row_offset(p, u3, lane & 15);   // lane-held copies, read back with bpermute in the epilogue
   const int memv = p.members[cl * U + (lane & (U - 1))];
 
   // byte offset of this lane's NC bf16 columns in each of its rows, relative to the stage base

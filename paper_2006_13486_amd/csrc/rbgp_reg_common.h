@@ -68,6 +68,7 @@ struct RegParams {
                            //   see rbgp_reg_pairs
   int fold;                // tile rows per row of G_o
   int rowofs[16];          // output row of weight row r of a group, relative to its (tile row, u_i) base
+  const int32_t *rowmap;   // [a_i][16] the same where it depends on u_i (rbgp_mask::merged), or nullptr
   int tm;                  // rows of one tile row: a_r * a_i * a_b
   int ntiles;              // column tiles: ceil(N / columns per wave)
   int lgS;                 // log2 of the waves that share a column tile (split of the stage list)
@@ -120,6 +121,10 @@ __device__ __forceinline__ bool wg_coord(const RegParams &p, WgCoord *c) {
     c->u3 = unit - c->ntq * p.a3;
   }
   return true;
+}
+
+__device__ __forceinline__ int row_offset(const RegParams &p, int u3, int r) {
+  return p.rowmap ? p.rowmap[u3 * 16 + r] : p.rowofs[r];
 }
 
 __device__ __forceinline__ f32x4 load_x4(__amdgpu_buffer_rsrc_t r, int voff, int soff) {

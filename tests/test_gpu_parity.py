@@ -1208,3 +1208,34 @@ def test_non_finite_input_stays_in_its_column():
         assert not np.isfinite(spoilt[touched, n_bad]).any()
         if kernel == GEN:
             assert np.array_equal(clean[~touched, n_bad].view(np.uint32), spoilt[~touched, n_bad].view(np.uint32))
+
+
+# masks of 3x3 convolutions whose G_i has groups of vertices with one adjacency list: the register family runs on the mask with a
+# group's rows in G_r, rows permuted (rows, cols, degrees, rows per column set before and after)
+MERGED_ROW_SHAPES = [
+    ((8, 4, 8, 1), (8, 4, 4, 9), (4, 4, 1, 9), 4, 8),     # pairs: tile rows paired tile by tile where the batch fills the chip
+    ((6, 2, 8, 1), (4, 2, 2, 9), (2, 2, 1, 9), 2, 8),     # fours, six tile rows
+    ((4, 4, 16, 1), (4, 1, 4, 9), (4, 1, 1, 9), 4, 16),   # fours: whole MFMA groups
+    ((4, 1, 8, 2), (8, 1, 4, 9), (2, 1, 1, 9), 2, 4),     # rows of G_b next to the merged ones
+]
+
+
+@pytest.mark.parametrize("idx", range(len(MERGED_ROW_SHAPES)))
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+def test_register_family_on_the_mask_with_merged_rows(idx, dtype):
+    rows, cols, deg, before, after = MERGED_ROW_SHAPES[idx]
+    w = wl.Workload(f"merged_rows{idx}", rows, cols, deg, 0, dtype, 310 + idx, 320 + idx, 330 + idx, 1.0)
+    mask = rb.rbgp_make_mask(rows, cols, deg, w.mask_seed)
+    plan = rb.rbgp_mask_reg_plan(mask)
+    assert rows[1] * rows[3] == before and plan[14] == after
+    rb.rbgp_mask_check_tables(mask)
+    for N in (8, 328, 4104):   # split lists, a ragged last tile, whole lists (and pairs of tile rows)
+        gh.check_parity(w, N=N, kernel=REG, ld_pad=8, expect_kernel=REG)
+    gh.check_parity(w, N=200, kernel=REG, tune=(0, 0, 0, 1, 0, 0), expect_kernel=REG)
+    vals, X = wl.kept_weights(w), wl.conv_activations(w, 37, 4, 8)
+    if dtype == wl.BF16:
+        vals, X = wl.to_bf16_bits(vals), wl.to_bf16_bits(X)
+    out = gh.library_conv3x3(w, vals, X)
+    as_f32 = wl.bf16_bits_as_f32 if dtype == wl.BF16 else (lambda a: a)
+    ref, den = gh.oracle_spmm(w, as_f32(vals), orc.im2col_3x3(as_f32(X)))
+    assert orc.normalised_error(out, ref, den) <= gh.TOL[dtype]
