@@ -591,7 +591,9 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
             !(one_launch && (uneven || (!conv && N > 512 && (N < 1408 || broken))));
     if (count(RBl, NBl) < 256) {
       NBl = std::min(nbt, 3);
-      if (RBl == 2 && count(2, NBl) < 256 && (count(1, NBl) >= 256 || count(2, NBl) * most < 256)) RBl = 1;
+      // (fused, single row groups on short batches as well: us, 2 x 3 -> 1 x 3, layer 1 at 1/2, 37888 columns 14.3 -> 12.8, 65536 15.9 ->
+      // 15.0, 98304 18.6 -> 18.8; layer 2 at 1/2, 16384 12.2 -> 11.0; layer 3 at 1/2, 16384 13.8 -> 13.9, 24576 15.9 -> 17.4)
+      if (RBl == 2 && count(2, NBl) < 256 && (count(1, NBl) >= 256 || count(2, NBl) * most < 256 || (conv && count(1, NBl) * N < int64_t(5) << 19))) RBl = 1;
       parts = std::min((256 + count(RBl, NBl) - 1) / count(RBl, NBl), most);
     }
     // A unit that stays with one workgroup has only its longer steps to gain from, on the lowered input: not where the batch
@@ -614,22 +616,39 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
       lines = false;
   } else {
     // fp32: where one round of workgroups of 2 x 3 groups (or, on short batches, 1 x 3) covers the units (us, before -> 2 x 3
-    // / 1 x 3: conv5, 2048 columns 22.9 -> 20.5 / 26, fused 23.2 -> 20.6; layer 6 at 1/2, 8192 columns 72.7 -> 59.1; at 1/4,
-    // 2368 columns 19.1 -> 21.4 / 16.3, 8192 38.1 -> 56 / 43.9); below 1024 columns not where sddmm_reg needs one launch on the
-    // lowered input (layer 6 at 1/4, 320 columns 10.9 -> 6.7; conv5 fused, 512 columns 13.7 -> 10.2, lowered 9.8 -> 10.3), and
-    // from 512 on only where a unit is split over workgroups (layer 2 at 1/4, 512 0.98, 768 1.05; split 0.60-0.95).
-    // From 1024 on (ratios): two row groups 0.87-0.97, fused until the loads of the windows outweigh the second launch (layer 6
-    // at 1/2, 4352 columns 0.97, 5248 1.04, 8192 1.07); halved to one row group until 2560 (layers 4 at 1/2 and 5 at 1/4, 2560
-    // 0.91 and 0.87, fused 0.95, 2816 0.97 and 0.95, fused 1.0-1.02, 4096 1.03 and 1.00, fused 1.06, 8192 1.24, fused 1.33);
-    // one row group to begin with fused only (layer 9 at 1/16, 1024 0.89, 1696 0.99, 1760 to 2048 1.02-1.06; lowered 1024
-    // 1.10, 1536 0.97, 2048 1.12).
-    if (RBl == 2 && count(2, NBl) < 224) RBl = 1;
-    const int64_t wgs = count(RBl, NBl);
-    if (N < 1024)
-      lines = wgs <= 256 && N > 64 && (conv || !one_launch || N <= 256) && (N <= 512 || wgs > units);
-    else
-      lines = wgs <= 256 && wgs >= 224 && (RBl == 2 ? !conv || N < 4480 : RB == 2 ? N <= 2560 : conv && N < 1728);
+    // / 1 x 3: conv5, 2048 columns 22.9 -> 20.5 / 26; layer 6 at 1/2, 8192 columns 72.7 -> 59.1; at 1/4, 2368 columns 19.1 -> 21.4 /
+    // 16.3); below 1024 columns not where sddmm_reg needs one launch on the lowered input (layer 6 at 1/4, 320 columns 10.9 -> 6.7;
+    // conv5 lowered, 512 9.8 -> 10.3), and from 512 on only where a unit is split over workgroups (layer 2 at 1/4, 512 0.98, 768 1.05;
+    // split 0.60-0.95).  Lowered, from 1024 on (ratios): two row groups 0.87-0.97, halved to one row group until 2560 (layers 4 at 1/2
+    // and 5 at 1/4, 2560 0.91 and 0.87, 4096 1.03 and 1.00, 8192 1.24), one row group to begin with 1.10 (layer 9 at 1/16, 1024 columns).
+    const int64_t narrow = count(1, NBl);   // workgroups with one row group
+    if (conv) {
+      // The windows' loads and splits serve RB groups, so that the batch is split as well where units are few.  Two row groups where they
+      // fill the chip or the batch is long, else one (us, sddmm_reg / 1 x 3 / 2 x 3: layer 4 at 1/4, 1024 columns 12.0 / 9.2 / 10.2,
+      // 4096 16.3 / 13.8 / 14.2, 6144 20.8 / 17.6 / 16.7; layer 2 at 1/2, 9472 20.1 / 16.0 / 16.3, 32768 36.5 / 36.1 / 31.4; layer 6
+      // at 1/4, 4096 22.5 / 18.7 / 19.1, 8192 33.5 / 33.3 / 29.9; all of G_i, layer 1 at 1/4, 37888 31.1 / 25.2 / 25.4, 65536 40.5 /
+      // 37.2 / 34.1).  Parts of two steps a wave and more.
+      if (RB == 2 && count(2, NBl) < 224 && narrow <= 256 && narrow * N < int64_t(narrow >= 224 ? 5 : gi ? 6 : 3) << 18) RBl = 1;
+      const int64_t wgs = count(RBl, NBl);
+      const int64_t longest = std::max<int64_t>(1, N / 512);
+      parts = std::max<int64_t>(1, std::min(256 / wgs, longest));
+      // sddmm_reg keeps more units than CUs (layer 8 at 1/2, 1024 columns 18.5 against 20.7), single row groups on long batches where
+      // half of the second piece of a stage is padding (layer 6 at 1/16, 4096 14.4 / 13.5, 8192 20.8 / 21.3), and, with a workgroup
+      // per unit, batches beyond which it was the faster before the windows (layer 9 at 1/16, layer 6 at 1/2).
+      lines = wgs <= 256 && (wgs * parts >= 160 || parts == longest);
+      if (RB == 1 && nbt > 3 && narrow * N >= int64_t(narrow >= 128 ? 1 : 2) << 20) lines = false;
+      if (wgs >= 224 && RBl == RB && N >= (RB == 2 ? 4480 : 1728)) lines = false;
+    } else {
+      if (RBl == 2 && count(2, NBl) < 224) RBl = 1;
+      const int64_t wgs = count(RBl, NBl);
+      if (N < 1024)
+        lines = wgs <= 256 && N > 64 && (!one_launch || N <= 256) && (N <= 512 || wgs > units);
+      else
+        lines = wgs <= 256 && wgs >= 224 && RB == 2 && (RBl == 2 || N <= 2560);
+    }
   }
+  if (lines && parts > 1 && !B.grow && size_t(parts) * size_t(nnz) * sizeof(float) > B.partial_bytes) lines = false;
+  if (conv && m->M * ld_dO * (bf16 ? 2 : 4) >= int64_t(1) << 32) lines = false;   // (32-bit offsets into dO)
   int64_t blocks, chunk, nsplit;
   int halves = 1;
   sddmm_fn fn;

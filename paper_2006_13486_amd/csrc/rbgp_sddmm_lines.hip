@@ -3,19 +3,22 @@
 // of a row, one cache line: 32 columns in fp32, 64 in bf16.  Compared with sddmm_reg (steps of 64 bytes, four waves, whole
 // stages): twice the bytes in flight, lines asked for once, a unit's outputs split over workgroups before the batch is (no
 // partial sums, no second launch), the workgroups of an XCD chosen for the rows they share.
-// CONV: the three horizontal taps of a channel row are one window of a lane's columns and one pixel to either side, loaded once
-// (16 bytes and 4 or 8 more, aligned to 4 bytes) and written to LDS three times, shifted: a third of the rows of sddmm_reg,
-// whose bf16 loads are mostly aligned to 2 bytes.
+// CONV: the three horizontal taps of a channel row are one window of a lane's columns and one pixel to either side (16 bytes and 4
+// or 8 more, aligned to 4 bytes): a third of the rows of sddmm_reg, whose bf16 loads are mostly aligned to 2 bytes.  Stages of
+// 36 steps and more (WIN) pass the window through LDS once and make the taps from it in registers, so that fp32 splits it once:
+// 194 vector instructions a step for 2 x 3 groups, where three shifted copies of the rows took 260 (and 1.4 times the LDS traffic,
+// in bf16 1.8 times).  Shorter stages, whose windows do not fill a group, write it three times, shifted.
 // fp32: operands are split (rbgp_split.h) after the pass through LDS, and their products go through the bf16 matrix core: 6.5
 // vector instructions a value, 36 MFMAs of 16 cycles instead of 48 of 32 for 2 x 3 groups x 32 columns.
 //
-// us, before (sddmm_reg, with its second launch) -> this kernel: VGG19 conv3 bf16, 8192 columns, fused 19.0 -> 13.7, lowered
-// 20.5 -> 15.5, 2368 columns 13.0 -> 8.2; WRN group 1 bf16 fused 27.9 -> 22; conv5 bf16 11.8 -> 10.1, fp32 fused 23.2 -> 20.6;
-// VGG19 layer 6 at 1/4 fp32, 2368 columns 19.1 -> 16.3, 320 columns 10.9 -> 6.7; fp32 error against 64-bit sums 1.8e-7 -> 0.8e-7.
-// What bounds it (conv5 fp32 fused, timing-only builds): empty loops 5.3 (launch, tables, adding up eight waves), the loads
-// alone 11 (lowered 13.4: memory), the passes through LDS alone 12.5, loads and LDS 14.5; the splits keep a wave's issue slot
-// (4 to 6 cycles an instruction) busy for 1200 cycles a step.  Tried: twelve waves (23.2, spills), four (25), one step in flight
-// (21.1), fp32 MFMAs (22.5), each workgroup's steps starting elsewhere in its range (no change).
+// us, before (sddmm_reg, with its second launch) -> this kernel, lowered: VGG19 conv3 bf16, 8192 columns 20.5 -> 15.5, 2368 13.0
+// -> 8.2; layer 6 at 1/4 fp32, 2368 columns 19.1 -> 16.3, 320 columns 10.9 -> 6.7; fused, shifted copies / windows: conv3 bf16
+// 19.0 -> 13.7 / 11.6, WRN group 1 bf16 27.9 -> 21.2 / 18.5, conv5 fp32 23.2 -> 19.0 / 16.5, layer 6 at 1/4 fp32, 2368 columns
+// 18 -> 16.3 / 12.8; fp32 error against 64-bit sums 1.8e-7 -> 0.8e-7.
+// What bounds it (conv5 fp32 fused, timing-only builds of the shifted copies): empty loops 5.3 (launch, tables, adding up eight waves),
+// the loads alone 11 (lowered 13.4: memory), the passes through LDS alone 12.5, loads and LDS 14.5.  Tried: twelve waves (23.2,
+// spills), four (25), one step in flight (21.1), fp32 MFMAs (22.5), each workgroup's steps starting elsewhere in its range (no
+// change); lowered, buffer loads with scalar column offsets, 30 of 280 vector instructions a step fewer (no change).
 #include <hip/hip_runtime.h>
 
 #include "rbgp_sddmm.h"
@@ -27,8 +30,7 @@ using rbgp_sddmm_detail::SddmmParams;
 namespace {
 
 constexpr int kWaves = rbgp_sddmm_detail::kLinesWaves;
-typedef f32x4 f32x4_u __attribute__((aligned(4)));
-typedef bf16x8 bf16x8_u __attribute__((aligned(4)));
+typedef u32x4 u32x4_u __attribute__((aligned(4)));
 typedef bf16x8 bf16x8_any __attribute__((aligned(2)));
 
 template <bool BF16>
@@ -38,10 +40,10 @@ struct Operand;
 template <>
 struct Operand<false> {
   static constexpr int CPL = 4;   // columns per lane and load
-  static __device__ __forceinline__ u32x4 load(const void *base, int64_t elem) {
-    return __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4_u *>(static_cast<const float *>(base) + elem));
+  static constexpr int WX = 2;    // dwords of a window past a lane's 16 bytes
+  static __device__ __forceinline__ u32x4 load_any(const unsigned char *at) {
+    return *reinterpret_cast<const u32x4_u *>(at);
   }
-  static __device__ __forceinline__ u32x4 load_any(const void *base, int64_t elem) { return load(base, elem); }
   // moved down by s columns (1 to 3), zeros behind
   static __device__ __forceinline__ u32x4 moved(u32x4 x, int s) {
     x = s & 1 ? u32x4{x[1], x[2], x[3], 0} : x;
@@ -52,6 +54,29 @@ struct Operand<false> {
     const float x[8] = {__uint_as_float(lo[0]), __uint_as_float(lo[1]), __uint_as_float(lo[2]), __uint_as_float(lo[3]),
                         __uint_as_float(hi[0]), __uint_as_float(hi[1]), __uint_as_float(hi[2]), __uint_as_float(hi[3])};
     return split8(x);
+  }
+  // the operands of the three horizontal taps, from the lane's two windows of six columns (split once)
+  static __device__ __forceinline__ void windows(frag (&f)[3], const u32x4 (&b)[2], const uint32_t (&w)[2][WX]) {
+    u32x4 o[3][3];                // [tap][part]
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t p[3][3];           // [pair of columns][part]
+      split2(__uint_as_float(b[h][0]), __uint_as_float(b[h][1]), p[0]);
+      split2(__uint_as_float(b[h][2]), __uint_as_float(b[h][3]), p[1]);
+      split2(__uint_as_float(w[h][0]), __uint_as_float(w[h][1]), p[2]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        o[0][k][2 * h] = p[0][k];
+        o[0][k][2 * h + 1] = o[2][k][2 * h] = p[1][k];
+        o[2][k][2 * h + 1] = p[2][k];
+        o[1][k][2 * h] = __builtin_amdgcn_alignbit(p[1][k], p[0][k], 16);
+        o[1][k][2 * h + 1] = __builtin_amdgcn_alignbit(p[2][k], p[1][k], 16);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) f[d].p[k] = __builtin_bit_cast(bf16x8, o[d][k]);
   }
   template <int RB>
   static __device__ __forceinline__ void mac(const frag (&a)[RB], const frag &b, f32x4 (&acc)[RB], f32x4 (&cor)[RB]) {
@@ -73,11 +98,9 @@ struct Operand<false> {
 template <>
 struct Operand<true> {
   static constexpr int CPL = 8;
-  static __device__ __forceinline__ u32x4 load(const void *base, int64_t elem) {
-    return __builtin_bit_cast(u32x4, *reinterpret_cast<const bf16x8_u *>(static_cast<const uint16_t *>(base) + elem));
-  }
-  static __device__ __forceinline__ u32x4 load_any(const void *base, int64_t elem) {   // (any alignment)
-    return __builtin_bit_cast(u32x4, *reinterpret_cast<const bf16x8_any *>(static_cast<const uint16_t *>(base) + elem));
+  static constexpr int WX = 1;
+  static __device__ __forceinline__ u32x4 load_any(const unsigned char *at) {   // (any alignment)
+    return __builtin_bit_cast(u32x4, *reinterpret_cast<const bf16x8_any *>(at));
   }
   static __device__ __forceinline__ u32x4 moved(u32x4 x, int s) {   // (1 to 7)
     x = s & 1 ? u32x4{__builtin_amdgcn_alignbit(x[1], x[0], 16), __builtin_amdgcn_alignbit(x[2], x[1], 16),
@@ -89,6 +112,16 @@ struct Operand<true> {
     u32x4 lo, hi;
   };
   static __device__ __forceinline__ frag make(const u32x4 &lo, const u32x4 &hi) { return frag{lo, hi}; }
+  // one column up: b[0] and the next of every pair, behind b[3] the first of w
+  static __device__ __forceinline__ u32x4 up(const u32x4 &b, uint32_t w) {
+    return u32x4{__builtin_amdgcn_alignbit(b[1], b[0], 16), __builtin_amdgcn_alignbit(b[2], b[1], 16),
+                 __builtin_amdgcn_alignbit(b[3], b[2], 16), __builtin_amdgcn_alignbit(w, b[3], 16)};
+  }
+  static __device__ __forceinline__ void windows(frag (&f)[3], const u32x4 (&b)[2], const uint32_t (&w)[2][WX]) {
+    f[0] = frag{b[0], b[1]};
+    f[1] = frag{up(b[0], w[0][0]), up(b[1], w[1][0])};
+    f[2] = frag{u32x4{b[0][1], b[0][2], b[0][3], w[0][0]}, u32x4{b[1][1], b[1][2], b[1][3], w[1][0]}};
+  }
   template <int RB>
   static __device__ __forceinline__ void mac(const frag (&a)[RB], const frag &b, f32x4 (&acc)[RB], f32x4 (&)[RB]) {
 #pragma unroll
@@ -102,18 +135,22 @@ struct Operand<true> {
   }
 };
 
-// RB: groups of 16 rows of dO per wave; NB: groups of 16 contraction steps per wave.
+// RB: groups of 16 rows of dO per wave; NB: groups of 16 contraction steps per wave.  WIN (CONV, NB = 3 and 6): a group is one
+// horizontal tap of 16 pixel rows (channel, dy), and the three taps of the same 16 rows (24 with NB = 6) come out of one window.
 template <int RB, int NB, bool BF16, bool CONV, bool GI>
 __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   typedef Operand<BF16> Op;
   constexpr int CPL = Op::CPL, CPI = 8 * CPL;   // columns per lane load / per step: 128 bytes of a row
   constexpr int ES = BF16 ? 2 : 4;
-  constexpr int NG = RB + NB;
-  // CONV: pixel rows (channel, dy), three taps each, whose windows one step loads: eight per load instruction
-  constexpr int NPL = (16 * NB + 23) / 24 < 3 ? (16 * NB + 23) / 24 : 3;   // (a stage has at most 72 steps)
+  constexpr bool WIN = CONV && NB >= 3;
+  static_assert(!WIN || NB % 3 == 0, "whole windows");
+  constexpr int NGB = WIN ? NB / 3 : NB;        // groups of 16 rows of B in LDS
+  constexpr int NG = RB + NGB;
+  // CONV: pixel rows, three taps each, whose windows one step loads: eight per load instruction
+  constexpr int NPL = WIN ? (NB == 6 ? 3 : 2) : (16 * NB + 23) / 24;   // (a stage has at most 72 steps)
   constexpr int NLI = CONV ? NPL : 2 * NB;      // 16-byte loads of rows of I per step
-  constexpr bool kDump = CONV && 24 * NPL > 16 * NB;
-  constexpr int kTile = NG * 128 + (kDump ? 64 : 0);   // 16-byte slots of a wave: 16 rows x 128 bytes per group
+  constexpr int kExtra = WIN ? NGB * 32 * Op::WX : CONV ? 64 : 0;   // ends of windows; without WIN what is past the last step
+  constexpr int kTile = NG * 128 + kExtra;      // 16-byte slots of a wave: 16 rows x 128 bytes per group
   __shared__ union {
     u32x4 stage[kWaves][kTile];
     float red[kWaves][RB * NB * 4][64];
@@ -169,25 +206,32 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       o.row = ((int64_t(crow[o.entry]) * p.a2 + ri / p.a4) * p.a3 + o.ui) * p.a4 + ri % p.a4;
     return o;
   };
-  int64_t offA[2 * RB];   // element offset of this lane's 16 bytes in step 0
+  // Byte offsets of this lane's 16 bytes in step 0.  CONV: below 2 GiB (inside X) and 4 GiB (inside dO), checked by the host, and the
+  // column of a step is a scalar offset of buffer loads, which costs no vector instruction (on the lowered input no gain, and spills).
+  typedef typename std::conditional<CONV, uint32_t, int64_t>::type Off;
+  Off offA[2 * RB];
 #pragma unroll
   for (int i = 0; i < 2 * RB; ++i) {
     const int64_t row = row_of(i / 2, lr + 8 * (i % 2)).row;
-    offA[i] = (row < 0 ? 0 : row) * p.ld_dO + ls * CPL;
+    offA[i] = Off((row < 0 ? 0 : row) * p.ld_dO * ES + ls * 16);
   }
-  int64_t offB[NLI];      // CONV: byte offset of the row's window inside X (below 2 GiB)
-  int wslotB[CONV ? NPL : 1][3];
+  const unsigned char *const bytesA = static_cast<const unsigned char *>(p.dO);
+  const unsigned char *const bytesB = static_cast<const unsigned char *>(p.I);
+  Off offB[NLI];
+  int wslotB[CONV && !WIN ? NPL : 1][3];
   if constexpr (CONV) {
 #pragma unroll
     for (int i = 0; i < NPL; ++i) {
-      const int kk = 48 * (b0 / 3) + 3 * (8 * i + lr);     // first tap of the pair (b0 is a multiple of 3)
+      const int kk = 16 * b0 + 3 * (8 * i + lr);           // first tap of the pair (b0 is a multiple of 3)
       const int sr = GI ? (kk < p.src_rows ? kk : 0) : (kk < p.KCR ? p.rowtab[u3 * p.nbt * 16 + kk] : 0);
       const int k = base + sr;                             // channel k / 9, dy = (k % 9) / 3 - 1, dx = -1
-      offB[i] = (int64_t(k / 9) * p.chan_elems + ((k % 9) / 3 - 1) * p.conv_w2 - 1) * ES;
+      offB[i] = Off((int64_t(k / 9) * p.chan_elems + ((k % 9) / 3 - 1) * p.conv_w2 - 1) * ES);
+      if constexpr (!WIN) {
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int row = 3 * (8 * i + lr) + d;
-        wslotB[i][d] = row < 16 * NB ? (RB + row / 16) * 128 + (row % 16) * 8 + (ls ^ (row & 7)) : NG * 128 + lane;
+        for (int d = 0; d < 3; ++d) {
+          const int row = 3 * (8 * i + lr) + d;
+          wslotB[i][d] = row < 16 * NB ? (RB + row / 16) * 128 + (row % 16) * 8 + (ls ^ (row & 7)) : NG * 128 + lane;
+        }
       }
     }
   } else {
@@ -195,24 +239,30 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     for (int i = 0; i < NLI; ++i) {   // padding steps read row 0 of the stage
       const int b = b0 + i / 2, r = lr + 8 * (i % 2), sr = 16 * b + r;
       const int k = base + (GI ? (sr < p.src_rows ? sr : 0) : (b < p.nbt ? p.rowtab[(u3 * p.nbt + b) * 16 + r] : 0));
-      offB[i] = int64_t(k) * p.ldI + ls * CPL;
+      offB[i] = Off(int64_t(k) * p.ldI * ES + ls * 16);
     }
   }
   // CONV: where this lane's group of columns starts inside a channel (columns are pixels in image order)
   auto pixel = [&](int64_t n) { return CONV ? p.colbase[n / CPL + ls] * ES : 0; };
-  __amdgpu_buffer_rsrc_t xrsrc;
-  if constexpr (CONV) xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.I), 0, int(p.x_bytes), 0x00020000);
+  __amdgpu_buffer_rsrc_t arsrc, xrsrc;
+  if constexpr (CONV) {
+    arsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.dO), 0, -1, kRsrcFlags);
+    xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.I), 0, int(p.x_bytes), kRsrcFlags);
+  }
 
   // What one step has in flight.  CONV: the window of CPL + 2 pixels that the three horizontal taps of a lane's columns share.
   struct Raw {
     u32x4 a[2 * RB], b[NLI];
-    uint32_t w[CONV ? NPL : 1][2];
+    uint32_t w[CONV ? NPL : 1][Op::WX];
   };
   // (`at`: pixel(n), looked up by the caller -- ahead of time inside the loop, where a lookup right before its use
   // would have to wait for every load in flight)
   auto load_all = [&](Raw &r, int64_t n, int at) {
 #pragma unroll
-    for (int i = 0; i < 2 * RB; ++i) r.a[i] = Op::load(p.dO, offA[i] + n);
+    for (int i = 0; i < 2 * RB; ++i) {
+      if constexpr (CONV) r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, int(offA[i]), int(uint32_t(n) * ES), 0);
+      else r.a[i] = *reinterpret_cast<const u32x4_u *>(bytesA + offA[i] + n * ES);
+    }
 #pragma unroll
     for (int i = 0; i < NLI; ++i) {
       if constexpr (CONV) {
@@ -226,28 +276,40 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
           r.w[i][1] = w[1];
         }
       } else {
-        r.b[i] = Op::load(p.I, offB[i] + n);
+        r.b[i] = *reinterpret_cast<const u32x4_u *>(bytesB + offB[i] + n * ES);
       }
     }
   };
   // load layout -> operand layout through this wave's tiles (LDS instructions of one wave execute in order)
   u32x4 *const tile = lds.stage[wave];
-  auto transpose_all = [&](u32x4 (&o)[NG][2], const Raw &r) {
+  // WIN: the end of row r's window in segment s, behind the groups: eight bytes (bf16: four), segments of a row exchanged so that the
+  // 32 (64) lanes that read at a time fall on different banks
+  auto end_of = [&](int r, int s) {
+    return reinterpret_cast<uint32_t *>(tile + NG * 128) + Op::WX * (8 * r + (s ^ (BF16 ? 4 * (r >> 3 & 1) : 2 * (r >> 2 & 3))));
+  };
+  struct Ops {   // what a lane multiplies: its two segments of a row of every group, and (WIN) the ends of the windows
+    u32x4 o[NG][2];
+    uint32_t w[WIN ? NGB : 1][2][Op::WX];
+  };
+  auto transpose_all = [&](Ops &x, const Raw &r) {
 #pragma unroll
     for (int i = 0; i < 2 * RB; ++i) tile[(i / 2) * 128 + (i % 2) * 64 + wslot] = r.a[i];
 #pragma unroll
     for (int i = 0; i < NLI; ++i) {
-      if constexpr (CONV) {
+      if constexpr (WIN) {
+        tile[(RB + i / 2) * 128 + (i % 2) * 64 + wslot] = r.b[i];
+        uint32_t *const e = end_of(8 * i + lr, ls);
+        if constexpr (BF16) *e = r.w[i][0];
+        else *reinterpret_cast<u32x2 *>(e) = u32x2{r.w[i][0], r.w[i][1]};
+      } else if constexpr (CONV) {
         const u32x4 b = r.b[i];
-        const uint32_t w0 = r.w[i][0], w1 = r.w[i][1];
         tile[wslotB[i][0]] = b;
         if constexpr (BF16) {
-          tile[wslotB[i][1]] = u32x4{__builtin_amdgcn_alignbit(b[1], b[0], 16), __builtin_amdgcn_alignbit(b[2], b[1], 16),
-                                     __builtin_amdgcn_alignbit(b[3], b[2], 16), __builtin_amdgcn_alignbit(w0, b[3], 16)};
-          tile[wslotB[i][2]] = u32x4{b[1], b[2], b[3], w0};
+          tile[wslotB[i][1]] = Op::up(b, r.w[i][0]);
+          tile[wslotB[i][2]] = u32x4{b[1], b[2], b[3], r.w[i][0]};
         } else {
-          tile[wslotB[i][1]] = u32x4{b[1], b[2], b[3], w0};
-          tile[wslotB[i][2]] = u32x4{b[2], b[3], w0, w1};
+          tile[wslotB[i][1]] = u32x4{b[1], b[2], b[3], r.w[i][0]};
+          tile[wslotB[i][2]] = u32x4{b[2], b[3], r.w[i][0], r.w[i][1]};
         }
       } else {
         tile[(RB + i / 2) * 128 + (i % 2) * 64 + wslot] = r.b[i];
@@ -256,9 +318,23 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
-      o[i][0] = tile[i * 128 + rslot0];
-      o[i][1] = tile[i * 128 + rslot1];
+      x.o[i][0] = tile[i * 128 + rslot0];
+      x.o[i][1] = tile[i * 128 + rslot1];
     }
+    if constexpr (WIN)
+#pragma unroll
+      for (int g = 0; g < NGB; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t *const e = end_of(16 * g + j, q + 4 * h);
+          if constexpr (BF16) {
+            x.w[g][h][0] = *e;
+          } else {
+            const u32x2 v = *reinterpret_cast<const u32x2 *>(e);
+            x.w[g][h][0] = v[0];
+            x.w[g][h][1] = v[1];
+          }
+        }
     __builtin_amdgcn_wave_barrier();
   };
   f32x4 acc[NB][RB], cor[NB][RB];
@@ -268,12 +344,22 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) a[b][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
-  auto mac_all = [&](const u32x4 (&o)[NG][2]) {
+  auto mac_all = [&](const Ops &x) {
     typename Op::frag a[RB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) a[rb] = Op::make(o[rb][0], o[rb][1]);
+    for (int rb = 0; rb < RB; ++rb) a[rb] = Op::make(x.o[rb][0], x.o[rb][1]);
+    if constexpr (WIN) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) Op::template mac<RB>(a, Op::make(o[RB + b][0], o[RB + b][1]), acc[b], cor[b]);
+      for (int g = 0; g < NGB; ++g) {
+        typename Op::frag f[3];
+        Op::windows(f, x.o[RB + g], x.w[g]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) Op::template mac<RB>(a, f[d], acc[3 * g + d], cor[3 * g + d]);
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) Op::template mac<RB>(a, Op::make(x.o[RB + b][0], x.o[RB + b][1]), acc[b], cor[b]);
+    }
   };
   // The last, partly empty step: columns at and past N count as zero on both sides.  A lane whose columns are not all there
   // loads the row's last CPL ones (the host takes this kernel for N >= CPL) and moves them down: no load waits for another
@@ -284,10 +370,10 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     const bool valid = s == 0;
     const bool odd = p.N % CPL != 0;
 #pragma unroll
-    for (int i = 0; i < 2 * RB; ++i) r.a[i] = Op::load_any(p.dO, offA[i] + off);
+    for (int i = 0; i < 2 * RB; ++i) r.a[i] = Op::load_any(bytesA + offA[i] + off * ES);
     if constexpr (!CONV)
 #pragma unroll
-      for (int i = 0; i < NLI; ++i) r.b[i] = Op::load_any(p.I, offB[i] + off);
+      for (int i = 0; i < NLI; ++i) r.b[i] = Op::load_any(bytesB + offB[i] + off * ES);
     auto cut = [&](u32x4 &x) {
       if (odd) x = Op::moved(x, s);
 #pragma unroll
@@ -302,8 +388,8 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       for (int i = 0; i < NLI; ++i) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) r.b[i][e] = valid ? t.b[i][e] : 0u;
-        r.w[i][0] = valid ? t.w[i][0] : 0u;
-        if constexpr (!BF16) r.w[i][1] = valid ? t.w[i][1] : 0u;
+#pragma unroll
+        for (int e = 0; e < Op::WX; ++e) r.w[i][e] = valid ? t.w[i][e] : 0u;
       }
     } else {
 #pragma unroll
@@ -330,7 +416,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
 #pragma unroll
     for (int d = 0; d < 2; ++d) at_next[d] = pixel(column(2 + d));
     auto step = [&](int d, int64_t k) {
-      u32x4 o[NG][2];
+      Ops o;
       transpose_all(o, raw[d]);
       const int at = at_next[d];
       at_next[d] = pixel(column(k + 4));
@@ -348,7 +434,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   if (n_lo + steps * CPI < n_hi) {
     Raw r;
     load_ragged(r, n_lo + steps * CPI);
-    u32x4 o[NG][2];
+    Ops o;
     transpose_all(o, r);
     mac_all(o);
   }
@@ -368,14 +454,22 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       for (int64_t n = n_lo; n < n_hi; n += CPI) {
         Raw r;
         load_ragged(r, n);
-        u32x4 o[NG][2];
-        transpose_all(o, r);
+        Ops x;
+        transpose_all(x, r);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) Op::mac_fp32(o[rb][h], o[RB + b][h], cor[b][rb]);
+            for (int h = 0; h < 2; ++h) {
+              u32x4 v = x.o[RB + (WIN ? b / 3 : b)][h];
+              if constexpr (WIN) {
+                const uint32_t (&w)[Op::WX] = x.w[b / 3][h];
+                if (b % 3 == 1) v = u32x4{v[1], v[2], v[3], w[0]};
+                if (b % 3 == 2) v = u32x4{v[2], v[3], w[0], w[1]};
+              }
+              Op::mac_fp32(x.o[rb][h], v, cor[b][rb]);
+            }
       }
 #pragma unroll
       for (int b = 0; b < NB; ++b)
@@ -387,8 +481,8 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     }
   }
 
-  // acc[b][rb][i] = dW block element (row 4 * q + i of row group rb, contraction step 16 * b + j); the waves take turns
-  // at adding them up
+  // acc[b][rb][i] = dW block element (row 4 * q + i of row group rb, contraction step 16 * b + j; WIN: tap b % 3 of pixel row
+  // 16 * (b / 3) + j); the waves take turns at adding them up
   __syncthreads();   // (the tiles are done with)
 #pragma unroll
   for (int b = 0; b < NB; ++b)
@@ -407,8 +501,8 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
     float *dst = p.out + int64_t(part) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
     // contraction step of this lane's column: 16 * b + j, or (gi) wherever G_i puts stage row 16 * b + j for u_i
-    const int st = 16 * (b0 + b) + j;
-    const int kk = b0 + b >= p.nbt ? -1 : GI ? p.spos[o.ui * p.nbt * 16 + st] : (st < p.KCR ? st : -1);
+    const int st = WIN ? 16 * b0 + 3 * (16 * (b / 3) + j) + b % 3 : 16 * (b0 + b) + j;
+    const int kk = st >= p.nbt * 16 ? -1 : GI ? p.spos[o.ui * p.nbt * 16 + st] : (st < p.KCR ? st : -1);
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; w += 4)
@@ -425,8 +519,11 @@ rbgp_sddmm_fn pick_nb(int NB) {
     case 3: return sddmm_lines<RB, 3, BF16, CONV, GI>;
   }
   if constexpr (BF16) {
-    if (NB == 4) return sddmm_lines<RB, 4, true, CONV, GI>;
-    if (NB == 5) return sddmm_lines<RB, 5, true, CONV, GI>;
+    if (CONV && (NB == 4 || NB == 5)) return sddmm_lines<RB, 6, true, true, GI>;   // (24 pixel rows)
+    if constexpr (!CONV) {
+      if (NB == 4) return sddmm_lines<RB, 4, true, false, GI>;
+      if (NB == 5) return sddmm_lines<RB, 5, true, false, GI>;
+    }
   }
   return nullptr;
 }

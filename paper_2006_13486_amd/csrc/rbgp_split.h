@@ -8,6 +8,7 @@ namespace rbgp_split {
 
 using namespace rbgp_reg;
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 

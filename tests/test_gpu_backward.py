@@ -258,6 +258,26 @@ def test_weight_gradient_of_a_convolution_keeps_infinities(case):
     assert same.any() and np.array_equal(got[same], clean[same])
 
 
+# fp32 convolutions whose units do not fill the chip: (mask, images of 8 x 8 pixels, kernel)
+BATCH_IN_PARTS = [(((8, 4, 4, 2), (4, 4, 8, 9), (2, 4, 4, 9)), 17, "1, 3, 0, 1, 0"), (((8, 4, 4, 2), (4, 4, 8, 9), (2, 4, 4, 9)), 97, "2, 3, 0, 1, 0"),
+                  (((8, 2, 4, 1), (8, 2, 4, 9), (2, 2, 2, 9)), 33, "1, 3, 0, 1, 1"), (((4, 4, 4, 2), (8, 2, 4, 9), (4, 2, 2, 9)), 65, "1, 3, 0, 1, 0")]
+
+
+@pytest.mark.parametrize("mask,images,kernel", BATCH_IN_PARTS)
+def test_weight_gradient_of_a_convolution_in_parts_of_the_batch(mask, images, kernel):
+    """Partial sums of parts with a ragged last step, one of them with an infinite pixel."""
+    w = wl.Workload("parts", *mask, 0, wl.F32, 101, 102, 103, 1.0)
+    X, dO = wl.conv_activations(w, images, 8, 8), wl.output_gradients(w, images * 64)
+    X[1, images - 1, 7, 7] = np.inf
+    got = gh.library_conv3x3_sddmm(w, dO, X)
+    assert rb.rbgp_last_kernel() == f"sddmm_lines<{kernel}> + sddmm_reduce"
+    I = orc.im2col_3x3(X)
+    ref, size = _kept_products(w, dO, I), _kept_products(w, np.abs(dO), np.abs(I))
+    fin = np.isfinite(ref)
+    assert fin.any() and not fin.all() and np.array_equal(np.isfinite(got), fin)
+    assert (np.abs(got[fin] - ref[fin]) <= 4e-6 * size[fin]).all()   # (as test_weight_gradient_whole_lines: chains are no longer)
+
+
 @pytest.mark.parametrize("N", [130, 200])
 def test_weight_gradient_split_operands_keep_infinities_and_tiny_operands(N):
     """fp32 weight gradients on split operands against the plain kernel: the same sums are infinite or not a number, operands
