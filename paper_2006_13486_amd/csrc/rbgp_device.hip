@@ -387,8 +387,8 @@ bool mfma_covers(const rbgp_mask *m) {
 // Estimated seconds per column of I: one of 1024 SIMDs at ~2.07 GHz serves 64 columns per instruction.  The
 // constants are fitted to the 4096^3 products of Tables 2 and 3 (27 masks, each on every family that covers it) on the
 // fp32 MFMA forms; the kernels on split operands (spmm_reg_split*, spmm_mfma_split) and those that share columns are not
-// in them.  One mask of Tables 2 and 3 would go elsewhere with them: G_o and G_i at 1/4, four rows per column set, on the
-// filled mask (us, LDS family -> filled: 64 columns 46 -> 9, 512 46 -> 34, 1000 61 -> 59, 1531 84 -> 77, 4096 168 -> 168).
+// in them.  One mask of Tables 2 and 3 would go elsewhere with them, for few columns: G_o and G_i at 1/4, four rows per column set (us,
+// LDS family / its filled mask: 64 columns 25 / 9, 256 25 / 25, 512 25 / 41, 1000 41 / 50, 1531 56 / 56, 4096 127 / 145).
 // Register family: a wave walks the stages of its (cluster, G_i vertex) pair; a stage of KC steps costs KC 16-row
 // MFMAs of ~36 cycles (fp32), or ~8 cycles per step in bf16 (the loads of the stage; its 32-step MFMAs hide behind
 // them, a second MFMA block for the remainder of a stage does not), plus what does not overlap.
@@ -793,21 +793,25 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
   const int epc = bf16 ? 8 : 4;
   if ((reinterpret_cast<uintptr_t>(dev_I) & 15) || (ldI % epc)) return RBGP_ESHAPE;
   // fp32 on the bf16 matrix core (spmm_mfma_split): four rows per column set, 32 rows of I per stage of which G_i keeps 8 or
-  // 16 (16: where a caller asks for this family; AUTO runs such masks filled), whole workgroups of 32 G_i vertices, and
-  // five workgroups for eight CUs.  4096 x 4096, G_o and G_i at 1/4 (a vertex keeps one weight of two steps: the sparse MFMA),
-  // us, spmm_mfma -> spmm_mfma_split: N = 16 46.1 -> 45.1, 256 48.2 -> 50.8, 512 48.9 -> 51.1 (128 workgroups), 600 84.8 -> 51.0
-  // (160), 1000 90.6 -> 54.6, 1531 127.9 -> 77.5, 2048 112 -> 83, 4096 200 -> 151.  (With a non-finite column at 1531 103, without
-  // a finite one 115: spmm_mfma's time does not depend on the values.)
+  // 16 (16: where a caller asks for this family; AUTO runs such masks filled), whole workgroups of 32 G_i vertices.  64 columns a
+  // workgroup, three on a CU; 128, two on a CU, where they fill four fifths of their last round; the stages dealt to two groups of
+  // waves while 64 columns leave a CU one workgroup.  4096 x 4096, G_o and G_i at 1/4 (a vertex keeps one weight of two steps: the
+  // sparse MFMA), us, spmm_mfma / 128 columns / 64 / 64 and two groups: N = 1 46 / 46 / 29 / 23, 256 46 / 50 / 31 / 25, 512 47 / 50 /
+  // 31 / 25, 600 85 / 50 / 40 / 43, 1000 91 / 50 / 41 / 44, 1152 - / 62 / 53 / 62, 1531 128 / 66 / 56 / 66, 1664 - / 66 / 67, 2048
+  // 112 / 66 / 68, 2304 - / 106 / 85, 3072 - / 106 / 98, 3584 - / 127 / 113, 4096 200 / 127 / 128.  Without pairs of steps from 160
+  // workgroups of 128 columns on.  (spmm_mfma's time does not depend on the values; a column that is not finite costs a second pass.)
   {
     const int tsp = dev->tune[RBGP_TUNE_SPLIT_OPERANDS];
-    const int64_t tiles = (N + 127) / 128, wgs = int64_t(m->a[0]) * (m->a[2] / 32) * tiles;
+    auto wgs = [&](int nt) { return int64_t(m->a[0]) * (m->a[2] / 32) * ((N + 32 * nt - 1) / (32 * nt)); };
+    const int KSP = wgs(2) <= 256 ? 2 : 1, NT = wgs(2) > 256 && (wgs(4) + 511) % 512 >= 409 ? 4 : 2;
+    const int64_t tiles = (N + 32 * NT - 1) / (32 * NT);
     const bool knobs = dev->tune[RBGP_TUNE_COLS_PER_LANE] || dev->tune[RBGP_TUNE_COLS_PER_WORKGROUP] ||
                        dev->tune[RBGP_TUNE_GROUPS_PER_WORKGROUP];
     const bool can = !bf16 && !knobs && pl.R == 4 && pl.SR == 32 && (pl.KS == 8 || pl.KS == 16) && pl.KS == m->d[2] * m->c[3] &&
                      m->a[2] % 32 == 0 && (int64_t(32) * ldI + 128) * 4 < (int64_t(1) << 31) &&
                      8 * ((tiles + 7) / 8) * m->a[0] * (m->a[2] / 32) <= 0x7fffffff;
     if (tsp > 3 || (tsp >= 2 && !can)) return RBGP_EUNSUPPORTED;
-    if (can && (tsp >= 2 || (tsp == 0 && wgs >= 160))) {
+    if (can && (tsp >= 2 || (tsp == 0 && (dev->one_of_two || wgs(4) >= 160)))) {
       rbgp_reg::SplitTileParams sp;
       sp.Wp = static_cast<const float *>(dev_packed); sp.I = static_cast<const float *>(dev_I); sp.O = static_cast<float *>(dev_O);
       sp.adj0 = dev->adj[0]; sp.rowoff = dev->rowoff;
@@ -815,7 +819,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
       sp.a1 = m->a[0]; sp.a2 = m->a[1]; sp.a3 = m->a[2]; sp.a4 = m->a[3]; sp.d1 = m->d[0]; sp.c2 = m->c[1];
       sp.ntiles = int(tiles);
       const int64_t nblocks = 8 * ((tiles + 7) / 8) * m->a[0] * (m->a[2] / 32);
-      hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS, dev->one_of_two), dim3(unsigned(nblocks)), dim3(256), 0, st, sp);
+      hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS, dev->one_of_two, NT, KSP), dim3(unsigned(nblocks)), dim3(unsigned(256 * KSP)), 0, st, sp);
       RBGP_HIP(hipGetLastError());
       rbgp_set_last_kernel("spmm_mfma_split", {pl.KS, dev->one_of_two});
       return RBGP_OK;

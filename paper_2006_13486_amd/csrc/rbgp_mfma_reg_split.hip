@@ -440,8 +440,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // The LDS family's product (RBGP_KERNEL_MFMA, fp32) on the bf16 matrix core, for masks whose G_o and G_i are both sparse:
 // a tile of G_o with four rows per column set and |G_i.V| |G_b.V| = 32 columns is multiplied as a dense 32-step block, the
 // structural zeros of G_i included (at most three in four), because a 32x32x16 bf16 MFMA does 16 times the products of
-// the 4x4x1 fp32 form per cycle.  Workgroup: 128 rows of a tile row (32 G_i vertices, a wave eight of them) x 128
-// columns.  A stage's kept weights (one 16-byte load per lane holds four rows of one step; two for KS = 16) are split and
+// the 4x4x1 fp32 form per cycle.  Workgroup: 128 rows of a tile row (32 G_i vertices, a wave eight of them) x 32 NT columns; with KSP =
+// 2, two such groups of four waves take every other stage and add their sums through LDS.  A stage's kept weights (one 16-byte load per lane holds four rows of one step; two for KS = 16) are split and
 // scattered to their steps in a wave-private LDS block whose other entries stay zero: the pattern of G_i is the same in
 // every tile.  I as in spmm_reg_split_shared, a round being one stage.  One Inf in I makes every sum of its
 // column in the tile rows with that tile non-finite (the zeros of G_i are multiplied): such sums are added up again from
@@ -449,14 +449,26 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // 126 -> 83 us, error against 64-bit sums 2.0e-7 -> 7.6e-8, with the sparse MFMA (SPARSE, see spmm_reg_split_shared: no
 // vertex keeps both k and k + 16; the weights are scattered among the 16 steps) 65 and 7.4e-8; inputs with one infinity 1.34 times
 // that, with no finite column 1.49 times (dense, a lane adding its sums up one by one: 3.7 and 11 times).
-template <int KS, bool SPARSE>
-__global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
-  constexpr int CW = 128, IT = KS / 8;
-  __shared__ __attribute__((aligned(16))) u32x4 parts[2][2][4][3][64];
+// What bounds it: a stage's chain (split, LDS, barrier, LDS, 24 products of two accumulators each) with 1.5 waves a SIMD, 128 columns:
+// 64 columns a workgroup need half of the registers and 37 KB of LDS, three run on a CU: 65 -> 56 us.  Tried there: two stages of
+// loads in flight 57; the next stage split beside the products of this one 63 (the loads are waited for earlier); four groups of
+// waves on few columns 24-28 (spills) against 23-25 with two.
+template <int KS, bool SPARSE, int NT, int KSP>
+__global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_mfma_split(SplitTileParams p) {
+  constexpr int CW = 32 * NT, IT = KS / 8;
+  constexpr int TU = NT / 2;                    // blocks of 16 steps that a wave splits, of one column block
+  struct Stage {                                // of the waves that take every KSP-th stage
+    u32x4 parts[2][2][NT][3][64];
+  };
   constexpr int WB = SPARSE ? 1 : 2;            // blocks of operands that hold a stage's weights
-  __shared__ __attribute__((aligned(16))) u32x4 wparts[4][3][WB][64];  // [wave][part][16 steps][operand lane]
+  __shared__ __attribute__((aligned(16))) union {
+    Stage stage[KSP];
+    float red[KSP > 1 ? KSP - 1 : 1][KSP > 1 ? NT : 1][16][4][64];   // sums of the others
+  } lds;
+  __shared__ __attribute__((aligned(16))) u32x4 wparts[4 * KSP][3][WB][64];  // [wave][part][16 steps][operand lane]
   const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), wid = wave & 3, ks = wave >> 2;
+  auto &parts = lds.stage[ks].parts;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;   // (same columns of I -> same XCD, as spmm_mfma)
   const int gz = p.a3 / 32, mt = p.a1 * gz;
   const int nt = xcd + 8 * (slot / mt);
@@ -476,10 +488,10 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
                     : ((k >> 4) * 64 + ((k >> 3) & 1) * 32 + (lane >> 3) * 4) * 8 + (k & 7);
     if constexpr (SPARSE) late[it] = k >> 4;
   }
-  halfword *const wl = reinterpret_cast<halfword *>(wparts[wid]);
+  halfword *const wl = reinterpret_cast<halfword *>(wparts[wave]);
   auto no_weights = [&]() {
 #pragma unroll
-    for (int k = 0; k < 3 * WB; ++k) wparts[wid][k / WB][k % WB][lane] = u32x4{0, 0, 0, 0};
+    for (int k = 0; k < 3 * WB; ++k) wparts[wave][k / WB][k % WB][lane] = u32x4{0, 0, 0, 0};
     __builtin_amdgcn_wave_barrier();
   };
   no_weights();
@@ -488,7 +500,7 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
 #pragma unroll
     for (int it = 0; it < IT; ++it) wl[to[it]] = halfword(late[it]);
     __builtin_amdgcn_wave_barrier();
-    const u32x4 at = wparts[wid][0][0][lane & ~3];   // (the four rows of a vertex have the same steps)
+    const u32x4 at = wparts[wave][0][0][lane & ~3];   // (the four rows of a vertex have the same steps)
 #pragma unroll
     for (int e = 0; e < 8; ++e) which |= (2 * (e & 1) + int((at[e / 2] >> (16 * (e & 1))) & 1u)) << (2 * e);
     __builtin_amdgcn_wave_barrier();
@@ -497,12 +509,14 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
   const int nstages = p.d1 * p.c2;
   const float *const wbase = p.Wp + ((int64_t(u1) * nstages) * p.a3 + ub + (lane >> 3)) * 64 + (lane & 7) * 4;
   const int row_bytes = int(p.ldI * 4);         // (32 rows and a column tile stay below 2^31 bytes: checked by the host)
-  const int voff = h * 8 * row_bytes + (32 * wid + j) * 4;
+  const int own_t = wid % NT, own_u = NT == 2 ? wid >> 1 : 0;   // the column block, and first 16 steps, that the wave splits
+  const int voff = (h * 8 + (SPARSE ? 4 : 16) * own_u) * row_bytes + (32 * own_t + j) * 4;
   auto first_row = [&](int s) {
     const int j1 = s / p.c2, v1 = j1 < 64 ? __builtin_amdgcn_readlane(adj_lo, j1) : __builtin_amdgcn_readlane(adj_hi, j1 - 64);
     return (int64_t(v1) * p.c2 + (s - j1 * p.c2)) * 32;
   };
-  float braw[2][8];
+  // sparse: row e of both halves of the stage in braw[2 e], braw[2 e + 1]; else row e of block own_u + u in braw[8 u + e]
+  float braw[8 * TU];
   f32x4 araw[IT];
   // extent: to the last column of the stage's last row (columns past it read zeros or the next row; never stored)
   auto stage_rsrc = [&](int s) {
@@ -515,31 +529,25 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     for (int it = 0; it < IT; ++it)
       araw[it] = *reinterpret_cast<const f32x4_u *>(wbase + int64_t(s) * p.a3 * 64 + 32 * it);
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        braw[u][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, voff, (16 * u + e) * row_bytes, 0));
+    for (int e = 0; e < 8 * TU; ++e)
+      braw[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, voff, (SPARSE ? 16 * (e % 2) + e / 2 : 16 * (e / 8) + e % 8) * row_bytes, 0));
   };
-  f32x16 acc[4], cor[4];
+  f32x16 acc[NT], cor[NT];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[t][i] = cor[t][i] = 0.f;
-  load_round(0);
-  for (int s = 0; s < nstages; ++s) {
-    const int buf = s & 1;
+  load_round(ks < nstages ? ks : 0);
+  for (int r = 0; r < nstages; r += KSP) {
+    const int s = r + ks, buf = (r / KSP) & 1;
+    const bool mine = KSP == 1 || s < nstages;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      Split b;
-      if constexpr (SPARSE) {                   // groups of four: the rows of steps k, k + 16, k + 1, k + 17
-        const float x[8] = {braw[0][4 * u], braw[1][4 * u], braw[0][4 * u + 1], braw[1][4 * u + 1],
-                            braw[0][4 * u + 2], braw[1][4 * u + 2], braw[0][4 * u + 3], braw[1][4 * u + 3]};
-        b = split8(x);
-      } else {
-        b = split8(braw[u]);
-      }
+    for (int u = 0; u < TU; ++u) {              // (sparse: groups of four: the rows of steps k, k + 16, k + 1, k + 17)
+      const float x[8] = {braw[8 * u], braw[8 * u + 1], braw[8 * u + 2], braw[8 * u + 3],
+                          braw[8 * u + 4], braw[8 * u + 5], braw[8 * u + 6], braw[8 * u + 7]};
+      const Split b = split8(x);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) parts[buf][u][wid][k][lane] = __builtin_bit_cast(u32x4, b.p[k]);
+      for (int k = 0; k < 3; ++k) parts[buf][own_u + u][own_t][k][lane] = __builtin_bit_cast(u32x4, b.p[k]);
     }
 #pragma unroll
     for (int it = 0; it < IT; ++it)
@@ -553,17 +561,18 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
           wl[k * 512 * WB + to[it] + 8 * (r + 1)] = halfword(part[k] >> 16);
         }
       }
-    load_round(s + 1 < nstages ? s + 1 : s);
+    load_round(s + KSP < nstages ? s + KSP : mine ? s : 0);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
+    if (!mine) break;                           // (the last round)
     if constexpr (SPARSE) {
       bf16x8 a[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wid][k][0][lane]);
+      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wave][k][0][lane]);
 #pragma unroll
-      for (int t = 0; t < 4; t += 2) {
+      for (int t = 0; t < NT; t += 2) {
         bf16x16 b[2][3];
 #pragma unroll
         for (int x = 0; x < 2; ++x)
@@ -582,9 +591,9 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     for (int u = 0; u < (SPARSE ? 0 : 2); ++u) {
       bf16x8 a[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wid][k][u % WB][lane]);
+      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wave][k][u % WB][lane]);
 #pragma unroll
-      for (int t = 0; t < 4; t += 2) {
+      for (int t = 0; t < NT; t += 2) {
         bf16x8 b[2][3];
 #pragma unroll
         for (int x = 0; x < 2; ++x)
@@ -602,10 +611,27 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
     __builtin_amdgcn_wave_barrier();            // (the next stage's weights come after these reads: one wave, in order)
   }
   // register i of block t: row 8 (i / 4) + 4 h + i % 4 of the wave's 32 (vertex ub + row / 4, row % 4), column 32 t + j
-  uint32_t again[2] = {0, 0};                   // sums that are not finite: bit 16 (t % 2) + i of word t / 2
+  uint32_t again[TU] = {};                      // sums that are not finite: bit 16 (t % 2) + i of word t / 2
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    add_up(acc[t], cor[t]);
+  for (int t = 0; t < NT; ++t) add_up(acc[t], cor[t]);
+  if constexpr (KSP > 1) {
+    __syncthreads();
+    if (ks)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) lds.red[ks - 1][t][i][wid][lane] = acc[t][i];
+    __syncthreads();
+    if (ks) return;                             // (no barrier from here on)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int k = 0; k < KSP - 1; ++k) acc[t][i] += lds.red[k][t][i][wid][lane];
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
     const bool in = n0 + 32 * t + j < p.N;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -615,45 +641,54 @@ __global__ __launch_bounds__(256, 2) void spmm_mfma_split(SplitTileParams p) {
       if (in && !finite) again[t / 2] |= 1u << (16 * (t % 2) + i);
     }
   }
-  if (!__builtin_amdgcn_ballot_w64((again[0] | again[1]) != 0)) return;   // (no barrier from here on)
-  // The sums left out, from the kept weights alone and in the order of spmm_mfma: a G_i vertex of the wave after the other,
-  // four rows x 64 columns per MFMA, the lane on the columns lane and 64 + lane.
-  for (int v = 0; v < 8; ++v) {
-    uint32_t need[2];                           // rows of the vertex that miss the lane's columns
+  uint32_t any = 0;
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < TU; ++x) any |= again[x];
+  if (!__builtin_amdgcn_ballot_w64(any != 0)) return;   // (no barrier from here on)
+  // The sums left out, from the kept weights alone and in the order of spmm_mfma: a G_i vertex of the wave after the other,
+  // four rows x 64 columns per MFMA, the lane on the columns lane (and 64 + lane).
+  for (int v = 0; v < 8; ++v) {
+    uint32_t need[TU], some = 0;                // rows of the vertex that miss the lane's columns
+#pragma unroll
+    for (int x = 0; x < TU; ++x) {
       need[x] = (uint32_t(__builtin_amdgcn_ds_bpermute(((v & 1) * 32 + j) * 4, int(again[x]))) >> (16 * h + 4 * (v >> 1))) & 15u;
-    if (!__builtin_amdgcn_ballot_w64((need[0] | need[1]) != 0)) continue;
+      some |= need[x];
+    }
+    if (!__builtin_amdgcn_ballot_w64(some != 0)) continue;
     const int ui = ub + v;
     const int ro = p.rowoff[ui * KS + lane % KS] * row_bytes;
     const float *const wv = p.Wp + ((int64_t(u1) * nstages) * p.a3 + ui) * 64 + lane;
-    float wnext, bnext[2][KS];
+    float wnext, bnext[TU][KS];
     auto load_stage = [&](int s) {
       const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
       wnext = wv[int64_t(s) * p.a3 * 64];
 #pragma unroll
       for (int b = 0; b < KS; ++b)
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < TU; ++x)
           bnext[x][b] = __uint_as_float(
               __builtin_amdgcn_raw_buffer_load_b32(rb, __builtin_amdgcn_readlane(ro, b) + (64 * x + lane) * 4, 0, 0));
     };
-    f32x4 sum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    f32x4 sum[TU];
+#pragma unroll
+    for (int x = 0; x < TU; ++x) sum[x] = f32x4{0.f, 0.f, 0.f, 0.f};
     load_stage(0);
     for (int s = 0; s < nstages; ++s) {
       const float w = wnext;
-      float b[2][KS];
+      float b[TU][KS];
 #pragma unroll
-      for (int k = 0; k < KS; ++k) b[0][k] = bnext[0][k], b[1][k] = bnext[1][k];
+      for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int x = 0; x < TU; ++x) b[x][k] = bnext[x][k];
       load_stage(s + 1 < nstages ? s + 1 : s);
       static_for<0, KS>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
 #pragma unroll
-        for (int x = 0; x < 2; ++x) sum[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(w, b[x][k], sum[x], 4, k, 0);
+        for (int x = 0; x < TU; ++x) sum[x] = __builtin_amdgcn_mfma_f32_4x4x1f32(w, b[x][k], sum[x], 4, k, 0);
       });
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < TU; ++x)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t m = ((int64_t(u1) * p.a2 + r / p.a4) * p.a3 + ui) * p.a4 + r % p.a4;
@@ -668,8 +703,17 @@ rbgp_reg_fn rbgp_reg_split_kernel(int RW, bool sparse) {
   return RW == 4 ? (sparse ? spmm_reg_split_shared<true> : spmm_reg_split_shared<false>) : RW == 1 ? spmm_reg_split : nullptr;
 }
 
-rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse) {
-  return KS == 8    ? (sparse ? spmm_mfma_split<8, true> : spmm_mfma_split<8, false>)
-         : KS == 16 ? (sparse ? spmm_mfma_split<16, true> : spmm_mfma_split<16, false>)
+namespace {
+
+template <int NT, int KSP>
+rbgp_split_tile_fn pick_split_tile(int KS, bool sparse) {
+  return KS == 8    ? (sparse ? spmm_mfma_split<8, true, NT, KSP> : spmm_mfma_split<8, false, NT, KSP>)
+         : KS == 16 ? (sparse ? spmm_mfma_split<16, true, NT, KSP> : spmm_mfma_split<16, false, NT, KSP>)
                     : nullptr;
+}
+
+}  // namespace
+
+rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse, int NT, int KSP) {
+  return NT == 4 ? pick_split_tile<4, 1>(KS, sparse) : KSP == 1 ? pick_split_tile<2, 1>(KS, sparse) : pick_split_tile<2, 2>(KS, sparse);
 }

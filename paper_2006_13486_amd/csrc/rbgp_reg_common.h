@@ -163,7 +163,7 @@ struct SplitTileParams {
   const int32_t *rowoff;   // [a_i][KS]: row of the stage of each step
   int64_t N, ldI, ldO;
   int a1, a2, a3, a4, d1, c2;
-  int ntiles;              // column tiles of 128
+  int ntiles;              // column tiles of 32 NT
 };
 }  // namespace rbgp_reg
 
@@ -205,9 +205,9 @@ rbgp_reg_fn rbgp_reg_bf16_shared_kernel(int RV, int PR);
 rbgp_reg_fn rbgp_reg_split_kernel(int RW, bool sparse);
 // fp32 kernel of workgroups that take all rows of a row of G_o (rbgp_mfma_reg_rows.hip)
 rbgp_reg_fn rbgp_reg_rows_kernel();
-// LDS family, fp32, on the bf16 matrix core: KS kept steps of 32 per stage (8 or 16; sparse: never both k and k + 16);
-// nullptr: not built
-rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse);
+// LDS family, fp32, on the bf16 matrix core: KS kept steps of 32 per stage (8 or 16; sparse: never both k and k + 16), workgroups of
+// 32 NT columns (2, 4) and 4 KSP waves (1, or 2 with NT = 2); nullptr: not built
+rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse, int NT, int KSP);
 // fp32 kernel with lo/hi pairing of the tile rows (8-row halves; tables of rbgp_reg_dual in the
 // stages / counts / members fields); nullptr when KC is not built.
 rbgp_dual_fn rbgp_reg_dual_kernel(int KC);

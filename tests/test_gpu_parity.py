@@ -1239,3 +1239,19 @@ def test_register_family_on_the_mask_with_merged_rows(idx, dtype):
     as_f32 = wl.bf16_bits_as_f32 if dtype == wl.BF16 else (lambda a: a)
     ref, den = gh.oracle_spmm(w, as_f32(vals), orc.im2col_3x3(as_f32(X)))
     assert orc.normalised_error(out, ref, den) <= gh.TOL[dtype]
+
+
+@pytest.mark.parametrize("N", [1, 63, 100, 2047, 2112, 6700])
+def test_lds_family_split_operands_by_width(N):
+    """Two groups of waves, 64 and 128 columns a workgroup, ragged last tiles; one column that is not finite stays by itself."""
+    w = wl.Workload("split_tiles", (8, 4, 32, 1), (32, 1, 32, 1), (8, 1, 8, 1), N, wl.F32, 351, 352, 353, 1.0)
+    vl, I, _, _ = gh.host_inputs(w, N)
+    I = I.copy()
+    I[7, N - 1] = np.inf
+    out, used = gh.library_spmm(w, vl, I, kernel=MFMA, ld_pad=(-N) % 4)
+    assert used == MFMA and rb.rbgp_last_kernel() == "spmm_mfma_split<8, 1>"
+    with np.errstate(invalid="ignore"):
+        ref, den = gh.oracle_spmm(w, vl, I)
+    assert np.array_equal(np.isfinite(out), np.isfinite(ref))
+    fin = np.isfinite(ref)
+    assert orc.normalised_error(out[fin], ref[fin], den[fin]) <= gh.TOL[wl.F32] / 10   # (split operands: below the fp32 forms' 1e-6)
