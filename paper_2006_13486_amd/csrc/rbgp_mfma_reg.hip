@@ -1264,13 +1264,19 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   if (!bf16 && !conv && !dual && in_order && pl.VC == 4 && pl.NSTG == 1 && m->c[2] == 4 && m->d[2] == 2 && m->c[3] == 2 && m->d[3] == 2 &&
       tab->max_stages <= 12 && 8 * groups * 32 <= 9 * rows_wg && groups <= 64 && !tune[RBGP_TUNE_ROW_GROUPS] && !tune[RBGP_TUNE_K_SPLIT] &&
       !tune[RBGP_TUNE_COLUMN_TILES] && !tune[RBGP_TUNE_REGISTER_SETS] && !tune[RBGP_TUNE_SPLIT_OPERANDS]) {
-    const int64_t tiles = (N + 63) / 64, all = tiles * (pl.TR / pl.fold);
-    const int64_t wgs = tiles >= 8 ? 8 * ((tiles + 7) / 8) * (pl.TR / pl.fold) : all;
-    const size_t bytes = size_t(tab->max_stages) * 12288 + size_t(groups) * 512;
-    const bool uneven = tab->max_stages <= 2 && (all > 256 ? tiles < 24 : tiles > 16 && tiles <= 20);
+    const int64_t rows_o = pl.TR / pl.fold, tiles64 = (N + 63) / 64, tiles96 = (N + 95) / 96, all = tiles64 * rows_o;
+    auto launched = [&](int64_t tiles) { return rows_o * (tiles >= 8 ? 8 * ((tiles + 7) / 8) : tiles); };
+    // 96 columns where 64 give some CUs a second workgroup and 96 none (us, 64 columns -> 96: layers 5-7 at 1/4, 296 workgroups
+    // 16.2 -> 13.6, 384 16.4 -> 13.8; layers 5-7 at 1/8, 296 13.5 -> 11.9; layer 9 at 1/16, 384 13.2 -> 11.6); not beyond: a
+    // workgroup of 96 takes a quarter to a third longer than one of 64 (layer 6 at 1/4: 192 workgroups of 64 10.2, 128 of 96 13.0;
+    // 512 of 64 16.7, 344 of 96 23.9).
+    const bool uneven = tab->max_stages <= 2 && (all > 256 ? tiles64 < 24 : tiles64 > 16 && tiles64 <= 20);
+    const bool wide = !uneven && tab->max_stages <= 4 && all > 256 && launched(tiles96) <= 256;
+    const int64_t tiles = wide ? tiles96 : tiles64, wgs = launched(tiles);
+    const size_t bytes = size_t(tab->max_stages) * (wide ? 18432 : 12288) + size_t(groups) * 512;
     if (all >= 160 && !uneven && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
       rp.ntiles = int(tiles);
-      rp.ncl = pl.TR / pl.fold;
+      rp.ncl = int(rows_o);
       rp.order = tiles >= 8 ? 2 : 0;
       rp.ct_cnt = tab->max_stages;
       // A wave per group while every workgroup has a CU to itself, or lists are longer than four stages (eight: LDS holds one
@@ -1278,8 +1284,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // one, 4 waves / 9: six stages, 592 workgroups 33.9 / 31.9, 1024 40.9 / 44.9, five, 296 18.3 / 19.7, 768 32.3 / 30.8);
       // else four waves, three workgroups a CU (layer 6: 4 waves / 9, 256 workgroups 14.1 / 10.4, 296 16.5 / 18.1, 768 21.4 /
       // 27.0).
-      const int waves = all <= 256 || tab->max_stages > 4 ? std::min(groups, 9) : 4;
-      reg_fn rows = rbgp_reg_rows_kernel();
+      const int waves = wide || all <= 256 || tab->max_stages > 4 ? std::min(groups, 9) : 4;
+      reg_fn rows = rbgp_reg_rows_kernel(wide ? 3 : 2);
       if (bytes > 64 * 1024)
         RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(rows), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
       hipLaunchKernelGGL(rows, dim3(unsigned(wgs)), dim3(unsigned(64 * waves)), bytes, static_cast<hipStream_t>(stream), rp);

@@ -5,8 +5,9 @@
 // columns).  spmm_reg walks such a tile once per G_i vertex, in stages of 16 steps, each row of I loaded |G_i.U| / 2 times
 // for 9 to 12 of 16 MFMA rows: it waits for the load path.
 //
-// Here a workgroup takes all rows of a row of G_o (p.fold tile rows x G_i vertices x R) x 64 columns: every stage's 32 rows x
-// 64 columns are loaded and split once, by one wave, and stay in LDS (12 KB a stage); then every wave multiplies groups of 32 rows, whatever G_i vertices they belong to, with
+// Here a workgroup takes all rows of a row of G_o (p.fold tile rows x G_i vertices x R) x 64 or 96 columns: every stage's 32 rows
+// are loaded and split once, and stay in LDS (6 KB a stage for 32 columns); then every wave multiplies groups of 32 rows, whatever
+// G_i vertices they belong to, with
 // v_smfmac_f32_32x32x32_bf16: its index operand names the kept ones among the four columns of G_i, row by row, so that one
 // instruction serves rows of different G_i vertices and no zero of G_i is multiplied.  The packed weights are those of
 // spmm_reg, loaded four stages ahead.
@@ -16,8 +17,11 @@
 // What bounds it: a workgroup's chain of latencies (tables, rows of I, four to eight stages of six dependent products each),
 // and from a few hundred workgroups on the stores of O, 9 |G_r.U| rows for every 32 of I.  us, before -> after: VGG19 layer 6
 // at density 1/4, 2368 columns 24.3 -> 16, 8192 49 -> 30; layer 9 at 1/4, 2048 columns 44 -> 27; layer 3, 32768 columns
-// 62 -> 42; error against 64-bit sums 8.3e-8 -> 5.0e-8.
-// Tried: waves of 32 columns at four waves per SIMD (15.7 / 32 / 29 / 48), two stages of weights ahead with 14 spilled
+// 62 -> 42; error against 64-bit sums 8.3e-8 -> 5.0e-8.  96 columns, where 64 leave some CUs two workgroups and others one: the
+// products and stores of a block overlap the next one's in the other waves of the SIMD only, but a wave splits its weights once for
+// three blocks and before it waits for the rows of I (layer 6, 2368 columns 16.2 -> 13.6).
+// Tried: 32 and 128 columns a workgroup in the same manner (2368 columns, layer 6: 19 and 15.8), five and four waves of 96 columns
+// (16.9, 22.3); waves of 32 columns at four waves per SIMD (15.7 / 32 / 29 / 48), two stages of weights ahead with 14 spilled
 // registers (15.6 / 33 / 33 / 41), one edge of four (half of the weights zero; VGG19 conv5 24.9 -> 26.2), the next stage's
 // operands prepared beside the products (21 / 39 / 32 / 53).
 #include <hip/hip_runtime.h>
@@ -36,8 +40,11 @@ typedef float f32x2_s __attribute__((ext_vector_type(2)));
 
 constexpr int kAhead = 4;                       // stages of weights in flight
 
+// T = 2: 64 columns, a pair of them per lane, lists of up to twelve stages.  T = 3: 96 columns, a block of 32 at a time, lists of up
+// to four stages.
+template <int T>
 __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
-  constexpr int CW = 64;
+  constexpr int CW = 32 * T;
   // [stage][column block][part][half of the 16 steps of a lane][lane], then what every row needs (info)
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
@@ -61,7 +68,7 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   u32x4 *const parts = reinterpret_cast<u32x4 *>(lds);
   // of every row: its row of O relative to the tile row's first (-1: none), its weights relative to a stage's, the places
   // of its G_i vertex's two edges (the index operand)
-  int4 *const info = reinterpret_cast<int4 *>(lds + p.ct_cnt * 12288);
+  int4 *const info = reinterpret_cast<int4 *>(lds + p.ct_cnt * (T * 6144));
   const int per_row = p.a3 * p.R, rows = p.fold * per_row, groups = (rows + 31) >> 5;
   const int row_bytes = int(p.row_bytes);
   const __amdgpu_buffer_rsrc_t rw =
@@ -100,6 +107,103 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     const int e0 = in ? p.rowtab[ui * p.no4] >> 1 : 0, e1 = in ? p.rowtab[ui * p.no4 + 2] >> 1 : 0;
     info[x] = int4{in ? f * p.tm + ui * p.a4 + (i / p.a4) * p.a3 * p.a4 + i % p.a4 : -1, a_of(x), (e0 | e1 << 2) * 0x1111, 0};
   }
+  auto keep = [&](const float (&x)[16], int block) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const float y[8] = {x[8 * half], x[8 * half + 1], x[8 * half + 2], x[8 * half + 3],
+                          x[8 * half + 4], x[8 * half + 5], x[8 * half + 6], x[8 * half + 7]};
+      const Split b = split8(y);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) parts[((block * 3 + k) * 2 + half) * 64 + lane] = __builtin_bit_cast(u32x4, b.p[k]);
+    }
+  };
+  auto weights = [&](const A &a) {
+    const float w[8] = {a.x[0][0], a.x[1][0], a.x[0][1], a.x[1][1], a.x[0][2], a.x[1][2], a.x[0][3], a.x[1][3]};
+    return split8(w);
+  };
+  // sums of a column block (f32x16 pair) with one stage's weights
+  auto multiply = [&](const Split &a, int block, int which, f32x16 &acc, f32x16 &cor) {
+    constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
+    bf16x16 b[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b[k] = joined(parts[((block * 3 + k) * 2) * 64 + lane], parts[((block * 3 + k) * 2 + 1) * 64 + lane]);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      f32x16 &c = k == 0 ? acc : cor;
+      c = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a.p[pa[k]], b[pb[k]], c, which, 0, 0);
+    }
+  };
+  float *const out = p.O;
+  const int64_t out_ld = p.ldO, out_n = p.N;
+  if constexpr (T == 3) {
+    // every wave splits some of the stages' column blocks, then its first group's weights
+    for (int item = wid; item < cnt * T; item += W) {
+      const int s = item / T, t = item - s * T;
+      const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+      float x[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        x[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, row_of(h, e) * row_bytes + (32 * t + j) * 4, 0, 0));
+      keep(x, item);
+    }
+    Split a[kAhead];
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) a[d] = weights(ring[d]);
+    __syncthreads();
+    for (int g = wid; g < groups; g += W) {
+      const int which = info[g * 32 + j].z;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        f32x16 acc, cor;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = cor[i] = 0.f;
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d)
+          if (d < cnt) multiply(a[d], d * T + t, which, acc, cor);
+        const int64_t n = n0 + 32 * t + j;
+        if (__builtin_amdgcn_ballot_w64(add_up(acc, cor) && n < out_n)) {   // (as below, with the one block)
+          uint64_t left = __builtin_amdgcn_ballot_w64(info[g * 32 + j].x >= 0);
+          while (left) {
+            const int pair = __builtin_amdgcn_readlane(which, __builtin_ctzll(left));
+            left &= ~__builtin_amdgcn_ballot_w64(which == pair);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) cor[i] = 0.f;
+            for (int s = 0; s < cnt; ++s) {
+              const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+              A aw;
+              load_a(aw, a_base, s);
+#pragma unroll
+              for (int w = 0; w < 4; ++w)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                  const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(
+                      rb, ((w * 4 + (pair >> (2 * e) & 3)) * 2 + h) * row_bytes + (32 * t + j) * 4, 0, 0);
+                  cor = __builtin_amdgcn_mfma_f32_32x32x2f32(aw.x[e][w], __uint_as_float(x), cor, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+              const bool mine = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].z == pair;
+              acc[i] = acc[i] * 0.f == 0.f || !mine ? acc[i] : cor[i];
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int m = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].x;
+          if (m >= 0 && n < out_n) __builtin_nontemporal_store(acc[i], out + (int64_t(u1) * p.tm + m) * out_ld + n);
+        }
+      }
+      if (g + W < groups) {
+        a_base = info[(g + W) * 32 + j].y + h * 256;
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) load_a(ring[d], d < cnt ? a_base : kOob, d < cnt ? d : 0);
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) a[d] = weights(ring[d]);
+      }
+    }
+    return;
+  }
   // every wave splits the rows of some stages
   for (int s = wid; s < cnt; s += W) {
     const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
@@ -111,20 +215,10 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
       x[1][e] = __uint_as_float(v[1]);
     }
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const float y[8] = {x[t][8 * half], x[t][8 * half + 1], x[t][8 * half + 2], x[t][8 * half + 3],
-                            x[t][8 * half + 4], x[t][8 * half + 5], x[t][8 * half + 6], x[t][8 * half + 7]};
-        const Split b = split8(y);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) parts[(((s * 2 + t) * 3 + k) * 2 + half) * 64 + lane] = __builtin_bit_cast(u32x4, b.p[k]);
-      }
+    for (int t = 0; t < 2; ++t) keep(x[t], s * 2 + t);
   }
   __syncthreads();
 
-  float *const out = p.O;
-  const int64_t out_ld = p.ldO, out_n = p.N;
   const bool vec_ok = (out_ld % 2 == 0) && (reinterpret_cast<uintptr_t>(out) % 8 == 0) && n0 + 2 * j + 2 <= out_n;
   for (int g = wid; g < groups; g += W) {
     const int which = info[g * 32 + j].z, base = a_base;
@@ -139,24 +233,11 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
       for (int d = 0; d < kAhead; ++d) {
         const int s = s0 + d;
         if (s < cnt) {
-          const float w[8] = {ring[d].x[0][0], ring[d].x[1][0], ring[d].x[0][1], ring[d].x[1][1],
-                              ring[d].x[0][2], ring[d].x[1][2], ring[d].x[0][3], ring[d].x[1][3]};
-          const Split a = split8(w);
+          const Split a = weights(ring[d]);
           const bool more = s + kAhead < cnt;
           load_a(ring[d], more ? base : a_base, more ? s + kAhead : d);
-          constexpr int pa[6] = {0, 0, 1, 1, 0, 2}, pb[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            bf16x16 b[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-              b[k] = joined(parts[(((s * 2 + t) * 3 + k) * 2) * 64 + lane], parts[(((s * 2 + t) * 3 + k) * 2 + 1) * 64 + lane]);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-              f32x16 &c = k == 0 ? acc[t] : cor[t];
-              c = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a.p[pa[k]], b[pb[k]], c, which, 0, 0);
-            }
-          }
+          for (int t = 0; t < 2; ++t) multiply(a, s * 2 + t, which, acc[t], cor[t]);
         }
       }
     }
@@ -217,4 +298,4 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
 
 }  // namespace
 
-rbgp_reg_fn rbgp_reg_rows_kernel() { return spmm_reg_rows; }
+rbgp_reg_fn rbgp_reg_rows_kernel(int T) { return T == 3 ? spmm_reg_rows<3> : T == 2 ? spmm_reg_rows<2> : nullptr; }

@@ -535,6 +535,29 @@ def test_many_rows_per_tile_of_short_lists_by_batch():
             assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == taken, (rows, N)
 
 
+# lists of one, two and four stages; nine and three full groups of 32 rows, and four with 24 rows in the last
+@pytest.mark.parametrize("rows,cols,deg", [((8, 4, 8, 9), (8, 4, 4, 2), (1, 4, 2, 2)), MANY_ROWS[1],
+                                           ((4, 4, 8, 3), (8, 4, 4, 2), (4, 4, 2, 2))])
+def test_many_rows_per_tile_in_tiles_of_96_columns(rows, cols, deg):
+    """Batches that 64 columns a workgroup spread over 257 to 384 workgroups: the first and the last width, with odd leading
+    dimensions, and one column beyond; an infinity in the last column of each block of 32 and a NaN in the last column of all."""
+    w = wl.Workload("many_rows", rows, cols, deg, 333, wl.F32, 71, 72, 73, 1.0)
+    tiles = 256 // rows[0]
+    for N, pad in ((64 * tiles + 1, 0), (64 * tiles + 31, 1), (96 * tiles, 0), (96 * tiles + 1, 3)):
+        gh.check_parity(w, N=N, ld_pad=pad, expect_kernel=REG)
+        assert rb.rbgp_last_kernel() == "spmm_reg_rows"
+    N = 96 * tiles - 33
+    vl, Il, _, _ = gh.host_inputs(w, N)
+    bad, at = Il.copy(), [31, 63, 95, N - 1]
+    bad[21, at] = [np.inf, -np.inf, np.inf, np.nan]
+    run = lambda X, tune=None: gh.library_spmm(w, vl, X, tune=tune, tag="tiles of 96")[0]
+    clean, got, ref = run(Il), run(bad), run(bad, (0,) * 8 + (1,))
+    others = np.delete(np.arange(N), at)
+    assert np.array_equal(got[:, others].view(np.uint32), clean[:, others].view(np.uint32))
+    for test in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(test(got[:, at]), test(ref[:, at]))
+
+
 @pytest.mark.parametrize("rows,cols,deg", MANY_ROWS[:2])
 def test_many_rows_per_tile_infinities_of_columns_a_row_does_not_keep(rows, cols, deg):
     """Two rows of one stage of I that are not finite in the same column: a row that keeps one of them has the sum of its own kept
