@@ -450,9 +450,12 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // vertex keeps both k and k + 16; the weights are scattered among the 16 steps) 65 and 7.4e-8; inputs with one infinity 1.34 times
 // that, with no finite column 1.49 times (dense, a lane adding its sums up one by one: 3.7 and 11 times).
 // What bounds it: a stage's chain (split, LDS, barrier, LDS, 24 products of two accumulators each) with 1.5 waves a SIMD, 128 columns:
-// 64 columns a workgroup need half of the registers and 37 KB of LDS, three run on a CU: 65 -> 56 us.  Tried there: two stages of
+// 64 columns a workgroup need half of the registers and 37 KB of LDS, three run on a CU: 65 -> 56 us.  Vector instructions (half of them splits) and products, one after the other on a SIMD, are
+// then nine tenths of a CU's time.  The rows of a wave's weights in different banks (row_to; a scattered write met four others):
+// bank conflicts 7.1 M -> 2.4 M cycles, 57.5 -> 55 us, one column 24 -> 22.7.  Tried there: two stages of
 // loads in flight 57; the next stage split beside the products of this one 63 (the loads are waited for earlier); four groups of
-// waves on few columns 24-28 (spills) against 23-25 with two.
+// waves on few columns 24-28 (spills) against 23-25 with two; weights through LDS as loaded, split in operand layout with their zeros
+// (fewer LDS instructions, a quarter more vector ones) 59.
 template <int KS, bool SPARSE, int NT, int KSP>
 __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_mfma_split(SplitTileParams p) {
   constexpr int CW = 32 * NT, IT = KS / 8;
@@ -483,12 +486,16 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int k = p.rowoff[(ub + (lane >> 3)) * KS + (lane & 7) + 8 * it];
-    // in halfwords; + 8 per row.  Sparse: step k or k + 16 is place k % 4 + 4 (k / 8) of operand half k / 4 % 2
-    to[it] = SPARSE ? (((k >> 2) & 1) * 32 + (lane >> 3) * 4) * 8 + (k & 3) + ((k >> 1) & 4)
-                    : ((k >> 4) * 64 + ((k >> 3) & 1) * 32 + (lane >> 3) * 4) * 8 + (k & 7);
+    // in halfwords, row 0.  Sparse: step k or k + 16 is place k % 4 + 4 (k / 8) of operand half k / 4 % 2
+    to[it] = SPARSE ? (((k >> 2) & 1) * 8 + (lane >> 3)) * 8 + (k & 3) + ((k >> 1) & 4)
+                    : ((k >> 4) * 64 + ((k >> 3) & 1) * 8 + (lane >> 3)) * 8 + (k & 7);
     if constexpr (SPARSE) late[it] = k >> 4;
   }
   halfword *const wl = reinterpret_cast<halfword *>(wparts[wave]);
+  // Row r of vertex v, operand half x lies at piece 16 r + ((8 x + v) ^ 4 r): the 16 pieces that an instruction writes (one r) and
+  // the 16 that a quarter of a wave reads (four v, all r) are in different banks.
+  auto row_to = [&](int base, int r) { return (base ^ 32 * r) + 128 * r; };
+  const int own_w = 16 * (j & 3) + ((8 * h + (j >> 2)) ^ 4 * (j & 3));   // the lane's own piece
   auto no_weights = [&]() {
 #pragma unroll
     for (int k = 0; k < 3 * WB; ++k) wparts[wave][k / WB][k % WB][lane] = u32x4{0, 0, 0, 0};
@@ -500,7 +507,7 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
 #pragma unroll
     for (int it = 0; it < IT; ++it) wl[to[it]] = halfword(late[it]);
     __builtin_amdgcn_wave_barrier();
-    const u32x4 at = wparts[wave][0][0][lane & ~3];   // (the four rows of a vertex have the same steps)
+    const u32x4 at = wparts[wave][0][0][8 * h + (j >> 2)];   // (the four rows of a vertex have the same steps)
 #pragma unroll
     for (int e = 0; e < 8; ++e) which |= (2 * (e & 1) + int((at[e / 2] >> (16 * (e & 1))) & 1u)) << (2 * e);
     __builtin_amdgcn_wave_barrier();
@@ -557,8 +564,8 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
         split2(araw[it][r], araw[it][r + 1], part);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          wl[k * 512 * WB + to[it] + 8 * r] = halfword(part[k]);
-          wl[k * 512 * WB + to[it] + 8 * (r + 1)] = halfword(part[k] >> 16);
+          wl[k * 512 * WB + row_to(to[it], r)] = halfword(part[k]);
+          wl[k * 512 * WB + row_to(to[it], r + 1)] = halfword(part[k] >> 16);
         }
       }
     load_round(s + KSP < nstages ? s + KSP : mine ? s : 0);
@@ -570,7 +577,7 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
     if constexpr (SPARSE) {
       bf16x8 a[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wave][k][0][lane]);
+      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wave][k][0][own_w]);
 #pragma unroll
       for (int t = 0; t < NT; t += 2) {
         bf16x16 b[2][3];
@@ -591,7 +598,7 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
     for (int u = 0; u < (SPARSE ? 0 : 2); ++u) {
       bf16x8 a[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wave][k][u % WB][lane]);
+      for (int k = 0; k < 3; ++k) a[k] = __builtin_bit_cast(bf16x8, wparts[wave][k][u % WB][own_w]);
 #pragma unroll
       for (int t = 0; t < NT; t += 2) {
         bf16x8 b[2][3];
