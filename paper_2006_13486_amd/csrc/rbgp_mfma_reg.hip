@@ -585,7 +585,6 @@ struct RegState {
                                                         //   kernel arguments of the pairing kernel)
   int32_t *rowtab_bf16 = nullptr;  // bf16 kernels: [a_i][NKB*16]
   int32_t *pairs = nullptr;        // rbgp_mask::pairs
-  int32_t *rowmap = nullptr;       // RegParams::rowmap of a mask with merged G_i vertices
   uint64_t *conv_tiles = nullptr;  // conv_tile: ConvTileParams::sel, ::tiles
   bool conv_tiles_none = false;    //   G_i does not keep one of v and v + 4 everywhere: no such tables
   int32_t *rowtab_conv[2] = {nullptr, nullptr};   // fused convolution, fp32 / bf16: byte offsets for the geometry below
@@ -739,7 +738,6 @@ void rbgp_reg_release(void *state) {
   if (st->rowtab) (void)hipFree(st->rowtab);
   if (st->rowtab_bf16) (void)hipFree(st->rowtab_bf16);
   if (st->pairs) (void)hipFree(st->pairs);
-  if (st->rowmap) (void)hipFree(st->rowmap);
   if (st->conv_tiles) (void)hipFree(st->conv_tiles);
   for (int32_t *t : st->rowtab_conv)
     if (t) (void)hipFree(t);
@@ -844,6 +842,11 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       }
       ckey[0] = conv->images; ckey[1] = conv->height; ckey[2] = conv->width;
     }
+    for (int u = 0; u < a3; ++u)   // row_offset's table
+      for (int r = 0; r < 16; ++r) {
+        const int64_t row = (int64_t(r / m->a[3]) * a3 + u) * m->a[3] + r % m->a[3];   // (of tile row 0)
+        rt.push_back(r < pl.R ? int32_t(rbgp_twin_row(m, row) - u * m->a[3]) : 0);
+      }
     int rc = upload(rt, rowtab);
     if (rc) return rc;
     if (!bf16) (conv ? st->rowtab_conv_host : st->rowtab_host) = rt;
@@ -1226,17 +1229,6 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   rp.frag_bytes = bf16 ? (rbgp_bf16_blocks32(pl.KC) + (rbgp_bf16_tail16(pl.KC) ? 1 : 0)) * 4 * pl.RS * 16 : pl.NQ * 4 * pl.RS * 16;
   rp.nq = bf16 ? (pl.KCR + 31) / 32 : (pl.KCR + 15) / 16;
   for (int r = 0; r < 16; ++r) rp.rowofs[r] = (r / m->a[3]) * m->a[2] * m->a[3] + r % m->a[3];
-  if (!m->merged.empty() && !st->rowmap) {
-    std::vector<int32_t> h(size_t(m->a[2]) * 16, 0);
-    for (int u = 0; u < m->a[2]; ++u)
-      for (int r = 0; r < pl.R; ++r) {
-        const int64_t row = (int64_t(r / m->a[3]) * m->a[2] + u) * m->a[3] + r % m->a[3];   // (of tile row 0)
-        h[size_t(u) * 16 + r] = int32_t(rbgp_twin_row(m, row) - u * m->a[3]);
-      }
-    int rc = upload(h, &st->rowmap);
-    if (rc) return rc;
-  }
-  rp.rowmap = st->rowmap;
   rp.ntiles = int(ntiles);
   rp.lgS = lgS;
   const int64_t tiles_per_wg = split_rw > 1 ? 1 : share_rv ? 1 : (4 >> lgS) * CT;
@@ -1311,7 +1303,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     DualParams dq;
     dq.r = rp;
     const rbgp_reg_dual &du = m->reg_dual;
-    const int NP4 = (pl.NO + 3) / 4 * 4, n_row = m->a[2] * 4 * NP4, cmax = std::max(du.max_wave, 1);
+    const int NP4 = (pl.NO + 3) / 4 * 4, n_row = m->a[2] * (4 * NP4 + 16), cmax = std::max(du.max_wave, 1);
     dq.rt_stride = NP4;
     dq.cmax = cmax;
     dq.o_stages = n_row;
@@ -1320,9 +1312,12 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     if (!*dtab) {   // (the fused convolution's table goes with its row table when the geometry changes)
       std::vector<int32_t> h(size_t(dq.o_quads) + size_t(du.nq) * 8, 0);
       const std::vector<int32_t> &rt = conv ? st->rowtab_conv_host : st->rowtab_host;
-      for (int u = 0; u < m->a[2]; ++u)
+      for (int u = 0; u < m->a[2]; ++u) {
+        int32_t *const own = h.data() + size_t(u) * (4 * NP4 + 16);
         for (int o = 0; o < pl.NO; ++o)
-          for (int gg = 0; gg < 4; ++gg) h[(size_t(u) * 4 + gg) * NP4 + o] = rt[(size_t(u) * pl.NO + o) * 4 + gg];
+          for (int gg = 0; gg < 4; ++gg) own[gg * NP4 + o] = rt[(size_t(u) * pl.NO + o) * 4 + gg];
+        for (int r = 0; r < 16; ++r) own[4 * NP4 + r] = rt[(size_t(m->a[2]) * pl.NO) * 4 + size_t(u) * 16 + r];
+      }
       for (int wv = 0; wv < du.nq * 4; ++wv)
         for (int sg = 0; sg < cmax; ++sg)
           for (int k = 0; k < 3; ++k)

@@ -66,10 +66,10 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
   const i32x4 *stg = reinterpret_cast<const i32x4 *>(tab + dp.o_stages) + ((cl * 2 + x) * 2 + y) * cmax;
   const i32x4 entry = stg[lane < cmax ? lane : cmax - 1];
   // stage-relative row of I of contraction step 4 * o + g, for this lane's g
+  constexpr int NP = (NO + 3) / 4;
   int rrow[NO];
   {
-    constexpr int NP = (NO + 3) / 4;
-    const i32x4 *rt = reinterpret_cast<const i32x4 *>(tab) + (u3 * 4 + g) * NP;
+    const i32x4 *rt = reinterpret_cast<const i32x4 *>(tab) + u3 * (4 * NP + 4) + g * NP;
     i32x4 piece[NP];
 #pragma unroll
     for (int k = 0; k < NP; ++k) piece[k] = rt[k];
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
   const int rowH = __builtin_amdgcn_readfirstlane(y ? quad_rows[3] : quad_rows[2]);
   const int cnt = __builtin_amdgcn_readfirstlane(quad_counts[x * 2 + y]);   // stages of this wave
   const int tb = lane < cnt ? entry[0] : -1, tflo = lane < cnt ? entry[1] : -1, tfhi = lane < cnt ? entry[2] : -1;
-  const int rov = row_offset(p, u3, lane & 15);   // lane-held copy, read back with bpermute in the epilogue
+  const int rov = tab[(u3 * (4 * NP + 4) + 4 * NP) * 4 + (lane & 15)];   // lane-held copy, read back with bpermute in the epilogue
   auto table_lane = [&](int s) { return s < 63 ? s : 63; };   // lanes past the count hold sentinels
 
   // byte offset of this lane's 16 bytes in every slot, relative to the stage base

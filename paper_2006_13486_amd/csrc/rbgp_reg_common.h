@@ -37,7 +37,7 @@ struct RegParams {
   const float *I;          // activations (same)
   float *O;                // fp32, or bf16 bits when obf16 is set (ldO counts elements of that type)
   int obf16;               // bf16 kernels: round the sums to bf16 when storing O
-  const int32_t *rowtab;   // [a_i][NO*4]: stage-relative I row of each contraction step (padding -> 0)
+  const int32_t *rowtab;   // [a_i][NO*4]: stage-relative I row of each contraction step (padding -> 0); row_offset's table after it
   const int32_t *stages;   // [ncl][1+MG][tstride]: per stage the base row of the stage, then per
                            //   cluster member j_o * NSTG + (stage within the tile), the position of its
                            //   weight fragment among the member's fragments; -1 past the end (sentinel
@@ -67,8 +67,7 @@ struct RegParams {
   const int32_t *pairs;    // split operands, filled masks whose kept weights share the steps of a stage two by two: [fold][2][16],
                            //   see rbgp_reg_pairs
   int fold;                // tile rows per row of G_o
-  int rowofs[16];          // output row of weight row r of a group, relative to its (tile row, u_i) base
-  const int32_t *rowmap;   // [a_i][16] the same where it depends on u_i (rbgp_mask::merged), or nullptr
+  int rowofs[16];          // output row of weight row r of a group, relative to its (tile row, u_i) base (masks without merged rows)
   int tm;                  // rows of one tile row: a_r * a_i * a_b
   int ntiles;              // column tiles: ceil(N / columns per wave)
   int lgS;                 // log2 of the waves that share a column tile (split of the stage list)
@@ -123,8 +122,12 @@ __device__ __forceinline__ bool wg_coord(const RegParams &p, WgCoord *c) {
   return true;
 }
 
+// rowofs[r], or the same of G_i vertex u3 where it depends on that (rbgp_mask::merged).  Read from the row table for all masks: a
+// choice between two tables in the prologue puts a latency of the scalar loads before the first vector loads (us against rowofs alone:
+// conv5 fp32, 2048 columns, +0.46, conv3 bf16, 8192 columns, +0.18; from one table -0.07 and -0.11, one image of a VGG19 layer in bf16
+// 6.78 -> 6.55).
 __device__ __forceinline__ int row_offset(const RegParams &p, int u3, int r) {
-  return p.rowmap ? p.rowmap[u3 * 16 + r] : p.rowofs[r];
+  return p.rowtab[p.a3 * p.no4 + u3 * 16 + r];
 }
 
 __device__ __forceinline__ f32x4 load_x4(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
@@ -144,7 +147,8 @@ namespace rbgp_reg {
 // 1.6 - 2.3 us (the one copy is fetched from memory once and then shared; it is not a hot spot).
 struct DualParams {
   RegParams r;          // (rowtab / stages / counts / members are not used)
-  const int32_t *tab;   // row table [a_i][4 lane groups][rt_stride] (stage-relative row of I of step 4 * o + g at [g][o]) first
+  const int32_t *tab;   // first, for every G_i vertex: [4 lane groups][rt_stride], the stage-relative row of I of step 4 * o + g at
+                        //   [g][o], and 16 entries as row_offset gives them
   int rt_stride;        // NO rounded up to 4
   int cmax;             // stages stored per wave (>= the longest stage list)
   int o_stages;         // word offsets into tab of: stages [quad][x][y][cmax][4] (base row of I, position of L_x's
