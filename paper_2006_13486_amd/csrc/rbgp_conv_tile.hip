@@ -21,7 +21,9 @@
 // stand at the dispatch rule.  What bounds it: a chain of latencies (launch 2.5; tables 1; the channels, all of conv3's in one
 // round of loads; their first use) and then issue: 1000 vector instructions and 800 cycles of products a wave, two waves a SIMD.
 // Counters (conv3): waves wait for 44 % of their cycles (four waves 41, of a longer launch), matrix core 11 % busy, vector
-// instructions 40 % of a SIMD's cycles, bank conflicts 3400 cycles per CU (5000 without the places of place_of).
+// instructions 40 % of a SIMD's cycles, bank conflicts 3070 cycles per CU (3420 with lane j on pixel j, 36.3 -> 35.9 for the training
+// step; planes an odd number of places apart, pixels in order and a wave's tasks over eight planes 2560, but its loads are
+// then spread over more lines: 36.9).
 // Tried: fp32, operands split in three: layer 6 at 1/4, 8192 pixels 25.7 -> 29, its gradient 34.7 -> 29 (the one that gained), layer 9
 // 25 -> 51 (three times the LDS: one or two tiles at once).
 #include <hip/hip_runtime.h>
@@ -82,14 +84,16 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
   };
   const int n0 = nt * 32 * T, n_last = (n0 + 32 * T < p.n ? n0 + 32 * T : p.n) - 1;
   const int p_lo = center(n0) - p.w2 - 1, px = center(n_last) + p.w2 + 2 - p_lo;
-  // Pixel q of a plane lies in place q ^ (q / 8) % 8 of its octet: the eight pixels that a lane stores and the runs of pixels
-  // that neighbouring lanes read then fall on different banks.
+  // Pixel q of a plane lies in place q ^ (q / 16) % 8 of its octet: the eight pixels that a lane stores and the runs of pixels
+  // that neighbouring lanes read then fall on (nearly) different banks.  A 16-byte read takes the lanes 0-3, 12-15, 20-27 of a half at a
+  // time, then the others: those hold 16 pixels in a row each.
+  const int pixel = 16 * (__builtin_popcount(j >> 2) & 1) + 4 * (j >> 3) + (j & 3);   // the lane's of a column block
   const int plane8 = (px + 7) & ~7, plane = plane8 * 16;   // places, bytes
-  auto place_of = [](int q) { return q ^ ((q >> 3) & 7); };
+  auto place_of = [](int q) { return q ^ ((q >> 4) & 7); };
   int at[T];                                    // the lane's pixel of every column block, counted from p_lo
 #pragma unroll
   for (int t = 0; t < T; ++t) {
-    const int n = n0 + 32 * t + j;
+    const int n = n0 + 32 * t + pixel;
     at[t] = center(n < p.n ? n : n_last) - p_lo;
   }
   // the lane's row of a tile: G_i vertex and row of R
@@ -204,7 +208,7 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
   for (int e = 0; e < 16; ++e)
 #pragma unroll
     for (int t = 0; t < T; ++t)
-      red[((ws * kRows + wr) * 32 + 8 * (e / 4) + 4 * h + e % 4) * PX + 32 * t + j] = acc[t][e];
+      red[((ws * kRows + wr) * 32 + 8 * (e / 4) + 4 * h + e % 4) * PX + 32 * t + pixel] = acc[t][e];
   __syncthreads();
   const int es = p.obf16 ? 2 : 4;
   const bool wide = (reinterpret_cast<uintptr_t>(p.O) | uintptr_t(p.ldO * es)) % 16 == 0;
