@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <numeric>
 
 #include "rbgp_internal.h"
 
@@ -1019,9 +1020,13 @@ void rbgp_reg_plan_dual(const rbgp_mask *m, rbgp_reg_dual *out) {
 void rbgp_build_pack_perm(const rbgp_mask *m, int kernel, bool bf16, std::vector<int32_t> &perm) {
   if (kernel == RBGP_KERNEL_MFMA_REG && m->regroup && (!bf16 || m->regroup_bf16)) {   // the register layout of the regrouped mask
     rbgp_build_pack_perm(m->regroup, kernel, bf16, perm);         //   (same kept values, same canonical indices, rows apart)
-    if (!m->regroup->merged.empty())
+    if (!m->regroup->merged.empty()) {   // (own indices row by row: divisions per element made conv5's layout 4.6 ms instead of 1.7)
+      std::vector<int32_t> own(size_t(m->nnz));
+      for (int64_t r = 0; r < m->M; ++r)
+        std::iota(own.begin() + r * m->rowdeg, own.begin() + (r + 1) * m->rowdeg, int32_t(rbgp_twin_row(m->regroup, r) * m->rowdeg));
       for (int32_t &s : perm)
-        if (s >= 0) s = int32_t(rbgp_twin_row(m->regroup, s / m->rowdeg) * m->rowdeg + s % m->rowdeg);
+        if (s >= 0) s = own[size_t(s)];
+    }
     return;
   }
   if (kernel == RBGP_KERNEL_MFMA_REG_FILLED) {
