@@ -1278,3 +1278,22 @@ def test_lds_family_split_operands_by_width(N):
     assert np.array_equal(np.isfinite(out), np.isfinite(ref))
     fin = np.isfinite(ref)
     assert orc.normalised_error(out[fin], ref[fin], den[fin]) <= gh.TOL[wl.F32] / 10   # (split operands: below the fp32 forms' 1e-6)
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("side", [7, 64, 724, 725])
+def test_pack_writes_the_layout(side, shift, dtype):
+    """One element a thread and four (from 524 288 on, aligned buffers only), with a remainder; nothing past the packed weights."""
+    import torch
+    mask = rb.rbgp_make_mask((1, side, 1, 1), (1, side, 1, 1), (1, side, 1, 1), 371)   # nnz = side * side
+    rb.rbgp_mask_set_kernel(mask, GEN)
+    layout = rb.rbgp_pack_layout(mask, dtype)
+    vals = torch.randn(side * side, device="cuda:0").to(torch.float32 if dtype == wl.F32 else torch.bfloat16)
+    out = torch.full((layout.size + 8,), 3.0, dtype=vals.dtype, device="cuda:0")
+    rb.rbgp_pack_device(mask, dtype, vals.data_ptr(), out.data_ptr() + shift * out.element_size(), 0)
+    torch.cuda.synchronize()
+    want = torch.where(torch.from_numpy(layout < 0), 0.0, vals.float().cpu()[torch.from_numpy(np.maximum(layout, 0)).long()])
+    got = out.float().cpu()
+    assert torch.equal(got[shift:shift + layout.size], want)
+    assert (got[:shift] == 3.0).all() and (got[shift + layout.size:] == 3.0).all()
