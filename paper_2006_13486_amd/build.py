@@ -10,7 +10,7 @@ CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "librbgp.so")
 SOURCES = ["rbgp_mfma_reg_bf16_wide.hip", "rbgp_mfma_reg_bf16.hip", "rbgp_mfma_reg_bf16_lean.hip", "rbgp_mfma_reg.hip", "rbgp_host.cpp",
            "rbgp_device.hip", "rbgp_mfma_reg_dual.hip", "rbgp_mfma_reg_split.hip",
-           "rbgp_mfma_reg_bf16_shared.hip", "rbgp_mfma_reg_rows.hip", "rbgp_conv_tile.hip", "rbgp_sddmm.hip", "rbgp_sddmm_lines.hip", "rbgp_mfma_tile.hip"]
+           "rbgp_mfma_reg_bf16_shared.hip", "rbgp_mfma_reg_rows.hip", "rbgp_mfma_reg_narrow.hip", "rbgp_conv_tile.hip", "rbgp_sddmm.hip", "rbgp_sddmm_lines.hip", "rbgp_mfma_tile.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=default",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

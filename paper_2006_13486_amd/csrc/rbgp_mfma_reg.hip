@@ -1286,6 +1286,26 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       return RBGP_OK;
     }
   }
+  // Few columns: workgroups of 16 columns whose eight waves share a list (rbgp_mfma_reg_narrow.hip), while each has a CU, or with stages
+  // of up to 36 steps half of one.  us, spmm_reg / this one, VGG19: layer 13 at 1/2 (32 lists of 72-step stages), 16 columns 12.3 / 5.8, 128
+  // (256 workgroups) 13.0 / 10.7, 256 13.6 / 16.7; at 1/4 10.2 / 5.2, 10.5 / 7.9, 11.0 / 11.1; at 1/16 6.1 / 3.9, 6.1 / 4.2, 6.4 / 6.6; layer
+  // 6 at 1/4 (16 lists), 64 columns 6.0 / 4.1, 256 6.1 / 4.3, 512 6.4 / 7.1; layer 9 fused at 1/4, 128 9.5 / 7.2, 256 10.0 / 9.3; transposes,
+  // stages of 18 and 32 steps: layer 13 at 1/4 (384 lists), 16 columns 5.3 / 3.9, 32 5.3 / 5.0, 64 5.3 / 7.8; layer 8 at 1/2 (144), 32
+  // 4.7 / 4.0, 64 4.7 / 5.1.
+  if (!bf16 && !dual && !split && NGf == 1 && CT == 1 && !tune[RBGP_TUNE_K_SPLIT] && !tune[RBGP_TUNE_ROW_GROUPS] &&
+      !tune[RBGP_TUNE_REGISTER_SETS] && !tune[RBGP_TUNE_COLUMN_TILES]) {
+    const int64_t tiles = (N + 15) / 16, lists = int64_t(ncl) * m->a[2];
+    reg_fn narrow = lists * tiles <= (pl.KC > 36 ? 256 : 512) ? rbgp_reg_narrow_kernel(pl.KC, pl.RS) : nullptr;
+    if (narrow) {
+      rp.ntiles = rp.ngroups = int(tiles);
+      rp.order = (m->e[2] == 1 && tiles <= 64) ? 1 : tiles >= 8 ? 2 : 0;
+      rp.per_xcd = int(rp.order == 2 ? lists * ((tiles + 7) / 8) : (lists * tiles + 7) / 8);
+      hipLaunchKernelGGL(narrow, dim3(unsigned(8 * rp.per_xcd)), dim3(512), 0, static_cast<hipStream_t>(stream), rp);
+      RBGP_HIP(hipGetLastError());
+      rbgp_set_last_kernel("spmm_reg_narrow");
+      return RBGP_OK;
+    }
+  }
   reg_fn fn = dual     ? nullptr
               : share_rv ? rbgp_reg_bf16_shared_kernel(share_rv, share_pr)
               : bf16   ? (lean ? rbgp_reg_bf16_lean_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW) : rbgp_reg_bf16_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW))

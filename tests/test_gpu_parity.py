@@ -1297,3 +1297,36 @@ def test_pack_writes_the_layout(side, shift, dtype):
     got = out.float().cpu()
     assert torch.equal(got[shift:shift + layout.size], want)
     assert (got[:shift] == 3.0).all() and (got[shift + layout.size:] == 3.0).all()
+
+
+# VGG19 layers on few columns, fp32: workgroups of 16 columns and eight waves a list (layer, log2 of 1 / density, transposed), stages of
+# 72 steps in clusters of one, two and four tile rows, of 36, of 32 and of 18
+NARROW = [(13, 1, False), (13, 2, False), (4, 4, False), (3, 4, False), (13, 1, True), (13, 2, True)]
+
+
+@pytest.mark.parametrize("N", [1, 15, 17, 64])
+@pytest.mark.parametrize("layer, density_log2, transposed", NARROW)
+def test_register_family_on_few_columns(layer, density_log2, transposed, N):
+    w = replace(wl.vgg19_sweep_workload(layer, density_log2, wl.F32), N=N)
+    vals = wl.kept_weights(w)
+    if transposed:
+        lib, f32 = gh.backward_inputs(w)
+        out, used = gh.library_spmm_transposed(w, lib[0], lib[2], ld_pad=(-N) % 4)
+        ref, den, _, _ = gh.oracle_backward(w, *f32)
+    else:
+        _, I, _, _ = gh.host_inputs(w, N)
+        out, used = gh.library_spmm(w, vals, I, kernel=REG, ld_pad=(-N) % 4 + 4)
+        ref, den = gh.oracle_spmm(w, vals, I)
+    assert used == REG
+    assert (rb.rbgp_last_kernel() == "spmm_reg_narrow") == (N <= 16 or not transposed)   # (transposes have 288 and 384 lists)
+    assert orc.normalised_error(out, ref, den) <= gh.TOL[wl.F32]
+
+
+@pytest.mark.parametrize("layer, images", [(9, 1), (9, 3), (4, 1), (13, 5)])
+def test_fused_convolution_on_few_columns(layer, images):
+    w = wl.vgg19_sweep_workload(layer, 2, wl.F32)
+    vals, X = wl.kept_weights(w), wl.conv_activations(w, images, 4, 4 if layer != 4 else 8)
+    out = gh.library_conv3x3(w, vals, X)
+    assert rb.rbgp_last_kernel() == "spmm_reg_narrow"
+    ref, den = gh.oracle_spmm(w, vals, orc.im2col_3x3(X))
+    assert orc.normalised_error(out, ref, den) <= gh.TOL[wl.F32]
