@@ -117,8 +117,8 @@ enum {
                                          rbgp_mask_reg_plan, has the tile rows of that factoring) */
   RBGP_TUNE_K_SPLIT = 5,              /* MFMA_REG: waves that share a column tile and split its
                                          nonzero tiles between them, 1, 2 or 4 (default: 1 unless N
-                                         is too small to give every SIMD a wave; fp32 on few columns, where
-                                         knobs 4 to 7 are not set: eight waves on 16 columns) */
+                                         is too small to give every SIMD a wave; on few columns, where
+                                         knobs 1 and 4 to 7 are not set: eight waves on 16 columns) */
   RBGP_TUNE_COLUMN_TILES = 6,         /* MFMA_REG fp32, stages of up to 8 contraction steps, every tile row with
                                          the same number of tiles: column tiles (64 columns each) a wave takes
                                          one after the other, 1, 2, 4 or 8 (EUNSUPPORTED where the stage lists of

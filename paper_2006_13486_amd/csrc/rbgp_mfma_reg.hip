@@ -1291,11 +1291,12 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // (256 workgroups) 13.0 / 10.7, 256 13.6 / 16.7; at 1/4 10.2 / 5.2, 10.5 / 7.9, 11.0 / 11.1; at 1/16 6.1 / 3.9, 6.1 / 4.2, 6.4 / 6.6; layer
   // 6 at 1/4 (16 lists), 64 columns 6.0 / 4.1, 256 6.1 / 4.3, 512 6.4 / 7.1; layer 9 fused at 1/4, 128 9.5 / 7.2, 256 10.0 / 9.3; transposes,
   // stages of 18 and 32 steps: layer 13 at 1/4 (384 lists), 16 columns 5.3 / 3.9, 32 5.3 / 5.0, 64 5.3 / 7.8; layer 8 at 1/2 (144), 32
-  // 4.7 / 4.0, 64 4.7 / 5.1.
-  if (!bf16 && !dual && !split && NGf == 1 && CT == 1 && !tune[RBGP_TUNE_K_SPLIT] && !tune[RBGP_TUNE_ROW_GROUPS] &&
+  // 4.7 / 4.0, 64 4.7 / 5.1.  bf16 (spmm_reg_bf16 with one row group on 64 columns): layer 13 at 1/2, 4 columns 9.9 / 4.6, 128 10.2 / 8.0; at 1/4
+  // 64 8.0 / 5.5, 128 8.2 / 6.3; layer 8 fused at 1/2, 64 8.0 / 4.0; gradients of layer 8 at 1/2, 32 columns 10.0 / 9.2 (both).
+  if ((bf16 ? G == 1 && CW == 64 && !share_rv && !tune[RBGP_TUNE_COLS_PER_WORKGROUP] : !dual && !split && NGf == 1 && CT == 1) && !tune[RBGP_TUNE_K_SPLIT] && !tune[RBGP_TUNE_ROW_GROUPS] &&
       !tune[RBGP_TUNE_REGISTER_SETS] && !tune[RBGP_TUNE_COLUMN_TILES]) {
     const int64_t tiles = (N + 15) / 16, lists = int64_t(ncl) * m->a[2];
-    reg_fn narrow = lists * tiles <= (pl.KC > 36 ? 256 : 512) ? rbgp_reg_narrow_kernel(pl.KC, pl.RS) : nullptr;
+    reg_fn narrow = lists * tiles <= (pl.KC > 36 ? 256 : 512) ? rbgp_reg_narrow_kernel(pl.KC, pl.RS, bf16) : nullptr;
     if (narrow) {
       rp.ntiles = rp.ngroups = int(tiles);
       rp.order = (m->e[2] == 1 && tiles <= 64) ? 1 : tiles >= 8 ? 2 : 0;

@@ -1299,34 +1299,41 @@ def test_pack_writes_the_layout(side, shift, dtype):
     assert (got[:shift] == 3.0).all() and (got[shift + layout.size:] == 3.0).all()
 
 
-# VGG19 layers on few columns, fp32: workgroups of 16 columns and eight waves a list (layer, log2 of 1 / density, transposed), stages of
+# VGG19 layers on few columns: workgroups of 16 columns and eight waves a list (layer, log2 of 1 / density, transposed), stages of
 # 72 steps in clusters of one, two and four tile rows, of 36, of 32 and of 18
 NARROW = [(13, 1, False), (13, 2, False), (4, 4, False), (3, 4, False), (13, 1, True), (13, 2, True)]
 
 
 @pytest.mark.parametrize("N", [1, 15, 17, 64])
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("layer, density_log2, transposed", NARROW)
-def test_register_family_on_few_columns(layer, density_log2, transposed, N):
-    w = replace(wl.vgg19_sweep_workload(layer, density_log2, wl.F32), N=N)
-    vals = wl.kept_weights(w)
+def test_register_family_on_few_columns(layer, density_log2, transposed, dtype, N):
+    w = replace(wl.vgg19_sweep_workload(layer, density_log2, dtype), N=N)
     if transposed:
         lib, f32 = gh.backward_inputs(w)
-        out, used = gh.library_spmm_transposed(w, lib[0], lib[2], ld_pad=(-N) % 4)
+        out, used = gh.library_spmm_transposed(w, lib[0], lib[2], ld_pad=(-N) % 8)
         ref, den, _, _ = gh.oracle_backward(w, *f32)
     else:
-        _, I, _, _ = gh.host_inputs(w, N)
-        out, used = gh.library_spmm(w, vals, I, kernel=REG, ld_pad=(-N) % 4 + 4)
-        ref, den = gh.oracle_spmm(w, vals, I)
+        vl, I, vals_f, I_f = gh.host_inputs(w, N)
+        out, used = gh.library_spmm(w, vl, I, kernel=REG, ld_pad=(-N) % 8 + 8)
+        ref, den = gh.oracle_spmm(w, vals_f, I_f)
     assert used == REG
-    assert (rb.rbgp_last_kernel() == "spmm_reg_narrow") == (N <= 16 or not transposed)   # (transposes have 288 and 384 lists)
-    assert orc.normalised_error(out, ref, den) <= gh.TOL[wl.F32]
+    if dtype == wl.F32:   # (transposes have 288 and 384 lists; the bf16 kernels take 128 columns a wave or share them first)
+        assert (rb.rbgp_last_kernel() == "spmm_reg_narrow") == (N <= 16 or not transposed)
+    elif not transposed:
+        assert rb.rbgp_last_kernel() == "spmm_reg_narrow"
+    assert orc.normalised_error(out, ref, den) <= gh.TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("layer, images", [(9, 1), (9, 3), (4, 1), (13, 5)])
-def test_fused_convolution_on_few_columns(layer, images):
-    w = wl.vgg19_sweep_workload(layer, 2, wl.F32)
+def test_fused_convolution_on_few_columns(layer, images, dtype):
+    w = wl.vgg19_sweep_workload(layer, 1, dtype)
     vals, X = wl.kept_weights(w), wl.conv_activations(w, images, 4, 4 if layer != 4 else 8)
+    as_f32 = wl.bf16_bits_as_f32 if dtype == wl.BF16 else (lambda a: a)
+    if dtype == wl.BF16:
+        vals, X = wl.to_bf16_bits(vals), wl.to_bf16_bits(X)
     out = gh.library_conv3x3(w, vals, X)
     assert rb.rbgp_last_kernel() == "spmm_reg_narrow"
-    ref, den = gh.oracle_spmm(w, vals, orc.im2col_3x3(X))
-    assert orc.normalised_error(out, ref, den) <= gh.TOL[wl.F32]
+    ref, den = gh.oracle_spmm(w, as_f32(vals), orc.im2col_3x3(as_f32(X)))
+    assert orc.normalised_error(out, ref, den) <= gh.TOL[dtype]
