@@ -997,8 +997,11 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const int tp = tune[RBGP_TUNE_ROW_PAIRING];
     if (tp < 0 || tp > 2) return RBGP_EUNSUPPORTED;
     const bool can = !bf16 && !taps && m->reg_dual.ok && rbgp_reg_dual_kernel(pl.KC) && !tune[RBGP_TUNE_K_SPLIT];
-    if (tp == 2 && !can) return RBGP_EUNSUPPORTED;
-    dual = can && (tp == 2 || (tp == 0 && lgS == 0 && m->reg_dual.max_stages < m->reg_clusters.max_stages));
+    // (merged rows: the caller's mask repeats its rows too few times for pairs, and its knobs count as on that mask)
+    const bool merged = !m->merged.empty();
+    if (tp == 2 && (!can || merged)) return RBGP_EUNSUPPORTED;
+    dual = can && (tp == 2 || (tp == 0 && lgS == 0 && m->reg_dual.max_stages < m->reg_clusters.max_stages &&
+                               !(merged && tune[RBGP_TUNE_REGISTER_SETS])));
   }
   if (dual) lgS = 1;   // (two column tiles per workgroup, as with a stage list split in two)
   RegTables *tab = bf16 ? &st->tab_bf16[G == 4 ? 2 : G == 2 ? 1 : 0] : &st->tab;

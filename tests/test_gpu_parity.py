@@ -1264,6 +1264,21 @@ def test_register_family_on_the_mask_with_merged_rows(idx, dtype):
     assert orc.normalised_error(out, ref, den) <= gh.TOL[dtype]
 
 
+@pytest.mark.parametrize("tune,N", [((0,) * 7 + (1,), 4104), ((0,) * 7 + (1,), 64), ((0,) * 7 + (2,), 4104)])
+def test_merged_rows_take_the_knobs_of_the_mask_as_given(tune, N):
+    """fp32 with four rows per column set: RBGP_TUNE_REGISTER_SETS where the default pairs the merged tile rows, and no
+    RBGP_TUNE_ROW_PAIRING = 2, which masks of such rows refuse."""
+    rows, cols, deg, *_ = MERGED_ROW_SHAPES[0]
+    w = wl.Workload("merged_knobs", rows, cols, deg, N, wl.F32, 310, 320, 330, 1.0)
+    gh.check_parity(w, kernel=REG, expect_kernel=REG)
+    assert rb.rbgp_last_kernel() == ("spmm_reg_dual" if N > 64 else "spmm_reg_narrow")
+    gh.check_parity(w, kernel=REG, tune=tune, expect_kernel=REG)
+    assert rb.rbgp_last_kernel() == "spmm_reg"
+    with pytest.raises(rb.RbgpError) as e:
+        gh.check_parity(w, kernel=REG, tune=(0, 0, 0, 2))
+    assert e.value.code == rb.EUNSUPPORTED
+
+
 @pytest.mark.parametrize("N", [1, 63, 100, 2047, 2112, 6700])
 def test_lds_family_split_operands_by_width(N):
     """Two groups of waves, 64 and 128 columns a workgroup, ragged last tiles; one column that is not finite stays by itself."""
