@@ -574,15 +574,13 @@ const RegEntry *find_reg(int KC, int RS) {
   return nullptr;
 }
 
-struct RegTables {  // device tables of the clustering
+struct RegTables {  // device tables of the clustering, in one allocation
   int ncl = 0, tstride = 64, max_stages = 0;
   int32_t *stages = nullptr, *counts = nullptr, *members = nullptr;
 };
 
 struct RegState {
-  int32_t *rowtab = nullptr;       // fp32 kernels: [a_i][NO*4]
-  std::vector<int32_t> rowtab_host, rowtab_conv_host;   //   host copies, plain and fused convolution (they travel in the
-                                                        //   kernel arguments of the pairing kernel)
+  int32_t *rowtab = nullptr;       // fp32 kernels: [a_i][NO*4]; the pairing kernel's table after it (dual_layout), as in rowtab_conv[0]
   int32_t *rowtab_bf16 = nullptr;  // bf16 kernels: [a_i][NKB*16]
   int32_t *pairs = nullptr;        // rbgp_mask::pairs
   uint64_t *conv_tiles = nullptr;  // conv_tile: ConvTileParams::sel, ::tiles
@@ -591,7 +589,6 @@ struct RegState {
   int32_t *colbase[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [dtype][wide tile]: pixel offsets of the column groups
   int64_t conv_key[2][3] = {{0, 0, 0}, {0, 0, 0}};  // images, height, width of rowtab_conv
   RegTables tab;                   // fp32: clusters of one 16-row group
-  int32_t *dual_tab[2] = {nullptr, nullptr};   // fp32 lo/hi pairing: the kernel's one table buffer, plain / fused convolution
   RegTables tab_bf16[3];           // bf16: clusters of 1, 2, 4 groups
   bool g2_shared = false;          // the clusters of two groups have (nearly) half the stages in total: their tile rows share their tiles
   int g2_stages = -1, g2_ncl = 0;  // longest stage list and number of the clusters of two groups (-2: too long,
@@ -686,27 +683,24 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
 
 void free_tables(RegTables *t) {
   if (t->stages) (void)hipFree(t->stages);
-  if (t->counts) (void)hipFree(t->counts);
-  if (t->members) (void)hipFree(t->members);
   *t = RegTables();
 }
 
-// Upload three tables; the state is touched only when all three are on the device.
+// The state is touched only when the tables are on the device.
 int upload_tables(const rbgp_reg_clusters &cl, RegTables *t) {
-  const int ncl = cl.ncl;
-  const std::vector<int32_t> &stages = cl.stages, &counts = cl.counts, &members = cl.members;
-  RegTables fresh;
-  fresh.ncl = ncl;
-  fresh.tstride = cl.tstride;
-  fresh.max_stages = cl.max_stages;
-  int rc = upload(stages, &fresh.stages);
-  if (!rc) rc = upload(counts, &fresh.counts);
-  if (!rc) rc = upload(members, &fresh.members);
-  if (rc) {
-    free_tables(&fresh);
-    return rc;
-  }
-  *t = fresh;
+  std::vector<int32_t> all;
+  auto append = [&](const std::vector<int32_t> &part) {
+    const size_t at = (all.size() + 63) / 64 * 64;
+    all.resize(at);
+    all.insert(all.end(), part.begin(), part.end());
+    return at;
+  };
+  append(cl.stages);
+  const size_t counts = append(cl.counts), members = append(cl.members);
+  int32_t *dev = nullptr;
+  if (const int rc = upload(all, &dev)) return rc;
+  t->ncl = cl.ncl; t->tstride = cl.tstride; t->max_stages = cl.max_stages;
+  t->stages = dev; t->counts = dev + counts; t->members = dev + members;
   return RBGP_OK;
 }
 
@@ -720,6 +714,45 @@ int build_tables(const rbgp_mask *m, int U, RegTables *t) {
   }
   if (cl->max_stages > kRegMaxStages) return RBGP_EUNSUPPORTED;   // one stage per lane plus sentinels, four waves
   return upload_tables(*cl, t);
+}
+
+// The table of the pairing kernel (DualParams::tab), in the buffer of the row table that it repeats: word offsets, and their end.
+struct DualLayout {
+  int np4, cmax, stages, quads, words;   // stages, quads: from the table's own start
+  size_t first;                          // of the table, in the buffer
+};
+DualLayout dual_layout(const rbgp_mask *m) {
+  const rbgp_reg_dual &du = m->reg_dual;
+  DualLayout l;
+  l.np4 = (m->reg.NO + 3) / 4 * 4;
+  l.cmax = std::max(du.max_wave, 1);
+  l.stages = m->a[2] * (4 * l.np4 + 16);
+  l.quads = l.stages + du.nq * 4 * l.cmax * 4;
+  l.words = l.quads + du.nq * 8;
+  l.first = (size_t(m->a[2]) * (m->reg.NO * 4 + 16) + 63) / 64 * 64;
+  return l;
+}
+// rt: the row table with row_offset's table behind it
+void append_dual_table(const rbgp_mask *m, std::vector<int32_t> &rt) {
+  const rbgp_reg_plan &pl = m->reg;
+  const rbgp_reg_dual &du = m->reg_dual;
+  const DualLayout l = dual_layout(m);
+  rt.resize(l.first + l.words, 0);
+  int32_t *const h = rt.data() + l.first;
+  for (int u = 0; u < m->a[2]; ++u) {
+    int32_t *const own = h + size_t(u) * (4 * l.np4 + 16);
+    for (int o = 0; o < pl.NO; ++o)
+      for (int gg = 0; gg < 4; ++gg) own[gg * l.np4 + o] = rt[(size_t(u) * pl.NO + o) * 4 + gg];
+    for (int r = 0; r < 16; ++r) own[4 * l.np4 + r] = rt[(size_t(m->a[2]) * pl.NO) * 4 + size_t(u) * 16 + r];
+  }
+  for (int wv = 0; wv < du.nq * 4; ++wv)
+    for (int sg = 0; sg < l.cmax; ++sg)
+      for (int k = 0; k < 3; ++k) h[size_t(l.stages) + (size_t(wv) * l.cmax + sg) * 4 + k] = du.stages[(size_t(wv) * 3 + k) * 64 + sg];
+  for (int q = 0; q < du.nq; ++q)
+    for (int k = 0; k < 4; ++k) {
+      h[size_t(l.quads) + size_t(q) * 8 + k] = du.members[size_t(q) * 4 + k];
+      h[size_t(l.quads) + size_t(q) * 8 + 4 + k] = du.counts[size_t(q) * 4 + k];
+    }
 }
 
 }  // namespace
@@ -745,8 +778,6 @@ void rbgp_reg_release(void *state) {
     for (int32_t *t : pair)
       if (t) (void)hipFree(t);
   free_tables(&st->tab);
-  for (int32_t *t : st->dual_tab)
-    if (t) (void)hipFree(t);
   for (RegTables &t : st->tab_bf16) free_tables(&t);
   delete st;
 }
@@ -816,10 +847,6 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   if (conv && *rowtab && (ckey[0] != conv->images || ckey[1] != conv->height || ckey[2] != conv->width)) {
     (void)hipFree(*rowtab);   // (waits for launches that still read the old table)
     *rowtab = nullptr;
-    if (!bf16 && st->dual_tab[1]) {
-      (void)hipFree(st->dual_tab[1]);
-      st->dual_tab[1] = nullptr;
-    }
     for (int32_t *&t : st->colbase[bf16]) {
       if (t) (void)hipFree(t);
       t = nullptr;
@@ -847,9 +874,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         const int64_t row = (int64_t(r / m->a[3]) * a3 + u) * m->a[3] + r % m->a[3];   // (of tile row 0)
         rt.push_back(r < pl.R ? int32_t(rbgp_twin_row(m, row) - u * m->a[3]) : 0);
       }
+    if (!bf16 && m->reg_dual.ok && rbgp_reg_dual_kernel(pl.KC)) append_dual_table(m, rt);
     int rc = upload(rt, rowtab);
     if (rc) return rc;
-    if (!bf16) (conv ? st->rowtab_conv_host : st->rowtab_host) = rt;
   }
   int64_t ntiles = (N + CW - 1) / CW;
   // bf16: 16-row groups per wave (G) and waves per column tile (S).  More groups mean fewer
@@ -857,6 +884,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // the two balance out, so the default is one group unless the rule below finds two worth it.
   // The stage list is split when there are fewer (cluster, G_i vertex, column tile) triples than SIMDs.
   int G = 1, lgS = 0;
+  bool two_groups = false, four_groups = false;   // a batch of another size may take them
   {
     const int tg = bf16 ? tune[RBGP_TUNE_ROW_GROUPS] : 0, ts = tune[RBGP_TUNE_K_SPLIT];
     if (tg) {
@@ -878,7 +906,16 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         st->g2_stages = (c2.max_stages > kRegMaxStages || m->reg_clusters.U != pl.MG || 5 * total2 > 4 * total1) ? -2 : c2.max_stages;
         st->g2_ncl = c2.ncl;
         st->g2_shared = 20 * total2 <= 11 * total1;
+        if (st->g2_stages > 0 && !st->tab_bf16[1].stages) {
+          int rc = upload_tables(c2, &st->tab_bf16[1]);
+          if (rc) {
+            st->g2_stages = -1;
+            return rc;
+          }
+        }
       }
+      two_groups = st->g2_stages > 0;
+      four_groups = two_groups && st->g2_shared && pl.MG == 1 && pl.fold % 4 == 0 && pl.KC <= 36 && st->g2_stages >= 32;
       if (st->g2_stages > 0) {
         const int64_t waves2 = int64_t(st->g2_ncl) * m->a[2] * ntiles;
         int S2 = 1;
@@ -895,7 +932,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         // filled masks of Tables 2-3): four groups per wave, where the chip stays full and the accumulators fit without
         // spilling (stages of up to 36 steps).  4096^3 with one row per column set: 182 / 122 / 111 us with 1 / 2 / 4 groups.
         // (stage lists of 16: 53.9 us against 51.1 with two groups -- long lists only)
-        if (G == 2 && st->g2_shared && pl.MG == 1 && pl.fold % 4 == 0 && pl.KC <= 36 && st->g2_stages >= 32) {
+        if (G == 2 && four_groups) {
           const int64_t waves4 = int64_t(pl.TR / 4) * m->a[2] * ntiles;
           int S4 = 1;
           while (S4 < 4 && (waves4 * S4 < 1024 || st->g2_stages > kRegWaveStages * S4)) S4 *= 2;
@@ -1004,11 +1041,14 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
                                !(merged && tune[RBGP_TUNE_REGISTER_SETS])));
   }
   if (dual) lgS = 1;   // (two column tiles per workgroup, as with a stage list split in two)
+  // The first call makes the tables of every kernel that a batch of another size takes (it may come under capture): fp32 those of
+  // the clusters also where tile rows are paired, bf16 those of one group and of the larger clusters (two groups: above).
   RegTables *tab = bf16 ? &st->tab_bf16[G == 4 ? 2 : G == 2 ? 1 : 0] : &st->tab;
-  if (!dual && !tab->stages) {
-    int rc = build_tables(m, G * pl.MG, tab);
-    if (rc) return rc;
-  }
+  auto make_tables = [&](int groups, RegTables *t) { return t->stages ? RBGP_OK : build_tables(m, groups * pl.MG, t); };
+  int rc_tables = make_tables(G, tab);
+  if (!rc_tables && two_groups) rc_tables = make_tables(1, &st->tab_bf16[0]);
+  if (!rc_tables && four_groups) rc_tables = make_tables(4, &st->tab_bf16[2]);
+  if (rc_tables) return rc_tables;
   if (!dual) {
     // a stage list longer than a wave's table is split over enough waves of the workgroup
     int need = 0;
@@ -1326,35 +1366,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   if (dual) {
     DualParams dq;
     dq.r = rp;
-    const rbgp_reg_dual &du = m->reg_dual;
-    const int NP4 = (pl.NO + 3) / 4 * 4, n_row = m->a[2] * (4 * NP4 + 16), cmax = std::max(du.max_wave, 1);
-    dq.rt_stride = NP4;
-    dq.cmax = cmax;
-    dq.o_stages = n_row;
-    dq.o_quads = dq.o_stages + du.nq * 4 * cmax * 4;
-    int32_t **dtab = &st->dual_tab[conv ? 1 : 0];
-    if (!*dtab) {   // (the fused convolution's table goes with its row table when the geometry changes)
-      std::vector<int32_t> h(size_t(dq.o_quads) + size_t(du.nq) * 8, 0);
-      const std::vector<int32_t> &rt = conv ? st->rowtab_conv_host : st->rowtab_host;
-      for (int u = 0; u < m->a[2]; ++u) {
-        int32_t *const own = h.data() + size_t(u) * (4 * NP4 + 16);
-        for (int o = 0; o < pl.NO; ++o)
-          for (int gg = 0; gg < 4; ++gg) own[gg * NP4 + o] = rt[(size_t(u) * pl.NO + o) * 4 + gg];
-        for (int r = 0; r < 16; ++r) own[4 * NP4 + r] = rt[(size_t(m->a[2]) * pl.NO) * 4 + size_t(u) * 16 + r];
-      }
-      for (int wv = 0; wv < du.nq * 4; ++wv)
-        for (int sg = 0; sg < cmax; ++sg)
-          for (int k = 0; k < 3; ++k)
-            h[size_t(dq.o_stages) + (size_t(wv) * cmax + sg) * 4 + k] = du.stages[(size_t(wv) * 3 + k) * 64 + sg];
-      for (int q = 0; q < du.nq; ++q)
-        for (int k = 0; k < 4; ++k) {
-          h[size_t(dq.o_quads) + size_t(q) * 8 + k] = du.members[size_t(q) * 4 + k];
-          h[size_t(dq.o_quads) + size_t(q) * 8 + 4 + k] = du.counts[size_t(q) * 4 + k];
-        }
-      int rc = upload(h, dtab);
-      if (rc) return rc;
-    }
-    dq.tab = *dtab;
+    const DualLayout l = dual_layout(m);
+    dq.rt_stride = l.np4; dq.cmax = l.cmax; dq.o_stages = l.stages; dq.o_quads = l.quads;
+    dq.tab = *rowtab + l.first;
     rbgp_dual_fn dfn = rbgp_reg_dual_kernel(pl.KC);
     hipLaunchKernelGGL(dfn, dim3(unsigned(8 * per_xcd)), dim3(512), lds, static_cast<hipStream_t>(stream), dq);
   } else {

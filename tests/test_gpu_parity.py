@@ -1279,6 +1279,50 @@ def test_merged_rows_take_the_knobs_of_the_mask_as_given(tune, N):
     assert e.value.code == rb.EUNSUPPORTED
 
 
+# (mask, element type, columns of the eager call, of the captured one): merged rows; tile rows paired without them; bf16 clusters of
+# one, two and four groups of rows
+OTHER_WIDTHS = [(MERGED_ROW_SHAPES[0][:3], wl.F32, 40960, 64), (MERGED_ROW_SHAPES[0][:3], wl.F32, 64, 40960),
+                (MERGED_ROW_SHAPES[1][:3], wl.F32, 40960, 64), (MERGED_ROW_SHAPES[1][:3], wl.BF16, 40960, 64),
+                (MERGED_ROW_SHAPES[2][:3], wl.BF16, 40960, 64), (MERGED_ROW_SHAPES[2][:3], wl.BF16, 64, 40960),
+                (((16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 2, 9)), wl.F32, 2048, 64), (((16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 2, 9)), wl.F32, 64, 2048),
+                (((8, 4, 8, 1), (8, 4, 4, 9), (4, 4, 1, 9)), wl.BF16, 64, 40960),
+                (((32, 4, 32, 4), (16, 1, 32, 1), (8, 1, 16, 1)), wl.BF16, 64, 4096), (((32, 4, 32, 4), (16, 1, 32, 1), (8, 1, 16, 1)), wl.BF16, 4096, 64)]
+
+
+@pytest.mark.parametrize("mask_of,dtype,first,then", OTHER_WIDTHS)
+def test_register_family_on_another_batch_allocates_nothing(mask_of, dtype, first, then):
+    """An eager call, then the capture of one on another number of columns, which other kernels and clusters take: three replays
+    on fresh inputs against the eager result."""
+    import torch
+    w = wl.Workload("other_width", *mask_of, 0, dtype, 310, 320, 330, 1.0)
+    mask, ld = gh.make_mask(w), max(first, then)
+    rb.rbgp_mask_set_kernel(mask, REG)
+    t = torch.float32 if dtype == wl.F32 else torch.bfloat16
+    stream = lambda: torch.cuda.current_stream().cuda_stream
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, dtype), dtype=torch.uint8, device="cuda:0")
+    vals = wl.kept_weights(w)
+    rb.rbgp_pack(mask, dtype, wl.to_bf16_bits(vals) if dtype == wl.BF16 else vals, packed.data_ptr(), stream())
+    I, O = torch.zeros((w.K, ld), dtype=t, device="cuda:0"), torch.zeros((w.M, ld), device="cuda:0")
+    call = lambda n: rb.rbgp_spmm(mask, dtype, w.M, w.K, n, packed.data_ptr(), I.data_ptr(), ld, O.data_ptr(), ld, stream())
+    call(first)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(then)
+    for seed in (1, 2, 3):
+        I.copy_(torch.randn(I.shape, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(seed)))
+        O.fill_(float("nan"))
+        call(then)
+        torch.cuda.synchronize()
+        want = O[:, :then].clone()
+        O.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(O[:, :then], want)
+        call(first)
+
+
 @pytest.mark.parametrize("N", [1, 63, 100, 2047, 2112, 6700])
 def test_lds_family_split_operands_by_width(N):
     """Two groups of waves, 64 and 128 columns a workgroup, ragged last tiles; one column that is not finite stays by itself."""
