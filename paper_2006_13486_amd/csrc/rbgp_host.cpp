@@ -260,7 +260,7 @@ thread_local char g_hip_error[256] = "";
 
 struct LastKernel {
   const char *name = "", *then = nullptr;
-  int nargs = 0, args[5] = {};
+  int nargs = 0, args[6] = {};
 };
 thread_local LastKernel g_last_kernel;   // (put into words only when asked for: every launch writes it)
 
@@ -282,7 +282,7 @@ void rbgp_set_last_kernel(const char *name, std::initializer_list<int> args, con
   k.then = then;
   k.nargs = 0;
   for (int a : args)
-    if (k.nargs < 5) k.args[k.nargs++] = a;
+    if (k.nargs < 6) k.args[k.nargs++] = a;
 }
 
 // Decide whether the MFMA kernels cover this mask and derive their tile shape.

@@ -648,7 +648,9 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     }
   }
   if (lines && parts > 1 && !B.grow && size_t(parts) * size_t(nnz) * sizeof(float) > B.partial_bytes) lines = false;
-  if (conv && m->M * ld_dO * (bf16 ? 2 : 4) >= int64_t(1) << 32) lines = false;   // (32-bit offsets into dO)
+  // (us, sddmm_reg / 64-bit offsets, bf16, 32 x 32 images, 16 channels: 64 rows x 34000 images 3098 / 1546, 128 x 17000 2801 / 1574,
+  // 256 x 8500 1042 / 807)
+  const bool far = lines && conv && m->M * ld_dO * (bf16 ? 2 : 4) >= int64_t(1) << 32;
   int64_t blocks, chunk, nsplit;
   int halves = 1;
   sddmm_fn fn;
@@ -661,7 +663,7 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     blocks = units * RBG * halves;
     chunk = ((N + parts * kLinesWaves - 1) / (parts * kLinesWaves) + cpi - 1) / cpi * cpi;
     nsplit = (N + chunk * kLinesWaves - 1) / (chunk * kLinesWaves);      // workgroups per unit = partial sums
-    fn = rbgp_sddmm_lines_kernel(RB, NB, bf16, conv != nullptr, gi);
+    fn = rbgp_sddmm_lines_kernel(RB, NB, bf16, conv != nullptr, gi, far);
   } else {
     // ranges of the batch: enough waves for a few per SIMD (1024 SIMDs), at least two iterations each
     const int cpi = bf16 ? 32 : 16;
@@ -756,7 +758,9 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     sddmm_reduce<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
     RBGP_HIP(hipGetLastError());
   }
-  rbgp_set_last_kernel(lines ? "sddmm_lines" : "sddmm_reg", {RB, NB, bf16, conv != nullptr, gi}, nsplit > 1 ? "sddmm_reduce" : nullptr);
+  const char *then = nsplit > 1 ? "sddmm_reduce" : nullptr;
+  if (far) rbgp_set_last_kernel("sddmm_lines", {RB, NB, bf16, 1, gi, 1}, then);
+  else rbgp_set_last_kernel(lines ? "sddmm_lines" : "sddmm_reg", {RB, NB, bf16, conv != nullptr, gi}, then);
   return RBGP_OK;
 }
 

@@ -137,7 +137,7 @@ struct Operand<true> {
 
 // RB: groups of 16 rows of dO per wave; NB: groups of 16 contraction steps per wave.  WIN (CONV, NB = 3 and 6): a group is one
 // horizontal tap of 16 pixel rows (channel, dy), and the three taps of the same 16 rows (24 with NB = 6) come out of one window.
-template <int RB, int NB, bool BF16, bool CONV, bool GI>
+template <int RB, int NB, bool BF16, bool CONV, bool GI, bool FAR>
 __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   typedef Operand<BF16> Op;
   constexpr int CPL = Op::CPL, CPI = 8 * CPL;   // columns per lane load / per step: 128 bytes of a row
@@ -208,12 +208,14 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   };
   // Byte offsets of this lane's 16 bytes in step 0.  CONV: below 2 GiB (inside X) and 4 GiB (inside dO), checked by the host, and the
   // column of a step is a scalar offset of buffer loads, which costs no vector instruction (on the lowered input no gain, and spills).
+  // FAR (CONV): 64-bit offsets into a dO of 4 GiB and more.
+  typedef typename std::conditional<CONV && !FAR, uint32_t, int64_t>::type OffA;
   typedef typename std::conditional<CONV, uint32_t, int64_t>::type Off;
-  Off offA[2 * RB];
+  OffA offA[2 * RB];
 #pragma unroll
   for (int i = 0; i < 2 * RB; ++i) {
     const int64_t row = row_of(i / 2, lr + 8 * (i % 2)).row;
-    offA[i] = Off((row < 0 ? 0 : row) * p.ld_dO * ES + ls * 16);
+    offA[i] = OffA((row < 0 ? 0 : row) * p.ld_dO * ES + ls * 16);
   }
   const unsigned char *const bytesA = static_cast<const unsigned char *>(p.dO);
   const unsigned char *const bytesB = static_cast<const unsigned char *>(p.I);
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   auto pixel = [&](int64_t n) { return CONV ? p.colbase[n / CPL + ls] * ES : 0; };
   __amdgpu_buffer_rsrc_t arsrc, xrsrc;
   if constexpr (CONV) {
-    arsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.dO), 0, -1, kRsrcFlags);
+    if constexpr (!FAR) arsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.dO), 0, -1, kRsrcFlags);
     xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.I), 0, int(p.x_bytes), kRsrcFlags);
   }
 
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   auto load_all = [&](Raw &r, int64_t n, int at) {
 #pragma unroll
     for (int i = 0; i < 2 * RB; ++i) {
-      if constexpr (CONV) r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, int(offA[i]), int(uint32_t(n) * ES), 0);
+      if constexpr (CONV && !FAR) r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(arsrc, int(offA[i]), int(uint32_t(n) * ES), 0);
       else r.a[i] = *reinterpret_cast<const u32x4_u *>(bytesA + offA[i] + n * ES);
     }
 #pragma unroll
@@ -511,32 +513,33 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   }
 }
 
-template <int RB, bool BF16, bool CONV, bool GI>
+template <int RB, bool BF16, bool CONV, bool GI, bool FAR>
 rbgp_sddmm_fn pick_nb(int NB) {
   switch (NB) {
-    case 1: return sddmm_lines<RB, 1, BF16, CONV, GI>;
-    case 2: return sddmm_lines<RB, 2, BF16, CONV, GI>;
-    case 3: return sddmm_lines<RB, 3, BF16, CONV, GI>;
+    case 1: return sddmm_lines<RB, 1, BF16, CONV, GI, FAR>;
+    case 2: return sddmm_lines<RB, 2, BF16, CONV, GI, FAR>;
+    case 3: return sddmm_lines<RB, 3, BF16, CONV, GI, FAR>;
   }
   if constexpr (BF16) {
-    if (CONV && (NB == 4 || NB == 5)) return sddmm_lines<RB, 6, true, true, GI>;   // (24 pixel rows)
+    if (CONV && (NB == 4 || NB == 5)) return sddmm_lines<RB, 6, true, true, GI, FAR>;   // (24 pixel rows)
     if constexpr (!CONV) {
-      if (NB == 4) return sddmm_lines<RB, 4, true, false, GI>;
-      if (NB == 5) return sddmm_lines<RB, 5, true, false, GI>;
+      if (NB == 4) return sddmm_lines<RB, 4, true, false, GI, false>;
+      if (NB == 5) return sddmm_lines<RB, 5, true, false, GI, false>;
     }
   }
   return nullptr;
 }
-template <bool CONV, bool GI>
+template <bool CONV, bool GI, bool FAR>
 rbgp_sddmm_fn find(int RB, int NB, bool bf16) {
-  if (RB == 1) return bf16 ? pick_nb<1, true, CONV, GI>(NB) : pick_nb<1, false, CONV, GI>(NB);
-  if (RB == 2) return bf16 ? pick_nb<2, true, CONV, GI>(NB) : pick_nb<2, false, CONV, GI>(NB);
+  if (RB == 1) return bf16 ? pick_nb<1, true, CONV, GI, FAR>(NB) : pick_nb<1, false, CONV, GI, FAR>(NB);
+  if (RB == 2) return bf16 ? pick_nb<2, true, CONV, GI, FAR>(NB) : pick_nb<2, false, CONV, GI, FAR>(NB);
   return nullptr;
 }
 
 }  // namespace
 
-rbgp_sddmm_fn rbgp_sddmm_lines_kernel(int RB, int NB, bool bf16, bool conv, bool gi) {
-  return conv ? (gi ? find<true, true>(RB, NB, bf16) : find<true, false>(RB, NB, bf16))
-              : (gi ? find<false, true>(RB, NB, bf16) : find<false, false>(RB, NB, bf16));
+rbgp_sddmm_fn rbgp_sddmm_lines_kernel(int RB, int NB, bool bf16, bool conv, bool gi, bool far) {
+  if (conv && far) return gi ? find<true, true, true>(RB, NB, bf16) : find<true, false, true>(RB, NB, bf16);
+  return conv ? (gi ? find<true, true, false>(RB, NB, bf16) : find<true, false, false>(RB, NB, bf16))
+              : (gi ? find<false, true, false>(RB, NB, bf16) : find<false, false, false>(RB, NB, bf16));
 }

@@ -278,6 +278,34 @@ def test_weight_gradient_of_a_convolution_in_parts_of_the_batch(mask, images, ke
     assert (np.abs(got[fin] - ref[fin]) <= 4e-6 * size[fin]).all()   # (as test_weight_gradient_whole_lines: chains are no longer)
 
 
+@pytest.mark.parametrize("dtype,images", [(wl.BF16, 32771), (wl.F32, 16387)])
+@pytest.mark.parametrize("mask", [((8, 2, 4, 1), (2, 2, 4, 9), (2, 2, 2, 9)), ((8, 2, 4, 1), (4, 1, 4, 9), (2, 1, 4, 9))])
+def test_weight_gradient_of_a_convolution_with_gradients_beyond_4_gib(mask, dtype, images):
+    """Rows of dO past 4 GiB: gradients in some columns at both ends and between, zeros elsewhere."""
+    import torch
+    w = wl.Workload("far", *mask, 0, dtype, 107, 108, 109, 1.0)
+    t, side, C = torch.float32 if dtype == wl.F32 else torch.bfloat16, 32, w.K // 9
+    N = images * side * side
+    g = torch.Generator(device="cuda:0").manual_seed(1)
+    X = torch.zeros((C, images, side + 2, side + 2), dtype=t, device="cuda:0")
+    X[:, :, 1:-1, 1:-1] = torch.randn((C, images, side, side), generator=g, device="cuda:0").to(t)
+    dO = torch.zeros((w.M, N), dtype=t, device="cuda:0")
+    assert dO.numel() * dO.element_size() > 2 ** 32 and X.numel() * X.element_size() < 2 ** 31
+    at = torch.cat([torch.arange(70), torch.randint(70, N - 70, (400,), generator=torch.Generator().manual_seed(2)).unique(), torch.arange(N - 70, N)]).cuda()
+    dO[:, at] = torch.randn((w.M, at.numel()), generator=g, device="cuda:0").to(t)
+    mask_ = gh.make_mask(w)
+    dW = torch.full((w.nnz,), float("nan"), device="cuda:0")
+    rb.rbgp_conv3x3_sddmm(mask_, dtype, w.M, C, images, side, side, dO.data_ptr(), N, X.data_ptr(), dW.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rb.rbgp_last_kernel() == f"sddmm_lines<{1 if mask[1][1] == 2 else 2}, 3, {int(dtype == wl.BF16)}, 1, 0, 1> + sddmm_reduce"
+    img, y, x = at // side ** 2, at % side ** 2 // side, at % side
+    I = torch.stack([X[:, img, y + dy, x + dx] for dy in range(3) for dx in range(3)], 1).reshape(w.K, -1).double()   # row 9 c + tap
+    kept = torch.from_numpy(rb.rbgp_mask_columns(mask_).reshape(w.M, -1)).long().cuda()
+    take = lambda a, b: torch.gather(a @ b.T, 1, kept).reshape(-1)
+    d = dO[:, at].double()
+    assert bool(((dW.double() - take(d, I)).abs() <= 4e-6 * take(d.abs(), I.abs())).all())
+
+
 @pytest.mark.parametrize("N", [130, 200])
 def test_weight_gradient_split_operands_keep_infinities_and_tiny_operands(N):
     """fp32 weight gradients on split operands against the plain kernel: the same sums are infinite or not a number, operands
