@@ -811,14 +811,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const bool ok64 = conv ? true : (ldI % 4 == 0) && (reinterpret_cast<uintptr_t>(I) % 8 == 0);
     const bool ok128 = conv ? conv->width % 8 == 0 : (ldI % 8 == 0) && (reinterpret_cast<uintptr_t>(I) % 16 == 0);
     const int tc = tune[RBGP_TUNE_COLS_PER_WORKGROUP];
-    // Masks with merged rows, fp32 sums: rows of I a multiple of 128 KiB apart that the 256 MB Infinity Cache holds are read faster in
-    // narrow tiles (us, mask as given / merged, 128 / 64 columns: WRN group 1, 65536 columns 17.9 / 19.4 / 18.0, 131072 37.4 / 38.7 /
-    // 36.2; past the cache 262144 77.5 / 68 / 74, other strides 57344 16.2 / 15.3 / 16.6).
-    const bool crowded = !m->merged.empty() && !conv && !out_bf16 && ldI % 65536 == 0 && m->K * ldI * 2 <= (int64_t(256) << 20);
     if (tc != 0 && tc != 64 && tc != 128) return RBGP_EUNSUPPORTED;
     if (tc)
       CW = tc;
-    else if (ok128 && int64_t((pl.TR + pl.MG - 1) / pl.MG) * m->a[2] * ((N + 127) / 128) >= 512 && !crowded)
+    else if (ok128 && int64_t((pl.TR + pl.MG - 1) / pl.MG) * m->a[2] * ((N + 127) / 128) >= 512)
       CW = 128;
     if (!(CW == 128 ? ok128 : ok64)) return RBGP_ESHAPE;
   }
