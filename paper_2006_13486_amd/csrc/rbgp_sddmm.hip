@@ -647,7 +647,6 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
         lines = wgs <= 256 && wgs >= 224 && RB == 2 && (RBl == 2 || N <= 2560);
     }
   }
-  if (lines && parts > 1 && !B.grow && size_t(parts) * size_t(nnz) * sizeof(float) > B.partial_bytes) lines = false;
   // (us, sddmm_reg / 64-bit offsets, bf16, 32 x 32 images, 16 channels: 64 rows x 34000 images 3098 / 1546, 128 x 17000 2801 / 1574,
   // 256 x 8500 1042 / 807)
   const bool far = lines && conv && m->M * ld_dO * (bf16 ? 2 : 4) >= int64_t(1) << 32;
