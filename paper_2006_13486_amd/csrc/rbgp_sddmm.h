@@ -41,7 +41,7 @@ constexpr int kLinesWaves = 8;   // waves of a workgroup of sddmm_lines
 }  // namespace rbgp_sddmm_detail
 
 typedef void (*rbgp_sddmm_fn)(rbgp_sddmm_detail::SddmmParams);
-// sddmm_lines with RB (1, 2) groups of 16 rows of dO and NB (1 to 3; bf16 also 4 and 5) groups of 16 steps per wave;
+// sddmm_lines with RB (1, 2) groups of 16 rows of dO and NB (1 to 3; bf16 also 4 and 5, with conv 6) groups of 16 steps per wave;
 // far (conv): dO of 4 GiB and more; nullptr: not built
 rbgp_sddmm_fn rbgp_sddmm_lines_kernel(int RB, int NB, bool bf16, bool conv, bool gi, bool far);
 

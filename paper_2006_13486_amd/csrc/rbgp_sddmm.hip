@@ -566,7 +566,7 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   const int nbt = NB;
   const int64_t units = int64_t(m->c[0]) * pl.NSTG * (gi ? 1 : m->a[2]);
   // The kernel of whole cache lines (rbgp_sddmm_lines.hip): workgroups of RBl row groups x NBl step groups
-  int RBl = RB, NBl = std::min(nbt, bf16 ? 5 : 3);
+  int RBl = RB, NBl = bf16 && conv && nbt > 3 ? 6 : std::min(nbt, bf16 ? 5 : 3);   // (6: 24 pixel rows, three taps each)
   int64_t parts = 1;
   auto count = [&](int r, int n) { return units * ((groups + r - 1) / r) * ((nbt + n - 1) / n); };
   const int64_t most_parts = (256 + count(RB, nbt) - 1) / count(RB, nbt);   // partial sums that any batch takes, in either kernel

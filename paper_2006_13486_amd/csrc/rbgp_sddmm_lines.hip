@@ -521,8 +521,9 @@ rbgp_sddmm_fn pick_nb(int NB) {
     case 3: return sddmm_lines<RB, 3, BF16, CONV, GI, FAR>;
   }
   if constexpr (BF16) {
-    if (CONV && (NB == 4 || NB == 5)) return sddmm_lines<RB, 6, true, true, GI, FAR>;   // (24 pixel rows)
-    if constexpr (!CONV) {
+    if constexpr (CONV) {
+      if (NB == 6) return sddmm_lines<RB, 6, true, true, GI, FAR>;
+    } else {
       if (NB == 4) return sddmm_lines<RB, 4, true, false, GI, false>;
       if (NB == 5) return sddmm_lines<RB, 5, true, false, GI, false>;
     }

@@ -134,7 +134,7 @@ def test_weight_gradient_every_kernel_of_whole_lines(dtype, RB, NB, gi, N, rows,
     """On the lowered input, with a ragged last step and rows at odd dwords, and (nine taps) as a convolution of 7 x 8 images."""
     w = wl.Workload("lines", rows, cols, deg, 0, dtype, 91, 92, 93, 1.0)
     images = N // 56
-    name = lambda conv: f"sddmm_lines<{RB}, {NB}, {int(dtype == wl.BF16)}, {conv}, {gi}>" + (" + sddmm_reduce" if N >= 4096 else "")
+    name = lambda conv: f"sddmm_lines<{RB}, {6 if conv and NB > 3 else NB}, {int(dtype == wl.BF16)}, {conv}, {gi}>" + (" + sddmm_reduce" if N >= 4096 else "")
 
     def check(got, dO, I, want):
         assert rb.rbgp_last_kernel() == want
