@@ -842,7 +842,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
       const int64_t nblocks = 8 * ((tiles + 7) / 8) * m->a[0] * (m->a[2] / 32);
       hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS, dev->one_of_two, NT, KSP), dim3(unsigned(nblocks)), dim3(unsigned(256 * KSP)), 0, st, sp);
       RBGP_HIP(hipGetLastError());
-      rbgp_set_last_kernel("spmm_mfma_split", {pl.KS, dev->one_of_two});
+      rbgp_set_last_kernel("spmm_mfma_split", {pl.KS, dev->one_of_two, NT, KSP});
       return RBGP_OK;
     }
   }

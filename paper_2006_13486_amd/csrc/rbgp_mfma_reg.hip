@@ -676,7 +676,7 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
     RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
   hipLaunchKernelGGL(fn, dim3(unsigned(wgs)), dim3(unsigned(256 * S)), bytes, static_cast<hipStream_t>(stream), cp);
   RBGP_HIP(hipGetLastError());
-  rbgp_set_last_kernel("conv_tile", {T});
+  rbgp_set_last_kernel("conv_tile", {T, S});
   *taken = true;
   return RBGP_OK;
 }
@@ -1321,7 +1321,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(rows), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
       hipLaunchKernelGGL(rows, dim3(unsigned(wgs)), dim3(unsigned(64 * waves)), bytes, static_cast<hipStream_t>(stream), rp);
       RBGP_HIP(hipGetLastError());
-      rbgp_set_last_kernel("spmm_reg_rows");
+      rbgp_set_last_kernel("spmm_reg_rows", {wide ? 3 : 2});
       return RBGP_OK;
     }
   }

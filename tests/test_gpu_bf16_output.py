@@ -100,27 +100,35 @@ def test_fused_conv3x3(case):
         assert float(np.max(np.abs(out16.astype(np.float64) - exact) / bound)) <= 1.0
 
 
-IMAGE_TILES = [  # rows of G_o no multiple of four, ragged last tiles, one or several chunks of tiles; 32 and 64 pixels, R = 4 and 8
-    (wl.Workload("tiles32_r4", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 101, 102, 103, 1.0), 343, 3, 4),
-    (wl.Workload("tiles64_r4", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 104, 105, 106, 1.0), 129, 2, 32),
-    (wl.Workload("tiles32_r8", (18, 2, 4, 4), (3, 4, 8, 9), (3, 4, 4, 9), 0, wl.BF16, 107, 108, 109, 1.0), 42, 5, 8),
-    (wl.Workload("tiles64_r8", (8, 4, 4, 2), (16, 4, 8, 9), (8, 4, 4, 9), 0, wl.BF16, 110, 111, 112, 1.0), 129, 1, 64),
+# rows of G_o no multiple of four, ragged last tiles, R = 4 and 8: mask, images and their sides, 32-pixel blocks and waves a row of a
+# workgroup, most chunks of tiles that one passes through LDS
+IMAGE_TILES = [
+    (wl.Workload("tiles32_r4", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 101, 102, 103, 1.0), 343, 3, 4, "1, 1", 1),
+    (wl.Workload("tiles64_r4", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 104, 105, 106, 1.0), 129, 2, 32, "2, 1", 2),
+    (wl.Workload("tiles32_r8", (18, 2, 4, 4), (3, 4, 8, 9), (3, 4, 4, 9), 0, wl.BF16, 107, 108, 109, 1.0), 42, 5, 8, "1, 1", 1),
+    (wl.Workload("tiles64_r8", (8, 4, 4, 2), (16, 4, 8, 9), (8, 4, 4, 9), 0, wl.BF16, 110, 111, 112, 1.0), 129, 1, 64, "2, 1", 8),
+    (wl.Workload("tiles32_one", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 131, 132, 133, 1.0), 1, 2, 8, "1, 2", 1),
+    (wl.Workload("tiles32_odd", (8, 4, 8, 1), (24, 4, 8, 9), (6, 4, 4, 9), 0, wl.BF16, 134, 135, 136, 1.0), 61, 1, 4, "1, 2", 3),
+    (wl.Workload("tiles64_rows", (16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 4, 9), 0, wl.BF16, 137, 138, 139, 1.0), 132, 4, 4, "2, 2", 3),
+    (wl.Workload("tiles32_pairs", (16, 4, 4, 2), (16, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 140, 141, 142, 1.0), 174, 3, 4, "1, 1", 2),
 ]
 
 
-IMAGE_TILES += [  # two waves a row: one image, a row of pixels that is no multiple of eight, two chunks; three; one wave a row, two chunks
-    (wl.Workload("tiles32_one", (6, 4, 8, 1), (4, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 131, 132, 133, 1.0), 1, 2, 8),
-    (wl.Workload("tiles32_odd", (8, 4, 8, 1), (24, 4, 8, 9), (6, 4, 4, 9), 0, wl.BF16, 134, 135, 136, 1.0), 61, 1, 4),
-    (wl.Workload("tiles64_rows", (16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 4, 9), 0, wl.BF16, 137, 138, 139, 1.0), 132, 4, 4),
-    (wl.Workload("tiles32_pairs", (16, 4, 4, 2), (16, 4, 8, 9), (2, 4, 4, 9), 0, wl.BF16, 140, 141, 142, 1.0), 139, 3, 4),
-]
+def _chunks(w, H, W, blocks, waves):
+    """Chunks of the workgroup with the most tile columns: a thread stages one run of eight padded pixels a chunk, 75 KiB hold one."""
+    rows = 32 * blocks // W
+    octets = -(-(rows + 2 * ((rows + H - 2) // H) + 2) * (W + 2) // 8)
+    chunk = min(w.cols[0], 75 * 1024 // (512 * octets), 64 * waves // octets)
+    lists = rb.rbgp_mask_factor(gh.make_mask(w), 0)[3]
+    return max(-(-len(set(lists[u:u + 4].ravel())) // chunk) for u in range(0, w.rows[0], 4))
 
 
 @pytest.mark.parametrize("case", IMAGE_TILES, ids=lambda c: c[0].name)
 def test_fused_conv3x3_with_channels_in_lds(case):
     """The kernel that keeps the channels of its tiles in LDS, fp32 and bf16 sums; an infinite activation reaches the sums of
     its neighbours and of the rows that keep its channel, no others."""
-    w, B, H, W = case
+    w, B, H, W, form, chunks = case
+    assert _chunks(w, H, W, *map(int, form.split(", "))) == chunks
     X = wl.conv_activations(w, B, H, W)
     X[5, B - 1, H - 1, W - 1] = X[40, 0, 0, 0] = np.inf
     vals_lib, X_lib = wl.to_bf16_bits(wl.kept_weights(w)), wl.to_bf16_bits(X)
@@ -128,7 +136,7 @@ def test_fused_conv3x3_with_channels_in_lds(case):
     with np.errstate(invalid="ignore"):
         exact, den = gh.oracle_spmm(w, vals, orc.im2col_3x3(X))
     out32 = gh.library_conv3x3(w, vals_lib, X_lib)
-    assert rb.rbgp_last_kernel() == f"conv_tile<{1 if 'tiles32' in w.name else 2}>"
+    assert rb.rbgp_last_kernel() == f"conv_tile<{form}>"
     out16 = gh.library_conv3x3(w, vals_lib, X_lib, out_bf16=True)
     assert np.array_equal((out16.view(np.uint32) >> 16).astype(np.uint16), orc.f32_to_bf16_bits(out32))
     finite = np.isfinite(exact)

@@ -508,7 +508,7 @@ def test_many_rows_per_tile_with_two_of_four_kept(rows, cols, deg):
     enough = -(-160 // rows[0]) * 64 - 63
     for N, pad in ((enough - 1, 0), (enough, 1), (enough + 63, 0), (enough + 64, 3)):
         gh.check_parity(w, N=N, ld_pad=pad, expect_kernel=REG)
-        assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == (N >= enough)
+        assert (rb.rbgp_last_kernel() == "spmm_reg_rows<2>") == (N >= enough)
     N = enough + 1
     vl, Il, vf, If = gh.host_inputs(w, N)
     bad, k = Il.copy(), 21
@@ -532,7 +532,7 @@ def test_many_rows_per_tile_of_short_lists_by_batch():
         w = wl.Workload("many_rows", (rows, 4, 8, 3), (rows, 4, 4, 2), (2, 4, 2, 2), 333, wl.F32, 71, 72, 73, 1.0)
         for N, taken in widths:
             gh.check_parity(w, N=N, expect_kernel=REG)
-            assert (rb.rbgp_last_kernel() == "spmm_reg_rows") == taken, (rows, N)
+            assert rb.rbgp_last_kernel().startswith("spmm_reg_rows<") == taken, (rows, N)
 
 
 # lists of one, two and four stages; nine and three full groups of 32 rows, and four with 24 rows in the last
@@ -545,13 +545,15 @@ def test_many_rows_per_tile_in_tiles_of_96_columns(rows, cols, deg):
     tiles = 256 // rows[0]
     for N, pad in ((64 * tiles + 1, 0), (64 * tiles + 31, 1), (96 * tiles, 0), (96 * tiles + 1, 3)):
         gh.check_parity(w, N=N, ld_pad=pad, expect_kernel=REG)
-        assert rb.rbgp_last_kernel() == "spmm_reg_rows"
+        assert rb.rbgp_last_kernel() == f"spmm_reg_rows<{3 if N <= 96 * tiles else 2}>"
     N = 96 * tiles - 33
     vl, Il, _, _ = gh.host_inputs(w, N)
     bad, at = Il.copy(), [31, 63, 95, N - 1]
     bad[21, at] = [np.inf, -np.inf, np.inf, np.nan]
     run = lambda X, tune=None: gh.library_spmm(w, vl, X, tune=tune, tag="tiles of 96")[0]
-    clean, got, ref = run(Il), run(bad), run(bad, (0,) * 8 + (1,))
+    clean, got = run(Il), run(bad)
+    assert rb.rbgp_last_kernel() == "spmm_reg_rows<3>"
+    ref = run(bad, (0,) * 8 + (1,))
     others = np.delete(np.arange(N), at)
     assert np.array_equal(got[:, others].view(np.uint32), clean[:, others].view(np.uint32))
     for test in (np.isnan, np.isposinf, np.isneginf):
@@ -574,7 +576,7 @@ def test_many_rows_per_tile_infinities_of_columns_a_row_does_not_keep(rows, cols
                 bad[at(v), n], bad[at(u), n] = x, y
                 n += 1
     got = gh.library_spmm(w, vl, bad, tag="many rows")[0][:, :n]
-    assert rb.rbgp_last_kernel() == "spmm_reg_rows"
+    assert rb.rbgp_last_kernel() == "spmm_reg_rows<2>"
     kept = rb.rbgp_mask_columns(gh.make_mask(w)).reshape(w.M, -1)
     W, X = vf.reshape(w.M, -1).astype(np.float64), bad[:, :n].astype(np.float64)
     with np.errstate(invalid="ignore"):
@@ -657,13 +659,13 @@ def test_filled_mask_on_a_wider_batch_allocates_nothing():
 @pytest.mark.parametrize("rows,cols,deg", [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1)), ((4, 1, 32, 4), (8, 3, 32, 1), (2, 3, 16, 1)),
                                            ((2, 2, 64, 2), (4, 2, 16, 2), (2, 2, 4, 2)), ((4, 4, 8, 4), (8, 1, 8, 4), (4, 1, 8, 2))])
 def test_lds_family_split_operands(rows, cols, deg):
-    """RBGP_TUNE_SPLIT_OPERANDS on the LDS family: widths around the 128-column tile, one and two groups of G_i vertices,
-    8 and 16 kept steps; infinities and tiny operands as the fp32 kernel gives them."""
+    """RBGP_TUNE_SPLIT_OPERANDS on the LDS family: widths around the tile of two groups of waves, one and two groups of G_i
+    vertices, 8 and 16 kept steps; infinities and tiny operands as the fp32 kernel gives them."""
     w = wl.Workload("lds_split", rows, cols, deg, 333, wl.F32, 11, 12, 13, 1.0)
     forced, never = (0,) * 8 + (2,), (0,) * 8 + (1,)
     for N, pad in ((4, 0), (100, 4), (128, 0), (129, 3), (300, 0)):
         gh.check_parity(w, N=N, kernel=MFMA, tune=forced, ld_pad=pad, expect_kernel=MFMA)
-        assert rb.rbgp_last_kernel() == f"spmm_mfma_split<{deg[2] * deg[3]}, {int(deg[2] < cols[2])}>"
+        assert rb.rbgp_last_kernel() == f"spmm_mfma_split<{deg[2] * deg[3]}, {int(deg[2] < cols[2])}, 2, 2>"
     N = 132
     vl, Il, vf, If = gh.host_inputs(w, N)
     bad = Il.copy()
@@ -678,6 +680,37 @@ def test_lds_family_split_operands(rows, cols, deg):
     fin = np.isfinite(ref)
     scale = np.abs(np.where(fin, ref, 0)).max(axis=0)       # (column by column: a few rounding errors of 6e-8 of its sums)
     assert (np.abs(np.where(fin, got, 0).astype(np.float64) - np.where(fin, ref, 0)) <= 1e-6 * scale).all()
+
+
+# 8 and 16 kept steps on the sparse form, 8 and 16 on the dense one (vertices that keep both k and k + 16); four workgroups a column tile
+SPLIT_FORMS = [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1), "8, 1"), ((2, 1, 64, 4), (4, 3, 32, 1), (2, 3, 16, 1), "16, 1"),
+               ((4, 4, 2, 16, 1), (8, 1, 2, 16, 1), (4, 1, 2, 4, 1), "8, 0"), ((4, 4, 8, 4), (8, 1, 8, 4), (4, 1, 8, 2), "16, 0")]
+
+
+@pytest.mark.parametrize("form,N", [("2, 2", 132), ("2, 1", 4196), ("4, 1", 13092)])
+@pytest.mark.parametrize("rows,cols,deg,steps", SPLIT_FORMS)
+def test_lds_family_split_operands_in_every_form(rows, cols, deg, steps, form, N):
+    """Two groups of waves on 64 columns a workgroup, one, and one on 128: the sums of the fp32 kernel, and its bits in columns with
+    infinities, operands of 2^105 and more or nothing that is a number, one in every column block of a tile and in the last."""
+    w = wl.Workload("split_forms", rows, cols, deg, N, wl.F32, 41, 42, 43, 1.0, **({"roles": (0, 1, 2, 2, 3)} if len(rows) == 5 else {}))
+    run = lambda X, v: gh.library_spmm(w, vl, X, kernel=MFMA, tune=(0,) * 8 + (v,), tag="every form")[0]
+    vl, Il, vf, If = gh.host_inputs(w, N)
+    bad, cols_bad = Il.copy(), [5, 37, 70, 101, 128, N - 40, N - 1]
+    bad[3, 5], bad[w.K - 1, 70], bad[:, 101], bad[17, N - 1] = np.inf, -np.inf, np.nan, np.float32(3e38)
+    bad[:, [37, 128, N - 40]] *= np.float32(2.0 ** 110)
+    clean, got = run(Il, 2), run(bad, 2)
+    assert rb.rbgp_last_kernel() == f"spmm_mfma_split<{steps}, {form}>"
+    plain, ref = run(Il, 1), run(bad, 1)
+    assert rb.rbgp_last_kernel() == "spmm_mfma"
+    assert (np.abs(clean.astype(np.float64) - plain) <= 1e-6 * np.abs(plain).max(axis=0)).all()   # (a few rounding errors of 6e-8)
+    others = np.delete(np.arange(N), cols_bad)
+    assert np.array_equal(got[:, others].view(np.uint32), clean[:, others].view(np.uint32))
+    assert np.isfinite(ref[:, 37]).all()
+    for n in cols_bad:   # (tiles without the operand of 3e38 keep the split's sums)
+        same = got[:, n].view(np.uint32) == ref[:, n].view(np.uint32)
+        kept = got[:, n].view(np.uint32) == clean[:, n].view(np.uint32)
+        assert (same | kept | np.isnan(got[:, n]) & np.isnan(ref[:, n])).all()
+        assert same.all() or n not in (37, 128, N - 40)
 
 
 @pytest.mark.parametrize("rows,cols,deg", [((4, 4, 32, 1), (8, 1, 32, 1), (4, 1, 8, 1)), ((4, 1, 64, 4), (8, 3, 32, 1), (2, 3, 16, 1)),
@@ -1331,7 +1364,7 @@ def test_lds_family_split_operands_by_width(N):
     I = I.copy()
     I[7, N - 1] = np.inf
     out, used = gh.library_spmm(w, vl, I, kernel=MFMA, ld_pad=(-N) % 4)
-    assert used == MFMA and rb.rbgp_last_kernel() == "spmm_mfma_split<8, 1>"
+    assert used == MFMA and rb.rbgp_last_kernel() == f"spmm_mfma_split<8, 1, {'2, 2' if N < 2112 else '2, 1' if N < 6700 else '4, 1'}>"
     with np.errstate(invalid="ignore"):
         ref, den = gh.oracle_spmm(w, vl, I)
     assert np.array_equal(np.isfinite(out), np.isfinite(ref))
@@ -1359,7 +1392,7 @@ def test_pack_writes_the_layout(side, shift, dtype):
 
 
 # VGG19 layers on few columns: workgroups of 16 columns and eight waves a list (layer, log2 of 1 / density, transposed), stages of
-# 72 steps in clusters of one, two and four tile rows, of 36, of 32 and of 18
+# 72 steps in clusters of one, two and four tile rows, of 36, in fp32 of 32 and of 18
 NARROW = [(13, 1, False), (13, 2, False), (4, 4, False), (3, 4, False), (13, 1, True), (13, 2, True)]
 
 
@@ -1382,6 +1415,21 @@ def test_register_family_on_few_columns(layer, density_log2, transposed, dtype, 
     elif not transposed:
         assert rb.rbgp_last_kernel() == "spmm_reg_narrow"
     assert orc.normalised_error(out, ref, den) <= gh.TOL[dtype]
+
+
+# stages of 18 and 32 steps with few lists (bf16: one group of rows on 64 columns), and lists of up to 128 stages
+NARROW_MASKS = [((4, 4, 4, 2), (4, 1, 4, 9), (2, 1, 2, 9)), ((4, 4, 8, 2), (4, 1, 64, 1), (2, 1, 32, 1)), ((2, 4, 4, 2), (128, 1, 4, 9), (64, 1, 2, 9))]
+
+
+@pytest.mark.parametrize("N", [1, 17, 63])
+@pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
+@pytest.mark.parametrize("rows,cols,deg", NARROW_MASKS)
+def test_few_columns_on_short_stages_and_long_lists(rows, cols, deg, dtype, N):
+    w = wl.Workload("narrow", rows, cols, deg, N, dtype, 361, 362, 363, 1.0)
+    plan = rb.rbgp_mask_reg_plan(gh.make_mask(w))
+    assert plan[2] == (32 if cols[3] == 1 else 18) and (plan[5] > 64) == (cols[0] == 128)
+    gh.check_parity(w, kernel=REG, ld_pad=(-N) % 4, expect_kernel=REG)
+    assert rb.rbgp_last_kernel() == "spmm_reg_narrow"
 
 
 @pytest.mark.parametrize("dtype", [wl.F32, wl.BF16])
