@@ -62,8 +62,8 @@ struct RegParams {
                            //   group of columns one lane loads (4, or 8 with the wide bf16 tile); padded to whole tiles
   int a2, a3, a4, R;
   int fpm;                 // weight fragments per member: d_o * NSTG
-  int no4, kcr, frag_bytes, nq;   // split-operand and shared bf16 kernels: entries of a G_i vertex's row table and how many
-                           //   are steps, bytes of one weight fragment, blocks of 16 (bf16: 32) steps of a stage
+  int no4, kcr, frag_bytes, nq;   // entries of a G_i vertex's row table (all register kernels: row_offset); split-operand and shared
+                           //   bf16 kernels: how many are steps, bytes of one weight fragment, blocks of 16 (bf16: 32) steps of a stage
   const int32_t *pairs;    // split operands, filled masks whose kept weights share the steps of a stage two by two: [fold][2][16],
                            //   see rbgp_reg_pairs
   int fold;                // tile rows per row of G_o

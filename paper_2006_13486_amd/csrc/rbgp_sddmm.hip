@@ -591,8 +591,8 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
             !(one_launch && (uneven || (!conv && N > 512 && (N < 1408 || broken))));
     if (count(RBl, NBl) < 256) {
       NBl = std::min(nbt, 3);
-      // (fused, single row groups on short batches as well: us, 2 x 3 -> 1 x 3, layer 1 at 1/2, 37888 columns 14.3 -> 12.8, 65536 15.9 ->
-      // 15.0, 98304 18.6 -> 18.8; layer 2 at 1/2, 16384 12.2 -> 11.0; layer 3 at 1/2, 16384 13.8 -> 13.9, 24576 15.9 -> 17.4)
+      // (fused, single row groups on short batches as well: time of 1 x 3 to 2 x 3 by workgroups x columns / 2^19, 32 workgroups 0.90 at 2.3,
+      // 0.91-0.95 at 4, 0.97 at 5.1, 0.97-1.01 at 6, 1.03 at 8; 64 0.99 at 4, 1.05 at 6; 128 0.94 at 2.3, 1.01 at 3, 1.04 at 4, 1.08 at 6)
       if (RBl == 2 && count(2, NBl) < 256 && (count(1, NBl) >= 256 || count(2, NBl) * most < 256 || (conv && count(1, NBl) * N < int64_t(5) << 19))) RBl = 1;
       parts = std::min((256 + count(RBl, NBl) - 1) / count(RBl, NBl), most);
     }
@@ -602,9 +602,10 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     if (!conv && count(RBl, NBl) == units && (N <= 256 || (!gi && units >= 32 && N > 3200 && units * parts < 256))) lines = false;
     // Long batches: a row group by itself loads every row of I for half as many rows of dO.  Not where both groups of a unit
     // would go to one workgroup of sddmm_reg (layers 4 at 1/2 and 5 at 1/4, ratios: lowered 16384 columns 0.90-0.95, 24576
-    // 0.95-0.99, 32768 0.98-1.03, 49152 1.12-1.18; fused 16384 0.96, 20480 1.00, 24576 1.02, 65536 1.20), nor, on the lowered
+    // 0.95-0.99, 32768 0.98-1.03, 49152 1.12-1.18), nor, on the lowered
     // input, where a unit has one row group, full, and needs partial sums as well (layer 8 at 1/16: 3584 columns 0.91, in two
-    // parts 4096 1.06, 16384 1.34; half full, layer 5 at 1/16, 0.83-1.02).
+    // parts 4096 1.06, 16384 1.34; half full, layer 5 at 1/16, 0.83-1.02).  Fused, the line is the one drawn for three shifted copies of
+    // the rows (20480 1.00, 65536 1.20); with windows 1 x 3 is the faster beyond it too (24576 0.79, 32768 0.82; 2 x 6 0.63 and 0.61).
     if (RB == 2 && RBl == 1 && parts == 1 && N > (conv ? 20480 : 24576)) lines = false;
     if (!conv && !gi && RB == 1 && parts > 1 && nbt > 3 && B.EO == pl.MG) lines = false;
     // Stages of one step group have nothing to split.  With many units (4096 x 4096 masks, ratios) not around four steps per wave
@@ -624,17 +625,21 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     const int64_t narrow = count(1, NBl);   // workgroups with one row group
     if (conv) {
       // The windows' loads and splits serve RB groups, so that the batch is split as well where units are few.  Two row groups where they
-      // fill the chip or the batch is long, else one (us, sddmm_reg / 1 x 3 / 2 x 3: layer 4 at 1/4, 1024 columns 12.0 / 9.2 / 10.2,
-      // 4096 16.3 / 13.8 / 14.2, 6144 20.8 / 17.6 / 16.7; layer 2 at 1/2, 9472 20.1 / 16.0 / 16.3, 32768 36.5 / 36.1 / 31.4; layer 6
-      // at 1/4, 4096 22.5 / 18.7 / 19.1, 8192 33.5 / 33.3 / 29.9; all of G_i, layer 1 at 1/4, 37888 31.1 / 25.2 / 25.4, 65536 40.5 /
-      // 37.2 / 34.1).  Parts of two steps a wave and more.
+      // fill the chip or the batch is long, else one (time of 1 x 3 to 2 x 3 by narrow * N / 2^18: 256 workgroups of one row group 0.93-0.95
+      // at 3, 0.97-1.00 at 4, 1.04 at 5.1, 1.13 at 8; all of G_i 0.94-1.00 at 3, 1.00-1.04 at 4, 1.06-1.08 at 6; fewer 0.92-1.01 at
+      // 2, 1.00 at 2.5, 1.00-1.06 at 3, 1.03-1.10 at 4).  us, sddmm_reg / 1 x 3 / 2 x 3: layer 4 at 1/4, 1024 columns 12.0 / 9.2 / 10.3, 4096
+      // 16.9 / 14.1 / 13.9, 16384 33.4 / 33.9 / 28.8; layer 5 at 1/4, 2368 18.1 / 13.2 / 14.5, 8192 32.1 / 31.9 / 28.5; all of G_i, layer
+      // 1 at 1/4, 37888 31.2 / 24.9 / 24.9, 65536 39.4 / 36.0 / 32.9.  Parts of two steps a wave and more.
       if (RB == 2 && count(2, NBl) < 224 && narrow <= 256 && narrow * N < int64_t(narrow >= 224 ? 5 : gi ? 6 : 3) << 18) RBl = 1;
       const int64_t wgs = count(RBl, NBl);
       const int64_t longest = std::max<int64_t>(1, N / 512);
       parts = std::max<int64_t>(1, std::min(256 / wgs, longest));
-      // sddmm_reg keeps more units than CUs (layer 8 at 1/2, 1024 columns 18.5 against 20.7), single row groups on long batches where
-      // half of the second piece of a stage is padding (layer 6 at 1/16, 4096 14.4 / 13.5, 8192 20.8 / 21.3), and, with a workgroup
-      // per unit, batches beyond which it was the faster before the windows (layer 9 at 1/16, layer 6 at 1/2).
+      // sddmm_reg keeps more workgroups than CUs (layer 8 at 1/2, 512 of 2 x 3: 1024 columns 18.4 against 20.0, 2048 29.3 / 29.9, 4096 52.5 /
+      // 50.0).  The three other lines were drawn for shifted copies of the rows; with windows this kernel is at least as fast beyond them:
+      // 129 to 159 workgroups in one part (6 x 6 columns of a 72-step mask, 144: 1024 columns 12.1 / 7.7, 4096 20.4 / 17.8, 8192 30.7 / 30.9);
+      // single row groups on long batches (ratios, 128 workgroups 0.96-0.99 at 8192 columns, 0.99-1.00 at 32768, 64 0.95-0.97 at
+      // 32768, 1.00 at 65536, all of G_i 0.86-0.91); a workgroup per unit, batches from 4480 (layer 5 at 1/2: 5248 38.0 / 31.8, 8192 55.0 /
+      // 46.0, 32768 191 / 172) and 1728 columns on (layer 9 at 1/16: 2048 15.1 / 11.7, 4096 21.2 / 18.9, 8192 35.2 / 32.7).
       lines = wgs <= 256 && (wgs * parts >= 160 || parts == longest);
       if (RB == 1 && nbt > 3 && narrow * N >= int64_t(narrow >= 128 ? 1 : 2) << 20) lines = false;
       if (wgs >= 224 && RBl == RB && N >= (RB == 2 ? 4480 : 1728)) lines = false;
