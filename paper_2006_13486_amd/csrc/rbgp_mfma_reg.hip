@@ -880,7 +880,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // the two balance out, so the default is one group unless the rule below finds two worth it.
   // The stage list is split when there are fewer (cluster, G_i vertex, column tile) triples than SIMDs.
   int G = 1, lgS = 0;
-  bool two_groups = false, four_groups = false;   // a batch of another size may take them
+  bool two_groups = false, four_groups = false;   // rbgp_spmm: a batch of another size may take them
   {
     const int tg = bf16 ? tune[RBGP_TUNE_ROW_GROUPS] : 0, ts = tune[RBGP_TUNE_K_SPLIT];
     if (tg) {
@@ -902,7 +902,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         st->g2_stages = (c2.max_stages > kRegMaxStages || m->reg_clusters.U != pl.MG || 5 * total2 > 4 * total1) ? -2 : c2.max_stages;
         st->g2_ncl = c2.ncl;
         st->g2_shared = 20 * total2 <= 11 * total1;
-        if (st->g2_stages > 0 && !st->tab_bf16[1].stages) {
+        if (st->g2_stages > 0 && !conv && !st->tab_bf16[1].stages) {
           int rc = upload_tables(c2, &st->tab_bf16[1]);
           if (rc) {
             st->g2_stages = -1;
@@ -910,8 +910,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
           }
         }
       }
-      two_groups = st->g2_stages > 0;
-      four_groups = two_groups && st->g2_shared && pl.MG == 1 && pl.fold % 4 == 0 && pl.KC <= 36 && st->g2_stages >= 32;
+      two_groups = st->g2_stages > 0 && !conv;
+      const bool can4 = st->g2_stages > 0 && st->g2_shared && pl.MG == 1 && pl.fold % 4 == 0 && pl.KC <= 36 && st->g2_stages >= 32;
+      four_groups = can4 && !conv;
       if (st->g2_stages > 0) {
         const int64_t waves2 = int64_t(st->g2_ncl) * m->a[2] * ntiles;
         int S2 = 1;
@@ -928,7 +929,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         // filled masks of Tables 2-3): four groups per wave, where the chip stays full and the accumulators fit without
         // spilling (stages of up to 36 steps).  4096^3 with one row per column set: 182 / 122 / 111 us with 1 / 2 / 4 groups.
         // (stage lists of 16: 53.9 us against 51.1 with two groups -- long lists only)
-        if (G == 2 && four_groups) {
+        if (G == 2 && can4) {
           const int64_t waves4 = int64_t(pl.TR / 4) * m->a[2] * ntiles;
           int S4 = 1;
           while (S4 < 4 && (waves4 * S4 < 1024 || st->g2_stages > kRegWaveStages * S4)) S4 *= 2;
@@ -1037,12 +1038,13 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
                                !(merged && tune[RBGP_TUNE_REGISTER_SETS])));
   }
   if (dual) lgS = 1;   // (two column tiles per workgroup, as with a stage list split in two)
-  // The first call makes the tables of every kernel that a batch of another size takes (it may come under capture): fp32 those of
-  // the clusters also where tile rows are paired, bf16 those of one group and of the larger clusters (two groups: above).
+  // The first call makes the tables of every kernel that a batch of another size takes (it may come under capture; the fused
+  // convolution's batch is part of its geometry): fp32 those of the clusters also where tile rows are paired, bf16 those of all groups.
   RegTables *tab = bf16 ? &st->tab_bf16[G == 4 ? 2 : G == 2 ? 1 : 0] : &st->tab;
   auto make_tables = [&](int groups, RegTables *t) { return t->stages ? RBGP_OK : build_tables(m, groups * pl.MG, t); };
-  int rc_tables = make_tables(G, tab);
+  int rc_tables = dual && conv ? RBGP_OK : make_tables(G, tab);
   if (!rc_tables && two_groups) rc_tables = make_tables(1, &st->tab_bf16[0]);
+  if (!rc_tables && two_groups) rc_tables = make_tables(2, &st->tab_bf16[1]);
   if (!rc_tables && four_groups) rc_tables = make_tables(4, &st->tab_bf16[2]);
   if (rc_tables) return rc_tables;
   if (!dual) {

@@ -1318,7 +1318,7 @@ OTHER_WIDTHS = [(MERGED_ROW_SHAPES[0][:3], wl.F32, 40960, 64), (MERGED_ROW_SHAPE
                 (MERGED_ROW_SHAPES[1][:3], wl.F32, 40960, 64), (MERGED_ROW_SHAPES[1][:3], wl.BF16, 40960, 64),
                 (MERGED_ROW_SHAPES[2][:3], wl.BF16, 40960, 64), (MERGED_ROW_SHAPES[2][:3], wl.BF16, 64, 40960),
                 (((16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 2, 9)), wl.F32, 2048, 64), (((16, 4, 4, 2), (16, 4, 8, 9), (8, 4, 2, 9)), wl.F32, 64, 2048),
-                (((8, 4, 8, 1), (8, 4, 4, 9), (4, 4, 1, 9)), wl.BF16, 64, 40960),
+                (MERGED_ROW_SHAPES[0][:3], wl.BF16, 64, 40960),
                 (((32, 4, 32, 4), (16, 1, 32, 1), (8, 1, 16, 1)), wl.BF16, 64, 4096), (((32, 4, 32, 4), (16, 1, 32, 1), (8, 1, 16, 1)), wl.BF16, 4096, 64)]
 
 
@@ -1337,6 +1337,8 @@ def test_register_family_on_another_batch_allocates_nothing(mask_of, dtype, firs
     rb.rbgp_pack(mask, dtype, wl.to_bf16_bits(vals) if dtype == wl.BF16 else vals, packed.data_ptr(), stream())
     I, O = torch.zeros((w.K, ld), dtype=t, device="cuda:0"), torch.zeros((w.M, ld), device="cuda:0")
     call = lambda n: rb.rbgp_spmm(mask, dtype, w.M, w.K, n, packed.data_ptr(), I.data_ptr(), ld, O.data_ptr(), ld, stream())
+    if dtype == wl.BF16 and w.cols[3] == 9 and first > then:   # (a convolution before: it looks at clusters of two groups, too)
+        rb.rbgp_conv3x3(mask, dtype, w.M, w.K // 9, 1, 4, 8, packed.data_ptr(), I.data_ptr(), O.data_ptr(), 32, stream())
     call(first)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
