@@ -151,7 +151,7 @@ enum {
 /* Device tables.  A mask keeps small index tables in device memory (adjacency lists, stage lists,
  * pack permutations; a few KB to a few hundred KB), built on first use: the first rbgp_pack /
  * rbgp_spmm / rbgp_conv3x3 / rbgp_sddmm call on a mask -- and the first after another kernel choice or
- * tuning value, with another convolution geometry, or, for rbgp_sddmm, with a larger N -- allocates
+ * tuning value, with another convolution geometry, or, for rbgp_sddmm, with a larger N (not rbgp_spmm: any N) -- allocates
  * and uploads them (hipMalloc, synchronous copies).  Every later call with the same configuration
  * only launches kernels on `hip_stream`: it may be recorded into a HIP graph and replayed (make one
  * eager call first).  The tables belong to the mask and go with rbgp_mask_free.  All calls that use
@@ -414,7 +414,10 @@ int rbgp_mask_original_order(const rbgp_mask_t *derived, int32_t *out);
  * factored as G_o (x) G_r (x) (G_i (x) J(q, 1)) (x) J(|G_b.U| / q, |G_b.V|), which fills more of the 16 rows of an
  * MFMA group; [14] = rows of a group in use there, [15] = its tile rows (0, 0: the mask runs as given).  Masks with
  * a complete G_o run (both dtypes) with G_o (x) G_r merged into one tile column, J(a_o, 1) (x) J(a_r, c_o c_r), where
- * that makes the stages longer and the walk cheaper; [14], [15] then describe that factoring. */
+ * that makes the stages longer and the walk cheaper; [14], [15] then describe that factoring.  Masks of 3x3 convolutions with
+ * up to four rows per column set whose G_i vertices come in groups with one adjacency list run (fp32; bf16 unless G_i is of
+ * eight columns, four kept, beside |G_r.V| = 4) with the rows of a group in G_r; [14], [15] describe that factoring, and the
+ * tuning knobs count as on the mask as given. */
 int rbgp_mask_reg_plan(const rbgp_mask_t *mask, int32_t info[16]);
 
 /* Host-only self check of the index tables the RBGP_KERNEL_MFMA_REG kernels read for this mask: every

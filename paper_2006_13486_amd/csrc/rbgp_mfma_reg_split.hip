@@ -450,8 +450,8 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
 // vertex keeps both k and k + 16; the weights are scattered among the 16 steps) 65 and 7.4e-8; inputs with one infinity 1.34 times
 // that, with no finite column 1.49 times (dense, a lane adding its sums up one by one: 3.7 and 11 times).
 // What bounds it: a stage's chain (split, LDS, barrier, LDS, 24 products of two accumulators each) with 1.5 waves a SIMD, 128 columns:
-// 64 columns a workgroup need half of the registers and 37 KB of LDS, three run on a CU: 65 -> 56 us.  Vector instructions (half of them splits) and products, one after the other on a SIMD, are
-// then nine tenths of a CU's time.  The rows of a wave's weights in different banks (row_to; a scattered write met four others):
+// 64 columns a workgroup need half of the registers and 37 KB of LDS, three run on a CU: 65 -> 56 us.  Vector instructions (half of them
+// splits) and products, one after the other on a SIMD, are then 49 k and 37 k of its 114 k cycles at 2.07 GHz.  The rows of a wave's weights in different banks (row_to; a scattered write met four others):
 // bank conflicts 7.1 M -> 2.4 M cycles, 57.5 -> 55 us, one column 24 -> 22.7.  Tried there: two stages of
 // loads in flight 57; the next stage split beside the products of this one 63 (the loads are waited for earlier); four groups of
 // waves on few columns 24-28 (spills) against 23-25 with two; weights through LDS as loaded, split in operand layout with their zeros
