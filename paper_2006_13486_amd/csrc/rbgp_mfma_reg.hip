@@ -591,6 +591,7 @@ struct RegState {
   RegTables tab;                   // fp32: clusters of one 16-row group
   RegTables tab_bf16[3];           // bf16: clusters of 1, 2, 4 groups
   bool g2_shared = false;          // the clusters of two groups have (nearly) half the stages in total: their tile rows share their tiles
+  bool g4_none = false;            // the clusters of four groups have too long a list
   int g2_stages = -1, g2_ncl = 0;  // longest stage list and number of the clusters of two groups (-2: too long,
                                    //   or their stage lists add up to more than 0.8 of those of one group)
 };
@@ -1045,7 +1046,13 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   int rc_tables = dual && conv ? RBGP_OK : make_tables(G, tab);
   if (!rc_tables && two_groups) rc_tables = make_tables(1, &st->tab_bf16[0]);
   if (!rc_tables && two_groups) rc_tables = make_tables(2, &st->tab_bf16[1]);
-  if (!rc_tables && four_groups) rc_tables = make_tables(4, &st->tab_bf16[2]);
+  if (!rc_tables && four_groups && !st->g4_none) {
+    rc_tables = make_tables(4, &st->tab_bf16[2]);
+    if (rc_tables == RBGP_EUNSUPPORTED && G != 4) {   // (too long a list, which this batch does not walk)
+      st->g4_none = true;
+      rc_tables = RBGP_OK;
+    }
+  }
   if (rc_tables) return rc_tables;
   if (!dual) {
     // a stage list longer than a wave's table is split over enough waves of the workgroup
