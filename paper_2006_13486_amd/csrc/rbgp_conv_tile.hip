@@ -60,7 +60,12 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
   const int lane = threadIdx.x & 63, h = lane >> 5, j = lane & 31;
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), wr = wid & (kRows - 1), ws = wid / kRows;
   const int per = (p.a1 + kRows - 1) / kRows;   // workgroups of one column tile, all on XCD tile % 8
-  const int slot = blockIdx.x >> 3, nt = int(blockIdx.x & 7) + 8 * (slot / per), ug = slot % per;
+  // (what the prologue reads of the kernel arguments, at once: see grid_args)
+  asm volatile("" ::"s"(p.by_per.mul), "s"(p.by_per.shift), "s"(p.by_hw.mul), "s"(p.by_hw.shift), "s"(p.by_w.mul), "s"(p.by_w.shift),
+               "s"(p.by_R.mul), "s"(p.by_R.shift), "s"(p.a1), "s"(p.ntiles), "s"(p.tiles),
+               "s"(p.sel), "s"(p.Wp), "s"(p.X), "s"(p.chan), "s"(p.n), "s"(p.h), "s"(p.w), "s"(p.w2), "s"(p.hw), "s"(p.R), "s"(p.RS),
+               "s"(p.frag_bytes), "s"(p.a3), "s"(p.w_bytes), "s"(p.d1));
+  const int slot = blockIdx.x >> 3, stripe = rbgp_fast::quotient(slot, p.by_per), nt = int(blockIdx.x & 7) + 8 * stripe, ug = slot - stripe * per;
   if (nt >= p.ntiles) return;
   const int u1 = ug * kRows + wr;
   uint64_t mine = 0, left = 0;                  // tile columns of the wave's row; those of the workgroup's rows still to come
@@ -79,7 +84,7 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
 
   // the padded pixels from the row above the first pixel to the row below the last one (whole rows: W divides 32 T)
   auto center = [&](int n) {
-    const int img = n / p.hw, r = n - img * p.hw, y = r / p.w, x = r - y * p.w;
+    const int img = rbgp_fast::quotient(n, p.by_hw), r = n - img * p.hw, y = rbgp_fast::quotient(r, p.by_w), x = r - y * p.w;
     return (img * (p.h + 2) + y + 1) * p.w2 + x + 1;
   };
   const int n0 = nt * 32 * T, n_last = (n0 + 32 * T < p.n ? n0 + 32 * T : p.n) - 1;
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
     at[t] = center(n < p.n ? n : n_last) - p_lo;
   }
   // the lane's row of a tile: G_i vertex and row of R
-  const int ui = j / p.R, i = j - ui * p.R;
+  const int ui = rbgp_fast::quotient(j, p.by_R), i = j - ui * p.R;
   const int4 sel = p.sel[ui];                   // byte selectors of the channels in places 0, 1 and 2, 3; index operand
   const int wofs = (h * p.a3 + ui) * p.frag_bytes + i * 16;
   const __amdgpu_buffer_rsrc_t rw =
@@ -122,7 +127,8 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
     return c;
   };
   auto fetch = [&](uint64_t chunk) {
-    const int pl = int(threadIdx.x) / octets, q = int(threadIdx.x) - pl * octets, k = pl >> 2;
+    // (threadIdx.x + 1/2) / octets lies at least 1 / (2 octets) from a whole number, 2^-11 of it: far beyond the reciprocal's error
+    const int pl = int((float(int(threadIdx.x)) + 0.5f) * __builtin_amdgcn_rcpf(float(octets))), q = int(threadIdx.x) - pl * octets, k = pl >> 2;
     dst = -1;
     if (k >= __popcll(chunk)) return;
     uint64_t c = chunk;
@@ -223,8 +229,8 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
       v[0] += s1[0];
       v[1] += s1[1];
     }
-    const int rui = r / p.R, ri = r - rui * p.R;
-    const int64_t o = (((int64_t(o1) * p.a2 + ri / p.a4) * p.a3 + rui) * p.a4 + ri % p.a4) * p.ldO + n0 + x;
+    const int rui = rbgp_fast::quotient(r, p.by_R), ri = r - rui * p.R, ra = rbgp_fast::quotient(ri, p.by_a4);
+    const int64_t o = (((int64_t(o1) * p.a2 + ra) * p.a3 + rui) * p.a4 + ri - ra * p.a4) * p.ldO + n0 + x;
     if (p.obf16) {
       uint16_t *const out = static_cast<uint16_t *>(p.O) + o;
       const u32x4 w = {bf16_pair(v[0][0], v[0][1]), bf16_pair(v[0][2], v[0][3]), bf16_pair(v[1][0], v[1][1]), bf16_pair(v[1][2], v[1][3])};

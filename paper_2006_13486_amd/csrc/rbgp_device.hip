@@ -839,6 +839,7 @@ static int spmm_impl(const rbgp_mask_t *m, rbgp_dtype_t dtype, int64_t M, int64_
       sp.N = N; sp.ldI = ldI; sp.ldO = ldO;
       sp.a1 = m->a[0]; sp.a2 = m->a[1]; sp.a3 = m->a[2]; sp.a4 = m->a[3]; sp.d1 = m->d[0]; sp.c2 = m->c[1];
       sp.ntiles = int(tiles);
+      sp.by_mt = rbgp_fast::div_by(int64_t(m->a[0]) * (m->a[2] / 32)); sp.by_gz = rbgp_fast::div_by(m->a[2] / 32); sp.by_c2 = rbgp_fast::div_by(m->c[1]);
       const int64_t nblocks = 8 * ((tiles + 7) / 8) * m->a[0] * (m->a[2] / 32);
       hipLaunchKernelGGL(rbgp_mfma_split_kernel(pl.KS, dev->one_of_two, NT, KSP), dim3(unsigned(nblocks)), dim3(unsigned(256 * KSP)), 0, st, sp);
       RBGP_HIP(hipGetLastError());

@@ -82,7 +82,8 @@ namespace {
 // instead of one).
 // KL: stage size of the packed layout and the row table (see rbgp_reg_walk).
 template <int KC, int RS, bool TAPS = false, int NG = 1, bool CTILES = false, bool LEAN = false, int KL = KC>
-__global__ __launch_bounds__(256, (LEAN || (NG == 2 && (KC <= 32 || (KC == 36 && TAPS))) ? 2
+__global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || TAPS)    ? 4   // (128 registers)
+                                   : LEAN || (NG == 2 && (KC <= 32 || (KC == 36 && TAPS))) ? 2
                                    : KC <= 8 && NG == 1                                   ? (CTILES ? 2 : RS >= 4 ? 4 : 3)
                                                                                           : 1)) void spmm_reg(RegParams p) {
   static_assert(!CTILES || (KC <= 8 && !TAPS), "column tiles per wave: short stages, not the fused convolution");
@@ -109,6 +110,7 @@ __global__ __launch_bounds__(256, (LEAN || (NG == 2 && (KC <= 32 || (KC == 36 &&
   // 4 / S column tiles.  Used when N is too small to give every SIMD a wave otherwise.
   const int lgS = p.lgS, S = 1 << lgS;
   const int ks = wid & (S - 1);
+  table_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;
   const int cl = wg.cl * NG, u3 = wg.u3, ntq = wg.ntq;   // (NG > 1: the first of the wave's NG tile rows; all share its tables)
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(256, (LEAN || (NG == 2 && (KC <= 32 || (KC == 36 &&
   const int TS = p.tstride;
   int own = ks + (lane << lgS), ctile = 0;
   if (CTILES) {
-    ctile = lane / p.ct_cnt;
+    ctile = rbgp_fast::quotient(lane, p.by_ct_cnt);
     own = lane - ctile * p.ct_cnt;
   }
   // byte offset of the first column (of the lane's table entry's tile) in a row of I (fused convolution: the
@@ -671,6 +673,8 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
   cp.frag_bytes = (rbgp_bf16_blocks32(pl.KC) + (rbgp_bf16_tail16(pl.KC) ? 1 : 0)) * 4 * pl.RS * 16;
   cp.chunk = int(std::min({int64_t(m->c[0]), most / tile_bytes, 64 * S / octets}));   // (a thread stages one octet of a plane; two buffers)
   cp.obf16 = out_bf16 ? 1 : 0;
+  cp.by_per = rbgp_fast::div_by(per); cp.by_hw = rbgp_fast::div_by(H * W); cp.by_w = rbgp_fast::div_by(W);
+  cp.by_R = rbgp_fast::div_by(pl.R); cp.by_a4 = rbgp_fast::div_by(m->a[3]);
   const size_t bytes = size_t(std::max((cp.chunk < m->c[0] ? 2 : 1) * cp.chunk * tile_bytes, int64_t(S * T) * 16 * 1024));   // (sums of a row's waves)
   rbgp_conv_tile_fn fn = rbgp_conv_tile_kernel(T, S);
   if (bytes > 64 * 1024)
@@ -1282,6 +1286,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   const int64_t tiles_per_wg = split_rw > 1 ? 1 : share_rv ? 1 : (4 >> lgS) * CT;
   rp.ct = CT;
   rp.ct_cnt = tab->max_stages;
+  rp.by_ct_cnt = rbgp_fast::div_by(std::max(1, rp.ct_cnt));
   const int64_t nquads = (ntiles + tiles_per_wg - 1) / tiles_per_wg;
   // one-dimensional grid, items dealt to the XCDs in blocks (see RegParams)
   // (measured on one box, us: conv5 18.0 / 18.2 / 18.2 with order 1 / 0 / 2; conv3 bf16 20.2 / 17.8 / 17.6; WRN 90.9 / 76.4 / 75.9)
@@ -1292,6 +1297,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   rp.ncl = ncl;
   rp.per_xcd = int(per_xcd);
   rp.ngroups = int(nquads);
+  set_grid(&rp);
   // Many rows per tile, one stage of 32 rows of I with two of every four kept (transposes of lowered 3x3 layers): workgroups
   // of all rows of a row of G_o x 64 columns (rbgp_mfma_reg_rows.hip), from five workgroups per eight CUs on (us, the kernels
   // above -> this one: VGG19 layer 6 at 1/4, 128 workgroups 8.9 -> 9.6, 192 13.6 -> 10.0, 256 15.3 -> 10.4, 512 26.9 -> 17.4;
@@ -1318,6 +1324,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       rp.ntiles = int(tiles);
       rp.ncl = int(rows_o);
       rp.order = tiles >= 8 ? 2 : 0;
+      set_grid(&rp);
+      rp.by_row = rbgp_fast::div_by(int64_t(rp.a3) * rp.R); rp.by_r = rbgp_fast::div_by(rp.R); rp.by_a4 = rbgp_fast::div_by(rp.a4);
       rp.ct_cnt = tab->max_stages;
       // A wave per group while every workgroup has a CU to itself, or lists are longer than four stages (eight: LDS holds one
       // workgroup, 4 waves 36, 9 waves 27 at 512 workgroups; five and six: two of four waves fit, nine leave registers for
@@ -1349,6 +1357,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       rp.ntiles = rp.ngroups = int(tiles);
       rp.order = (m->e[2] == 1 && tiles <= 64) ? 1 : tiles >= 8 ? 2 : 0;
       rp.per_xcd = int(rp.order == 2 ? lists * ((tiles + 7) / 8) : (lists * tiles + 7) / 8);
+      set_grid(&rp);
       hipLaunchKernelGGL(narrow, dim3(unsigned(8 * rp.per_xcd)), dim3(512), 0, static_cast<hipStream_t>(stream), rp);
       RBGP_HIP(hipGetLastError());
       rbgp_set_last_kernel("spmm_reg_narrow");

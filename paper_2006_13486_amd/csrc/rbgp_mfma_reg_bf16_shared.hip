@@ -36,6 +36,7 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_bf16_shared(RegParams p) {
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int wr = wid / NTC, wc = wid % NTC;     // row group and column tile; as a loader, block and column tile
+  table_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;                // (the whole workgroup)
   const int u1 = (wg.cl * RV + wr) * 2 * PR, u3 = wg.u3;   // first of the wave's 2 PR tile rows

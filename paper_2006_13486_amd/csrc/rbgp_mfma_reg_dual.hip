@@ -43,6 +43,9 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
 
   // A workgroup is one (quad, G_i vertex) pair on two neighbouring column tiles, four waves each (see wg_coord
   // for how the workgroups map to the XCDs).
+  asm volatile("" ::"s"(dp.tab), "s"(dp.cmax), "s"(dp.o_stages), "s"(dp.o_quads), "s"(p.conv), "s"(p.Wp), "s"(p.I), "s"(p.w_bytes),
+               "s"(p.row_bytes), "s"(p.n_bytes), "s"(p.last_row), "s"(p.src_rows), "s"(p.fpm), "s"(int(p.ldI)), "s"(p.colbase));
+  grid_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;   // (the whole workgroup leaves)
   const int cl = wg.cl, u3 = wg.u3;

@@ -40,6 +40,7 @@ __global__ __launch_bounds__(64 * W) void spmm_reg_narrow(RegParams p) {
   __shared__ float red[W][4][64];
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  table_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;
   const int cl = wg.cl, u3 = wg.u3, n0 = wg.ntq * 16;

@@ -53,11 +53,12 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   int uo, nt;                                   // row of G_o, column tile (order 2: one on XCD tile % 8, as in wg_coord)
   if (p.order == 2) {
     const int slot = blockIdx.x >> 3;
-    nt = int(blockIdx.x & 7) + 8 * (slot / p.ncl);
-    uo = slot % p.ncl;
+    const int q = rbgp_fast::quotient(slot, p.by_ncl);
+    nt = int(blockIdx.x & 7) + 8 * q;
+    uo = slot - q * p.ncl;
   } else {
-    nt = int(blockIdx.x) / p.ncl;
-    uo = int(blockIdx.x) % p.ncl;
+    nt = rbgp_fast::quotient(int(blockIdx.x), p.by_ncl);
+    uo = int(blockIdx.x) - nt * p.ncl;
   }
   if (nt >= p.ntiles) return;                   // (the whole workgroup)
   const int64_t n0 = int64_t(nt) * CW;
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     f32x4 x[2];
   };
   auto a_of = [&](int r) {                      // its weights; kOob: no such row
-    const int f = r / per_row, q = r - f * per_row, ui = q / p.R, i = q - ui * p.R;
+    const int f = rbgp_fast::quotient(r, p.by_row), q = r - f * per_row, ui = rbgp_fast::quotient(q, p.by_r), i = q - ui * p.R;
     return r < rows ? ((u1 + f) * p.fpm * p.a3 + ui) * p.frag_bytes + i * 16 : kOob;
   };
   auto load_a = [&](A &a, int base, int s) {
@@ -102,10 +103,11 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   for (int d = 0; d < kAhead; ++d) load_a(ring[d], d < cnt ? a_base : kOob, d < cnt ? d : 0);
 
   for (int x = threadIdx.x; x < groups * 32; x += blockDim.x) {
-    const int f = x / per_row, q = x - f * per_row, ui = q / p.R, i = q - ui * p.R;
+    const int f = rbgp_fast::quotient(x, p.by_row), q = x - f * per_row, ui = rbgp_fast::quotient(q, p.by_r), i = q - ui * p.R;
+    const int ia = rbgp_fast::quotient(i, p.by_a4);
     const bool in = x < rows;
     const int e0 = in ? p.rowtab[ui * p.no4] >> 1 : 0, e1 = in ? p.rowtab[ui * p.no4 + 2] >> 1 : 0;
-    info[x] = int4{in ? f * p.tm + ui * p.a4 + (i / p.a4) * p.a3 * p.a4 + i % p.a4 : -1, a_of(x), (e0 | e1 << 2) * 0x1111, 0};
+    info[x] = int4{in ? f * p.tm + ui * p.a4 + ia * p.a3 * p.a4 + i - ia * p.a4 : -1, a_of(x), (e0 | e1 << 2) * 0x1111, 0};
   }
   auto keep = [&](const float (&x)[16], int block) {
 #pragma unroll

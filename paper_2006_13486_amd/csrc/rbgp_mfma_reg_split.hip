@@ -48,6 +48,7 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int lgS = p.lgS, S = 1 << lgS;
   const int ks = wid & (S - 1);
+  table_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;                // (the whole workgroup)
   const int u1 = wg.cl * 2, u3 = wg.u3;         // first of the wave's two tile rows
@@ -245,6 +246,7 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split_shared(RegParams p) {
   __shared__ __attribute__((aligned(16))) int rowoff[SPARSE ? 2 : 1][5 * 16];   // [order of the steps][q][lane / 32][e]
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  table_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;
   const int u1 = wg.cl * 8 + 2 * wid, u3 = wg.u3;
@@ -473,10 +475,15 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), wid = wave & 3, ks = wave >> 2;
   auto &parts = lds.stage[ks].parts;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;   // (same columns of I -> same XCD, as spmm_mfma)
-  const int gz = p.a3 / 32, mt = p.a1 * gz;
-  const int nt = xcd + 8 * (slot / mt);
+  // (what the prologue reads of the kernel arguments, at once: see grid_args)
+  asm volatile("" ::"s"(p.by_mt.mul), "s"(p.by_mt.shift), "s"(p.by_gz.mul), "s"(p.by_gz.shift),
+               "s"(p.by_c2.mul), "s"(p.by_c2.shift),
+               "s"(p.ntiles), "s"(p.a1), "s"(p.a3), "s"(p.adj0), "s"(p.rowoff), "s"(p.d1), "s"(p.c2), "s"(p.Wp), "s"(p.I), "s"(p.ldI), "s"(p.N));
+  const int gz = p.a3 >> 5, mt = p.a1 * gz;
+  const int stripe = rbgp_fast::quotient(slot, p.by_mt), in_tile = slot - stripe * mt;
+  const int nt = xcd + 8 * stripe;
   if (nt >= p.ntiles) return;                   // (the whole workgroup)
-  const int u1 = (slot % mt) / gz, ub = (slot % mt) % gz * 32 + wid * 8;   // tile row, the wave's first G_i vertex
+  const int u1 = rbgp_fast::quotient(in_tile, p.by_gz), ub = (in_tile - u1 * gz) * 32 + wid * 8;   // tile row, the wave's first G_i vertex
   const int64_t n0 = int64_t(nt) * CW;
   const int h = lane >> 5, j = lane & 31;
   const int adj_lo = lane < p.d1 ? p.adj0[u1 * p.d1 + lane] : 0;
@@ -519,7 +526,7 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
   const int own_t = wid % NT, own_u = NT == 2 ? wid >> 1 : 0;   // the column block, and first 16 steps, that the wave splits
   const int voff = (h * 8 + (SPARSE ? 4 : 16) * own_u) * row_bytes + (32 * own_t + j) * 4;
   auto first_row = [&](int s) {
-    const int j1 = s / p.c2, v1 = j1 < 64 ? __builtin_amdgcn_readlane(adj_lo, j1) : __builtin_amdgcn_readlane(adj_hi, j1 - 64);
+    const int j1 = rbgp_fast::quotient(s, p.by_c2), v1 = j1 < 64 ? __builtin_amdgcn_readlane(adj_lo, j1) : __builtin_amdgcn_readlane(adj_hi, j1 - 64);
     return (int64_t(v1) * p.c2 + (s - j1 * p.c2)) * 32;
   };
   // sparse: row e of both halves of the stage in braw[2 e], braw[2 e + 1]; else row e of block own_u + u in braw[8 u + e]
@@ -618,6 +625,10 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
     __builtin_amdgcn_wave_barrier();            // (the next stage's weights come after these reads: one wave, in order)
   }
   // register i of block t: row 8 (i / 4) + 4 h + i % 4 of the wave's 32 (vertex ub + row / 4, row % 4), column 32 t + j
+  int64_t row_of[4];                            // row of O of row r of G_i vertex 0 (four rows a vertex: a4 is 1, 2 or 4)
+  const int lga4 = p.a4 >> 1;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) row_of[r] = (int64_t(u1) * p.a2 + (r >> lga4)) * p.a3 * p.a4 + (r & (p.a4 - 1));
   uint32_t again[TU] = {};                      // sums that are not finite: bit 16 (t % 2) + i of word t / 2
 #pragma unroll
   for (int t = 0; t < NT; ++t) add_up(acc[t], cor[t]);
@@ -642,7 +653,7 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
     const bool in = n0 + 32 * t + j < p.N;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const int64_t m = ((int64_t(u1) * p.a2 + (i % 4) / p.a4) * p.a3 + ub + 2 * (i / 4) + h) * p.a4 + (i % 4) % p.a4;
+      const int64_t m = row_of[i % 4] + (ub + 2 * (i / 4) + h) * p.a4;
       const bool finite = acc[t][i] * 0.f == 0.f;
       if (in && finite) __builtin_nontemporal_store(acc[t][i], p.O + m * p.ldO + n0 + 32 * t + j);
       if (in && !finite) again[t / 2] |= 1u << (16 * (t % 2) + i);
@@ -698,7 +709,7 @@ __global__ __launch_bounds__(256 * KSP, KSP == 1 && NT == 2 ? 3 : 2) void spmm_m
     for (int x = 0; x < TU; ++x)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t m = ((int64_t(u1) * p.a2 + r / p.a4) * p.a3 + ui) * p.a4 + r % p.a4;
+        const int64_t m = row_of[r] + int64_t(ui) * p.a4;
         if (need[x] >> r & 1u) p.O[m * p.ldO + n0 + 64 * x + lane] = sum[x][r];
       }
   }

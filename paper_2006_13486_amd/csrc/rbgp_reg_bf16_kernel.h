@@ -91,6 +91,7 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
   const int lgS = p.lgS, S = 1 << lgS;
   const int ks = wid & (S - 1);          // this wave's share of the stage list
   // workgroup -> (cluster, G_i vertex, 4/S neighbouring column tiles); see wg_coord
+  table_args(p);
   WgCoord wg;
   if (!wg_coord(p, &wg)) return;         // (the whole workgroup)
   const int cl = wg.cl, u3 = wg.u3, ntq = wg.ntq;

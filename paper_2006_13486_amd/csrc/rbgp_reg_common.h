@@ -8,6 +8,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "rbgp_fastdiv.h"
+
 namespace rbgp_reg {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -89,10 +91,34 @@ struct RegParams {
   int per_xcd;             // items (cluster, unit) per XCD
   int ngroups;             // groups of column tiles (one group per workgroup)
   int order;
+  int inner;               // G_i vertices, order 1: groups of column tiles
+  rbgp_fast::Div by_ncl, by_inner;   // (set_grid)
+  rbgp_fast::Div by_ct_cnt;
+  rbgp_fast::Div by_row, by_r, by_a4;   // spmm_reg_rows: a3 R, R, a4
 };
+
+// The fields that wg_coord divides by; after ncl, a3, ngroups and order.
+inline void set_grid(RegParams *p) {
+  p->inner = p->order == 1 ? p->ngroups : p->a3;
+  p->by_ncl = rbgp_fast::div_by(p->ncl);
+  p->by_inner = rbgp_fast::div_by(p->inner);
+}
 
 constexpr int kRsrcFlags = 0x00020000;  // raw buffer, 32-bit data format (gfx9 family)
 constexpr int kOob = 0x40000000;        // byte offset beyond any packed weight buffer (reads return 0)
+
+// What a prologue reads of the kernel arguments, requested at once: left to where they are used, they arrive in three or four scalar
+// loads that wait for one another.  Before wg_coord.
+__device__ __forceinline__ void grid_args(const RegParams &p) {
+  asm volatile("" ::"s"(p.order), "s"(p.per_xcd), "s"(p.ncl), "s"(p.inner), "s"(p.by_ncl.mul), "s"(p.by_ncl.shift), "s"(p.by_inner.mul),
+               "s"(p.by_inner.shift), "s"(p.ngroups), "s"(p.a3), "s"(p.ntiles));
+}
+__device__ __forceinline__ void table_args(const RegParams &p) {
+  asm volatile("" ::"s"(p.order), "s"(p.per_xcd), "s"(p.ncl), "s"(p.inner), "s"(p.by_ncl.mul), "s"(p.by_ncl.shift), "s"(p.by_inner.mul),
+               "s"(p.by_inner.shift), "s"(p.ngroups), "s"(p.a3), "s"(p.ntiles), "s"(p.lgS), "s"(p.rowtab), "s"(p.stages), "s"(p.counts),
+               "s"(p.members), "s"(p.tstride), "s"(p.no4), "s"(p.conv), "s"(p.Wp), "s"(p.I), "s"(p.w_bytes), "s"(p.row_bytes),
+               "s"(p.n_bytes), "s"(p.last_row), "s"(p.src_rows), "s"(p.fpm), "s"(int(p.ldI)));
+}
 
 // (cluster, G_i vertex, group of column tiles) of this workgroup; false: none (the workgroup leaves)
 struct WgCoord {
@@ -100,26 +126,13 @@ struct WgCoord {
 };
 __device__ __forceinline__ bool wg_coord(const RegParams &p, WgCoord *c) {
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  if (p.order == 2) {
-    const int per_group = p.ncl * p.a3, q = slot / per_group, rem = slot - q * per_group;
-    c->ntq = xcd + 8 * q;
-    if (c->ntq >= p.ngroups) return false;
-    c->u3 = rem / p.ncl;
-    c->cl = rem - c->u3 * p.ncl;
-    return true;
-  }
-  const int item = xcd * p.per_xcd + slot;
-  if (item >= p.ncl * p.a3 * p.ngroups) return false;
-  const int unit = item / p.ncl;
+  const int item = (p.order == 2 ? 0 : xcd * p.per_xcd) + slot;
+  const int unit = rbgp_fast::quotient(item, p.by_ncl);
   c->cl = item - unit * p.ncl;
-  if (p.order == 1) {
-    c->u3 = unit / p.ngroups;
-    c->ntq = unit - c->u3 * p.ngroups;
-  } else {
-    c->ntq = unit / p.a3;
-    c->u3 = unit - c->ntq * p.a3;
-  }
-  return true;
+  const int hi = rbgp_fast::quotient(unit, p.by_inner), lo = unit - hi * p.inner;
+  c->u3 = p.order == 1 ? hi : lo;
+  c->ntq = p.order == 1 ? lo : p.order == 2 ? xcd + 8 * hi : hi;
+  return p.order == 1 ? hi < p.a3 : c->ntq < p.ngroups;
 }
 
 // rowofs[r], or the same of G_i vertex u3 where it depends on that (rbgp_mask::merged).  Read from the row table for all masks: a
@@ -168,6 +181,7 @@ struct SplitTileParams {
   int64_t N, ldI, ldO;
   int a1, a2, a3, a4, d1, c2;
   int ntiles;              // column tiles of 32 NT
+  rbgp_fast::Div by_mt, by_gz, by_c2;   // workgroups of a column tile, of a tile row (a3 / 32)
 };
 }  // namespace rbgp_reg
 
@@ -185,6 +199,7 @@ struct ConvTileParams {
   int a1, a2, a3, a4, d1, R, RS, frag_bytes;
   int chunk;               // tiles staged at once
   int obf16;
+  rbgp_fast::Div by_per, by_hw, by_w, by_R, by_a4;   // per: workgroups of one column tile
 };
 }  // namespace rbgp_reg
 

@@ -4,6 +4,8 @@
 
 #include <cstdint>
 
+#include "rbgp_fastdiv.h"
+
 namespace rbgp_sddmm_detail {
 
 struct SddmmParams {
@@ -34,6 +36,8 @@ struct SddmmParams {
   int64_t chan_elems;       // elements of one channel of X
   int64_t x_bytes;          // size of X
   int conv_w2;              // W + 2
+  // workgroups that share the rows of I of a (tile column, stage) in sddmm_reg; the rest by name
+  rbgp_fast::Div by_sharing, by_halves, by_RBG, by_a3, by_NSTG, by_c1, by_R, by_a4;
 };
 
 constexpr int kLinesWaves = 8;   // waves of a workgroup of sddmm_lines

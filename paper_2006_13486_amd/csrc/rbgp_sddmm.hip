@@ -131,16 +131,21 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
   // a_i * RBG workgroups that share the rows of I of one (tile column, stage) take launch slots with
   // the same remainder modulo 8 (when the number of such groups is a multiple of 8).
   int x = blockIdx.x;
-  const int per_group = (GI ? 1 : p.a3) * p.RBG * p.halves, groups = gridDim.x / per_group;
+  const int per_group = (GI ? 1 : p.a3) * p.RBG * p.halves, groups = rbgp_fast::quotient(int(gridDim.x), p.by_sharing);
   if (groups % 8 == 0) {
-    const int xcd = x % 8, slot = x / 8;
-    x = ((slot / per_group) * 8 + xcd) * per_group + slot % per_group;
+    const int xcd = x & 7, slot = x >> 3, q = rbgp_fast::quotient(slot, p.by_sharing);
+    x = (q * 8 + xcd) * per_group + (slot - q * per_group);
   }
-  const int b0 = (x % p.halves) * NB; x /= p.halves;   // first 16-step group of this workgroup
-  const int g = x % p.RBG; x /= p.RBG;
+  auto split_off = [&](int n, rbgp_fast::Div by) {   // x = x / n; x % n
+    const int q = rbgp_fast::quotient(x, by), r = x - q * n;
+    x = q;
+    return r;
+  };
+  const int b0 = split_off(p.halves, p.by_halves) * NB;   // first 16-step group of this workgroup
+  const int g = split_off(p.RBG, p.by_RBG);
   int u3 = 0;
-  if constexpr (!GI) { u3 = x % p.a3; x /= p.a3; }
-  const int sg = x % p.NSTG, v1 = x / p.NSTG;
+  if constexpr (!GI) u3 = split_off(p.a3, p.by_a3);
+  const int sg = split_off(p.NSTG, p.by_NSTG), v1 = x;
   const int RS = 1 << p.lgRS;
   const int32_t *crow = p.colrows + v1 * p.EO, *cpos = p.colpos + v1 * p.EO;
   const int base = v1 * p.tile_rows + sg * p.stage_rows;
@@ -151,16 +156,18 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
     RowOf o{-1, 0, u3};
     int ri;
     if constexpr (GI) {
-      const int rho = (g * RB + rb) * 16 + r16;
-      ri = rho % p.R;
-      o.ui = (rho / p.R) % p.a3;
-      o.entry = rho / (p.R * p.a3);
+      const int rho = (g * RB + rb) * 16 + r16, block = rbgp_fast::quotient(rho, p.by_R);
+      ri = rho - block * p.R;
+      o.entry = rbgp_fast::quotient(block, p.by_a3);
+      o.ui = block - o.entry * p.a3;
     } else {
       o.entry = (g * RB + rb) * p.MG + (r16 >> p.lgRS);
       ri = r16 & (RS - 1);
     }
-    if (o.entry < p.EO && ri < p.R)
-      o.row = ((int64_t(crow[o.entry]) * p.a2 + ri / p.a4) * p.a3 + o.ui) * p.a4 + ri % p.a4;
+    if (o.entry < p.EO && ri < p.R) {
+      const int ra = rbgp_fast::quotient(ri, p.by_a4);
+      o.row = ((int64_t(crow[o.entry]) * p.a2 + ra) * p.a3 + o.ui) * p.a4 + (ri - ra * p.a4);
+    }
     return o;
   };
   int64_t off[NL];   // element offset of this lane's 16 bytes in iteration 0: dO rows, then I rows
@@ -753,6 +760,10 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   p.lgRS = 0;
   while ((1 << p.lgRS) < pl.RS) ++p.lgRS;
   p.MG = pl.MG; p.KCR = pl.KCR; p.rowdeg = int(m->rowdeg);
+  p.by_sharing = rbgp_fast::div_by(int64_t(gi ? 1 : p.a3) * RBG * halves);
+  p.by_halves = rbgp_fast::div_by(halves); p.by_RBG = rbgp_fast::div_by(RBG);
+  p.by_a3 = rbgp_fast::div_by(p.a3); p.by_NSTG = rbgp_fast::div_by(p.NSTG); p.by_c1 = rbgp_fast::div_by(p.c1);
+  p.by_R = rbgp_fast::div_by(p.R); p.by_a4 = rbgp_fast::div_by(p.a4);
   if (lines)
     fn<<<dim3(unsigned(blocks * nsplit)), dim3(64 * kLinesWaves), 0, hs>>>(p);
   else

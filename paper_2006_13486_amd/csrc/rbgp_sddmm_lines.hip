@@ -163,27 +163,36 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   // a tile in LDS: slot 8 * row + (segment ^ (row & 7)): eight consecutive lanes meet all banks, writing and reading
   const int wslot = 8 * lr + (ls ^ lr);
   const int rslot0 = 8 * j + (q ^ (j & 7)), rslot1 = 8 * j + ((q + 4) ^ (j & 7));
+  // (what the prologue reads of the kernel arguments, at once: see grid_args)
+  asm volatile("" ::"s"(p.by_halves.mul), "s"(p.by_halves.shift), "s"(p.by_RBG.mul), "s"(p.by_RBG.shift), "s"(p.by_a3.mul),
+               "s"(p.by_a3.shift), "s"(p.by_NSTG.mul), "s"(p.by_NSTG.shift), "s"(p.by_c1.mul), "s"(p.by_c1.shift), "s"(p.by_a4.mul),
+               "s"(p.by_a4.shift), "s"(p.order), "s"(p.colrows), "s"(p.rowtab), "s"(p.EO), "s"(p.dO), "s"(p.I), "s"(p.ld_dO), "s"(p.R),
+               "s"(p.tile_rows), "s"(p.stage_rows), "s"(p.lgRS), "s"(p.MG), "s"(p.chunk), "s"(p.N));
   // Workgroups go to the eight XCDs round-robin in launch order, and each XCD has its own L2: the unit numbers are dealt
   // to the XCDs in eight contiguous runs, so that those of one XCD read few rows (see `order`).
   int x;
   {
-    const int total = gridDim.x, xcd = blockIdx.x % 8, each = total / 8, more = total % 8;
-    x = xcd * each + (xcd < more ? xcd : more) + int(blockIdx.x) / 8;
+    const int total = gridDim.x, xcd = blockIdx.x & 7, each = total >> 3, more = total & 7;
+    x = xcd * each + (xcd < more ? xcd : more) + int(blockIdx.x >> 3);
   }
-  const int piece = x % p.halves; x /= p.halves;
-  const int b0 = piece * NB;                    // first 16-step group of this workgroup
-  const int g = x % p.RBG; x /= p.RBG;
-  const int nu3 = GI ? 1 : p.a3;
-  int u3 = 0, sg, v1, part;
+  auto split_off = [&](int n, rbgp_fast::Div by) {   // x = x / n; x % n
+    const int q = rbgp_fast::quotient(x, by), r = x - q * n;
+    x = q;
+    return r;
+  };
+  const int b0 = split_off(p.halves, p.by_halves) * NB;   // first 16-step group of this workgroup
+  const int g = split_off(p.RBG, p.by_RBG);
+  int u3 = 0, sg, v1;
   if (p.order == 1) {
-    sg = x % p.NSTG; x /= p.NSTG;
-    v1 = x % p.c1; x /= p.c1;
-    u3 = x % nu3; part = x / nu3;
+    sg = split_off(p.NSTG, p.by_NSTG);
+    v1 = split_off(p.c1, p.by_c1);
+    if constexpr (!GI) u3 = split_off(p.a3, p.by_a3);
   } else {
-    u3 = x % nu3; x /= nu3;
-    sg = x % p.NSTG; x /= p.NSTG;
-    v1 = x % p.c1; part = x / p.c1;
+    if constexpr (!GI) u3 = split_off(p.a3, p.by_a3);
+    sg = split_off(p.NSTG, p.by_NSTG);
+    v1 = split_off(p.c1, p.by_c1);
   }
+  const int part = x;
   const int RS = 1 << p.lgRS;
   const int32_t *crow = p.colrows + v1 * p.EO, *cpos = p.colpos + v1 * p.EO;
   const int base = v1 * p.tile_rows + sg * p.stage_rows;
@@ -194,16 +203,18 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     RowOf o{-1, 0, u3};
     int ri;
     if constexpr (GI) {
-      const int rho = (g * RB + rb) * 16 + r16;
-      ri = rho % p.R;
-      o.ui = (rho / p.R) % p.a3;
-      o.entry = rho / (p.R * p.a3);
+      const int rho = (g * RB + rb) * 16 + r16, block = rbgp_fast::quotient(rho, p.by_R);
+      ri = rho - block * p.R;
+      o.entry = rbgp_fast::quotient(block, p.by_a3);
+      o.ui = block - o.entry * p.a3;
     } else {
       o.entry = (g * RB + rb) * p.MG + (r16 >> p.lgRS);
       ri = r16 & (RS - 1);
     }
-    if (o.entry < p.EO && ri < p.R)
-      o.row = ((int64_t(crow[o.entry]) * p.a2 + ri / p.a4) * p.a3 + o.ui) * p.a4 + ri % p.a4;
+    if (o.entry < p.EO && ri < p.R) {
+      const int ra = rbgp_fast::quotient(ri, p.by_a4);
+      o.row = ((int64_t(crow[o.entry]) * p.a2 + ra) * p.a3 + o.ui) * p.a4 + (ri - ra * p.a4);
+    }
     return o;
   };
   // Byte offsets of this lane's 16 bytes in step 0.  CONV: below 2 GiB (inside X) and 4 GiB (inside dO), checked by the host, and the
