@@ -1320,7 +1320,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const bool wide = !uneven && tab->max_stages <= 4 && all > 256 && launched(tiles96) <= 256;
     const int64_t tiles = wide ? tiles96 : tiles64, wgs = launched(tiles);
     const size_t bytes = size_t(tab->max_stages) * (wide ? 18432 : 12288) + size_t(groups) * 512;
-    if (all >= 160 && !uneven && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
+    const bool near_rows = (int64_t(rows_wg) * ldO + 128) * 4 < (int64_t(1) << 32);   // (32-bit offsets into a workgroup's rows of O)
+    if (all >= 160 && !uneven && near_rows && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
       rp.ntiles = int(tiles);
       rp.ncl = int(rows_o);
       rp.order = tiles >= 8 ? 2 : 0;

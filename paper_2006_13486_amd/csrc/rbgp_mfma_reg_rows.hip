@@ -39,6 +39,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2_s __attribute__((ext_vector_type(2)));
 
 constexpr int kAhead = 4;                       // stages of weights in flight
+constexpr uint32_t kNone = 0xffffffffu;
 
 // T = 2: 64 columns, a pair of them per lane, lists of up to twelve stages.  T = 3: 96 columns, a block of 32 at a time, lists of up
 // to four stages.
@@ -63,14 +64,26 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   if (nt >= p.ntiles) return;                   // (the whole workgroup)
   const int64_t n0 = int64_t(nt) * CW;
   const int u1 = uo * p.fold, TS = p.tstride;
+  // The tables in one go (lanes past the list hold sentinels), the rows of I as soon as those are there, then the weights: a latency
+  // after the other from the first to the last of these took 9800 cycles before the first product, of 25000.
   const int32_t *stg = p.stages + int64_t(u1) * 2 * TS;
-  const int cnt = __builtin_amdgcn_readfirstlane(p.counts[u1]);
-  const int tb = lane < cnt ? stg[lane] : 0, tf = lane < cnt ? stg[TS + lane] : 0;   // (at most 12 stages)
+  const int tb0 = stg[lane], tf0 = stg[TS + lane], cnt0 = p.counts[u1];
   u32x4 *const parts = reinterpret_cast<u32x4 *>(lds);
-  // of every row: its row of O relative to the tile row's first (-1: none), its weights relative to a stage's, the places
-  // of its G_i vertex's two edges (the index operand)
-  int4 *const info = reinterpret_cast<int4 *>(lds + p.ct_cnt * (T * 6144));
+  // of every row: its byte offset in O from the tile row's first row (kNone: no such row), then: its weights relative to a stage's,
+  // the places of its G_i vertex's two edges (the index operand)
+  uint32_t *const row_at = reinterpret_cast<uint32_t *>(lds + p.ct_cnt * (T * 6144));
   const int per_row = p.a3 * p.R, rows = p.fold * per_row, groups = (rows + 31) >> 5;
+  int2 *const info = reinterpret_cast<int2 *>(row_at + groups * 32);
+  const uint32_t ld_bytes = uint32_t(p.ldO) * 4u;   // (a tile row of O is below 4 GiB: checked by the host)
+  // the edges of the G_i vertex of row x (of the rows that the thread prepares, the first)
+  auto edges_of = [&](int x) {
+    const int f = rbgp_fast::quotient(x, p.by_row), ui = rbgp_fast::quotient(x - f * per_row, p.by_r);
+    const int32_t *rt = p.rowtab + (x < rows ? ui * p.no4 : 0);
+    return int2{rt[0] >> 1, rt[2] >> 1};
+  };
+  int2 edges = edges_of(threadIdx.x);
+  const int cnt = __builtin_amdgcn_readfirstlane(cnt0);
+  const int tb = lane < cnt ? tb0 : 0, tf = lane < cnt ? tf0 : 0;   // (at most 12 stages)
   const int row_bytes = int(p.row_bytes);
   const __amdgpu_buffer_rsrc_t rw =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.Wp), 0, p.w_bytes, kRsrcFlags);
@@ -97,6 +110,27 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     a.x[0] = load_x4(rw, base + pos, 0);
     a.x[1] = load_x4(rw, base + pos, 512);
   };
+  // The rows of I that the wave splits, of its first two items (more only where a workgroup has few waves): T = 2: a stage, a pair of
+  // columns per lane; T = 3: a stage's column block.
+  constexpr int NV = T == 3 ? 16 : 32;
+  const int items = T == 3 ? cnt * T : cnt;
+  auto load_rows = [&](float (&x)[NV], int item) {
+    const int s = T == 3 ? item / 3 : item;
+    const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if constexpr (T == 3) {
+        x[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, row_of(h, e) * row_bytes + (32 * (item - 3 * s) + j) * 4, 0, 0));
+      } else {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rb, row_of(h, e) * row_bytes + j * 8, 0, 0);
+        x[e] = __uint_as_float(v[0]);
+        x[16 + e] = __uint_as_float(v[1]);
+      }
+    }
+  };
+  float x0[NV], x1[NV];
+  if (wid < items) load_rows(x0, wid);
+  if (wid + W < items) load_rows(x1, wid + W);
   A ring[kAhead];
   int a_base = a_of(wid * 32 + j) + h * 256;
 #pragma unroll
@@ -106,19 +140,28 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     const int f = rbgp_fast::quotient(x, p.by_row), q = x - f * per_row, ui = rbgp_fast::quotient(q, p.by_r), i = q - ui * p.R;
     const int ia = rbgp_fast::quotient(i, p.by_a4);
     const bool in = x < rows;
-    const int e0 = in ? p.rowtab[ui * p.no4] >> 1 : 0, e1 = in ? p.rowtab[ui * p.no4 + 2] >> 1 : 0;
-    info[x] = int4{in ? f * p.tm + ui * p.a4 + ia * p.a3 * p.a4 + i - ia * p.a4 : -1, a_of(x), (e0 | e1 << 2) * 0x1111, 0};
+    const int which = in ? (edges.x | edges.y << 2) * 0x1111 : 0;
+    if (x + int(blockDim.x) < groups * 32) edges = edges_of(x + int(blockDim.x));
+    row_at[x] = in ? uint32_t(f * p.tm + ui * p.a4 + ia * p.a3 * p.a4 + i - ia * p.a4) * ld_bytes : kNone;
+    info[x] = int2{a_of(x), which};
   }
-  auto keep = [&](const float (&x)[16], int block) {
+  auto keep = [&](const float (&x)[NV], int item) {
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int half = 0; half < NV / 8; ++half) {   // (T = 2: two column blocks)
+      const int block = T == 3 ? item : item * 2 + half / 2;
       const float y[8] = {x[8 * half], x[8 * half + 1], x[8 * half + 2], x[8 * half + 3],
                           x[8 * half + 4], x[8 * half + 5], x[8 * half + 6], x[8 * half + 7]};
       const Split b = split8(y);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) parts[((block * 3 + k) * 2 + half) * 64 + lane] = __builtin_bit_cast(u32x4, b.p[k]);
+      for (int k = 0; k < 3; ++k) parts[((block * 3 + k) * 2 + half % 2) * 64 + lane] = __builtin_bit_cast(u32x4, b.p[k]);
     }
   };
+  if (wid < items) keep(x0, wid);
+  if (wid + W < items) keep(x1, wid + W);
+  for (int item = wid + 2 * W; item < items; item += W) {
+    load_rows(x0, item);
+    keep(x0, item);
+  }
   auto weights = [&](const A &a) {
     const float w[8] = {a.x[0][0], a.x[1][0], a.x[0][1], a.x[1][1], a.x[0][2], a.x[1][2], a.x[0][3], a.x[1][3]};
     return split8(w);
@@ -135,25 +178,28 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
       c = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(a.p[pa[k]], b[pb[k]], c, which, 0, 0);
     }
   };
-  float *const out = p.O;
-  const int64_t out_ld = p.ldO, out_n = p.N;
-  if constexpr (T == 3) {
-    // every wave splits some of the stages' column blocks, then its first group's weights
-    for (int item = wid; item < cnt * T; item += W) {
-      const int s = item / T, t = item - s * T;
-      const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
-      float x[16];
+  // the tile row's first row of O, at the workgroup's first column; register i of the accumulators is row 8 (i / 4) + 4 h + i % 4 of a
+  // group
+  unsigned char *const out = reinterpret_cast<unsigned char *>(p.O + int64_t(u1) * p.tm * p.ldO + n0);
+  const int64_t out_n = p.N;
+  auto rows_at = [&](uint32_t (&at)[16], int g) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        x[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, row_of(h, e) * row_bytes + (32 * t + j) * 4, 0, 0));
-      keep(x, item);
+    for (int x = 0; x < 4; ++x) {
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(row_at + g * 32 + 8 * x + 4 * h);
+#pragma unroll
+      for (int y = 0; y < 4; ++y) at[4 * x + y] = v[y];
     }
+  };
+  if constexpr (T == 3) {
+    // (the first group's weights are split before the wave waits for the others)
     Split a[kAhead];
 #pragma unroll
     for (int d = 0; d < kAhead; ++d) a[d] = weights(ring[d]);
     __syncthreads();
     for (int g = wid; g < groups; g += W) {
-      const int which = info[g * 32 + j].z;
+      const int which = info[g * 32 + j].y;
+      uint32_t at[16];
+      rows_at(at, g);
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         f32x16 acc, cor;
@@ -164,7 +210,7 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
           if (d < cnt) multiply(a[d], d * T + t, which, acc, cor);
         const int64_t n = n0 + 32 * t + j;
         if (__builtin_amdgcn_ballot_w64(add_up(acc, cor) && n < out_n)) {   // (as below, with the one block)
-          uint64_t left = __builtin_amdgcn_ballot_w64(info[g * 32 + j].x >= 0);
+          uint64_t left = __builtin_amdgcn_ballot_w64(row_at[g * 32 + j] != kNone);
           while (left) {
             const int pair = __builtin_amdgcn_readlane(which, __builtin_ctzll(left));
             left &= ~__builtin_amdgcn_ballot_w64(which == pair);
@@ -185,19 +231,18 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-              const bool mine = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].z == pair;
+              const bool mine = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].y == pair;
               acc[i] = acc[i] * 0.f == 0.f || !mine ? acc[i] : cor[i];
             }
           }
         }
+        if (n < out_n)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int m = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].x;
-          if (m >= 0 && n < out_n) __builtin_nontemporal_store(acc[i], out + (int64_t(u1) * p.tm + m) * out_ld + n);
-        }
+          for (int i = 0; i < 16; ++i)
+            if (at[i] != kNone) __builtin_nontemporal_store(acc[i], reinterpret_cast<float *>(out + at[i] + uint32_t(128 * t + 4 * j)));
       }
       if (g + W < groups) {
-        a_base = info[(g + W) * 32 + j].y + h * 256;
+        a_base = info[(g + W) * 32 + j].x + h * 256;
 #pragma unroll
         for (int d = 0; d < kAhead; ++d) load_a(ring[d], d < cnt ? a_base : kOob, d < cnt ? d : 0);
 #pragma unroll
@@ -206,25 +251,12 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     }
     return;
   }
-  // every wave splits the rows of some stages
-  for (int s = wid; s < cnt; s += W) {
-    const __amdgpu_buffer_rsrc_t rb = stage_rsrc(s);
-    float x[2][16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rb, row_of(h, e) * row_bytes + j * 8, 0, 0);
-      x[0][e] = __uint_as_float(v[0]);
-      x[1][e] = __uint_as_float(v[1]);
-    }
-#pragma unroll
-    for (int t = 0; t < 2; ++t) keep(x[t], s * 2 + t);
-  }
   __syncthreads();
 
-  const bool vec_ok = (out_ld % 2 == 0) && (reinterpret_cast<uintptr_t>(out) % 8 == 0) && n0 + 2 * j + 2 <= out_n;
+  const bool vec_ok = (p.ldO % 2 == 0) && (reinterpret_cast<uintptr_t>(out) % 8 == 0) && n0 + 2 * j + 2 <= out_n;
   for (int g = wid; g < groups; g += W) {
-    const int which = info[g * 32 + j].z, base = a_base;
-    a_base = g + W < groups ? info[(g + W) * 32 + j].y + h * 256 : kOob;
+    const int which = info[g * 32 + j].y, base = a_base;
+    a_base = g + W < groups ? info[(g + W) * 32 + j].x + h * 256 : kOob;
     f32x16 acc[2], cor[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -249,7 +281,7 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     if (__builtin_amdgcn_ballot_w64(again)) {   // (wave-uniform; no barrier inside)
       // The rows of one pair of edges at a time, with the rows of I at these edges only: a row of I that is not finite must not
       // meet a zero in the place of a weight.
-      uint64_t left = __builtin_amdgcn_ballot_w64(info[g * 32 + j].x >= 0);
+      uint64_t left = __builtin_amdgcn_ballot_w64(row_at[g * 32 + j] != kNone);
       while (left) {
         const int pair = __builtin_amdgcn_readlane(which, __builtin_ctzll(left));
         left &= ~__builtin_amdgcn_ballot_w64(which == pair);
@@ -274,26 +306,26 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const bool mine = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].z == pair;
+          const bool mine = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].y == pair;
 #pragma unroll
           for (int t = 0; t < 2; ++t)   // (every finite sum stays as it is, bit for bit)
             acc[t][i] = acc[t][i] * 0.f == 0.f || !mine ? acc[t][i] : cor[t][i];
         }
       }
     }
+    uint32_t at[16];
+    rows_at(at, g);
+    if (vec_ok) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int m = info[g * 32 + 8 * (i / 4) + 4 * h + i % 4].x;
-      if (m >= 0) {
-        float *o = out + (int64_t(u1) * p.tm + m) * out_ld + n0 + 2 * j;
-        if (vec_ok) {
-          __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_s *>(o));
-        } else {
+      for (int i = 0; i < 16; ++i)
+        if (at[i] != kNone) __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_s *>(out + at[i] + uint32_t(8 * j)));
+    } else {
 #pragma unroll
-          for (int t = 0; t < 2; ++t)
-            if (n0 + 2 * j + t < out_n) o[t] = acc[t][i];
-        }
-      }
+      for (int t = 0; t < 2; ++t)
+        if (n0 + 2 * j + t < out_n)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (at[i] != kNone) *reinterpret_cast<float *>(out + at[i] + uint32_t(8 * j + 4 * t)) = acc[t][i];
     }
   }
 }
