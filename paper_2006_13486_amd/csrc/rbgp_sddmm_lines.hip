@@ -197,6 +197,27 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
   const int32_t *crow = p.colrows + v1 * p.EO, *cpos = p.colpos + v1 * p.EO;
   const int base = v1 * p.tile_rows + sg * p.stage_rows;
 
+  // The wave's columns, and where the first of them start inside a channel: requested with the tables, not behind them.
+  const int64_t n_lo = (int64_t(part) * kWaves + wave) * p.chunk;
+  const int64_t n_hi = n_lo + p.chunk < p.N ? n_lo + p.chunk : p.N;   // (n_lo may lie past N: empty range)
+  const int64_t steps = n_hi > n_lo ? (n_hi - n_lo) / CPI : 0;        // whole steps
+  // (past the last step the loads repeat it: in bounds)
+  const int64_t n_last = n_lo + (steps - 1) * CPI;
+  auto column = [&](int64_t k) {
+    const int64_t c = n_lo + k * CPI;
+    return c < n_last ? c : n_last;
+  };
+  // CONV: where this lane's group of columns starts inside a channel (columns are pixels in image order)
+  // (in elements: scaled here, a lookup would be waited for where it is made)
+  auto pixel = [&](int64_t n) { return CONV ? p.colbase[n / CPL + ls] : 0; };
+  int at_first[2] = {0, 0}, at_next[2] = {0, 0};   // pixel of steps 0 and 1; of the step that refills set d next, a round ahead
+  if (CONV && steps > 0) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) at_first[d] = pixel(column(d));
+#pragma unroll
+    for (int d = 0; d < 2; ++d) at_next[d] = pixel(column(2 + d));
+  }
+
   // row r16 of row group rb of this workgroup: (row of dO, or -1; its entry of the tile-row list; its u_i)
   struct RowOf { int64_t row; int entry, ui; };
   auto row_of = [&](int rb, int r16) {
@@ -255,8 +276,17 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       offB[i] = Off(int64_t(k) * p.ldI * ES + ls * 16);
     }
   }
-  // CONV: where this lane's group of columns starts inside a channel (columns are pixels in image order)
-  auto pixel = [&](int64_t n) { return CONV ? p.colbase[n / CPL + ls] * ES : 0; };
+  // Where the lane's sums go, with the tables as well: looked up at the end, row after row, they cost two latencies each.
+  float *dst[RB];                               // first of the row's kept values of the stage; nullptr: no such row
+  int dst_ui[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const RowOf o = row_of(rb, 4 * q + wave % 4);
+    // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
+    dst[rb] = o.row < 0 ? nullptr
+                        : p.out + int64_t(part) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
+    dst_ui[rb] = o.ui;
+  }
   __amdgpu_buffer_rsrc_t arsrc, xrsrc;
   if constexpr (CONV) {
     if constexpr (!FAR) arsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.dO), 0, -1, kRsrcFlags);
@@ -279,7 +309,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
 #pragma unroll
     for (int i = 0; i < NLI; ++i) {
       if constexpr (CONV) {
-        const int o = int(offB[i]) + at;
+        const int o = int(offB[i]) + at * ES;
         r.b[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, o, 0, 0);
         if constexpr (BF16) {
           r.w[i][0] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, o, 16, 0);
@@ -410,24 +440,13 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
     }
   };
 
-  const int64_t n_lo = (int64_t(part) * kWaves + wave) * p.chunk;
-  const int64_t n_hi = n_lo + p.chunk < p.N ? n_lo + p.chunk : p.N;   // (n_lo may lie past N: empty range)
-  const int64_t steps = n_hi > n_lo ? (n_hi - n_lo) / CPI : 0;        // whole steps
   clear(acc);
   if constexpr (!BF16) clear(cor);
   if (steps > 0) {
-    // two steps of loads in flight; past the last step the loads repeat it (in bounds)
-    const int64_t n_last = n_lo + (steps - 1) * CPI;
-    auto column = [&](int64_t k) {
-      const int64_t c = n_lo + k * CPI;
-      return c < n_last ? c : n_last;
-    };
+    // two steps of loads in flight
     Raw raw[2];
-    int at_next[2];   // pixel(column(k + 2)) of the step that refills set d next, requested one round earlier
 #pragma unroll
-    for (int d = 0; d < 2; ++d) load_all(raw[d], column(d), pixel(column(d)));
-#pragma unroll
-    for (int d = 0; d < 2; ++d) at_next[d] = pixel(column(2 + d));
+    for (int d = 0; d < 2; ++d) load_all(raw[d], column(d), at_first[d]);
     auto step = [&](int d, int64_t k) {
       Ops o;
       transpose_all(o, raw[d]);
@@ -496,6 +515,20 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
 
   // acc[b][rb][i] = dW block element (row 4 * q + i of row group rb, contraction step 16 * b + j; WIN: tap b % 3 of pixel row
   // 16 * (b / 3) + j); the waves take turns at adding them up
+  constexpr int TN = (RB * NB + kWaves / 4 - 1) / (kWaves / 4);
+  const int first_t = wave / 4;
+  float *to[TN];                                // nullptr: nothing to store
+#pragma unroll
+  for (int x = 0; x < TN; ++x) {
+    const int t = first_t + x * (kWaves / 4), b = t % NB;
+    // contraction step of this lane's column: 16 * b + j, or (gi) wherever G_i puts stage row 16 * b + j for u_i
+    const int st = WIN ? 16 * b0 + 3 * (16 * (b / 3) + j) + b % 3 : 16 * (b0 + b) + j;
+    float *const d = RB == 1 || t < NB ? dst[0] : dst[RB - 1];
+    const int ui = RB == 1 || t < NB ? dst_ui[0] : dst_ui[RB - 1];
+    const bool in = t < RB * NB && d && st < p.nbt * 16;
+    const int kk = !in ? -1 : GI ? p.spos[ui * p.nbt * 16 + st] : (st < p.KCR ? st : -1);
+    to[x] = kk >= 0 ? d + kk : nullptr;
+  }
   __syncthreads();   // (the tiles are done with)
 #pragma unroll
   for (int b = 0; b < NB; ++b)
@@ -505,23 +538,18 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       for (int i = 0; i < 4; ++i) lds.red[wave][(rb * NB + b) * 4 + i][lane] = acc[b][rb][i];
   __syncthreads();
   // wave w: register i = w % 4 of every other (row group, step group)
+  float sum[TN];
 #pragma unroll
-  for (int t = 0; t < RB * NB; ++t) {
-    if (t % (kWaves / 4) != wave / 4) continue;
-    const int rb = t / NB, b = t % NB, e = t * 4 + wave % 4;
-    const RowOf o = row_of(rb, 4 * q + wave % 4);
-    if (o.row < 0) continue;
-    // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
-    float *dst = p.out + int64_t(part) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
-    // contraction step of this lane's column: 16 * b + j, or (gi) wherever G_i puts stage row 16 * b + j for u_i
-    const int st = WIN ? 16 * b0 + 3 * (16 * (b / 3) + j) + b % 3 : 16 * (b0 + b) + j;
-    const int kk = st >= p.nbt * 16 ? -1 : GI ? p.spos[o.ui * p.nbt * 16 + st] : (st < p.KCR ? st : -1);
-    float sum = 0.f;
+  for (int x = 0; x < TN; ++x) {
+    const int e = (first_t + x * (kWaves / 4) < RB * NB ? first_t + x * (kWaves / 4) : 0) * 4 + wave % 4;
+    sum[x] = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; w += 4)
-      sum += (lds.red[w][e][lane] + lds.red[w + 1][e][lane]) + (lds.red[w + 2][e][lane] + lds.red[w + 3][e][lane]);
-    if (kk >= 0) dst[kk] = sum;
+      sum[x] += (lds.red[w][e][lane] + lds.red[w + 1][e][lane]) + (lds.red[w + 2][e][lane] + lds.red[w + 3][e][lane]);
   }
+#pragma unroll
+  for (int x = 0; x < TN; ++x)
+    if (to[x]) *to[x] = sum[x];
 }
 
 template <int RB, bool BF16, bool CONV, bool GI, bool FAR>
