@@ -373,9 +373,8 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
   float *const out = p.O;
   const int64_t out_ld = p.ldO, out_n = p.N;
   const int out_tm = p.tm, out_a4 = p.a4, out_r = p.R;
-  const bool out_aligned = (out_ld % 4 == 0) && (reinterpret_cast<uintptr_t>(out) % 16 == 0);
-  auto vec_ok_at = [&](int64_t n0c) { return out_aligned && (n0c + j * 4 + 4 <= out_n); };
-  auto store_unit = [&](int t, f32x4 v, int k, int64_t n0c, bool vec_ok) {
+  auto whole_at = [&](int64_t n0c) { return n0c + j * 4 + 4 <= out_n; };
+  auto store_unit = [&](int t, f32x4 v, int k, int64_t n0c, bool whole) {
     const int i16 = 4 * g + t, mm = i16 / RS, r = i16 % RS;
     int u1 = __builtin_amdgcn_ds_bpermute(mm * 4, memv);
     if constexpr (NG > 1) u1 = u1 >= 0 ? u1 + k : u1;   // (group k is the tile row after group k - 1's)
@@ -383,8 +382,8 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
     if (valid && u1 >= 0 && r < out_r) {
       const int64_t m = int64_t(u1) * out_tm + u3 * out_a4 + ro;
       float *o = out + m * out_ld + n0c + j * 4;
-      if (vec_ok) {
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(o));
+      if (whole) {
+        store_x4(o, v);
       } else {
 #pragma unroll
         for (int w = 0; w < 4; ++w)
@@ -393,11 +392,11 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
     }
   };
   auto store_tile = [&](int64_t n0c) {
-    const bool vec_ok = vec_ok_at(n0c);
+    const bool whole = whole_at(n0c);
 #pragma unroll
     for (int k = 0; k < NG; ++k)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) store_unit(t, unit(t, k), k, n0c, vec_ok);
+      for (int t = 0; t < 4; ++t) store_unit(t, unit(t, k), k, n0c, whole);
   };
 
   // The register sets take turns; stages past the end read zeros (sentinel table lanes).
@@ -466,7 +465,7 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
     // adds up the ones it owns in wave order, so the result does not depend on timing.
     f32x4 *const red4 = reinterpret_cast<f32x4 *>(wlds);
     const int per_wave = (4 >> lgS) * (S - 1);
-    const bool vec_ok = vec_ok_at(n0);
+    const bool whole = whole_at(n0);
 #pragma unroll
     for (int k = 0; k < NG; ++k)
 #pragma unroll
@@ -489,7 +488,7 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
             else
               v += red4[((k * 4 + w0 + kk) * per_wave + (t >> lgS) * (S - 1) + ks - (ks > kk ? 1 : 0)) * 64 + lane];
           }
-          store_unit(t, v, k, n0, vec_ok);
+          store_unit(t, v, k, n0, whole);
         }
       }
   }

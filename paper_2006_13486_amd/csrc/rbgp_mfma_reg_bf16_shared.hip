@@ -11,7 +11,9 @@
 // What bounds it: the traffic past the L2s (every XCD reads all packed weights of its columns; 5 TB/s with the stores,
 // what a copy reaches) and LDS reads, which a wave of two row pairs (PR = 2) halves per product.  Measured, 4096^3, density
 // 1/8, four rows per column set, fp32 output: 85 us -> 45 (740 TFLOP/s on the filled mask), bf16 output 72 -> 44; one wave
-// group of 4 x 1 with PR = 1 56; three waves per SIMD with one buffer 57; two rounds of loads in flight 49 (against 50).
+// group of 4 x 1 with PR = 1 56; three waves per SIMD with one buffer 57; two rounds of loads in flight 49 (against 50).  The
+// stores' offsets ahead of the stores and descriptors that the compiler knows to be uniform: fp32 output 41.8 us -> 40.2, transposed
+// VGG19 layer 3 at 1/2, 71 images 20 -> 17.5; rows of O in one store a lane whatever their alignment: store_x4.
 #include <hip/hip_runtime.h>
 
 #include "rbgp_internal.h"
@@ -119,6 +121,10 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_bf16_shared(RegParams p) {
     next(sa, qa);
     if (k < wr) next(si, qi);
   }
+  // (uniform, which the compiler does not see of a count that starts at the wave's number: it put a loop over the lanes' descriptors
+  // around every load of I, eight of 20 instructions each a round)
+  if (RV > 1) si = __builtin_amdgcn_readfirstlane(si);
+  if (RV > 1) qi = __builtin_amdgcn_readfirstlane(qi);
   load_i(si, qi);
   const int rounds = (cnt * nq + NB - 1) / NB;
   for (int r = 0; r < rounds; ++r) {
@@ -163,37 +169,42 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_bf16_shared(RegParams p) {
     });
   }
 
-  // lane j holds the columns 8 (j % 16) + 4 (j / 16) .. + 3, register i the weight row 8 (i / 4) + 4 h + i % 4 of the 32
+  // lane j holds the columns 8 (j % 16) + 4 (j / 16) .. + 3, register i the weight row 8 (i / 4) + 4 h + i % 4 of the 32: row
+  // 8 (i / 4 % 2) + 4 h + i % 4 of the i / 8-th tile row.  Offsets first, then the stores, so that none of them waits for another.
+  if (!valid) return;
   const bool aligned = out_ld % 4 == 0 && reinterpret_cast<uintptr_t>(out) % (out_bf16 ? 8 : 16) == 0;
   const int64_t n = n0 + 8 * (j & 15) + 4 * (j >> 4);
-  const bool vec_ok = aligned && n + 4 <= out_n;
+  const bool whole = n + 4 <= out_n;
+  int64_t row_at[8];                            // of the eight rows of a tile row that the lane holds; -1: none
+  row_offsets(row_at, rov, h, out_r, out_ld);
+  const int64_t first = (int64_t(u1) * out_tm + u3 * out_a4) * out_ld + n, next_row = int64_t(out_tm) * out_ld;
+  auto each = [&](auto put) {
 #pragma unroll
-  for (int y = 0; y < PR; ++y)
+    for (int y = 0; y < PR; ++y)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r32 = 8 * (i / 4) + 4 * h + i % 4, r = r32 & 15;
-      const int ro = __builtin_amdgcn_ds_bpermute(r * 4, rov);
-      if (valid && r < out_r) {
-        const int64_t at = (int64_t(u1 + 2 * y + (r32 >> 4)) * out_tm + u3 * out_a4 + ro) * out_ld + n;
-        const f32x4 v = {acc[y][0][i], acc[y][1][i], acc[y][2][i], acc[y][3][i]};
-        if (out_bf16) {
-          uint16_t *const d = reinterpret_cast<uint16_t *>(out) + at;
-          if (vec_ok) {
-            __builtin_nontemporal_store(u32x2{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])}, reinterpret_cast<u32x2 *>(d));
-          } else {
+      for (int i = 0; i < 16; ++i)
+        if (row_at[i & 7] >= 0)
+          put(first + (2 * y + (i >> 3)) * next_row + row_at[i & 7], f32x4{acc[y][0][i], acc[y][1][i], acc[y][2][i], acc[y][3][i]});
+  };
+  uint16_t *const out16 = reinterpret_cast<uint16_t *>(out);
+  // (aligned rows past the caches; of others, the parts of a line that two workgroups write meet in the L2: 2047 columns 46.8 -> 44.9 us)
+  if (whole && aligned && out_bf16)
+    each([&](int64_t at, const f32x4 &v) { store_x4(out16 + at, v); });
+  else if (whole && aligned)
+    each([&](int64_t at, const f32x4 &v) { store_x4(out + at, v); });
+  else if (whole && out_bf16)
+    each([&](int64_t at, const f32x4 &v) { store_x4<false>(out16 + at, v); });
+  else if (whole)
+    each([&](int64_t at, const f32x4 &v) { store_x4<false>(out + at, v); });
+  else
+    each([&](int64_t at, const f32x4 &v) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w)
-              if (n + w < out_n) d[w] = uint16_t(bf16_bits(v[w]));
-          }
-        } else if (vec_ok) {
-          __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(out + at));
-        } else {
-#pragma unroll
-          for (int w = 0; w < 4; ++w)
-            if (n + w < out_n) out[at + w] = v[w];
+      for (int w = 0; w < 4; ++w)
+        if (n + w < out_n) {
+          if (out_bf16) out16[at + w] = uint16_t(bf16_bits(v[w]));
+          else out[at + w] = v[w];
         }
-      }
-    }
+    });
 }
 
 }  // namespace

@@ -195,14 +195,17 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
     return v;
   };
   f32x4 *const x4 = reinterpret_cast<f32x4 *>(xlds);   // [column tile][x of the giver][unit][lane]
+  const int u1 = g < 2 ? rowL : rowH;
+  int ro[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) ro[t] = __builtin_amdgcn_ds_bpermute((4 * (g & 1) + t) * 4, rov);
   if (x != y) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) x4[((ct * 2 + x) * 4 + t) * 64 + lane] = unit(t);
   }
   __syncthreads();
   if (x != y) return;
-  const bool vec_ok = (out_ld % 4 == 0) && (reinterpret_cast<uintptr_t>(out) % 16 == 0) && (n0 + j * 4 + 4 <= out_n);
-  const int u1 = g < 2 ? rowL : rowH;
+  const bool whole = n0 + j * 4 + 4 <= out_n;
   // wave (0, 0): lo rows from (0, 1), hi rows from (1, 0); wave (1, 1): lo rows from (1, 0), hi rows from (0, 1)
   const int giver = g < 2 ? x : 1 - x;
 #pragma unroll
@@ -212,12 +215,11 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
     // (wave (., 0)'s sum first for a lo row, wave (0, .)'s for a hi row, whichever wave adds them)
     const f32x4 v = mine + other;
     const int r = 4 * (g & 1) + t;
-    const int ro = __builtin_amdgcn_ds_bpermute(r * 4, rov);
     if (valid && u1 >= 0 && r < out_r) {
-      const int64_t m = int64_t(u1) * out_tm + u3 * out_a4 + ro;
+      const int64_t m = int64_t(u1) * out_tm + u3 * out_a4 + ro[t];
       float *o = out + m * out_ld + n0 + j * 4;
-      if (vec_ok) {
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(o));
+      if (whole) {
+        store_x4(o, v);
       } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c)

@@ -37,6 +37,7 @@ namespace {
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2_s __attribute__((ext_vector_type(2)));
+typedef f32x2_s f32x2_any __attribute__((aligned(4)));
 
 constexpr int kAhead = 4;                       // stages of weights in flight
 constexpr uint32_t kNone = 0xffffffffu;
@@ -253,7 +254,7 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   }
   __syncthreads();
 
-  const bool vec_ok = (p.ldO % 2 == 0) && (reinterpret_cast<uintptr_t>(out) % 8 == 0) && n0 + 2 * j + 2 <= out_n;
+  const bool whole = n0 + 2 * j + 2 <= out_n;
   for (int g = wid; g < groups; g += W) {
     const int which = info[g * 32 + j].y, base = a_base;
     a_base = g + W < groups ? info[(g + W) * 32 + j].x + h * 256 : kOob;
@@ -315,10 +316,10 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     }
     uint32_t at[16];
     rows_at(at, g);
-    if (vec_ok) {
+    if (whole) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (at[i] != kNone) __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_s *>(out + at[i] + uint32_t(8 * j)));
+        if (at[i] != kNone) __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_any *>(out + at[i] + uint32_t(8 * j)));
     } else {
 #pragma unroll
       for (int t = 0; t < 2; ++t)

@@ -171,15 +171,15 @@ __global__ __launch_bounds__(256, 2) void spmm_reg_split(RegParams p) {
 
   // Epilogue.  Unit i = register i of the four accumulators: weight row 8 (i / 4) + 4 (lane / 32) + i % 4 of the wave's
   // 32, the lane's four columns 4 j .. 4 j + 3.
-  const bool vec_ok = (out_ld % 4 == 0) && (reinterpret_cast<uintptr_t>(out) % 16 == 0) && (n0 + j * 4 + 4 <= out_n);
+  const bool whole = n0 + j * 4 + 4 <= out_n;
   auto store_unit = [&](int i, f32x4 v) {
     const int r32 = 8 * (i / 4) + 4 * h + i % 4, r = r32 & 15;
     const int ro = __builtin_amdgcn_ds_bpermute(r * 4, rov);
     if (valid && r < out_r) {
       const int64_t m = int64_t(u1 + (r32 >> 4)) * out_tm + u3 * out_a4 + ro;
       float *o = out + m * out_ld + n0 + j * 4;
-      if (vec_ok) {
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(o));
+      if (whole) {
+        store_x4(o, v);
       } else {
 #pragma unroll
         for (int w = 0; w < 4; ++w)

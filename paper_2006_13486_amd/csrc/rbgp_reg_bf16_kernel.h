@@ -302,11 +302,9 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
 
   // Epilogue.  Unit (gi, t) = register t of group gi's NC accumulators: weight row
   // 4*(lane/16) + t of the group, lane j the columns NC*j + w.
-  // (bf16 output: a lane's NC columns are 2 * NC bytes, stored whole when they are aligned)
+  // (bf16 output: a lane's NC columns are 2 * NC bytes in one store)
   const bool obf = out_bf16 != 0;
-  const bool vec_ok = (n0 + j * NC + NC <= out_n) &&
-                      (obf ? (out_ld % NC == 0) && (reinterpret_cast<uintptr_t>(out) % (2 * NC) == 0)
-                           : (out_ld % 4 == 0) && (reinterpret_cast<uintptr_t>(out) % 16 == 0));
+  const bool whole = n0 + j * NC + NC <= out_n;
   auto unit_piece = [&](int gi, int t, int h) {
     return f32x4{acc[gi][4 * h][t], acc[gi][4 * h + 1][t], acc[gi][4 * h + 2][t], acc[gi][4 * h + 3][t]};
   };
@@ -318,14 +316,13 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
       const int64_t m = int64_t(u1) * out_tm + u3 * out_a4 + ro;
       if (obf) {
         uint16_t *o = reinterpret_cast<uint16_t *>(out) + m * out_ld + n0 + j * NC;
-        if (vec_ok) {
+        if (whole) {
           if constexpr (NH == 2) {
             const u32x4 w = {bf16_pair(v[0][0], v[0][1]), bf16_pair(v[0][2], v[0][3]), bf16_pair(v[1][0], v[1][1]),
                              bf16_pair(v[1][2], v[1][3])};
-            __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(o));
+            __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any *>(o));
           } else {
-            const u32x2 w = {bf16_pair(v[0][0], v[0][1]), bf16_pair(v[0][2], v[0][3])};
-            __builtin_nontemporal_store(w, reinterpret_cast<u32x2 *>(o));
+            store_x4(o, v[0]);
           }
         } else {
 #pragma unroll
@@ -337,9 +334,9 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
         return;
       }
       float *o = out + m * out_ld + n0 + j * NC;
-      if (vec_ok) {
+      if (whole) {
 #pragma unroll
-        for (int h = 0; h < NH; ++h) __builtin_nontemporal_store(v[h], reinterpret_cast<f32x4 *>(o) + h);
+        for (int h = 0; h < NH; ++h) store_x4(o + 4 * h, v[h]);
       } else {
 #pragma unroll
         for (int h = 0; h < NH; ++h)

@@ -143,6 +143,35 @@ __device__ __forceinline__ int row_offset(const RegParams &p, int u3, int r) {
   return p.rowtab[p.a3 * p.no4 + u3 * 16 + r];
 }
 
+// A lane's four neighbouring columns of a row of O in one store, whatever the alignment of the row (that of an element): rows of an odd
+// number of columns begin anywhere, and column by column their stores were a quarter of some kernels (4096 x 4096 at 1/8 in bf16, 4001
+// columns 37.5 us -> 31, 3374 54 -> 47; at 1/4, 331 columns 23.1 -> 20.9; fp32, 3331 columns 213 -> 202).  PAST: past the caches.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef unsigned int u32x2_out __attribute__((ext_vector_type(2)));
+typedef u32x2_out u32x2_any __attribute__((aligned(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+template <bool PAST = true>
+__device__ __forceinline__ void store_x4(float *o, const f32x4 &v) {
+  if constexpr (PAST) __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any *>(o));
+  else *reinterpret_cast<f32x4_any *>(o) = v;
+}
+template <bool PAST = true>
+__device__ __forceinline__ void store_x4(uint16_t *o, const f32x4 &v) {
+  const u32x2_out w = {bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])};
+  if constexpr (PAST) __builtin_nontemporal_store(w, reinterpret_cast<u32x2_any *>(o));
+  else *reinterpret_cast<u32x2_any *>(o) = w;
+}
+
+// Element offsets of the weight rows that a lane of half h holds of a 16-row group in the 32x32 MFMAs' layout, 8 (x / 4) + 4 h + x % 4,
+// from the group's first row of O; -1: no such row.  rov: row_offset of row lane % 16.
+__device__ __forceinline__ void row_offsets(int64_t (&at)[8], int rov, int h, int rows, int64_t ldO) {
+  int ro[8];
+#pragma unroll
+  for (int x = 0; x < 8; ++x) ro[x] = __builtin_amdgcn_ds_bpermute((8 * (x / 4) + 4 * h + x % 4) * 4, rov);
+#pragma unroll
+  for (int x = 0; x < 8; ++x) at[x] = 8 * (x / 4) + 4 * h + x % 4 < rows ? ro[x] * ldO : -1;
+}
+
 __device__ __forceinline__ f32x4 load_x4(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
   return f32x4{__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3])};
