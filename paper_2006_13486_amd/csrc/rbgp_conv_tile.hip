@@ -17,8 +17,9 @@
 // sums is then that of the register kernels or less (VGG19 layer 9 at 1/4: 6.7e-8 against 9.2e-8; one chain 13e-8).
 //
 // us, VGG19 conv3 at 8192 pixels, both ways: register kernels 15.3 and 16.7, four waves that load two pixels of a channel at a
-// time and pass the phases one after the other 13.5, this one 10.1; layer 9 at 1/8, 2048 pixels 14.6, 11.2, 8.5; the other sizes
-// stand at the dispatch rule.  What bounds it: a chain of latencies (launch 2.5; tables 1; the channels, all of conv3's in one
+// time and pass the phases one after the other 13.5, this one 9.5 (10.1 with the tiles of a row looked up and dealt to the waves in the
+// prologue and the weights loaded before the channels); layer 9 at 1/8, 2048 pixels 14.6, 11.2, 8; the other sizes
+// stand at the dispatch rule.  What bounds it: a chain of latencies (launch 2.5; tables 0.6; the channels, all of conv3's in one
 // round of loads; their first use) and then issue: 1000 vector instructions and 800 cycles of products a wave, two waves a SIMD.
 // Counters (conv3): waves wait for 44 % of their cycles (four waves 41, of a longer launch), matrix core 11 % busy, vector
 // instructions 40 % of a SIMD's cycles, bank conflicts 3070 cycles per CU (3420 with lane j on pixel j, 36.3 -> 35.9 for the training
@@ -62,25 +63,18 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
   const int per = (p.a1 + kRows - 1) / kRows;   // workgroups of one column tile, all on XCD tile % 8
   // (what the prologue reads of the kernel arguments, at once: see grid_args)
   asm volatile("" ::"s"(p.by_per.mul), "s"(p.by_per.shift), "s"(p.by_hw.mul), "s"(p.by_hw.shift), "s"(p.by_w.mul), "s"(p.by_w.shift),
-               "s"(p.by_R.mul), "s"(p.by_R.shift), "s"(p.a1), "s"(p.ntiles), "s"(p.tiles),
+               "s"(p.by_R.mul), "s"(p.by_R.shift), "s"(p.a1), "s"(p.ntiles), "s"(p.tiles), "s"(p.rows),
                "s"(p.sel), "s"(p.Wp), "s"(p.X), "s"(p.chan), "s"(p.n), "s"(p.h), "s"(p.w), "s"(p.w2), "s"(p.hw), "s"(p.R), "s"(p.RS),
                "s"(p.frag_bytes), "s"(p.a3), "s"(p.w_bytes), "s"(p.d1));
   const int slot = blockIdx.x >> 3, stripe = rbgp_fast::quotient(slot, p.by_per), nt = int(blockIdx.x & 7) + 8 * stripe, ug = slot - stripe * per;
   if (nt >= p.ntiles) return;
   const int u1 = ug * kRows + wr;
-  uint64_t mine = 0, left = 0;                  // tile columns of the wave's row; those of the workgroup's rows still to come
-#pragma unroll
-  for (int w = 0; w < kRows; ++w) {
-    const uint64_t t = ug * kRows + w < p.a1 ? p.tiles[ug * kRows + w] : 0;
-    left |= t;
-    if (w == wr) mine = t;
-  }
-  uint64_t todo = 0;                            // those that are this wave's (in ascending order, as the chunks are)
-  {
-    uint64_t m = mine;
-    for (int k = 0; m; ++k, m &= m - 1)
-      if (k % S == ws) todo |= m & -m;
-  }
+  // tile columns of the wave's row; those of the workgroup's rows still to come; those that are this wave's, in ascending order as the
+  // chunks are (one load of five words: row by row behind their conditions, and dealt to the waves here, they took 1100 cycles)
+  const uint64_t *const tiles = p.tiles + ug * kRows;
+  const uint64_t mine = tiles[wr];
+  uint64_t left = tiles[0] | tiles[1] | tiles[2] | tiles[3], todo = S == 1 ? mine : tiles[(1 + ws) * p.rows + wr];
+  static_assert(kRows == 4 && S <= 2, "the tables of the tiles");
 
   // the padded pixels from the row above the first pixel to the row below the last one (whole rows: W divides 32 T)
   auto center = [&](int n) {
@@ -120,6 +114,11 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
   int dst = -1, dst_px = 0;                     // plane of the task's pixels in a buffer, first of them; -1: no task
   auto take = [&]() {                           // the next tiles, as many as a buffer holds
     uint64_t c = 0;
+    if (__popcll(left) <= p.chunk) {
+      c = left;
+      left = 0;
+      return c;
+    }
     for (int k = 0; k < p.chunk && left; ++k) {
       c |= left & -left;
       left &= left - 1;
@@ -159,8 +158,8 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
   u32x4 raw[NL];
   uint64_t chunk = take();
+  fetch(chunk);                                 // (before the weights, which are wanted later: loads return in order)
   if (todo) load_w(raw, __builtin_ctzll(todo));
-  fetch(chunk);
   store(0);
   __syncthreads();
   for (int buf = 0;; buf ^= 1) {

@@ -636,9 +636,10 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
   const int64_t rows = cw / W, px = (rows + 2 * ((rows + H - 2) / H) + 2) * (W + 2), octets = (px + 7) / 8,
                 tile_bytes = 512 * octets, most = 75 * 1024;
   if (wgs > 0x7fffffff || tile_bytes > most) return RBGP_OK;
+  const size_t rows_o = size_t(per) * 4;
   if (!st->conv_tiles) {
     if (st->conv_tiles_none) return RBGP_OK;
-    std::vector<uint64_t> t(size_t(m->a[2]) * 2 + m->a[0], 0);   // ConvTileParams::sel, then ::tiles
+    std::vector<uint64_t> t(size_t(m->a[2]) * 2 + size_t(3) * rows_o, 0);   // ConvTileParams::sel, then ::tiles
     for (int u = 0; u < m->a[2]; ++u) {
       int at[4] = {-1, -1, -1, -1}, late[4];   // place in the adjacency list, and upper half, of the column kept of v and v + 4
       for (int k = 0; k < 4; ++k) {
@@ -657,13 +658,17 @@ int launch_conv_tile(const rbgp_mask *m, RegState *st, const int *tune, bool out
       t[size_t(u) * 2 + 1] = uint64_t(places | places << 8);
     }
     for (int u = 0; u < m->a[0]; ++u)
-      for (int k = 0; k < m->d[0]; ++k) t[size_t(m->a[2]) * 2 + u] |= uint64_t(1) << m->adj[0][size_t(u) * m->d[0] + k];
+      for (int k = 0; k < m->d[0]; ++k) {
+        const uint64_t bit = uint64_t(1) << m->adj[0][size_t(u) * m->d[0] + k];
+        t[size_t(m->a[2]) * 2 + u] |= bit;
+        t[size_t(m->a[2]) * 2 + size_t(1 + k % 2) * rows_o + u] |= bit;
+      }
     int rc = upload(t, &st->conv_tiles);
     if (rc) return rc;
   }
   ConvTileParams cp;
   cp.Wp = packed; cp.X = X; cp.O = O;
-  cp.sel = reinterpret_cast<const int4 *>(st->conv_tiles); cp.tiles = st->conv_tiles + m->a[2] * 2;
+  cp.sel = reinterpret_cast<const int4 *>(st->conv_tiles); cp.tiles = st->conv_tiles + m->a[2] * 2; cp.rows = int(rows_o);
   cp.ldO = ldO; cp.chan = chan; cp.w_bytes = w_bytes;
   cp.n = int(N); cp.ntiles = int(tiles);
   cp.h = int(H); cp.w = int(W); cp.w2 = int(W + 2); cp.hw = int(H * W);
@@ -998,7 +1003,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       const int64_t tall = !long_stages ? (m->reg_clusters.max_stages >= 32 ? round : 448)
                            : !out_bf16  ? 256
                                         : m->reg_clusters.max_stages >= 8 ? 320 : 384;
-      // (O in bf16 and rows of whole 8-byte stores: spmm_reg_bf16 needs 43 us where misaligned rows take it 55)
+      // (O in bf16 and rows of whole 8-byte stores: spmm_reg_bf16 needs 43 us where misaligned rows take it 51 and 1 x 2 47)
       const bool quick_stores = out_bf16 && ldO % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 8 == 0;
       if (fits(2)) {
         if (lists && (wgs(4) >= 384 || wgs(2) > round)) pick = 4;

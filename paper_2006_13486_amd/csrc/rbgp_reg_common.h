@@ -219,7 +219,9 @@ namespace rbgp_reg {
 struct ConvTileParams {
   const void *Wp, *X;
   void *O;
-  const uint64_t *tiles;   // [a_o] tile columns of a row of G_o (at most 64 of them), a bit each
+  const uint64_t *tiles;   // [3][rows] tile columns of a row of G_o (at most 64 of them), a bit each: all; every other one, from the first
+                           //   and from the second on.  rows: a_o rounded up to a multiple of four, the last ones empty
+  int rows;
   const int4 *sel;         // [a_i] byte selectors and index operand of a G_i vertex (see the kernel)
   int64_t ldO, chan;       // elements of one channel of X
   uint32_t w_bytes;
