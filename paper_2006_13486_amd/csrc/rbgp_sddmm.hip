@@ -187,6 +187,21 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
       off[RB + b] = int64_t(k) * p.ldI + ls * CPL;
     }
   }
+  // Where the lane's sums go: with the tables (CONV: before the last barrier, the registers are wanted in the loop); looked up
+  // behind the barrier, row after row, they cost two latencies each.
+  float *dst[RB];                               // first of the row's kept values of the stage; nullptr: no such row
+  int dst_ui[RB];
+  auto find_rows = [&]() {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const RowOf o = row_of(rb, 4 * q + wave);
+      // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
+      dst[rb] = o.row < 0 ? nullptr
+                          : p.out + int64_t(blockIdx.y) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
+      dst_ui[rb] = o.ui;
+    }
+  };
+  if constexpr (!CONV) find_rows();
   // CONV: where this lane's group of columns starts inside a channel (columns are pixels in image order)
   auto pixel = [&](int64_t n) { return CONV ? int64_t(p.colbase[n / CPL + ls]) : n; };
   // CONV: the tap shifts leave the 16-byte loads of X aligned to an element only (2 bytes for bf16), so
@@ -313,23 +328,23 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) red[wave][(rb * NB + b) * 4 + i][lane] = Op::total(acc[rb][b], i);
-  __syncthreads();
-  const int r16 = 4 * q + wave;
+  if constexpr (CONV) find_rows();
+  float *to[RB * NB];                           // nullptr: nothing to store
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const RowOf o = row_of(rb, r16);
-    if (o.row < 0) continue;
-    // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
-    float *dst = p.out + int64_t(blockIdx.y) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const int e = (rb * NB + b) * 4 + wave;
       // contraction step of this lane's column: 16 * b + j, or (gi) wherever G_i puts stage row 16 * b + j for u_i
       const int st = 16 * (b0 + b) + j;
-      const int kk = b0 + b >= p.nbt ? -1 : GI ? p.spos[o.ui * p.nbt * 16 + st] : (st < p.KCR ? st : -1);
-      const float v = (red[0][e][lane] + red[1][e][lane]) + (red[2][e][lane] + red[3][e][lane]);
-      if (kk >= 0) dst[kk] = v;
+      const int kk = !dst[rb] || b0 + b >= p.nbt ? -1 : GI ? p.spos[dst_ui[rb] * p.nbt * 16 + st] : (st < p.KCR ? st : -1);
+      to[rb * NB + b] = kk >= 0 ? dst[rb] + kk : nullptr;
     }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < RB * NB; ++t) {
+    const int e = t * 4 + wave;
+    const float v = (red[0][e][lane] + red[1][e][lane]) + (red[2][e][lane] + red[3][e][lane]);
+    if (to[t]) *to[t] = v;
   }
 }
 
@@ -340,6 +355,38 @@ __global__ __launch_bounds__(256) void sddmm_reduce(const float *__restrict__ pa
   float s = 0.f;
   for (int k = 0; k < nsplit; ++k) s += part[int64_t(k) * nnz + i];   // fixed order
   dW[i] = s;
+}
+
+// The same for many partial sums of few values, where a thread's chain of loads was the launch: W waves deal the partial sums of 64 values
+// among them, eight loads of a thread in flight, and meet in LDS.  One order, whatever the timing.  us, both gradients, a thread a value ->
+// this one: VGG19 layer 1 at 1/2 fp32, 20 images 48.1 -> 41.6, WRN group 1 fp32, 68 images 118 -> 112, bf16, 48 images 57.3 -> 54.6.
+// Below 8 partial sums a thread a value is as fast.
+template <int W>
+__global__ __launch_bounds__(64 * W) void sddmm_reduce_many(const float *__restrict__ part, float *__restrict__ dW, int64_t nnz, int nsplit) {
+  __shared__ float red[W][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t i = int64_t(blockIdx.x) * 64 + lane;
+  const float *const from = part + (i < nnz ? i : 0);
+  float s = 0.f;
+  int k = w;
+  for (; k + 7 * W < nsplit; k += 8 * W) {
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = from[int64_t(k + e * W) * nnz];
+    s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+  }
+  for (; k < nsplit; k += W) s += from[int64_t(k) * nnz];
+  red[w][lane] = s;
+  __syncthreads();
+  if (w || i >= nnz) return;
+  float t[W];
+#pragma unroll
+  for (int e = 0; e < W; ++e) t[e] = red[e][lane];
+#pragma unroll
+  for (int n = W / 2; n; n /= 2)
+#pragma unroll
+    for (int e = 0; e < n; ++e) t[e] += t[e + n];
+  dW[i] = t[0];
 }
 
 __global__ __launch_bounds__(256) void sddmm_zero(float *__restrict__ dW, int64_t nnz) {
@@ -770,7 +817,10 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
     fn<<<dim3(unsigned(blocks), unsigned(nsplit)), dim3(256), 0, hs>>>(p);
   RBGP_HIP(hipGetLastError());
   if (nsplit > 1) {
-    sddmm_reduce<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
+    const unsigned wgs64 = unsigned((nnz + 63) / 64);
+    if (nsplit >= 32) sddmm_reduce_many<16><<<dim3(wgs64), dim3(1024), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
+    else if (nsplit >= 8) sddmm_reduce_many<4><<<dim3(wgs64), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
+    else sddmm_reduce<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
     RBGP_HIP(hipGetLastError());
   }
   const char *then = nsplit > 1 ? "sddmm_reduce" : nullptr;
