@@ -9,6 +9,11 @@ import os
 
 import numpy as np
 
+try:   # the calls of a step without ctypes (csrc/rbgp_call.c); where it is not built, the functions below serve by themselves
+    from . import _call
+except ImportError:
+    _call = None
+
 F32, BF16_F32ACC, BF16 = 0, 1, 2   # BF16: as BF16_F32ACC with O stored as bf16 bits
 KERNEL_AUTO, KERNEL_GENERIC, KERNEL_MFMA, KERNEL_MFMA_REG, KERNEL_MFMA_TILE, KERNEL_MFMA_REG_FILLED = 0, 1, 2, 3, 4, 5
 TUNE_COLS_PER_LANE, TUNE_COLS_PER_WORKGROUP, TUNE_GROUPS_PER_WORKGROUP, TUNE_ROW_PAIRING = 0, 1, 2, 3
@@ -70,6 +75,9 @@ SIGNATURES = {
 }
 
 
+_FAST = ("rbgp_pack_device", "rbgp_pack_transposed_device", "rbgp_spmm", "rbgp_sddmm", "rbgp_conv3x3", "rbgp_conv3x3_sddmm")
+
+
 class RbgpError(RuntimeError):
     def __init__(self, code: int, where: str):
         self.code = code
@@ -100,6 +108,8 @@ def load():
             fn.restype = res
             fn.argtypes = args
         _lib = lib
+        if _call is not None:
+            _call.loaded(*[ctypes.cast(getattr(lib, name), _vp).value for name in _FAST])
     return _lib
 
 
@@ -321,3 +331,9 @@ def rbgp_spmm(mask: Mask, dtype: int, M: int, K: int, N: int, dev_packed_ptr: in
 def rbgp_last_kernel() -> str:
     """Kernel of the last product this thread launched, as a profiler lists it ("" before the first)."""
     return load().rbgp_last_kernel().decode()
+
+
+_WITH_CTYPES = {name: globals()[name] for name in _FAST}   # (what _call's functions leave to these)
+if _call is not None:
+    _call.setup(Mask, _vp, _check, *_WITH_CTYPES.values())
+    globals().update({name: getattr(_call, name) for name in _FAST})

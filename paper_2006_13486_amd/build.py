@@ -4,10 +4,12 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "librbgp.so")
+CALL = os.path.join(_HERE, "_call.so")   # the binding's calls without ctypes (csrc/rbgp_call.c)
 SOURCES = ["rbgp_mfma_reg_bf16_wide.hip", "rbgp_mfma_reg_bf16.hip", "rbgp_mfma_reg_bf16_lean.hip", "rbgp_mfma_reg.hip", "rbgp_host.cpp",
            "rbgp_device.hip", "rbgp_mfma_reg_dual.hip", "rbgp_mfma_reg_split.hip",
            "rbgp_mfma_reg_bf16_shared.hip", "rbgp_mfma_reg_rows.hip", "rbgp_mfma_reg_narrow.hip", "rbgp_conv_tile.hip", "rbgp_sddmm.hip", "rbgp_sddmm_lines.hip", "rbgp_mfma_tile.hip"]
@@ -36,6 +38,8 @@ def build(verbose: bool = False, extra: list[str] | None = None) -> str:
             print(out)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.check_call(cmd)
+    subprocess.check_call([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+                           "-o", CALL, os.path.join(CSRC, "rbgp_call.c")])
     return LIB
 
 
