@@ -889,6 +889,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // the two balance out, so the default is one group unless the rule below finds two worth it.
   // The stage list is split when there are fewer (cluster, G_i vertex, column tile) triples than SIMDs.
   int G = 1, lgS = 0;
+  int64_t lists = 0;   // (cluster, G_i vertex, column tile) triples (0: K_SPLIT is given)
   bool two_groups = false, four_groups = false;   // rbgp_spmm: a batch of another size may take them
   {
     const int tg = bf16 ? tune[RBGP_TUNE_ROW_GROUPS] : 0, ts = tune[RBGP_TUNE_K_SPLIT];
@@ -951,7 +952,20 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       if (ts != 1 && ts != 2 && ts != 4) return RBGP_EUNSUPPORTED;
       lgS = ts == 4 ? 2 : ts == 2 ? 1 : 0;
     } else {
-      while (lgS < 2 && ((ncl * m->a[2] * ntiles) << lgS) < 1024) ++lgS;
+      // Lists split until every SIMD has a wave, but long stages (36 and 72 steps, one row group) only where that shortens what the
+      // busiest SIMD walks: of L lists split in S, ceil(S L / 1024) waves of 1 / S list each.  Up to 256 lists that is a quarter
+      // with S = 4, up to 512 a half with 2 and with 4, up to 768 3/4 with 4 and a whole list otherwise -- worth the sum of the
+      // parts and a third start-up from lists of 12 stages on --, then a whole list whatever S.  In us, as many parts as fill every
+      // SIMD -> this: conv5, 48 images (384 lists) fp32 11.0 -> 9.8, bf16 (47) 8.9 -> 7.7; VGG19 layer 9 at 1/2, bf16, 57 images 18.3 ->
+      // 16.2; layer 4 at 1/4, bf16, 60 images 8.6 -> 6.9; layer 11 at 1/16, fp32, 75 images 12.6 -> 11.2; 12 stages and more: conv3, 44
+      // images 18.5 -> 14.9, layer 9 at 1/4, bf16, 84 images 19.3 -> 15.7; shorter ones in four 15.3 -> 19.6 and 10.8 -> 14.9.
+      // Stages of up to 32 steps keep the split (transposes: 32 steps, 4 stages, 864 lists 6.2, whole 7.8; 8 stages, 288 lists in
+      // four 6.1, in two 8.3): the waves of a short list mostly wait, and more of them hide more.
+      lists = ncl * m->a[2] * ntiles;
+      if (pl.KC > 32 && G == 1)
+        lgS = lists <= 256 ? 2 : lists <= 512 ? 1 : lists <= 768 && m->reg_clusters.max_stages >= 12 ? 2 : 0;
+      else
+        while (lgS < 2 && (lists << lgS) < 1024) ++lgS;
     }
   }
   const RegEntry *e = find_reg(pl.KC, pl.RS);
@@ -1033,8 +1047,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // (every lane is a whole image row there: nothing to share, only the extra instructions).
   const bool taps = conv && !bf16 && rbgp_reg_tap_grouped(m) && e->taps_fn && conv->width >= 8 && 64 % conv->width == 0;
   // fp32, two tile rows per MFMA group: lo/hi pairing of the tile rows (rbgp_mfma_reg_dual.hip) where its
-  // busiest SIMD walks fewer stages than the longest cluster of the fixed pairs, and there are enough
-  // (tile row, G_i vertex, column tile) triples to fill every SIMD without splitting stage lists.
+  // busiest SIMD walks fewer stages than the longest cluster of the fixed pairs, and stage lists are not split or there are
+  // enough of them, of long stages, for a wave on half of the SIMDs (us, fixed pairs split in two -> this: conv5, 96 images, 768
+  // lists, fused 16.4 -> 13.4, 69 images 15.6 -> 13.1; VGG19 layer 9 at 1/4, 72 images, 27.4 -> 22.1).
   bool dual = false;
   {
     const int tp = tune[RBGP_TUNE_ROW_PAIRING];
@@ -1043,7 +1058,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     // (merged rows: the caller's mask repeats its rows too few times for pairs, and its knobs count as on that mask)
     const bool merged = !m->merged.empty();
     if (tp == 2 && (!can || merged)) return RBGP_EUNSUPPORTED;
-    dual = can && (tp == 2 || (tp == 0 && lgS == 0 && m->reg_dual.max_stages < m->reg_clusters.max_stages &&
+    dual = can && (tp == 2 || (tp == 0 && (lgS == 0 || (lists > 512 && pl.KC > 32)) && m->reg_dual.max_stages < m->reg_clusters.max_stages &&
                                !(merged && tune[RBGP_TUNE_REGISTER_SETS])));
   }
   if (dual) lgS = 1;   // (two column tiles per workgroup, as with a stage list split in two)

@@ -1,0 +1,38 @@
+"""Batches around the counts at which stage lists are split in four, in two, or walked whole: sums as in 64 bits, whatever the split."""
+import pytest
+import torch
+
+from paper_2006_13486_amd import binding as rb
+from paper_2006_13486_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# conv5: 4 clusters of tile rows and 8 vertices of G_i, ten stages: 32 lists a tile of 64 columns; VGG19 layer 9 at 1/4 28 stages.
+# fp32 and bf16, last columns just inside and just past a tile, at 256, 512, 768 and 1024 lists.
+CONV5 = [c for tiles in (8, 16, 24, 32) for c in (64 * tiles - 3, 64 * tiles + 1)]
+CASES = [(wl.VGG19_CONV5, n, dtype) for n in CONV5 for dtype in (rb.F32, rb.BF16_F32ACC)]
+CASES += [(wl.vgg19_sweep_workload(9, 2, wl.F32), n, dtype) for n in (253, 513, 765, 769, 1021) for dtype in (rb.F32, rb.BF16_F32ACC)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0].name}_{c[1]}_{c[2]}")
+def test_splits_of_stage_lists(case):
+    w, N, dtype = case
+    t_in = torch.float32 if dtype == rb.F32 else torch.bfloat16
+    print(f"[gpu] stage list split {w.name} N={N} dtype={dtype}", flush=True)
+    mask = rb.rbgp_make_mask(w.rows, w.cols, w.row_deg, w.mask_seed)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    weights = (torch.randn(w.nnz, generator=gen, device="cuda") * w.w_std).to(t_in)
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, dtype), dtype=torch.uint8, device="cuda")
+    rb.rbgp_pack_device(mask, dtype, weights.data_ptr(), packed.data_ptr())
+    ldI = -(-N // 8) * 8
+    I = torch.randn((w.K, ldI), generator=gen, device="cuda").to(t_in)
+    out = torch.full((w.M + 1, N), -77.0, device="cuda")
+    rb.rbgp_spmm(mask, dtype, w.M, w.K, N, packed.data_ptr(), I.data_ptr(), ldI, out.data_ptr(), N)
+    torch.cuda.synchronize()
+    assert rb.rbgp_last_kernel().startswith("spmm_reg"), rb.rbgp_last_kernel()
+    assert (out[w.M] == -77).all()
+    cols = torch.from_numpy(rb.rbgp_mask_columns(mask).reshape(w.M, -1).astype("int64")).cuda()
+    dense = torch.zeros((w.M, w.K), dtype=torch.float64, device="cuda").scatter_(1, cols, weights.view(w.M, -1).double())
+    I64 = I[:, :N].double()
+    bound = cols.shape[1] * 2.0 ** -24 * (dense.abs() @ I64.abs())   # (one fp32 rounding per product and sum, in any order)
+    assert bool(((out[:w.M].double() - dense @ I64).abs() <= bound).all())
