@@ -959,11 +959,13 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // SIMD -> this: conv5, 48 images (384 lists) fp32 11.0 -> 9.8, bf16 (47) 8.9 -> 7.7; VGG19 layer 9 at 1/2, bf16, 57 images 18.3 ->
       // 16.2; layer 4 at 1/4, bf16, 60 images 8.6 -> 6.9; layer 11 at 1/16, fp32, 75 images 12.6 -> 11.2; 12 stages and more: conv3, 44
       // images 18.5 -> 14.9, layer 9 at 1/4, bf16, 84 images 19.3 -> 15.7; shorter ones in four 15.3 -> 19.6 and 10.8 -> 14.9.
+      // fp32 tile rows with one list, whose waves in four would go on to take two row groups, stay in two there (4096 x 4096, density
+      // 1/8, 181 columns, 768 lists 23.6, in four 25.8, with two groups 27.1; layer 5 at 1/2, 35 images, 560 lists 23.1, 21.2 and 26.7).
       // Stages of up to 32 steps keep the split (transposes: 32 steps, 4 stages, 864 lists 6.2, whole 7.8; 8 stages, 288 lists in
       // four 6.1, in two 8.3): the waves of a short list mostly wait, and more of them hide more.
       lists = ncl * m->a[2] * ntiles;
       if (pl.KC > 32 && G == 1)
-        lgS = lists <= 256 ? 2 : lists <= 512 ? 1 : lists <= 768 && m->reg_clusters.max_stages >= 12 ? 2 : 0;
+        lgS = lists <= 256 ? 2 : lists <= 512 ? 1 : lists <= 768 && m->reg_clusters.max_stages >= 12 ? (!bf16 && pl.fold > 1 ? 1 : 2) : 0;
       else
         while (lgS < 2 && (lists << lgS) < 1024) ++lgS;
     }
