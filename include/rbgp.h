@@ -107,7 +107,9 @@ enum {
                                          and pairs it, tile by tile, with one of two partner rows that has
                                          the same tile (EUNSUPPORTED where that kernel does not apply: bf16,
                                          other group sizes, more than 32 tile rows, with RBGP_TUNE_K_SPLIT);
-                                         default: 2 where it walks fewer tiles and N fills the chip */
+                                         default: 2 where it walks fewer tiles and there are 1024 lists of nonzero
+                                         tiles (one per tile row pair, G_i vertex and 64 columns), or 513 with stages
+                                         of 36 or 72 steps and knob 7 not set */
   RBGP_TUNE_ROW_GROUPS = 4,           /* MFMA_REG: 16-row MFMA groups per wave, 1, 2 or 4 (each loaded row of I
                                          is reused by all of them).  bf16: any mask (larger clusters of tile
                                          rows).  fp32: only tile rows that have the very same tiles -- masks

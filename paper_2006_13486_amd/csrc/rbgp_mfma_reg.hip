@@ -1060,8 +1060,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     // (merged rows: the caller's mask repeats its rows too few times for pairs, and its knobs count as on that mask)
     const bool merged = !m->merged.empty();
     if (tp == 2 && (!can || merged)) return RBGP_EUNSUPPORTED;
+    // (RBGP_TUNE_REGISTER_SETS is a knob of the fixed pairs, and asks for them wherever those would do)
+    const bool sets = tune[RBGP_TUNE_REGISTER_SETS] && (merged || lists < 1024);
     dual = can && (tp == 2 || (tp == 0 && (lgS == 0 || (lists > 512 && pl.KC > 32)) && m->reg_dual.max_stages < m->reg_clusters.max_stages &&
-                               !(merged && tune[RBGP_TUNE_REGISTER_SETS])));
+                               !sets));
   }
   if (dual) lgS = 1;   // (two column tiles per workgroup, as with a stage list split in two)
   // The first call makes the tables of every kernel that a batch of another size takes (it may come under capture; the fused

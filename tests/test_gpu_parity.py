@@ -1043,6 +1043,22 @@ def test_one_register_set_on_the_headline_layer_and_refusals():
         assert e.value.code == rb.EUNSUPPORTED
 
 
+@pytest.mark.parametrize("sets", [1, 2])
+@pytest.mark.parametrize("N", [1021, 1025, 1537, 1984])
+def test_register_sets_where_the_default_pairs_tile_rows(N, sets):
+    """RBGP_TUNE_REGISTER_SETS by itself below 1024 stage lists (conv5: 32 a tile of 64 columns) runs the kernel that has the knob,
+    also at sizes where the default pairs tile rows (from 513 lists on); with one set refused, as ever, where every list is paired."""
+    tune = (0,) * 7 + (sets,)
+    gh.check_parity(wl.VGG19_CONV5, N=N, kernel=REG, expect_kernel=REG)
+    assert rb.rbgp_last_kernel() == ("spmm_reg_dual" if N > 1024 else "spmm_reg")
+    gh.check_parity(wl.VGG19_CONV5, N=N, kernel=REG, tune=tune, expect_kernel=REG)
+    assert rb.rbgp_last_kernel() == "spmm_reg"
+    if sets == 1 and N == 1984:
+        with pytest.raises(rb.RbgpError) as e:
+            gh.check_parity(wl.VGG19_CONV5, N=1985, kernel=REG, tune=tune)
+        assert e.value.code == rb.EUNSUPPORTED
+
+
 def test_activations_beyond_4_gib():
     """An I of 4.6 GB (WRN shape, 2 000 037 columns, odd leading dimension): the kernels'
     32-bit offsets must only span one stage.  A sample of output columns is checked."""
