@@ -109,7 +109,7 @@ enum {
                                          other group sizes, more than 32 tile rows, with RBGP_TUNE_K_SPLIT);
                                          default: 2 where it walks fewer tiles and there are 1024 lists of nonzero
                                          tiles (one per tile row pair, G_i vertex and 64 columns), or 513 with stages
-                                         of 36 or 72 steps and knob 7 not set */
+                                         of 36 or 72 steps and knobs 4 and 7 not set */
   RBGP_TUNE_ROW_GROUPS = 4,           /* MFMA_REG: 16-row MFMA groups per wave, 1, 2 or 4 (each loaded row of I
                                          is reused by all of them).  bf16: any mask (larger clusters of tile
                                          rows).  fp32: only tile rows that have the very same tiles -- masks
@@ -119,7 +119,9 @@ enum {
                                          rbgp_mask_reg_plan, has the tile rows of that factoring) */
   RBGP_TUNE_K_SPLIT = 5,              /* MFMA_REG: waves that share a column tile and split its
                                          nonzero tiles between them, 1, 2 or 4 (default: 1 unless N
-                                         is too small to give every SIMD a wave; on few columns, where
+                                         is too small to give every SIMD a wave; with stages of 36 or 72
+                                         steps and knobs 4 and 7 not set, fewer where more would not
+                                         shorten the longest SIMD's work; on few columns, where
                                          knobs 1 and 4 to 7 are not set: eight waves on 16 columns) */
   RBGP_TUNE_COLUMN_TILES = 6,         /* MFMA_REG fp32, stages of up to 8 contraction steps, every tile row with
                                          the same number of tiles: column tiles (64 columns each) a wave takes

@@ -81,13 +81,17 @@ namespace {
 // three instead of two; 18 steps: four instead of three; two groups of 36 steps or of 72 tap-grouped ones: two
 // instead of one).
 // KL: stage size of the packed layout and the row table (see rbgp_reg_walk).
-template <int KC, int RS, bool TAPS = false, int NG = 1, bool CTILES = false, bool LEAN = false, int KL = KC>
-__global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || TAPS)    ? 4   // (128 registers)
+// HALF (one register set, one row group): a wave's list in two chains of sums, every other stage in the first and the rest in the second:
+// the chains of a list split over twice as many waves, which this stands in for (rule at the split of stage lists).  The first chain's
+// sums are put aside as the 16 of the epilogue's units: two sets of accumulators, one stage for each in turn, took 0.6 us more.
+template <int KC, int RS, bool TAPS = false, int NG = 1, bool CTILES = false, bool LEAN = false, int KL = KC, bool HALF = false>
+__global__ __launch_bounds__(256, (LEAN && !HALF && NG == 1 && RS == 16 && (KC == 32 || TAPS) ? 4   // (128 registers)
                                    : LEAN || (NG == 2 && (KC <= 32 || (KC == 36 && TAPS))) ? 2
                                    : KC <= 8 && NG == 1                                   ? (CTILES ? 2 : RS >= 4 ? 4 : 3)
                                                                                           : 1)) void spmm_reg(RegParams p) {
   static_assert(!CTILES || (KC <= 8 && !TAPS), "column tiles per wave: short stages, not the fused convolution");
   static_assert(!LEAN || (KC > 8 && !CTILES), "one register set: the long stages");
+  static_assert(!HALF || (LEAN && NG == 1), "two chains of sums: one register set, one row group");
   static_assert(!TAPS || KC % 12 == 0, "tap-grouped stages are multiples of 12 steps");
   static_assert(NG == 1 || RS == 16, "several groups per wave: one tile row per group");
   constexpr int MG = 16 / RS;            // tile rows per MFMA group = cluster size
@@ -160,7 +164,11 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
   const int memv = p.members[cl * MG + (lane & (MG - 1))];
   // table lane of the wave's s-th stage (all 64 lanes may hold stages: a stage past the wave's count is made a
   // sentinel where it is read back -- zero extent, weights past the end of the buffer)
-  auto table_lane = [&](int s) { return s < 63 ? s : 63; };
+  const int first = (cnt + 1) >> 1;   // HALF: stages of the first chain
+  auto table_lane = [&](int s) {
+    if constexpr (HALF) s = s < first ? 2 * s : 2 * (s - first) + 1;
+    return s < 63 ? s : 63;
+  };
 
   // byte offset of this lane's 16 bytes in every slot, relative to the stage base.  Columns
   // past N read whatever follows inside I (or zeros past its end): they are never stored.
@@ -363,11 +371,23 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
 
   // epilogue: add the four blocks (contraction steps 0..3 mod 4).  Unit t of the sum holds
   // weight row 4*(lane/16) + t of the group, lane j the columns 4j + w (of the column tile that starts at n0c).
+  f32x4 aside[HALF ? 4 : 1];   // HALF: the units of the first chain
+#pragma unroll
+  for (f32x4 &v : aside) v = f32x4{0.f, 0.f, 0.f, 0.f};
   auto unit = [&](int t, int k = 0) {
     f32x4 v;
 #pragma unroll
     for (int w = 0; w < 4; ++w) v[w] = (acc[k][w][t] + acc[k][w][4 + t]) + (acc[k][w][8 + t] + acc[k][w][12 + t]);
+    if constexpr (HALF) v = aside[t] + v;
     return v;
+  };
+  auto put_aside = [&]() {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) aside[HALF ? t : 0] = unit(t);
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[0][w][v] = 0.f;
   };
   // (the kernel arguments the stores need, read once: inside the store helpers they would be fetched again per unit)
   float *const out = p.O;
@@ -444,11 +464,13 @@ __global__ __launch_bounds__(256, (LEAN && NG == 1 && RS == 16 && (KC == 32 || T
       }
       return;
     }
-    for (; s + D <= cnt; s += D)
+    for (; s + D <= cnt; s += D) {
+      if (HALF && s == first) put_aside();   // (no loads: the wait counts stay exact)
       static_for<0, D>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         stage(s + k, Bs[k], As[k], std::true_type{});
       });
+    }
     static_for<0, D>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       if (s + k < cnt) stage(s + k, Bs[k], As[k], std::false_type{});
@@ -548,6 +570,16 @@ const RegLeanEntry kRegLeanTable[] = {RBGP_L4(18),  RBGP_L4(32),  RBGP_L4(36), R
 reg_fn find_reg_lean(int KC, int RS, bool taps, int NG) {
   for (const RegLeanEntry &e : kRegLeanTable)
     if (e.KC == KC && e.RS == RS && e.taps == taps && e.NG == NG) return e.fn;
+  return nullptr;
+}
+// the same in two chains of sums (stages of 36 steps and more, one row group)
+#define RBGP_H1(KC, RS, TAPS) {KC, RS, TAPS, 1, spmm_reg<KC, RS, TAPS, 1, false, true, KC, true>}
+#define RBGP_H4(KC, TAPS) RBGP_H1(KC, 2, TAPS), RBGP_H1(KC, 4, TAPS), RBGP_H1(KC, 8, TAPS), RBGP_H1(KC, 16, TAPS)
+const RegLeanEntry kRegHalfTable[] = {RBGP_H4(36, false), RBGP_H4(72, false), RBGP_H4(36, true), RBGP_H4(72, true),
+                                      {64, 16, false, 1, spmm_reg<64, 16, false, 1, false, true, 72, true>}};
+reg_fn find_reg_half(int KC, int RS, bool taps) {
+  for (const RegLeanEntry &e : kRegHalfTable)
+    if (e.KC == KC && e.RS == RS && e.taps == taps) return e.fn;
   return nullptr;
 }
 // waves that take several column tiles (stages of 8 steps): {RS, NG, kernel}
@@ -890,6 +922,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // The stage list is split when there are fewer (cluster, G_i vertex, column tile) triples than SIMDs.
   int G = 1, lgS = 0;
   int64_t lists = 0;   // (cluster, G_i vertex, column tile) triples (0: K_SPLIT is given)
+  bool halves = false;   // a wave's list in two chains of sums
+  // long stages split by what the busiest SIMD walks (not with the knobs whose kernels are no others than those of every other split)
+  const bool by_walk = pl.KC > 32 && !tune[RBGP_TUNE_ROW_GROUPS] && !tune[RBGP_TUNE_REGISTER_SETS];
   bool two_groups = false, four_groups = false;   // rbgp_spmm: a batch of another size may take them
   {
     const int tg = bf16 ? tune[RBGP_TUNE_ROW_GROUPS] : 0, ts = tune[RBGP_TUNE_K_SPLIT];
@@ -956,18 +991,28 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // busiest SIMD walks: of L lists split in S, ceil(S L / 1024) waves of 1 / S list each.  Up to 256 lists that is a quarter
       // with S = 4, up to 512 a half with 2 and with 4, up to 768 3/4 with 4 and a whole list otherwise -- worth the sum of the
       // parts and a third start-up from lists of 12 stages on --, then a whole list whatever S.  In us, as many parts as fill every
-      // SIMD -> this: conv5, 48 images (384 lists) fp32 11.0 -> 9.8, bf16 (47) 8.9 -> 7.7; VGG19 layer 9 at 1/2, bf16, 57 images 18.3 ->
-      // 16.2; layer 4 at 1/4, bf16, 60 images 8.6 -> 6.9; layer 11 at 1/16, fp32, 75 images 12.6 -> 11.2; 12 stages and more: conv3, 44
-      // images 18.5 -> 14.9, layer 9 at 1/4, bf16, 84 images 19.3 -> 15.7; shorter ones in four 15.3 -> 19.6 and 10.8 -> 14.9.
+      // SIMD -> this: conv5, 48 images (384 lists) fp32 10.9 -> 10.0, bf16 (47) 8.8 -> 7.4; VGG19 layer 9 at 1/2, bf16, 57 images 18.8 ->
+      // 16.4; layer 4 at 1/4, bf16, 60 images 8.9 -> 7.1; layer 11 at 1/16, fp32, 75 images 12.6 -> 11.5; 12 stages and more: conv3, 44
+      // images 18.3 -> 14.8, layer 9 at 1/4, bf16, 84 images 19.3 -> 15.6; shorter ones in four 15.3 -> 19.6 and 10.8 -> 14.9.
       // fp32 tile rows with one list, whose waves in four would go on to take two row groups, stay in two there (4096 x 4096, density
       // 1/8, 181 columns, 768 lists 23.6, in four 25.8, with two groups 27.1; layer 5 at 1/2, 35 images, 560 lists 23.1, 21.2 and 26.7).
       // Stages of up to 32 steps keep the split (transposes: 32 steps, 4 stages, 864 lists 6.2, whole 7.8; 8 stages, 288 lists in
       // four 6.1, in two 8.3): the waves of a short list mostly wait, and more of them hide more.
+      // Where that leaves fewer parts than fill every SIMD, each wave sums its list in two chains (HALF), so that no chain of fp32 sums
+      // grows: 0.25 us of a wave in fp32.  There two parts of up to 512 lists pay where they divide a list better than four do -- two
+      // waves of a quarter walk two stages more than one of a half where 4 k + 2 stages are to be dealt (us, four -> two: layer 10 at 1/16, 37
+      // images, six stages 9.3 -> 8.1; conv5, 48 images, ten 11.0 -> 10.0) -- or lists are long (layer 11 at 1/2, 32 stages 24.0 -> 22.5);
+      // else they cost up to 9 % (layer 7 at 1/4, 24 images, 12 stages 10.7 -> 10.9; WRN group 1, 4321 columns, eight 5.9 -> 6.4).
       lists = ncl * m->a[2] * ntiles;
-      if (pl.KC > 32 && G == 1)
-        lgS = lists <= 256 ? 2 : lists <= 512 ? 1 : lists <= 768 && m->reg_clusters.max_stages >= 12 ? (!bf16 && pl.fold > 1 ? 1 : 2) : 0;
-      else
-        while (lgS < 2 && (lists << lgS) < 1024) ++lgS;
+      while (lgS < 2 && (lists << lgS) < 1024) ++lgS;
+      if (by_walk && G == 1) {
+        const int fill = lgS;
+        const int n = m->reg_clusters.max_stages;
+        lgS = lists <= 256   ? 2
+              : lists <= 512 ? (bf16 || n % 4 == 2 || n >= 20 || lists == 512 ? 1 : 2)
+                             : lists <= 768 && n >= 12 ? (!bf16 && pl.fold > 1 ? 1 : 2) : 0;
+        halves = lgS < fill;
+      }
     }
   }
   const RegEntry *e = find_reg(pl.KC, pl.RS);
@@ -1051,8 +1096,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   // fp32, two tile rows per MFMA group: lo/hi pairing of the tile rows (rbgp_mfma_reg_dual.hip) where its
   // busiest SIMD walks fewer stages than the longest cluster of the fixed pairs, and stage lists are not split or there are
   // enough of them, of long stages, for a wave on half of the SIMDs (us, fixed pairs split in two -> this: conv5, 96 images, 768
-  // lists, fused 16.4 -> 13.4, 69 images 15.6 -> 13.1; VGG19 layer 9 at 1/4, 72 images, 27.4 -> 22.1).
-  bool dual = false;
+  // lists, fused 15.4 -> 13.4, 69 images 15.7 -> 13.7; VGG19 layer 9 at 1/4, 72 images, 27.0 -> 22.8).
+  bool dual = false, dual_half = false;
   {
     const int tp = tune[RBGP_TUNE_ROW_PAIRING];
     if (tp < 0 || tp > 2) return RBGP_EUNSUPPORTED;
@@ -1060,10 +1105,9 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     // (merged rows: the caller's mask repeats its rows too few times for pairs, and its knobs count as on that mask)
     const bool merged = !m->merged.empty();
     if (tp == 2 && (!can || merged)) return RBGP_EUNSUPPORTED;
-    // (RBGP_TUNE_REGISTER_SETS is a knob of the fixed pairs, and asks for them wherever those would do)
-    const bool sets = tune[RBGP_TUNE_REGISTER_SETS] && (merged || lists < 1024);
-    dual = can && (tp == 2 || (tp == 0 && (lgS == 0 || (lists > 512 && pl.KC > 32)) && m->reg_dual.max_stages < m->reg_clusters.max_stages &&
-                               !sets));
+    dual = can && (tp == 2 || (tp == 0 && (lgS == 0 || (by_walk && lists > 512)) && m->reg_dual.max_stages < m->reg_clusters.max_stages &&
+                               !(merged && tune[RBGP_TUNE_REGISTER_SETS])));
+    dual_half = dual && tp == 0 && lists < 1024;   // (in place of fixed pairs split in two)
   }
   if (dual) lgS = 1;   // (two column tiles per workgroup, as with a stage list split in two)
   // The first call makes the tables of every kernel that a batch of another size takes (it may come under capture; the fused
@@ -1081,6 +1125,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     }
   }
   if (rc_tables) return rc_tables;
+  if (dual || share_rv) halves = false;
   if (!dual) {
     // a stage list longer than a wave's table is split over enough waves of the workgroup
     int need = 0;
@@ -1088,6 +1133,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     if (need > lgS) {
       if (tune[RBGP_TUNE_K_SPLIT]) return RBGP_EUNSUPPORTED;
       lgS = need;
+      halves = false;
     }
   }
   // fp32, rows of G_r moved into the tile-row index: NG of the `fold` tile rows that share their tiles per wave
@@ -1390,9 +1436,10 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   }
   reg_fn fn = dual     ? nullptr
               : share_rv ? rbgp_reg_bf16_shared_kernel(share_rv, share_pr)
-              : bf16   ? (lean ? rbgp_reg_bf16_lean_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW) : rbgp_reg_bf16_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW))
+              : bf16   ? (halves ? rbgp_reg_bf16_half_kernel(walk, pl.RS, CW) : lean ? rbgp_reg_bf16_lean_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW) : rbgp_reg_bf16_kernel(G < 4 ? walk : pl.KC, pl.RS, G, CW))
               : split  ? rbgp_reg_split_kernel(split_rw, sparse)
               : CT > 1 ? find_reg_tiles(pl.KC, pl.RS, NGf)
+              : halves && NGf == 1 ? find_reg_half(taps ? pl.KC : walk, pl.RS, taps)
               : lean   ? find_reg_lean(taps ? pl.KC : walk, pl.RS, taps, NGf)
               : ge   ? (taps ? ge->taps_fn : ge->global_fn)
               : taps ? e->taps_fn
@@ -1407,7 +1454,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const DualLayout l = dual_layout(m);
     dq.rt_stride = l.np4; dq.cmax = l.cmax; dq.o_stages = l.stages; dq.o_quads = l.quads;
     dq.tab = *rowtab + l.first;
-    rbgp_dual_fn dfn = rbgp_reg_dual_kernel(pl.KC);
+    rbgp_dual_fn dfn = dual_half ? rbgp_reg_dual_half_kernel(pl.KC) : rbgp_reg_dual_kernel(pl.KC);
     hipLaunchKernelGGL(dfn, dim3(unsigned(8 * per_xcd)), dim3(512), lds, static_cast<hipStream_t>(stream), dq);
   } else {
     hipLaunchKernelGGL(fn, dim3(unsigned(8 * per_xcd)), dim3(256), lds, static_cast<hipStream_t>(stream), rp);

@@ -25,8 +25,9 @@ using namespace rbgp_reg;
 namespace {
 
 // KC: contraction steps per stage.  RegParams: stages / counts / members hold the tables of
-// rbgp_reg_dual (per quad and wave), ncl the number of quads.
-template <int KC>
+// rbgp_reg_dual (per quad and wave), ncl the number of quads.  HALF: the first half of a wave's sums is put aside and added at the end, so
+// that no chain of fp32 sums is longer than with fixed pairs whose lists are split in two, which this stands in for on few lists.
+template <int KC, bool HALF = false>
 __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
   const RegParams &p = dp.r;
   constexpr int RS = 8;
@@ -133,6 +134,17 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
   for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+  f32x4 aside[HALF ? 4 : 1];   // HALF: the units of the first half
+#pragma unroll
+  for (f32x4 &v : aside) v = f32x4{0.f, 0.f, 0.f, 0.f};
+  // Unit t: the four blocks (contraction steps 0..3 mod 4) added (see the epilogue)
+  auto unit = [&](int t) {
+    f32x4 v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = (acc[c][t] + acc[c][4 + t]) + (acc[c][8 + t] + acc[c][12 + t]);
+    if constexpr (HALF) v = aside[t] + v;
+    return v;
+  };
 
   f32x4 B[NO];
   f32x4 A[NQ];
@@ -164,6 +176,14 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
       else if (left == 2) __builtin_amdgcn_s_setprio(1);
       else __builtin_amdgcn_s_setprio(0);
     }
+    if (HALF && s == (cnt + 1) >> 1) {   // (no loads: the wait counts stay exact)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) aside[HALF ? t : 0] = unit(t);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+    }
     const __amdgpu_buffer_rsrc_t rb = b_rsrc(s + 1);
     const int av = a_addr(s + 1);
     static_for<0, NO>([&](auto oc) {
@@ -184,16 +204,9 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
   }
   __builtin_amdgcn_s_waitcnt(0);
 
-  // Epilogue.  Unit t: the four blocks (contraction steps 0..3 mod 4) added; it holds weight row
-  // 4 * (lane / 16) + t of the group -- lanes 0..31 rows of L_x, lanes 32..63 rows of H_y -- and lane j
+  // Epilogue.  Unit t holds weight row 4 * (lane / 16) + t of the group -- lanes 0..31 rows of L_x, lanes 32..63 rows of H_y -- and lane j
   // the columns 4j + c.  Of a column tile's four waves, (0, 0) stores L0 and H0, (1, 1) stores L1 and
   // H1; the other two leave their units in LDS: L_x = (x, 0) + (x, 1), H_y = (0, y) + (1, y).
-  auto unit = [&](int t) {
-    f32x4 v;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = (acc[c][t] + acc[c][4 + t]) + (acc[c][8 + t] + acc[c][12 + t]);
-    return v;
-  };
   f32x4 *const x4 = reinterpret_cast<f32x4 *>(xlds);   // [column tile][x of the giver][unit][lane]
   const int u1 = g < 2 ? rowL : rowH;
   int ro[4];
@@ -230,6 +243,8 @@ __global__ __launch_bounds__(512) void spmm_reg_dual(DualParams dp) {
 }
 
 }  // namespace
+
+rbgp_dual_fn rbgp_reg_dual_half_kernel(int KC) { return KC == 36 ? spmm_reg_dual<36, true> : KC == 72 ? spmm_reg_dual<72, true> : nullptr; }
 
 rbgp_dual_fn rbgp_reg_dual_kernel(int KC) {
   switch (KC) {

@@ -70,8 +70,9 @@ __device__ __forceinline__ s16x4 as_s16x4(unsigned lo, unsigned hi) {
 // next stage right after their last use -- so that two waves fit a SIMD where the two sets fill the register file of one.
 // KL: stage size of the packed layout and the row table (stages of up to 64 steps in the layout of 72: the last block of
 // 16 is all padding and is left out; rbgp_reg_walk).
-template <int KC, int RS, int G, int CW, bool LEAN = false, int KL = KC>
-__global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) {
+// HALF (one group): a wave's list in two chains of sums, as in the fp32 kernel.  One wave a SIMD, so registers for two sets of sums.
+template <int KC, int RS, int G, int CW, bool LEAN = false, int KL = KC, bool HALF = false>
+__global__ __launch_bounds__(256, LEAN && !HALF ? 2 : 1) void spmm_reg_bf16(RegParams p) {
   constexpr int NC = CW / 16;            // columns per lane: 4 or 8
   constexpr int LW = NC / 2;             // dwords per lane and row
   constexpr int NH = NC / 4;             // 16-byte pieces of a lane's output row
@@ -194,10 +195,14 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
   for (int gi = 0; gi < G; ++gi)
 #pragma unroll
     for (int w = 0; w < NC; ++w) acc[gi][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  static_assert(!HALF || G == 1, "two chains of sums: one row group");
+  f32x4 odd[HALF ? G : 1][NC];   // HALF: the sums of every other stage
+#pragma unroll
+  for (int w = 0; w < NC; ++w) odd[0][w] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // The MFMAs of block b: transpose the lane's 8 x NC (4 x NC) block of bf16 (dword d of a
   // row holds columns 2d and 2d+1), then per group one MFMA per column offset.
-  auto block = [&](auto bc, const Raw<LW> (&B)[NLD], const u32x4 (&A)[G][NB]) {
+  auto block = [&](f32x4 (&acc)[G][NC], auto bc, const Raw<LW> (&B)[NLD], const u32x4 (&A)[G][NB]) {
     constexpr int b = decltype(bc)::value;
     constexpr unsigned LO = 0x05040100u, HI = 0x07060302u;
     if constexpr (b < NK32) {
@@ -255,7 +260,7 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
   // sets) right after their last use, so about DIST stages of loads are in flight; the loop body is
   // branch-free and its wait counts are exact.
   constexpr int DIST = LEAN ? 1 : 2;
-  auto stage = [&](int s, Raw<LW> (&B)[NLD], u32x4 (&A)[G][NB], auto reload) {
+  auto stage_into = [&](f32x4 (&acc)[G][NC], int s, Raw<LW> (&B)[NLD], u32x4 (&A)[G][NB], auto reload) {
     constexpr bool RELOAD = decltype(reload)::value;
     int sofs = 0, av[G] = {};
     __amdgpu_buffer_rsrc_t rb2 = rw;
@@ -267,9 +272,14 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
       for (int gi = 0; gi < G; ++gi) av[gi] = a_addr(tl, live, gi);
     }
     static_for<0, NB>([&](auto bc) {
-      block(bc, B, A);
+      block(acc, bc, B, A);
       if constexpr (RELOAD) load_block(bc, B, A, rb2, sofs, av);
     });
+  };
+  auto stage = [&](int s, Raw<LW> (&B)[NLD], u32x4 (&A)[G][NB], auto reload) { stage_into(acc, s, B, A, reload); };
+  auto stage_odd = [&](int s, Raw<LW> (&B)[NLD], u32x4 (&A)[G][NB], auto reload) {
+    if constexpr (HALF) stage_into(odd, s, B, A, reload);
+    else stage(s, B, A, reload);
   };
   auto fill = [&](int s, Raw<LW> (&B)[NLD], u32x4 (&A)[G][NB]) {
     int sofs, av[G];
@@ -285,7 +295,14 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
     Raw<LW> B0[NLD];
     u32x4 A0[G][NB];
     fill(0, B0, A0);
-    for (int s = 0; s < cntw; ++s) stage(s, B0, A0, std::true_type{});   // (past the end: sentinels, no memory access)
+    int s = 0;                           // (past the end: sentinels, no memory access)
+    if constexpr (HALF) {
+      for (; s + 1 < cntw; s += 2) {
+        stage(s, B0, A0, std::true_type{});
+        stage_odd(s + 1, B0, A0, std::true_type{});
+      }
+    }
+    for (; s < cntw; ++s) stage(s, B0, A0, std::true_type{});
   } else {
     Raw<LW> B0[NLD], B1[NLD];
     u32x4 A0[G][NB], A1[G][NB];
@@ -294,11 +311,15 @@ __global__ __launch_bounds__(256, LEAN ? 2 : 1) void spmm_reg_bf16(RegParams p) 
     int s = 0;
     for (; s + 1 < cntw; s += 2) {
       stage(s, B0, A0, std::true_type{});
-      stage(s + 1, B1, A1, std::true_type{});
+      stage_odd(s + 1, B1, A1, std::true_type{});
     }
     if (s < cntw) stage(s, B0, A0, std::false_type{});
   }
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (HALF) {
+#pragma unroll
+    for (int w = 0; w < NC; ++w) acc[0][w] += odd[0][w];
+  }
 
   // Epilogue.  Unit (gi, t) = register t of group gi's NC accumulators: weight row
   // 4*(lane/16) + t of the group, lane j the columns NC*j + w.

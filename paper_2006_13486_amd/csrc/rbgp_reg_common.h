@@ -246,6 +246,8 @@ typedef void (*rbgp_dual_fn)(rbgp_reg::DualParams);
 rbgp_reg_fn rbgp_reg_bf16_kernel(int KC, int RS, int G, int CW);
 // the same with one register set (two waves per SIMD); nullptr where that variant is not built
 rbgp_reg_fn rbgp_reg_bf16_lean_kernel(int KC, int RS, int G, int CW);
+// a wave's list in two chains of sums: 64 columns with two register sets, 128 with one
+rbgp_reg_fn rbgp_reg_bf16_half_kernel(int KC, int RS, int CW);
 // bf16 kernel of workgroups of RV x (4 / RV) waves, each 2 PR tile rows x 128 columns, that pass I through LDS;
 // nullptr: not built
 rbgp_reg_fn rbgp_reg_bf16_shared_kernel(int RV, int PR);
@@ -264,5 +266,7 @@ rbgp_split_tile_fn rbgp_mfma_split_kernel(int KS, bool sparse, int NT, int KSP);
 // fp32 kernel with lo/hi pairing of the tile rows (8-row halves; tables of rbgp_reg_dual in the
 // stages / counts / members fields); nullptr when KC is not built.
 rbgp_dual_fn rbgp_reg_dual_kernel(int KC);
+// the same with a wave's list in two chains of sums (stages of 36 and 72 steps)
+rbgp_dual_fn rbgp_reg_dual_half_kernel(int KC);
 
 #endif

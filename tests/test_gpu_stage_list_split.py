@@ -38,3 +38,42 @@ def test_splits_of_stage_lists(case):
     I64 = I[:, :N].double()
     bound = cols.shape[1] * 2.0 ** -24 * (dense.abs() @ I64.abs())   # (one fp32 rounding per product and sum, in any order)
     assert bool(((out[:w.M].double() - dense @ I64).abs() <= bound).all())
+
+
+# (workload, columns, dtype, waves a list that fill every SIMD): one wave, or two, in their place, and paired tile rows
+CHAINS = [(wl.VGG19_CONV5, 765, rb.F32, 4), (wl.VGG19_CONV5, 765, rb.BF16_F32ACC, 4), (wl.VGG19_CONV5, 1537, rb.BF16_F32ACC, 2),
+          (wl.VGG19_CONV3_BF16, 4000, rb.BF16_F32ACC, 2), (wl.vgg19_sweep_workload(9, 1, wl.F32), 913, rb.F32, 4),
+          (wl.vgg19_sweep_workload(4, 4, wl.F32), 3072, rb.F32, 2), (wl.vgg19_sweep_workload(7, 3, wl.F32), 3072, rb.F32, 2),
+          (wl.vgg19_sweep_workload(5, 2, wl.F32), 2368, rb.F32, 2)]
+
+
+@pytest.mark.parametrize("case", CHAINS, ids=lambda c: f"{c[0].name}_{c[1]}_{c[2]}")
+def test_fewer_waves_a_list_have_no_longer_chains(case):
+    """Where fewer waves take a list than fill every SIMD, the error against 64-bit sums is that of as many waves as do (the same chains
+    of fp32 sums, whose totals meet in another order) or less."""
+    w, N, dtype, S = case
+    t_in = torch.float32 if dtype == rb.F32 else torch.bfloat16
+    print(f"[gpu] chains {w.name} N={N} dtype={dtype}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    weights = (torch.randn(w.nnz, generator=gen, device="cuda") * w.w_std).to(t_in)
+    ldI = -(-N // 8) * 8
+    I = torch.randn((w.K, ldI), generator=gen, device="cuda").to(t_in)
+    mask = rb.rbgp_make_mask(w.rows, w.cols, w.row_deg, w.mask_seed)
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, dtype), dtype=torch.uint8, device="cuda")
+    rb.rbgp_pack_device(mask, dtype, weights.data_ptr(), packed.data_ptr())
+    cols = torch.from_numpy(rb.rbgp_mask_columns(mask).reshape(w.M, -1).astype("int64")).cuda()
+    dense = torch.zeros((w.M, w.K), dtype=torch.float64, device="cuda").scatter_(1, cols, weights.view(w.M, -1).double())
+    want = dense @ I[:, :N].double()
+    out = torch.empty((w.M, N), device="cuda")
+
+    def error(split):
+        rb.rbgp_mask_tune(mask, rb.TUNE_K_SPLIT, split)
+        out.fill_(float("nan"))
+        rb.rbgp_spmm(mask, dtype, w.M, w.K, N, packed.data_ptr(), I.data_ptr(), ldI, out.data_ptr(), N)
+        torch.cuda.synchronize()
+        return float((out.double() - want).norm() / want.norm())
+
+    filled, default = error(S), error(0)
+    print(f"[gpu]   {default:.3e}, {S} waves a list {filled:.3e}", flush=True)
+    # (at least 40 chains' totals of as many products each: another order of the last two or four additions moves the norm by below 2 %)
+    assert default <= 1.02 * filled
