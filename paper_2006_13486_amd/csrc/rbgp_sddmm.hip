@@ -187,8 +187,8 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
       off[RB + b] = int64_t(k) * p.ldI + ls * CPL;
     }
   }
-  // Where the lane's sums go: with the tables (CONV: before the last barrier, the registers are wanted in the loop); looked up
-  // behind the barrier, row after row, they cost two latencies each.
+  // Where the lane's sums go: with the tables (CONV and GI: before the last barrier, held through the loop the pointers cost GI's kernels
+  // of 2 x 2 groups one of four waves a SIMD); looked up behind the barrier, row after row, they cost two latencies each.
   float *dst[RB];                               // first of the row's kept values of the stage; nullptr: no such row
   int dst_ui[RB];
   auto find_rows = [&]() {
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
       dst_ui[rb] = o.ui;
     }
   };
-  if constexpr (!CONV) find_rows();
+  if constexpr (!CONV && !GI) find_rows();
   // CONV: where this lane's group of columns starts inside a channel (columns are pixels in image order)
   auto pixel = [&](int64_t n) { return CONV ? int64_t(p.colbase[n / CPL + ls]) : n; };
   // CONV: the tap shifts leave the 16-byte loads of X aligned to an element only (2 bytes for bf16), so
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256) void sddmm_reg(SddmmParams p) {
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) red[wave][(rb * NB + b) * 4 + i][lane] = Op::total(acc[rb][b], i);
-  if constexpr (CONV) find_rows();
+  if constexpr (CONV || GI) find_rows();
   float *to[RB * NB];                           // nullptr: nothing to store
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)

@@ -276,17 +276,21 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
       offB[i] = Off(int64_t(k) * p.ldI * ES + ls * 16);
     }
   }
-  // Where the lane's sums go, with the tables as well: looked up at the end, row after row, they cost two latencies each.
+  // Where the lane's sums go, with the tables as well (FAR: before the last barrier, held through the loop the pointers cost <2, 1> the
+  // second workgroup on a CU); looked up at the end, row after row, they cost two latencies each.
   float *dst[RB];                               // first of the row's kept values of the stage; nullptr: no such row
   int dst_ui[RB];
+  auto find_rows = [&]() {
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const RowOf o = row_of(rb, 4 * q + wave % 4);
-    // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
-    dst[rb] = o.row < 0 ? nullptr
-                        : p.out + int64_t(part) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
-    dst_ui[rb] = o.ui;
-  }
+    for (int rb = 0; rb < RB; ++rb) {
+      const RowOf o = row_of(rb, 4 * q + wave % 4);
+      // the stage is fragment cpos * NSTG + sg of the row: KCR consecutive kept values
+      dst[rb] = o.row < 0 ? nullptr
+                          : p.out + int64_t(part) * p.nnz + o.row * p.rowdeg + int64_t(cpos[o.entry] * p.NSTG + sg) * p.KCR;
+      dst_ui[rb] = o.ui;
+    }
+  };
+  if constexpr (!FAR) find_rows();
   __amdgpu_buffer_rsrc_t arsrc, xrsrc;
   if constexpr (CONV) {
     if constexpr (!FAR) arsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.dO), 0, -1, kRsrcFlags);
@@ -515,6 +519,7 @@ __global__ __launch_bounds__(64 * kWaves) void sddmm_lines(SddmmParams p) {
 
   // acc[b][rb][i] = dW block element (row 4 * q + i of row group rb, contraction step 16 * b + j; WIN: tap b % 3 of pixel row
   // 16 * (b / 3) + j); the waves take turns at adding them up
+  if constexpr (FAR) find_rows();
   constexpr int TN = (RB * NB + kWaves / 4 - 1) / (kWaves / 4);
   const int first_t = wave / 4;
   float *to[TN];                                // nullptr: nothing to store
