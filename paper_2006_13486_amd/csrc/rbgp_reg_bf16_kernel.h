@@ -71,8 +71,14 @@ __device__ __forceinline__ s16x4 as_s16x4(unsigned lo, unsigned hi) {
 // KL: stage size of the packed layout and the row table (stages of up to 64 steps in the layout of 72: the last block of
 // 16 is all padding and is left out; rbgp_reg_walk).
 // HALF (one group): a wave's list in two chains of sums, as in the fp32 kernel.  One wave a SIMD, so registers for two sets of sums.
+// (64-column tiles of short stages, and of 36 steps with one group: told so, the compiler meets the bounds of four and seven waves a SIMD
+// without spilling; left to itself it ends just above them)
 template <int KC, int RS, int G, int CW, bool LEAN = false, int KL = KC, bool HALF = false>
-__global__ __launch_bounds__(256, LEAN && !HALF ? 2 : 1) void spmm_reg_bf16(RegParams p) {
+__global__ __launch_bounds__(256, HALF                                         ? 1
+                                   : LEAN                                       ? 2
+                                   : CW == 64 && KC == 8 && G == 1              ? 7
+                                   : CW == 64 && ((KC == 8 && G == 2) || (KC == 36 && G == 1)) ? 4
+                                                                                : 1) void spmm_reg_bf16(RegParams p) {
   constexpr int NC = CW / 16;            // columns per lane: 4 or 8
   constexpr int LW = NC / 2;             // dwords per lane and row
   constexpr int NH = NC / 4;             // 16-byte pieces of a lane's output row
