@@ -437,7 +437,8 @@ const char *rbgp_last_hip_error(void);
 /* The kernel of the last product that this thread launched (rbgp_spmm, rbgp_conv3x3, rbgp_sddmm, rbgp_sddmm_static,
  * rbgp_conv3x3_sddmm), as a profiler lists it; of those with split operands, shared columns, many rows per tile or image
  * tiles and of the weight gradients with the template arguments that a launch chooses between for one mask and dtype; and
- * " + sddmm_reduce" where a second launch adds partial sums; "" before the first.  For tests and
+ * " + sddmm_reduce" where a second launch adds partial sums (a profiler lists sddmm_reduce, sddmm_reduce<4> or sddmm_reduce<16>, by
+ * their number); "" before the first.  For tests and
  * profiles: names may change from version to version.  Valid until the thread's next call of this function. */
 const char *rbgp_last_kernel(void);
 

@@ -358,24 +358,29 @@ __global__ __launch_bounds__(256) void sddmm_reduce(const float *__restrict__ pa
 }
 
 // The same for many partial sums of few values, where a thread's chain of loads was the launch: W waves deal the partial sums of 64 values
-// among them, eight loads of a thread in flight, and meet in LDS.  One order, whatever the timing.  us, both gradients, a thread a value ->
-// this one: VGG19 layer 1 at 1/2 fp32, 20 images 48.1 -> 41.6, WRN group 1 fp32, 68 images 118 -> 112, bf16, 48 images 57.3 -> 54.6.
+// among them, four loads of a thread in flight (two to four each for the 8 to 64 partial sums of most masks, sixteen at the most), and meet
+// in LDS.  One order, whatever the timing.  us, the weight gradient, a thread a value -> this
+// one: VGG19 layer 1 at 1/2 fp32, 20 images 27.2 -> 20.6, WRN group 1 fp32, 68 images 40.8 -> 33.5, bf16, 48 images 18.6 -> 14.6; two units,
+// 4096 columns (32 partial sums) 15.3 -> 9.2, 15000 (118) 35.6 -> 9.4.
 // Below 8 partial sums a thread a value is as fast.
 template <int W>
-__global__ __launch_bounds__(64 * W) void sddmm_reduce_many(const float *__restrict__ part, float *__restrict__ dW, int64_t nnz, int nsplit) {
+__global__ __launch_bounds__(64 * W) void sddmm_reduce(const float *__restrict__ part, float *__restrict__ dW, int64_t nnz, int nsplit) {
   __shared__ float red[W][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int64_t i = int64_t(blockIdx.x) * 64 + lane;
   const float *const from = part + (i < nnz ? i : 0);
   float s = 0.f;
-  int k = w;
-  for (; k + 7 * W < nsplit; k += 8 * W) {
-    float x[8];
+  for (int k = w; k < nsplit; k += 4 * W) {
+    float x[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = from[int64_t(k + e * W) * nnz];
-    s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    for (int e = 0; e < 4; ++e) {                // (past the last one: that one again, not added)
+      const int r = k + e * W;
+      x[e] = from[int64_t(r < nsplit ? r : nsplit - 1) * nnz];
+    }
+#pragma unroll
+    for (int e = 1; e < 4; ++e) x[e] = k + e * W < nsplit ? x[e] : 0.f;
+    s += (x[0] + x[1]) + (x[2] + x[3]);
   }
-  for (; k < nsplit; k += W) s += from[int64_t(k) * nnz];
   red[w][lane] = s;
   __syncthreads();
   if (w || i >= nnz) return;
@@ -818,8 +823,8 @@ int launch_core(const rbgp_mask *m, SddmmBuffers &B, SddmmState *st, bool use_mf
   RBGP_HIP(hipGetLastError());
   if (nsplit > 1) {
     const unsigned wgs64 = unsigned((nnz + 63) / 64);
-    if (nsplit >= 32) sddmm_reduce_many<16><<<dim3(wgs64), dim3(1024), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
-    else if (nsplit >= 8) sddmm_reduce_many<4><<<dim3(wgs64), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
+    if (nsplit >= 32) sddmm_reduce<16><<<dim3(wgs64), dim3(1024), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
+    else if (nsplit >= 8) sddmm_reduce<4><<<dim3(wgs64), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
     else sddmm_reduce<<<dim3(unsigned((nnz + 255) / 256)), dim3(256), 0, hs>>>(B.partial, dW, nnz, int(nsplit));
     RBGP_HIP(hipGetLastError());
   }

@@ -55,3 +55,30 @@ def test_rows_that_begin_at_any_element(case, shift):
     # The dispatch may take another kernel for aligned rows: another order of at most 1152 fp32 sums (2^-24 sqrt(1152) = 2e-6 of the
     # result's norm), and where O is bf16 a rounding that falls the other way (2^-9 of a value, in few of them).
     assert (got - want).norm() <= (2e-3 if dtype == rb.BF16 else 2e-6) * want.norm()
+
+
+@pytest.mark.parametrize("ldO,kernel", [(3728269, "spmm_reg_rows<2>"), (3728270, "spmm_reg")])
+def test_rows_of_o_up_to_4_gib_of_a_workgroup_and_beyond(ldO, kernel):
+    """The last leading dimension at which a workgroup's 288 rows of O lie within 32-bit offsets, and the first beyond."""
+    w, N = wl.vgg19_sweep_workload(3, 2, wl.F32), 2999
+    print(f"[gpu] far rows of O {w.name} ldO={ldO}", flush=True)
+    mask = rb.rbgp_mask_transpose(rb.rbgp_make_mask(w.rows, w.cols, w.row_deg, w.mask_seed))
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    weights = torch.randn(w.nnz, generator=gen, device="cuda") * w.w_std
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, rb.F32), dtype=torch.uint8, device="cuda")
+    rb.rbgp_pack_transposed_device(mask, rb.F32, weights.data_ptr(), packed.data_ptr())
+    dO = torch.randn((w.M, 3000), generator=gen, device="cuda")
+
+    def product(ld):
+        out = torch.full((w.K, ld), -77.0, device="cuda")
+        rb.rbgp_spmm(mask, rb.F32, w.K, w.M, N, packed.data_ptr(), dO.data_ptr(), 3000, out.data_ptr(), ld)
+        torch.cuda.synchronize()
+        assert bool((out[:, N:] == -77).all())
+        return out[:, :N].clone()
+
+    near = product(3000)
+    assert rb.rbgp_last_kernel() == "spmm_reg_rows<2>"
+    far = product(ldO)
+    assert rb.rbgp_last_kernel() == kernel
+    # (the other kernel: another order of at most 64 fp32 sums)
+    assert torch.equal(far, near) if kernel != "spmm_reg" else (far - near).norm() <= 2e-6 * near.norm()
