@@ -72,6 +72,57 @@ def call(w, N, dtype=rb.F32, transposed=False, knobs={}, ldO=0, kind="spmm"):
             "knobs": knobs, "ldO": ldO}
 
 
+def waves_of(name, lds):
+    """Waves that a stage list is split over, of a launch of spmm_reg or spmm_reg_bf16: by the LDS of the partial sums."""
+    per_tile = 2 if name.startswith("spmm_reg_bf16") and ", 128, " in name else 1   # (pieces of 16 bytes of a lane's row)
+    return {0: 1, 8192: 2, 12288: 4}[lds // per_tile]
+
+
+# VGG19 conv5 (ten stages of 72 steps, 32 lists a tile of 64 columns), layers 9 and 7 at 1/4 (28 stages, as many lists; twelve, 16
+# lists), layer 5 at 1/2 and 4096 x 4096 at 1/8 (tile rows with one list): either side of 256, 512, 768 and 1024 lists.
+# (workload, columns, dtype, kernel, waves a list, two chains of sums)
+CONV5, L9, L7 = wl.VGG19_CONV5, wl.vgg19_sweep_workload(9, 2, wl.F32), wl.vgg19_sweep_workload(7, 2, wl.F32)
+SPLITS = [
+    (CONV5, 512, rb.F32, "spmm_reg", 4, False), (CONV5, 513, rb.F32, "spmm_reg", 2, True), (CONV5, 960, rb.F32, "spmm_reg", 2, True),
+    (CONV5, 1024, rb.F32, "spmm_reg", 2, False), (CONV5, 1025, rb.F32, "spmm_reg_dual", None, True),
+    (CONV5, 1984, rb.F32, "spmm_reg_dual", None, True), (CONV5, 1985, rb.F32, "spmm_reg_dual", None, False),
+    (CONV5, 512, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False), (CONV5, 513, rb.BF16_F32ACC, "spmm_reg_bf16", 2, True),
+    (CONV5, 1024, rb.BF16_F32ACC, "spmm_reg_bf16", 2, False), (CONV5, 1025, rb.BF16_F32ACC, "spmm_reg_bf16", 1, True),
+    (L9, 512, rb.F32, "spmm_reg", 4, False), (L9, 513, rb.F32, "spmm_reg", 2, True), (L9, 1025, rb.F32, "spmm_reg_dual", None, True),
+    (L9, 1025, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False), (L9, 1536, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False),
+    (L9, 1537, rb.BF16_F32ACC, "spmm_reg_bf16", 1, True),
+    (L7, 1536, rb.F32, "spmm_reg", 4, False), (L7, 1536, rb.BF16_F32ACC, "spmm_reg_bf16", 2, True),
+    (wl.vgg19_sweep_workload(5, 1, wl.F32), 2237, rb.F32, "spmm_reg", 2, False), (wl.sdmm4096_table2(1, 2), 181, rb.F32, "spmm_reg", 2, False),
+]
+
+
+@pytest.mark.parametrize("k", range(len(SPLITS)), ids=lambda k: f"{SPLITS[k][0].name}_{SPLITS[k][1]}_{SPLITS[k][2]}")
+def test_waves_of_a_stage_list(launches, k):
+    w, N, dtype, kernel, waves, chains = SPLITS[k]
+    rc, last, ran = launches([call(w, N, dtype)])[0]
+    assert rc == 0 and last == kernel and len(ran) == 1, (rc, last, ran)
+    name, lds = ran[0][0], ran[0][4]
+    assert name.startswith(kernel + "<") and name.endswith(", 1>") == chains, ran
+    assert waves is None or waves_of(name, lds) == waves, ran
+
+
+# knobs whose kernels are those of every split: lists are split until every SIMD has a wave, whatever their stages
+@pytest.mark.parametrize("N,waves", [(765, 4), (1024, 2), (1537, 2), (1984, 2)])
+@pytest.mark.parametrize("dtype,knobs", [(rb.F32, {rb.TUNE_REGISTER_SETS: 1}), (rb.F32, {rb.TUNE_REGISTER_SETS: 2}), (rb.F32, {rb.TUNE_ROW_GROUPS: 1}),
+                                         (rb.BF16_F32ACC, {rb.TUNE_ROW_GROUPS: 1}), (rb.BF16_F32ACC, {rb.TUNE_REGISTER_SETS: 2})])
+def test_knobs_of_the_waves_keep_full_splits(launches, dtype, knobs, N, waves):
+    rc, last, ran = launches([call(CONV5, N, dtype, knobs=knobs)])[0]
+    assert rc == 0 and last == ("spmm_reg_bf16" if dtype else "spmm_reg"), (rc, last)
+    assert waves_of(ran[0][0], ran[0][4]) == waves and not ran[0][0].endswith(", 1>"), ran
+
+
+def test_two_row_groups_by_hand_keep_full_splits(launches):
+    """fp32, two tile rows with one list a wave (VGG19 layer 5 at 1/2, 16 stages), 16 lists of two a tile of 64 columns."""
+    w = wl.vgg19_sweep_workload(5, 1, wl.F32)
+    ran = launches([call(w, N, knobs={rb.TUNE_ROW_GROUPS: 2}) for N in (16 * 64, 25 * 64, 35 * 64)])
+    assert [waves_of(r[2][0][0], r[2][0][4] // 2) for r in ran] == [4, 4, 2], ran
+
+
 # (mask, columns, partial sums of a value)
 FEW_UNITS = [((8, 2, 8, 1), (5, 1, 8, 9), (5, 1, 4, 9)), ((8, 2, 4, 1), (2, 1, 4, 9), (1, 1, 2, 9))]
 PARTIAL_SUMS = [(0, 2048, 7), (1, 1024, 8), (1, 3584, 28), (1, 3712, 29), (1, 3968, 31), (1, 4096, 32), (1, 14464, 113), (1, 15000, 118),
@@ -85,3 +136,11 @@ def test_reducers_by_the_number_of_partial_sums(launches):
         assert rc == 0 and ran[0][0].startswith("sddmm_reg<") and ran[0][2] == n, (N, n, ran)
         assert [r[0] for r in ran[1:]] == ["sddmm_reduce" if n < 8 else "sddmm_reduce<4>" if n < 32 else "sddmm_reduce<16>"], (N, ran)
         assert last.endswith(" + sddmm_reduce"), last
+
+
+def test_many_rows_per_tile_up_to_4_gib_of_rows_of_o(launches):
+    """Rows of O of a workgroup of spmm_reg_rows are 32-bit offsets apart: 288 rows of VGG19 layer 3 at 1/4 transposed, and 512 bytes."""
+    w = wl.vgg19_sweep_workload(3, 2, wl.F32)
+    last = (2 ** 32 // 4 - 128 - 1) // 288
+    near, far = launches([call(w, 3000, transposed=True, ldO=ldO) for ldO in (last, last + 1)])
+    assert near[:2] == (0, "spmm_reg_rows<2>") and far[:2] == (0, "spmm_reg"), (near, far)

@@ -7,8 +7,8 @@ from paper_2006_13486_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-# conv5: 4 clusters of tile rows and 8 vertices of G_i, ten stages: 32 lists a tile of 64 columns; VGG19 layer 9 at 1/4 28 stages.
-# fp32 and bf16, last columns just inside and just past a tile, at 256, 512, 768 and 1024 lists.
+# conv5 and VGG19 layer 9 at 1/4, ten and 28 stages: 32 lists a tile of 64 columns.  fp32 and bf16, last columns just inside and just past a
+# tile, at 256, 512, 768 and 1024 lists of conv5.  (test_dispatch.py names the kernels and splits)
 CONV5 = [c for tiles in (8, 16, 24, 32) for c in (64 * tiles - 3, 64 * tiles + 1)]
 CASES = [(wl.VGG19_CONV5, n, dtype) for n in CONV5 for dtype in (rb.F32, rb.BF16_F32ACC)]
 CASES += [(wl.vgg19_sweep_workload(9, 2, wl.F32), n, dtype) for n in (253, 513, 765, 769, 1021) for dtype in (rb.F32, rb.BF16_F32ACC)]
