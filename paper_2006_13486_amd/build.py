@@ -9,7 +9,8 @@ import sysconfig
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "librbgp.so")
-CALL = os.path.join(_HERE, "_call.so")   # the binding's calls without ctypes (csrc/rbgp_call.c)
+# the binding's calls without ctypes (csrc/rbgp_call.c), for this interpreter only: another one's objects are laid out otherwise
+CALL = os.path.join(_HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["rbgp_mfma_reg_bf16_wide.hip", "rbgp_mfma_reg_bf16.hip", "rbgp_mfma_reg_bf16_lean.hip", "rbgp_mfma_reg.hip", "rbgp_host.cpp",
            "rbgp_device.hip", "rbgp_mfma_reg_dual.hip", "rbgp_mfma_reg_split.hip",
            "rbgp_mfma_reg_bf16_shared.hip", "rbgp_mfma_reg_rows.hip", "rbgp_mfma_reg_narrow.hip", "rbgp_conv_tile.hip", "rbgp_sddmm.hip", "rbgp_sddmm_lines.hip", "rbgp_mfma_tile.hip"]
@@ -38,9 +39,23 @@ def build(verbose: bool = False, extra: list[str] | None = None) -> str:
             print(out)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.check_call(cmd)
-    subprocess.check_call([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
-                           "-o", CALL, os.path.join(CSRC, "rbgp_call.c")])
+    build_call()
     return LIB
+
+
+def build_call(out: str = CALL) -> bool:
+    """Compile the binding's calls without ctypes.  The binding does without them (see binding.py), so where there is no C compiler or
+    Python's headers are not installed that is said and no older file left in their place."""
+    for name in os.listdir(os.path.dirname(out)):
+        if name.startswith("_call.") and name.endswith(".so"):
+            os.remove(os.path.join(os.path.dirname(out), name))
+    try:
+        subprocess.check_call([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+                               "-o", out, os.path.join(CSRC, "rbgp_call.c")])
+    except (OSError, subprocess.CalledProcessError) as e:
+        print(f"{os.path.basename(out)} is not built ({e}): the binding's calls go through ctypes", file=sys.stderr)
+        return False
+    return True
 
 
 def build_sanitized() -> str:

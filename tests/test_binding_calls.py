@@ -1,14 +1,36 @@
 """The binding's calls without ctypes against its ctypes functions: the same calls accepted, refused and reported, on the CPU (no call
 reaches a launch: the library returns before one, for N = 0 or with an error)."""
 import inspect
+import os
+import shutil
+import sysconfig
 
 import numpy as np
 import pytest
 
 from paper_2006_13486_amd import binding as rb
+from paper_2006_13486_amd import build
 from paper_2006_13486_amd import workloads as wl
 
-pytestmark = pytest.mark.skipif(rb._call is None, reason="csrc/rbgp_call.c is not built")
+CAN_BUILD = shutil.which(os.environ.get("CC", "gcc")) and os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h"))
+
+
+def test_built_with_the_library_for_this_interpreter():
+    if not (os.path.exists(build.LIB) and CAN_BUILD):
+        pytest.skip("the library is not built, or this interpreter has no compiler and headers")
+    assert rb._call is not None
+    assert rb._call.__file__ == build.CALL and build.CALL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+@pytest.mark.skipif(not CAN_BUILD, reason="no compiler and headers")
+def test_a_failed_compile_leaves_no_older_file(tmp_path, monkeypatch, capfd):
+    out = tmp_path / os.path.basename(build.CALL)
+    (tmp_path / "_call.so").write_bytes(b"older")
+    assert build.build_call(str(out)) and [p.name for p in tmp_path.iterdir()] == [out.name]
+    monkeypatch.setenv("CC", "/nowhere/cc")
+    assert not build.build_call(str(out)) and not list(tmp_path.iterdir())
+    assert "ctypes" in capfd.readouterr().err
+
 
 M = K = 64
 PLAIN = {   # every argument after the mask, of a call that the library answers without a GPU
@@ -34,6 +56,7 @@ def outcome(fn, *args, **kwargs):
         return type(e), str(e).replace("_ctypes_", "_"), getattr(e, "code", None)
 
 
+@pytest.mark.skipif(rb._call is None, reason="csrc/rbgp_call.c is not built")
 @pytest.mark.parametrize("name", PLAIN)
 def test_same_outcome_as_through_ctypes(mask, name):
     fast, slow, args = getattr(rb, name), rb._WITH_CTYPES[name], PLAIN[name]

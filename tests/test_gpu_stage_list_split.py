@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 # tile, at 256, 512, 768 and 1024 lists of conv5.  (test_dispatch.py names the kernels and splits)
 CONV5 = [c for tiles in (8, 16, 24, 32) for c in (64 * tiles - 3, 64 * tiles + 1)]
 CASES = [(wl.VGG19_CONV5, n, dtype) for n in CONV5 for dtype in (rb.F32, rb.BF16_F32ACC)]
-CASES += [(wl.vgg19_sweep_workload(9, 2, wl.F32), n, dtype) for n in (253, 513, 765, 769, 1021) for dtype in (rb.F32, rb.BF16_F32ACC)]
+CASES += [(wl.vgg19_sweep_workload(9, 2, wl.F32), n, dtype) for n in (253, 513, 765, 769, 1021, 1025, 1535, 1537) for dtype in (rb.F32, rb.BF16_F32ACC)]
 # tile rows with one list: 560 and 768 lists in two
 CASES += [(wl.vgg19_sweep_workload(5, 1, wl.F32), 2237, rb.F32), (wl.sdmm4096_table2(1, 2), 181, rb.F32)]
 
