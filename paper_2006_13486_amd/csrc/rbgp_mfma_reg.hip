@@ -1001,7 +1001,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // Where that leaves fewer parts than fill every SIMD, each wave sums its list in two chains (HALF), so that no chain of fp32 sums
       // grows: 0.25 us of a wave in fp32.  There two parts of up to 512 lists pay where they divide a list better than four do -- two
       // waves of a quarter walk two stages more than one of a half where 4 k + 2 stages are to be dealt (us, four -> two: layer 10 at 1/16, 37
-      // images, six stages 9.3 -> 8.1; conv5, 48 images, ten 11.0 -> 10.0) -- or lists are long (layer 11 at 1/2, 32 stages 24.0 -> 22.5);
+      // images, six stages 9.3 -> 8.1; conv5, 48 images, ten 11.0 -> 10.0) -- or lists are long (layer 11 at 1/2, 32 stages 24.0 -> 22.5; fused, up
+      // to 448 lists: layer 9 at 1/4, 48 images 15.4 -> 15.1, 60 images 15.1 -> 15.9);
       // else they cost up to 9 % (layer 7 at 1/4, 24 images, 12 stages 10.7 -> 10.9; WRN group 1, 4321 columns, eight 5.9 -> 6.4).
       lists = ncl * m->a[2] * ntiles;
       while (lgS < 2 && (lists << lgS) < 1024) ++lgS;
@@ -1009,7 +1010,7 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
         const int fill = lgS;
         const int n = m->reg_clusters.max_stages;
         lgS = lists <= 256   ? 2
-              : lists <= 512 ? (bf16 || n % 4 == 2 || n >= 20 || lists == 512 ? 1 : 2)
+              : lists <= 512 ? (bf16 || n % 4 == 2 || (n >= 20 && (!conv || lists <= 448)) || lists == 512 ? 1 : 2)
                              : lists <= 768 && n >= 12 ? (!bf16 && pl.fold > 1 ? 1 : 2) : 0;
         halves = lgS < fill;
       }

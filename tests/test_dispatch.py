@@ -34,6 +34,8 @@ for c in json.load(sys.stdin):
     try:
         if c["call"] == "spmm":
             rb.rbgp_spmm(m, c["dtype"], M, K, N, at, at, ld, at, c["ldO"] or N)
+        elif c["call"] == "conv":
+            rb.rbgp_conv3x3(m, c["dtype"], M, K // 9, N // 16, 4, 4, at, at, at, N)
         else:
             rb.rbgp_sddmm(m, c["dtype"], M, K, N, at, ld, at, ld, at)
         rc = 0
@@ -80,7 +82,7 @@ def waves_of(name, lds):
 
 # VGG19 conv5 (ten stages of 72 steps, 32 lists a tile of 64 columns), layers 9 and 7 at 1/4 (28 stages, as many lists; twelve, 16
 # lists), layer 5 at 1/2 and 4096 x 4096 at 1/8 (tile rows with one list): either side of 256, 512, 768 and 1024 lists.
-# (workload, columns, dtype, kernel, waves a list, two chains of sums)
+# (workload, columns, dtype, kernel, waves a list, two chains of sums[, call: "conv" of 4 x 4 pixels])
 CONV5, L9, L7 = wl.VGG19_CONV5, wl.vgg19_sweep_workload(9, 2, wl.F32), wl.vgg19_sweep_workload(7, 2, wl.F32)
 SPLITS = [
     (CONV5, 512, rb.F32, "spmm_reg", 4, False), (CONV5, 513, rb.F32, "spmm_reg", 2, True), (CONV5, 960, rb.F32, "spmm_reg", 2, True),
@@ -89,6 +91,7 @@ SPLITS = [
     (CONV5, 512, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False), (CONV5, 513, rb.BF16_F32ACC, "spmm_reg_bf16", 2, True),
     (CONV5, 1024, rb.BF16_F32ACC, "spmm_reg_bf16", 2, False), (CONV5, 1025, rb.BF16_F32ACC, "spmm_reg_bf16", 1, True),
     (L9, 512, rb.F32, "spmm_reg", 4, False), (L9, 513, rb.F32, "spmm_reg", 2, True), (L9, 1025, rb.F32, "spmm_reg_dual", None, True),
+    (L9, 896, rb.F32, "spmm_reg", 2, True, "conv"), (L9, 912, rb.F32, "spmm_reg", 4, False, "conv"), (L9, 960, rb.F32, "spmm_reg", 2, True),
     (L9, 1025, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False), (L9, 1536, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False),
     (L9, 1537, rb.BF16_F32ACC, "spmm_reg_bf16", 1, True),
     (L7, 1536, rb.F32, "spmm_reg", 4, False), (L7, 1536, rb.BF16_F32ACC, "spmm_reg_bf16", 2, True),
@@ -96,10 +99,10 @@ SPLITS = [
 ]
 
 
-@pytest.mark.parametrize("k", range(len(SPLITS)), ids=lambda k: f"{SPLITS[k][0].name}_{SPLITS[k][1]}_{SPLITS[k][2]}")
+@pytest.mark.parametrize("k", range(len(SPLITS)), ids=lambda k: f"{SPLITS[k][0].name}_{SPLITS[k][1]}_{SPLITS[k][2]}_{len(SPLITS[k])}")
 def test_waves_of_a_stage_list(launches, k):
-    w, N, dtype, kernel, waves, chains = SPLITS[k]
-    rc, last, ran = launches([call(w, N, dtype)])[0]
+    w, N, dtype, kernel, waves, chains, kind = SPLITS[k] if len(SPLITS[k]) == 7 else SPLITS[k] + ("spmm",)
+    rc, last, ran = launches([call(w, N, dtype, kind=kind)])[0]
     assert rc == 0 and last == kernel and len(ran) == 1, (rc, last, ran)
     name, lds = ran[0][0], ran[0][4]
     assert name.startswith(kernel + "<") and name.endswith(", 1>") == chains, ran
