@@ -18,7 +18,7 @@
 //
 // us, VGG19 conv3 at 8192 pixels, both ways: register kernels 15.3 and 16.7, four waves that load two pixels of a channel at a
 // time and pass the phases one after the other 13.5, this one 9.5 (10.1 with the tiles of a row looked up and dealt to the waves in the
-// prologue and the weights loaded before the channels); layer 9 at 1/8, 2048 pixels 14.6, 11.2, 8; the other sizes
+// prologue and the weights loaded before the channels; 20 900 -> 19 400 cycles a wave); layer 9 at 1/8, 2048 pixels 14.6, 11.2, 8.3; the other sizes
 // stand at the dispatch rule.  What bounds it: a chain of latencies (launch 2.5; tables 0.6; the channels, all of conv3's in one
 // round of loads; their first use) and then issue: 1000 vector instructions and 800 cycles of products a wave, two waves a SIMD.
 // Counters (conv3): waves wait for 44 % of their cycles (four waves 41, of a longer launch), matrix core 11 % busy, vector
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256 * S, 2 / S) void conv_tile(ConvTileParams p) {
   if (nt >= p.ntiles) return;
   const int u1 = ug * kRows + wr;
   // tile columns of the wave's row; those of the workgroup's rows still to come; those that are this wave's, in ascending order as the
-  // chunks are (one load of five words: row by row behind their conditions, and dealt to the waves here, they took 1100 cycles)
+  // chunks are (one load of five words: row by row behind their conditions, and dealt to the waves here, each waited for the last)
   const uint64_t *const tiles = p.tiles + ug * kRows;
   const uint64_t mine = tiles[wr];
   uint64_t left = tiles[0] | tiles[1] | tiles[2] | tiles[3], todo = S == 1 ? mine : tiles[(1 + ws) * p.rows + wr];

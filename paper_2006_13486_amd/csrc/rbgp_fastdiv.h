@@ -1,10 +1,10 @@
 // Division by a number that is known when a kernel is launched, without a division.
 //
 // A kernel finds its tile, rows and steps by dividing its block and thread numbers by sizes of the mask.  The compiler turns
-// such a division into a reciprocal in vector registers and some 25 dependent instructions, half a microsecond for the two
-// or three of a prologue -- before the first table load can be issued, in kernels of 4 to 15 us.  The host computes
+// such a division into a reciprocal in vector registers and some 25 dependent instructions, two or three times a
+// prologue -- before the first table load can be issued, in kernels of 4 to 15 us.  The host computes
 // the multiplier instead: three scalar instructions.  Together with the kernel arguments of a prologue in one go (grid_args,
-// rbgp_reg_common.h), us, before -> after: VGG19 conv3 bf16, 8192 columns 13.4 -> 13.0, its fused training step 36.1 -> 35.0, layer 13
+// rbgp_reg_common.h) 800 to 1300 of a wave's 30 000 cycles in the register kernels; us, before -> after: VGG19 conv3 bf16, 8192 columns 13.4 -> 13.0, its fused training step 36.1 -> 35.0, layer 13
 // at 1/2 fp32, 512 columns 14.6 -> 14.1, kernels of 5 to 7 us 0.2 to 0.35.
 #ifndef RBGP_FASTDIV_H
 #define RBGP_FASTDIV_H
