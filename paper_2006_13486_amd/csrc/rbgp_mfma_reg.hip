@@ -1390,8 +1390,8 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
     const bool wide = !uneven && tab->max_stages <= 4 && all > 256 && launched(tiles96) <= 256;
     const int64_t tiles = wide ? tiles96 : tiles64, wgs = launched(tiles);
     const size_t bytes = size_t(tab->max_stages) * (wide ? 18432 : 12288) + size_t(groups) * 512;
-    const bool near_rows = (int64_t(rows_wg) * ldO + 128) * 4 < (int64_t(1) << 32);   // (32-bit offsets into a workgroup's rows of O)
-    if (all >= 160 && !uneven && near_rows && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
+    const bool far = (int64_t(rows_wg) * ldO + 128) * 4 >= (int64_t(1) << 32);   // (else 32-bit offsets into a workgroup's rows of O)
+    if (all >= 160 && !uneven && wgs <= 0x7fffffff && bytes <= 160 * 1024) {
       rp.ntiles = int(tiles);
       rp.ncl = int(rows_o);
       rp.order = tiles >= 8 ? 2 : 0;
@@ -1404,12 +1404,13 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // else four waves, three workgroups a CU (layer 6: 4 waves / 9, 256 workgroups 14.1 / 10.4, 296 16.5 / 18.1, 768 21.4 /
       // 27.0).
       const int waves = wide || all <= 256 || tab->max_stages > 4 ? std::min(groups, 9) : 4;
-      reg_fn rows = rbgp_reg_rows_kernel(wide ? 3 : 2);
+      reg_fn rows = rbgp_reg_rows_kernel(wide ? 3 : 2, far);
       if (bytes > 64 * 1024)
         RBGP_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(rows), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
       hipLaunchKernelGGL(rows, dim3(unsigned(wgs)), dim3(unsigned(64 * waves)), bytes, static_cast<hipStream_t>(stream), rp);
       RBGP_HIP(hipGetLastError());
-      rbgp_set_last_kernel("spmm_reg_rows", {wide ? 3 : 2});
+      if (far) rbgp_set_last_kernel("spmm_reg_rows", {wide ? 3 : 2, 1});
+      else rbgp_set_last_kernel("spmm_reg_rows", {wide ? 3 : 2});
       return RBGP_OK;
     }
   }

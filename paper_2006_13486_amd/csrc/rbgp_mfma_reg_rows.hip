@@ -43,8 +43,8 @@ constexpr int kAhead = 4;                       // stages of weights in flight
 constexpr uint32_t kNone = 0xffffffffu;
 
 // T = 2: 64 columns, a pair of them per lane, lists of up to twelve stages.  T = 3: 96 columns, a block of 32 at a time, lists of up
-// to four stages.
-template <int T>
+// to four stages.  FAR: a workgroup's rows of O lie 4 GiB apart and more: 64-bit offsets, made at the stores.
+template <int T, bool FAR>
 __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   constexpr int CW = 32 * T;
   // [stage][column block][part][half of the 16 steps of a lane][lane], then what every row needs (info)
@@ -70,12 +70,12 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   const int32_t *stg = p.stages + int64_t(u1) * 2 * TS;
   const int tb0 = stg[lane], tf0 = stg[TS + lane], cnt0 = p.counts[u1];
   u32x4 *const parts = reinterpret_cast<u32x4 *>(lds);
-  // of every row: its byte offset in O from the tile row's first row (kNone: no such row), then: its weights relative to a stage's,
+  // of every row: its byte offset in O from the tile row's first row (FAR: in rows; kNone: no such row), then: its weights relative to a stage's,
   // the places of its G_i vertex's two edges (the index operand)
   uint32_t *const row_at = reinterpret_cast<uint32_t *>(lds + p.ct_cnt * (T * 6144));
   const int per_row = p.a3 * p.R, rows = p.fold * per_row, groups = (rows + 31) >> 5;
   int2 *const info = reinterpret_cast<int2 *>(row_at + groups * 32);
-  const uint32_t ld_bytes = uint32_t(p.ldO) * 4u;   // (a tile row of O is below 4 GiB: checked by the host)
+  const uint32_t ld_bytes = FAR ? 1u : uint32_t(p.ldO) * 4u;   // (a tile row of O is below 4 GiB unless FAR: checked by the host)
   // the edges of the G_i vertex of row x (of the rows that the thread prepares, the first)
   auto edges_of = [&](int x) {
     const int f = rbgp_fast::quotient(x, p.by_row), ui = rbgp_fast::quotient(x - f * per_row, p.by_r);
@@ -182,7 +182,14 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
   // the tile row's first row of O, at the workgroup's first column; register i of the accumulators is row 8 (i / 4) + 4 h + i % 4 of a
   // group
   unsigned char *const out = reinterpret_cast<unsigned char *>(p.O + int64_t(u1) * p.tm * p.ldO + n0);
-  const int64_t out_n = p.N;
+  const int64_t out_n = p.N, far_ld = p.ldO * 4;
+  // Past the caches only where rows begin at whole 64 bytes: of others, the parts of a line that two workgroups write meet in the L2
+  // (us, past the caches / through them: layer 6 at 1/4, 8128 columns, rows of 8144 27.2 / 28.8, 8136 39.6 / 28.5, 8129 50.6 / 29.9;
+  // layer 3, 16320, rows of 16336 25.3 / 23.2, 16321 47.2 / 26.4; 96 columns, 2304, rows of 2320 12.2 / 13.7, 2305 15.7 / 14.1)
+  const bool past = p.ldO % 16 == 0 && reinterpret_cast<uintptr_t>(p.O) % 64 == 0;
+  auto place = [&](uint32_t at, uint32_t column) {
+    return reinterpret_cast<float *>(out + (FAR ? uint64_t(at) * uint64_t(far_ld) : uint64_t(at)) + column);
+  };
   auto rows_at = [&](uint32_t (&at)[16], int g) {
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
@@ -237,10 +244,15 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
             }
           }
         }
-        if (n < out_n)
+        if (n < out_n && past) {
 #pragma unroll
           for (int i = 0; i < 16; ++i)
-            if (at[i] != kNone) __builtin_nontemporal_store(acc[i], reinterpret_cast<float *>(out + at[i] + uint32_t(128 * t + 4 * j)));
+            if (at[i] != kNone) __builtin_nontemporal_store(acc[i], place(at[i], uint32_t(128 * t + 4 * j)));
+        } else if (n < out_n) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (at[i] != kNone) *place(at[i], uint32_t(128 * t + 4 * j)) = acc[i];
+        }
       }
       if (g + W < groups) {
         a_base = info[(g + W) * 32 + j].x + h * 256;
@@ -316,21 +328,28 @@ __global__ __launch_bounds__(576, 3) void spmm_reg_rows(RegParams p) {
     }
     uint32_t at[16];
     rows_at(at, g);
-    if (whole) {
+    if (whole && past) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (at[i] != kNone) __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_any *>(out + at[i] + uint32_t(8 * j)));
+        if (at[i] != kNone) __builtin_nontemporal_store(f32x2_s{acc[0][i], acc[1][i]}, reinterpret_cast<f32x2_any *>(place(at[i], uint32_t(8 * j))));
+    } else if (whole) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (at[i] != kNone) *reinterpret_cast<f32x2_any *>(place(at[i], uint32_t(8 * j))) = f32x2_s{acc[0][i], acc[1][i]};
     } else {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
         if (n0 + 2 * j + t < out_n)
 #pragma unroll
           for (int i = 0; i < 16; ++i)
-            if (at[i] != kNone) *reinterpret_cast<float *>(out + at[i] + uint32_t(8 * j + 4 * t)) = acc[t][i];
+            if (at[i] != kNone) *place(at[i], uint32_t(8 * j + 4 * t)) = acc[t][i];
     }
   }
 }
 
 }  // namespace
 
-rbgp_reg_fn rbgp_reg_rows_kernel(int T) { return T == 3 ? spmm_reg_rows<3> : T == 2 ? spmm_reg_rows<2> : nullptr; }
+rbgp_reg_fn rbgp_reg_rows_kernel(int T, bool far) {
+  if (T == 3) return far ? spmm_reg_rows<3, true> : spmm_reg_rows<3, false>;
+  return far ? spmm_reg_rows<2, true> : spmm_reg_rows<2, false>;
+}

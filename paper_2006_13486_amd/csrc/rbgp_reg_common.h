@@ -257,7 +257,7 @@ rbgp_reg_fn rbgp_reg_bf16_shared_kernel(int RV, int PR);
 rbgp_reg_fn rbgp_reg_split_kernel(int RW, bool sparse);
 // fp32 kernel of workgroups that take all rows of a row of G_o (rbgp_mfma_reg_rows.hip) x 32 T columns: 2, or 3 for lists of up to
 // four stages; nullptr: not built
-rbgp_reg_fn rbgp_reg_rows_kernel(int T);
+rbgp_reg_fn rbgp_reg_rows_kernel(int T, bool far);
 // kernel of workgroups of eight waves that share a stage list, on 16 columns (rbgp_mfma_reg_narrow.hip); nullptr: not built
 rbgp_reg_fn rbgp_reg_narrow_kernel(int KC, int RS, bool bf16);
 // LDS family, fp32, on the bf16 matrix core: KS kept steps of 32 per stage (8 or 16; sparse: never both k and k + 16), workgroups of

@@ -141,9 +141,11 @@ def test_reducers_by_the_number_of_partial_sums(launches):
         assert last.endswith(" + sddmm_reduce"), last
 
 
-def test_many_rows_per_tile_up_to_4_gib_of_rows_of_o(launches):
-    """Rows of O of a workgroup of spmm_reg_rows are 32-bit offsets apart: 288 rows of VGG19 layer 3 at 1/4 transposed, and 512 bytes."""
+def test_many_rows_per_tile_and_4_gib_of_rows_of_o(launches):
+    """Rows of O of a workgroup of spmm_reg_rows are 32-bit offsets apart up to 4 GiB (288 rows of VGG19 layer 3 at 1/4 transposed, and 512
+    bytes), 64-bit ones from there on."""
     w = wl.vgg19_sweep_workload(3, 2, wl.F32)
     last = (2 ** 32 // 4 - 128 - 1) // 288
     near, far = launches([call(w, 3000, transposed=True, ldO=ldO) for ldO in (last, last + 1)])
-    assert near[:2] == (0, "spmm_reg_rows<2>") and far[:2] == (0, "spmm_reg"), (near, far)
+    assert near[:2] == (0, "spmm_reg_rows<2>") and far[:2] == (0, "spmm_reg_rows<2, 1>"), (near, far)
+    assert near[2][0][0] == "spmm_reg_rows<2, 0>" and far[2][0][0] == "spmm_reg_rows<2, 1>" and near[2][0][1:] == far[2][0][1:], (near, far)
