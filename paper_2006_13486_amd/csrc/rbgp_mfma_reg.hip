@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256, (LEAN && !HALF && NG == 1 && RS == 16 && (KC =
   const int64_t out_ld = p.ldO, out_n = p.N;
   const int out_tm = p.tm, out_a4 = p.a4, out_r = p.R;
   auto whole_at = [&](int64_t n0c) { return n0c + j * 4 + 4 <= out_n; };
-  auto store_unit = [&](int t, f32x4 v, int k, int64_t n0c, bool whole) {
+  auto store_unit = [&](int t, f32x4 v, int k, int64_t n0c, bool whole, auto past) {
     const int i16 = 4 * g + t, mm = i16 / RS, r = i16 % RS;
     int u1 = __builtin_amdgcn_ds_bpermute(mm * 4, memv);
     if constexpr (NG > 1) u1 = u1 >= 0 ? u1 + k : u1;   // (group k is the tile row after group k - 1's)
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256, (LEAN && !HALF && NG == 1 && RS == 16 && (KC =
       const int64_t m = int64_t(u1) * out_tm + u3 * out_a4 + ro;
       float *o = out + m * out_ld + n0c + j * 4;
       if (whole) {
-        store_x4(o, v);
+        store_x4<decltype(past)::value>(o, v);
       } else {
 #pragma unroll
         for (int w = 0; w < 4; ++w)
@@ -411,12 +411,17 @@ __global__ __launch_bounds__(256, (LEAN && !HALF && NG == 1 && RS == 16 && (KC =
       }
     }
   };
-  auto store_tile = [&](int64_t n0c) {
+  auto store_tile_as = [&](int64_t n0c, auto past) {
     const bool whole = whole_at(n0c);
 #pragma unroll
     for (int k = 0; k < NG; ++k)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) store_unit(t, unit(t, k), k, n0c, whole);
+      for (int t = 0; t < 4; ++t) store_unit(t, unit(t, k), k, n0c, whole, past);
+  };
+  const bool through = p.through != 0;
+  auto store_tile = [&](int64_t n0c) {
+    if (through) store_tile_as(n0c, std::false_type{});
+    else store_tile_as(n0c, std::true_type{});
   };
 
   // The register sets take turns; stages past the end read zeros (sentinel table lanes).
@@ -510,7 +515,7 @@ __global__ __launch_bounds__(256, (LEAN && !HALF && NG == 1 && RS == 16 && (KC =
             else
               v += red4[((k * 4 + w0 + kk) * per_wave + (t >> lgS) * (S - 1) + ks - (ks > kk ? 1 : 0)) * 64 + lane];
           }
-          store_unit(t, v, k, n0, whole);
+          store_unit(t, v, k, n0, whole, std::true_type{});
         }
       }
   }
@@ -1305,6 +1310,12 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
   rp.I = static_cast<const float *>(I);
   rp.O = static_cast<float *>(O);
   rp.obf16 = out_bf16 ? 1 : 0;
+  // Stores past the caches, but not of rows that begin inside a segment of 64 bytes where O fills most of the Infinity Cache: the parts of a
+  // segment that two workgroups write meet in memory, and wait for one another there (us, a store an element / past the caches / through
+  // them: transposed WRN group 1, 112 MB of O 57.6 / 54.6 / 42.5, 160 MB 80.5 / 81.1 / 59.4, transposed layer 3 at 1/8, 24673 columns 59.8 / 62.9 /
+  // 43; 80 MB 43.1 / 38.3, through them 32 to 38; 240 MB, which nothing holds, 145 / 109 / 120).
+  const int64_t mb = m->M * N * 4 >> 20;
+  rp.through = mb >= 96 && mb < 192 && (ldO % 16 || reinterpret_cast<uintptr_t>(O) % 64);
   rp.rowtab = *rowtab;
   rp.stages = dual ? nullptr : tab->stages; rp.counts = dual ? nullptr : tab->counts; rp.members = dual ? nullptr : tab->members;
   rp.tstride = tab->tstride;

@@ -39,6 +39,7 @@ struct RegParams {
   const float *I;          // activations (same)
   float *O;                // fp32, or bf16 bits when obf16 is set (ldO counts elements of that type)
   int obf16;               // bf16 kernels: round the sums to bf16 when storing O
+  int through;             // spmm_reg, whole lists: store rows of O through the caches
   const int32_t *rowtab;   // [a_i][NO*4]: stage-relative I row of each contraction step (padding -> 0); row_offset's table after it
   const int32_t *stages;   // [ncl][1+MG][tstride]: per stage the base row of the stage, then per
                            //   cluster member j_o * NSTG + (stage within the tile), the position of its

@@ -20,6 +20,8 @@ CASES = [  # (workload, columns, transposed, dtype, kernel)
     (wl.vgg19_sweep_workload(6, 2, wl.F32), 2369, True, rb.F32, "spmm_reg_rows<3>"),
     (wl.vgg19_sweep_workload(6, 2, wl.F32), 8191, True, rb.F32, "spmm_reg_rows<2>"),
     (wl.vgg19_sweep_workload(6, 2, wl.F32), 2361, True, rb.F32, "spmm_reg_rows<3>"),
+    (wl.WRN_G1, 45001, True, rb.F32, "spmm_reg"),              # (99 MB of O: through the caches, several column tiles a wave)
+    (wl.vgg19_sweep_workload(1, 2, wl.F32), 47003, True, rb.F32, "spmm_reg"),
 ]
 
 
