@@ -1004,18 +1004,19 @@ int rbgp_reg_launch(const rbgp_mask *m, void **state, const int *tune, bool bf16
       // Stages of up to 32 steps keep the split (transposes: 32 steps, 4 stages, 864 lists 6.2, whole 7.8; 8 stages, 288 lists in
       // four 6.1, in two 8.3): the waves of a short list mostly wait, and more of them hide more.
       // Where that leaves fewer parts than fill every SIMD, each wave sums its list in two chains (HALF), so that no chain of fp32 sums
-      // grows: 0.25 us of a wave in fp32.  There two parts of up to 512 lists pay where they divide a list better than four do -- two
-      // waves of a quarter walk two stages more than one of a half where 4 k + 2 stages are to be dealt (us, four -> two: layer 10 at 1/16, 37
-      // images, six stages 9.3 -> 8.1; conv5, 48 images, ten 11.0 -> 10.0) -- or lists are long (layer 11 at 1/2, 32 stages 24.0 -> 22.5; fused, up
-      // to 448 lists: layer 9 at 1/4, 48 images 15.4 -> 15.1, 60 images 15.1 -> 15.9);
-      // else they cost up to 9 % (layer 7 at 1/4, 24 images, 12 stages 10.7 -> 10.9; WRN group 1, 4321 columns, eight 5.9 -> 6.4).
+      // grows: 0.25 us of a wave in fp32, 0.1 in bf16, where lists of four stages stay in four (layer 7 at 1/16, 20 images 6.25, in two
+      // 6.44).  fp32: two parts of up to 512 lists pay where they divide a list better than four do -- two waves of a quarter walk two
+      // stages more than one of a half where 4 k + 2 stages are to be dealt (us, four -> two: layer 10 at 1/16, 37 images, six stages 9.3 ->
+      // 8.1; conv5, 48 images, ten 11.0 -> 10.0) -- or lists are long (layer 11 at 1/2, 32 stages 24.0 -> 22.5; fused, up to 448 lists:
+      // layer 9 at 1/4, 48 images 15.4 -> 15.1, 60 images 15.1 -> 15.9); else they cost up to 9 % (layer 7 at 1/4, 24 images, 12 stages
+      // 10.7 -> 10.9; WRN group 1, 4321 columns, eight 5.9 -> 6.4).
       lists = ncl * m->a[2] * ntiles;
       while (lgS < 2 && (lists << lgS) < 1024) ++lgS;
       if (by_walk && G == 1) {
         const int fill = lgS;
         const int n = m->reg_clusters.max_stages;
         lgS = lists <= 256   ? 2
-              : lists <= 512 ? (bf16 || n % 4 == 2 || (n >= 20 && (!conv || lists <= 448)) || lists == 512 ? 1 : 2)
+              : lists <= 512 ? ((bf16 && n > 4) || n % 4 == 2 || (n >= 20 && (!conv || lists <= 448)) || lists == 512 ? 1 : 2)
                              : lists <= 768 && n >= 12 ? (!bf16 && pl.fold > 1 ? 1 : 2) : 0;
         halves = lgS < fill;
       }

@@ -95,6 +95,7 @@ SPLITS = [
     (L9, 1025, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False), (L9, 1536, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False),
     (L9, 1537, rb.BF16_F32ACC, "spmm_reg_bf16", 1, True),
     (L7, 1536, rb.F32, "spmm_reg", 4, False), (L7, 1536, rb.BF16_F32ACC, "spmm_reg_bf16", 2, True),
+    (wl.vgg19_sweep_workload(7, 4, wl.BF16), 1280, rb.BF16_F32ACC, "spmm_reg_bf16", 4, False),
     (wl.vgg19_sweep_workload(5, 1, wl.F32), 2237, rb.F32, "spmm_reg", 2, False), (wl.sdmm4096_table2(1, 2), 181, rb.F32, "spmm_reg", 2, False),
 ]
 
