@@ -11,11 +11,13 @@ from paper_2006_13486_amd import build
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 
-# template arguments of spmm_reg_bf16 (stage, rows a tile row, groups, columns, one register set, stage of the layout, two chains), sddmm_reg and sddmm_lines (row groups, step groups,
+# template arguments of spmm_reg (stage, rows a tile row, tap-grouped, groups, column tiles, one register set, stage of the layout, two
+# chains), spmm_reg_bf16 (stage, rows a tile row, groups, columns, one register set, stage of the layout, two chains), sddmm_reg and sddmm_lines (row groups, step groups,
 # bf16, convolution, all of G_i[, 64-bit offsets]) -> waves a SIMD.  sddmm_lines has two waves a SIMD in a workgroup: four are two of those.
 WAVES = {f"spmm_reg_bf16<36, {rs}, 1, 64, 0, 36, 0>": 4 for rs in (2, 4, 8, 16)}
 WAVES.update({f"spmm_reg_bf16<8, {rs}, 1, 64, 0, 8, 0>": 7 for rs in (2, 4, 8, 16)})
 WAVES.update({f"spmm_reg_bf16<8, {rs}, 2, 64, 0, 8, 0>": 4 for rs in (2, 4, 8, 16)})
+WAVES.update({"spmm_reg<32, 16, 0, 1, 0, 1, 32, 0>": 4, "spmm_reg<36, 16, 1, 1, 0, 1, 36, 0>": 4, "spmm_reg<72, 16, 1, 1, 0, 1, 72, 0>": 4})
 WAVES.update({f"sddmm_reg<2, 2, {b}, 0, 1>": 4 for b in (0, 1)})
 WAVES.update({"sddmm_reg<1, 1, 0, 0, 1>": 8})
 WAVES.update({f"sddmm_lines<2, 1, 1, 1, {g}, 1>": 4 for g in (0, 1)})
