@@ -35,7 +35,8 @@ for c in json.load(sys.stdin):
         if c["call"] == "spmm":
             rb.rbgp_spmm(m, c["dtype"], M, K, N, at, at, ld, at, c["ldO"] or N)
         elif c["call"] == "conv":
-            rb.rbgp_conv3x3(m, c["dtype"], M, K // 9, N // 16, 4, 4, at, at, at, N)
+            s = c["side"]
+            rb.rbgp_conv3x3(m, c["dtype"], M, K // 9, N // s // s, s, s, at, at, at, N)
         else:
             rb.rbgp_sddmm(m, c["dtype"], M, K, N, at, ld, at, ld, at)
         rc = 0
@@ -68,10 +69,10 @@ def launches(tmp_path_factory):
     return run
 
 
-def call(w, N, dtype=rb.F32, transposed=False, knobs={}, ldO=0, kind="spmm"):
+def call(w, N, dtype=rb.F32, transposed=False, knobs={}, ldO=0, kind="spmm", side=4):
     M, K = (w.K, w.M) if transposed else (w.M, w.K)
     return {"mask": [w.rows, w.cols, w.row_deg, w.mask_seed], "transposed": transposed, "call": kind, "dtype": dtype, "M": M, "K": K, "N": N,
-            "knobs": knobs, "ldO": ldO}
+            "knobs": knobs, "ldO": ldO, "side": side}
 
 
 def waves_of(name, lds):
@@ -108,6 +109,28 @@ def test_waves_of_a_stage_list(launches, k):
     name, lds = ran[0][0], ran[0][4]
     assert name.startswith(kernel + "<") and name.endswith(", 1>") == chains, ran
     assert waves is None or waves_of(name, lds) == waves, ran
+
+
+# A batch for every kernel of two chains of sums that the networks and SDMM tables reach: (layer, log2 of 1 / density) of VGG19 or a workload,
+# columns, dtype, side of the images of a fused convolution (0: lowered)
+TWO_CHAINS = [((4, 4), 2365, 0, 0), ((4, 4), 2368, 0, 8), ((1, 2), 7165, 0, 0), ((1, 2), 7168, 0, 32), ((2, 2), 6144, 0, 16), (wl.sdmm4096_table2(0, 4), 145, 0, 0),
+              ((9, 1), 555, 0, 0), ((4, 1), 2368, 0, 8), ((8, 4), 589, 0, 0), ((4, 3), 2368, 0, 8), ((9, 4), 573, 0, 0), ((5, 3), 1536, 0, 8), ((2, 2), 6141, 0, 0),
+              ((11, 2), 1027, 0, 0), ((4, 4), 4170, 1, 0), ((4, 4), 1203, 1, 0), ((1, 2), 24573, 1, 0), (wl.WRN_G1, 4321, 1, 0), ((2, 2), 9469, 1, 0),
+              ((2, 2), 2207, 1, 0), ((11, 1), 521, 1, 0), ((7, 4), 4143, 1, 0), ((8, 4), 589, 1, 0), ((4, 2), 4797, 1, 0), ((8, 2), 589, 1, 0),
+              ((8, 1), 592, 1, 4), ((5, 1), 1536, 1, 8)]
+
+
+def two_chains(k):
+    what, N, dtype, side = TWO_CHAINS[k]
+    return (wl.vgg19_sweep_workload(*what, dtype) if isinstance(what, tuple) else what), N, dtype, side
+
+
+def test_batches_in_two_chains_of_sums(launches):
+    cases = [two_chains(k) for k in range(len(TWO_CHAINS))]
+    ran = launches([call(w, N, dtype, kind="conv" if side else "spmm", side=side) for w, N, dtype, side in cases])
+    for k, (rc, last, kernels) in enumerate(ran):
+        assert rc == 0 and last in ("spmm_reg", "spmm_reg_dual", "spmm_reg_bf16") and kernels[0][0].endswith(", 1>"), (TWO_CHAINS[k], last, kernels)
+    assert len({r[2][0][0] for r in ran}) >= 25, sorted(r[2][0][0] for r in ran)
 
 
 # knobs whose kernels are those of every split: lists are split until every SIMD has a wave, whatever their stages

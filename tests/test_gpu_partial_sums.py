@@ -4,7 +4,7 @@ import torch
 
 from paper_2006_13486_amd import binding as rb
 from paper_2006_13486_amd import workloads as wl
-from .test_dispatch import FEW_UNITS, PARTIAL_SUMS
+from tests.test_dispatch import FEW_UNITS, PARTIAL_SUMS
 
 pytestmark = pytest.mark.gpu
 

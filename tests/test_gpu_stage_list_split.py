@@ -4,6 +4,7 @@ import torch
 
 from paper_2006_13486_amd import binding as rb
 from paper_2006_13486_amd import workloads as wl
+from tests.test_dispatch import TWO_CHAINS, two_chains
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +78,34 @@ def test_fewer_waves_a_list_have_no_longer_chains(case):
     print(f"[gpu]   {default:.3e}, {S} waves a list {filled:.3e}", flush=True)
     # (at least 40 chains' totals of as many products each: another order of the last two or four additions moves the norm by below 2 %)
     assert default <= 1.02 * filled
+
+
+@pytest.mark.parametrize("k", range(len(TWO_CHAINS)))
+def test_two_chains_of_sums(k):
+    """Every kernel of two chains, lowered with a ragged last tile and fused, against sums in 64 bits."""
+    w, N, dtype, side = two_chains(k)
+    t_in = torch.float32 if dtype == rb.F32 else torch.bfloat16
+    print(f"[gpu] two chains {w.name} N={N} dtype={dtype} side={side}", flush=True)
+    mask = rb.rbgp_make_mask(w.rows, w.cols, w.row_deg, w.mask_seed)
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    weights = (torch.randn(w.nnz, generator=gen, device="cuda") * w.w_std).to(t_in)
+    packed = torch.zeros(rb.rbgp_packed_bytes(mask, dtype), dtype=torch.uint8, device="cuda")
+    rb.rbgp_pack_device(mask, dtype, weights.data_ptr(), packed.data_ptr())
+    out = torch.full((w.M + 1, N), -77.0, device="cuda")
+    if side:
+        images, C = N // side ** 2, w.K // 9
+        X = torch.zeros((C, images, side + 2, side + 2), dtype=t_in, device="cuda")
+        X[:, :, 1:-1, 1:-1] = torch.randn((C, images, side, side), generator=gen, device="cuda")
+        rb.rbgp_conv3x3(mask, dtype, w.M, C, images, side, side, packed.data_ptr(), X.data_ptr(), out.data_ptr(), N)
+        I = torch.stack([X[:, :, dy:dy + side, dx:dx + side] for dy in range(3) for dx in range(3)], 1).reshape(w.K, N).double()
+    else:
+        ldI = -(-N // 8) * 8
+        rows = torch.randn((w.K, ldI), generator=gen, device="cuda").to(t_in)
+        rb.rbgp_spmm(mask, dtype, w.M, w.K, N, packed.data_ptr(), rows.data_ptr(), ldI, out.data_ptr(), N)
+        I = rows[:, :N].double()
+    torch.cuda.synchronize()
+    assert (out[w.M] == -77).all()
+    cols = torch.from_numpy(rb.rbgp_mask_columns(mask).reshape(w.M, -1).astype("int64")).cuda()
+    dense = torch.zeros((w.M, w.K), dtype=torch.float64, device="cuda").scatter_(1, cols, weights.view(w.M, -1).double())
+    bound = cols.shape[1] * 2.0 ** -24 * (dense.abs() @ I.abs())   # (one fp32 rounding per product and sum, in any order)
+    assert bool(((out[:w.M].double() - dense @ I).abs() <= bound).all())
